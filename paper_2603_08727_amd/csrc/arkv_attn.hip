@@ -2,8 +2,9 @@
 // causal attention, so the pass that computes the prompt's outputs already holds the window rows' softmax
 // maxima and sums).
 //
-// One workgroup = 32 query positions of one (sequence, kv-head); wave w = q-head w of the group, so the G
-// heads of a group share every key and value tile, which is fetched from HBM once per workgroup and staged
+// One workgroup = 32 QB query positions of one (sequence, kv-head) x the G heads of its group; a wave takes 32
+// positions of one head.  QB = 4 / G for G < 4 (else 1), so that at least four waves share every key and value tile,
+// which is fetched from HBM once per workgroup and staged
 // in LDS (keys in three buffers, values in two, one barrier per 32-key tile).  Keys are on the M side of the
 // logits MFMA (v_mfma_f32_32x32x16_bf16, S^T = K Q^T), which leaves ONE query row per lane: the online softmax
 // is per-lane arithmetic (the two lane halves of a row talk only when the row's reference maximum moves, which
@@ -57,8 +58,14 @@ constexpr float kSumLimit = 16384.0f;   // a lane's 16 probabilities may sum to 
 __device__ unsigned long long g_attn_clock[4];
 #endif
 
+// At least four waves per workgroup: fetching and staging a tile is work of the workgroup, and with one or two waves to
+// share it (LDS also admits few such workgroups per CU) the matrix pipe idled behind it.  One block of 32 positions at
+// G = 1, 2 against QB = 4 / G, 4096-token prompt, 8 kv-heads: d = 128 211 -> 97 us and 233 -> 119 us; d = 64, 2003 tokens,
+// 32 units, G = 1: 80.6 -> 51.7 us.
+template <int G> constexpr int kQBlocks = G < 4 ? 4 / G : 1;
+
 template <int D, int G>
-__global__ __launch_bounds__(64 * G, G >= 4 ? 2 : 1) void k_prefill_attn(AttnLaunch L) {
+__global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLaunch L) {
 #ifdef ARKV_PHASE_TRACE
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) { g_attn_clock[0] = clock64(); g_attn_clock[1] = wall_clock64(); }
 #endif
@@ -66,7 +73,8 @@ __global__ __launch_bounds__(64 * G, G >= 4 ? 2 : 1) void k_prefill_attn(AttnLau
   constexpr int KH = KK / 2;          // operands carried from the previous phase
   constexpr int CBN = D / 32;         // 32-channel blocks of the output
   constexpr int NPV = 2 * CBN;        // PV MFMAs per tile
-  constexpr int NT = 64 * G;
+  constexpr int QB = kQBlocks<G>;     // blocks of 32 query positions per workgroup
+  constexpr int NT = 64 * G * QB;
   constexpr int CPR = D / 8;          // 16-byte chunks per row
   constexpr int KCH = 32 * CPR;       // key chunks per tile
   constexpr int VCH = 16 * CPR;       // value chunk pairs (two adjacent keys, eight channels) per tile
@@ -76,15 +84,17 @@ __global__ __launch_bounds__(64 * G, G >= 4 ? 2 : 1) void k_prefill_attn(AttnLau
   __shared__ __align__(16) AttnLds<D> sm;
   const int qb = gridDim.x - 1 - blockIdx.x;      // long rows first
   const int u = blockIdx.y, b = u / L.Hkv, g = u % L.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = wave % G, wq = QB * qb + wave / G; // head of the group, block of 32 query positions
   const int n = lane & 31, hh = lane >> 5;
   const int T = L.T, Tq = L.Tq, q0 = T - Tq;
-  const int row = 32 * qb + n;                     // query row inside the block of T_q queries
+  const int row = 32 * wq + n;                     // query row inside the block of T_q queries
   const int rowc_ = row < Tq ? row : Tq - 1;
   const int pos = q0 + rowc_;                      // its position: sees keys j <= pos
-  const int jmax = min(T, q0 + 32 * qb + 32);      // keys any row of this workgroup can see
+  const int jmax = min(T, q0 + 32 * QB * (qb + 1));  // keys any row of this workgroup can see
   const int ntiles = (jmax + 31) / 32;
-  const int jfull = q0 + 32 * qb - 31;             // tiles starting at or before this need no mask
+  const int jfull = q0 + 32 * wq - 31;             // tiles starting at or before this need no mask
   const uint16_t* kbase = L.k + (size_t)u * T * D;
   const uint16_t* vbase = L.v + (size_t)u * T * D;
   const float scale2 = L.scale2;
@@ -327,8 +337,12 @@ __global__ __launch_bounds__(64 * G, G >= 4 ? 2 : 1) void k_prefill_attn(AttnLau
 
 hipError_t launch_prefill_attn(const AttnLaunch& a, hipStream_t s) {
   const int U = a.B * a.Hkv, G = a.Hq / a.Hkv;
-  dim3 grid((a.Tq + 31) / 32, U);
-#define ARKV_AT(D_, G_) if (a.D == D_ && G == G_) { hipLaunchKernelGGL((k_prefill_attn<D_, G_>), grid, dim3(64 * G_), 0, s, a); return hipGetLastError(); }
+#define ARKV_AT(D_, G_)                                                                                              \
+  if (a.D == D_ && G == G_) {                                                                                        \
+    const int rows = 32 * kQBlocks<G_>;                                                                              \
+    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), dim3((a.Tq + rows - 1) / rows, U), dim3(64 * G_ * kQBlocks<G_>), 0, s, a); \
+    return hipGetLastError();                                                                                        \
+  }
   ARKV_AT(128, 1) ARKV_AT(128, 2) ARKV_AT(128, 4) ARKV_AT(128, 8)
   ARKV_AT(64, 1) ARKV_AT(64, 2) ARKV_AT(64, 4) ARKV_AT(64, 8)
 #undef ARKV_AT
