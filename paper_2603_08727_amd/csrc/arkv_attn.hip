@@ -64,6 +64,34 @@ __device__ unsigned long long g_attn_clock[4];
 // 32 units, G = 1: 80.6 -> 51.7 us.
 template <int G> constexpr int kQBlocks = G < 4 ? 4 / G : 1;
 
+// four adjacent channels of an output row: bf16, and fp32 for the parity hook
+template <int D>
+__device__ __forceinline__ void store_out4(const AttnLaunch& L, size_t orow, int c, const float (&val)[4]) {
+  uint16_t o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t bits = __float_as_uint(val[e]);
+    bits += 0x7fffu + ((bits >> 16) & 1u);      // round to nearest even (finite values)
+    o[e] = (uint16_t)(bits >> 16);
+  }
+  if (L.outf) *reinterpret_cast<float4*>(L.outf + orow * D + c) = make_float4(val[0], val[1], val[2], val[3]);
+  *reinterpret_cast<uint2*>(L.out + orow * D + c) =
+      make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+}
+
+// Split over the keys, for launches whose workgroups do not fill the chip or whose longest workgroup outlasts the
+// average (attn_split decides).  A workgroup's key tiles whose first key every one of its rows sees are cut into
+// pieces of at most piece_tiles; the last piece also takes the tiles of the causal diagonal.  So every row sees the
+// first key of every piece, and no piece leaves a row's softmax reference unset.
+struct AttnPieces { int n, visible; };    // pieces; tiles that start at or before the first row's position
+__host__ __device__ inline AttnPieces attn_pieces(int first_pos, int piece_tiles) {
+  const int visible = first_pos / 32 + 1;
+  return {piece_tiles > 0 ? (visible + piece_tiles - 1) / piece_tiles : 1, visible};
+}
+// A piece's partial result per wave, in the order in which its lanes hold it: 4 * (D / 32) float4 per lane
+// [channel block][row group][lane] (unnormalised sums), then (reference maximum, sum) per row [32].
+template <int D> constexpr int kPieceFloats = 32 * D + 64;
+
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLaunch L) {
 #ifdef ARKV_PHASE_TRACE
@@ -94,6 +122,10 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   const int pos = q0 + rowc_;                      // its position: sees keys j <= pos
   const int jmax = min(T, q0 + 32 * QB * (qb + 1));  // keys any row of this workgroup can see
   const int ntiles = (jmax + 31) / 32;
+  const AttnPieces pc = attn_pieces(q0 + 32 * QB * qb, L.piece_tiles);
+  const int piece = blockIdx.z;
+  if (piece >= pc.n) return;
+  const int t0 = pc.visible * piece / pc.n, t1 = piece + 1 < pc.n ? pc.visible * (piece + 1) / pc.n : ntiles;
   const int jfull = q0 + 32 * wq - 31;             // tiles starting at or before this need no mask
   const uint16_t* kbase = L.k + (size_t)u * T * D;
   const uint16_t* vbase = L.v + (size_t)u * T * D;
@@ -210,8 +242,8 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   // The reference maximum is lazy: probabilities are taken against the row's current m_run, and only when a
   // lane's sum shows that they grew large (or the reference is still unset) does the row move its reference
   // to the tile's maximum and redo the tile.  A row decides from its own numbers only.
-  auto step = [&](f32x16a& C, f32x16a& Cn, int t) {
-    const int j0 = 32 * t, vb = t & 1;
+  auto step = [&](f32x16a& C, f32x16a& Cn, int t, const int vb) {     // vb: the buffer that holds the value tile
+    const int j0 = 32 * t;
     fetch_k(j0 + 96);
     fetch_v(j0 + 32);
     uint32_t ph[8];
@@ -278,13 +310,13 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
     __syncthreads();
   };
 
-  fetch_k(0);
-  fetch_v(0);
+  fetch_k(32 * t0);
+  fetch_v(32 * t0);
   stage_k(0);
   stage_v(0);
-  fetch_k(32);
+  fetch_k(32 * t0 + 32);
   stage_k(1);
-  fetch_k(64);
+  fetch_k(32 * t0 + 64);
   stage_k(2);
   __syncthreads();
   f32x16a C0, C1;
@@ -294,40 +326,39 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)
       C0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8a, k_operand(0, kk)), __builtin_bit_cast(bf16x8a, qreg[kk]), C0, 0, 0, 0);
-    mask(C0, 0);
+    mask(C0, 32 * t0);
 #pragma unroll
     for (int kk = 0; kk < KH; ++kk) kop[kk] = k_operand(1, kk);
   }
-  for (int t = 0; t < ntiles; t += 2) {
-    step(C0, C1, t);
-    if (t + 1 < ntiles) step(C1, C0, t + 1);
+  for (int t = t0; t < t1; t += 2) {
+    step(C0, C1, t, 0);
+    if (t + 1 < t1) step(C1, C0, t + 1, 1);
   }
 
 #ifdef ARKV_PHASE_TRACE
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) { g_attn_clock[2] = clock64(); g_attn_clock[3] = wall_clock64(); }
 #endif
   const float l_tot = l_run + __shfl_xor(l_run, 32);
+  if (pc.n > 1) {
+    float* part = L.part + ((((size_t)u * gridDim.x + qb) * gridDim.z + piece) * (G * QB) + wave) * kPieceFloats<D>;
+#pragma unroll
+    for (int cb = 0; cb < CBN; ++cb)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        *reinterpret_cast<float4*>(part + ((cb * 4 + i4) * 64 + lane) * 4) =
+            make_float4(acc[cb][4 * i4], acc[cb][4 * i4 + 1], acc[cb][4 * i4 + 2], acc[cb][4 * i4 + 3]);
+    if (hh == 0) *reinterpret_cast<float2*>(part + 32 * D + 2 * n) = make_float2(m_run, l_tot);
+    return;
+  }
   const float inv = 1.0f / l_tot;
   if (row < Tq) {
-    uint16_t* op = L.out + ((size_t)(b * L.Hq + g * G + w) * Tq + row) * D;
-    float* opf = L.outf ? L.outf + ((size_t)(b * L.Hq + g * G + w) * Tq + row) * D : nullptr;   // parity hook
+    const size_t orow = (size_t)(b * L.Hq + g * G + w) * Tq + row;
 #pragma unroll
     for (int cb = 0; cb < CBN; ++cb)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        uint16_t o[4];
-        float of[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float val = acc[cb][4 * i4 + e] * inv;
-          of[e] = val;
-          uint32_t bits = __float_as_uint(val);
-          bits += 0x7fffu + ((bits >> 16) & 1u);      // round to nearest even (finite values)
-          o[e] = (uint16_t)(bits >> 16);
-        }
-        if (opf) *reinterpret_cast<float4*>(opf + 32 * cb + 8 * i4 + 4 * hh) = make_float4(of[0], of[1], of[2], of[3]);
-        *reinterpret_cast<uint2*>(op + 32 * cb + 8 * i4 + 4 * hh) =
-            make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
+        const float val[4] = {acc[cb][4 * i4] * inv, acc[cb][4 * i4 + 1] * inv, acc[cb][4 * i4 + 2] * inv, acc[cb][4 * i4 + 3] * inv};
+        store_out4<D>(L, orow, 32 * cb + 8 * i4 + 4 * hh, val);
       }
     // the scorer's row constant c = max + log2(sum) of the window rows (row index: head-major, W per head)
     if (L.rowc && hh == 0 && pos >= T - L.W)
@@ -335,12 +366,100 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   }
 }
 
-hipError_t launch_prefill_attn(const AttnLaunch& a, hipStream_t s) {
+// Adds up the pieces of the workgroups that have more than one.  grid (query blocks, units, D / 32), the same waves and
+// lanes as above; a wave takes one block of 32 channels.  Bound by the partials' bytes (34 MB written and read at 512
+// queries x 16411 keys x 32 heads: 9 us of 148).
+template <int D, int G>
+__global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
+  constexpr int QB = kQBlocks<G>;
+  const int qb = gridDim.x - 1 - blockIdx.x, u = blockIdx.y, cb = blockIdx.z, b = u / L.Hkv, g = u % L.Hkv;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = wave % G, n = lane & 31, hh = lane >> 5;
+  const int T = L.T, Tq = L.Tq, q0 = T - Tq, row = 32 * (QB * qb + wave / G) + n;
+  const AttnPieces pc = attn_pieces(q0 + 32 * QB * qb, L.piece_tiles);
+  if (pc.n < 2 || row >= Tq) return;
+  const float* part = L.part + (((size_t)u * gridDim.x + qb) * max_pieces * (G * QB) + wave) * kPieceFloats<D>;
+  const size_t stride = (size_t)(G * QB) * kPieceFloats<D>;
+  float M = kNegBigA;
+  for (int p = 0; p < pc.n; ++p) M = fmaxf(M, part[p * stride + 32 * D + 2 * n]);
+  float l = 0.f, acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int p = 0; p < pc.n; ++p) {
+    const float* pp = part + p * stride;
+    const float2 ml = *reinterpret_cast<const float2*>(pp + 32 * D + 2 * n);
+    const float f = aexp2(ml.x - M);
+    l = fmaf(ml.y, f, l);
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const float4 v = *reinterpret_cast<const float4*>(pp + ((cb * 4 + i4) * 64 + lane) * 4);
+      acc[4 * i4] = fmaf(v.x, f, acc[4 * i4]);
+      acc[4 * i4 + 1] = fmaf(v.y, f, acc[4 * i4 + 1]);
+      acc[4 * i4 + 2] = fmaf(v.z, f, acc[4 * i4 + 2]);
+      acc[4 * i4 + 3] = fmaf(v.w, f, acc[4 * i4 + 3]);
+    }
+  }
+  const float inv = 1.0f / l;
+  const size_t orow = (size_t)(b * L.Hq + g * G + w) * Tq + row;
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) {
+    const float val[4] = {acc[4 * i4] * inv, acc[4 * i4 + 1] * inv, acc[4 * i4 + 2] * inv, acc[4 * i4 + 3] * inv};
+    store_out4<D>(L, orow, 32 * cb + 8 * i4 + 4 * hh, val);
+  }
+  if (L.rowc && cb == 0 && hh == 0 && q0 + row >= T - L.W)
+    L.rowc[(size_t)u * L.MP + w * L.W + (q0 + row - (T - L.W))] = M + log2f(l);
+}
+
+// Floats of scratch the pieces of such a launch take.
+size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
+  const int qb_rows = 32 * (G < 4 ? 4 / G : 1);
+  return max_pieces < 2 ? 0 : (size_t)units * ((Tq + qb_rows - 1) / qb_rows) * max_pieces * (G < 4 ? 4 : G) *
+                              (size_t)(D == 64 ? kPieceFloats<64> : kPieceFloats<128>);
+}
+constexpr size_t kAttnPartFloats = 32u << 20;   // no split that would take more than 128 MB of scratch
+
+// How far to split over the keys: tiles per piece (0: no split) and the largest number of pieces of a workgroup.
+// Measured at d = 128 (d = 64: about 0.65 of it): a tile step takes 0.75 us in a workgroup that has its CU to itself and
+// 1.06 us where two share it, so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU,
+// whichever is more; the merge costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where
+// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 158 us (4 pieces), 32 x 3000 x 16 units
+// (d = 64, G = 1) 66 -> 16 us.  It does not pay for a whole short prompt, whose imbalance is only the causal triangle
+// (1000 tokens x 8 kv-heads: 30 us unsplit, 37 us in 2 pieces), hence the margin and the floor of 32 tiles.
+void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {
+  *piece_tiles = 0; *max_pieces = 1;
+  const int QB = G < 4 ? 4 / G : 1, nqb = (Tq + 32 * QB - 1) / (32 * QB), q0 = T - Tq;
+  const int v0 = attn_pieces(q0, 0).visible, vmax = v0 + QB * (nqb - 1);         // visible tiles: v0 + QB i, i < nqb
+  const int cu_wgs = 256 * 4 / (G < 4 ? 4 : G);                                  // four-wave workgroups' worth per CU
+  if (vmax < 32 || (long long)nqb * units > 4 * cu_wgs) return;
+  const double c = D == 64 ? 0.65 : 1.0;
+  const double busy = 0.53 * c * 0.5 * ((double)v0 + vmax) * nqb * units / cu_wgs;
+  double best = 0.9 * (0.75 * c * vmax > busy ? 0.75 * c * vmax : busy);
+  for (int ns = 2; ns <= 16; ++ns) {
+    const int pt = (vmax + ns - 1) / ns;
+    const size_t floats = attn_part_floats(D, G, units, Tq, ns);
+    if (pt < 8 || floats > kAttnPartFloats) break;
+    long long items = 0;
+    for (int p = 0; p < ns; ++p) {                                               // workgroups with more than p pieces
+      const int i0 = (p * pt + 1 - v0 + QB - 1) / QB;                            // the first one (v0 + QB i > p pt)
+      items += nqb - (p * pt + 1 <= v0 ? 0 : (i0 < nqb ? i0 : nqb));
+    }
+    items *= units;
+    double t = items <= cu_wgs ? 0.75 * c * pt : items <= 2 * cu_wgs ? 1.06 * c * pt : busy + 0.53 * c * pt;
+    if (t < busy) t = busy;
+    t += 12.0 + 8.0e-7 * (double)floats;
+    if (t < best) { best = t; *piece_tiles = pt; *max_pieces = ns; }
+  }
+}
+
+hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s) {
   const int U = a.B * a.Hkv, G = a.Hq / a.Hkv;
 #define ARKV_AT(D_, G_)                                                                                              \
   if (a.D == D_ && G == G_) {                                                                                        \
-    const int rows = 32 * kQBlocks<G_>;                                                                              \
-    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), dim3((a.Tq + rows - 1) / rows, U), dim3(64 * G_ * kQBlocks<G_>), 0, s, a); \
+    constexpr int rows = 32 * kQBlocks<G_>, nt = 64 * G_ * kQBlocks<G_>;                                             \
+    const int nqb = (a.Tq + rows - 1) / rows;                                                                        \
+    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), dim3(nqb, U, max_pieces), dim3(nt), 0, s, a);                       \
+    if (max_pieces > 1)                                                                                              \
+      hipLaunchKernelGGL((k_prefill_attn_merge<D_, G_>), dim3(nqb, U, D_ / 32), dim3(nt), 0, s, a, max_pieces);      \
     return hipGetLastError();                                                                                        \
   }
   ARKV_AT(128, 1) ARKV_AT(128, 2) ARKV_AT(128, 4) ARKV_AT(128, 8)

@@ -183,10 +183,15 @@ struct AttnLaunch {
   uint16_t* out;          // [B][Hq][Tq][D]
   float* outf;            // [B][Hq][Tq][D] the same output before its rounding to bf16 (parity hook), or null
   float* rowc;            // [U][MP] max + log2(sum) of the last W rows per head, or null
+  float* part;            // partial results where the keys are split (piece_tiles > 0)
+  int piece_tiles;        // key tiles per piece, 0: not split
   int B, Hq, Hkv, D, T, Tq, W, MP;
   float scale2;
 };
-hipError_t launch_prefill_attn(const AttnLaunch& a, hipStream_t s);
+// split of a launch over the keys: a.piece_tiles and the max_pieces of launch_prefill_attn; floats of scratch it needs
+void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces);
+size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces);
+hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s);
 hipError_t launch_prefill_stats(const PrefillLaunch& a, float* rowc /*[U][MP] scratch*/, hipStream_t s);
 
 }  // namespace arkv

@@ -60,6 +60,7 @@ struct arkv_cache {
   float* rowc = nullptr; size_t rowc_cap = 0;
   int* stat_ticket = nullptr;     // [batch], zero between scorer calls
   uint64_t* ckeys = nullptr; size_t ckeys_cap = 0;
+  float* attn_part = nullptr; size_t attn_part_cap = 0;   // pieces of a prefill attention that is split over the keys
   int ckeys_layer = -1, ckeys_T = 0;
   hipStream_t last_stream = nullptr;
   // measurement hook: events around the attention kernel
@@ -286,6 +287,7 @@ int arkv_cache_destroy(arkv_cache* c) {
   if (c->rowc) (void)hipFree(c->rowc);
   if (c->stat_ticket) (void)hipFree(c->stat_ticket);
   if (c->ckeys) (void)hipFree(c->ckeys);
+  if (c->attn_part) (void)hipFree(c->attn_part);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   delete c;
   return ARKV_OK;
@@ -308,7 +310,7 @@ int arkv_cache_reset(arkv_cache* c, int32_t layer) {
 // rows' softmax constants in the scratch, so the scorer's own first pass over the keys is skipped.  lse != nullptr:
 // the caller's attention produced those constants.
 static int run_scorer(arkv_cache* c, int32_t layer, const uint16_t* q_win, size_t q_head_stride, const uint16_t* k,
-                      int32_t T, float softmax_scale, float* stats, hipStream_t s, AttnLaunch* attn,
+                      int32_t T, float softmax_scale, float* stats, hipStream_t s, AttnLaunch* attn, int attn_pieces,
                       const float* lse = nullptr) {
   LayerState& ls = c->layers[(size_t)layer];
   const int U = c->U, G = c->P.G, W = c->cfg.window;
@@ -334,7 +336,7 @@ static int run_scorer(arkv_cache* c, int32_t layer, const uint16_t* q_win, size_
   if ((rc = grow(&c->rowc, &c->rowc_cap, (size_t)U * MP + 2 * stat_doubles)) != ARKV_OK) return rc;
   if (attn) {
     attn->rowc = c->rowc; attn->MP = MP; attn->W = W;
-    HIP_TRY(launch_prefill_attn(*attn, s));
+    HIP_TRY(launch_prefill_attn(*attn, attn_pieces, s));
   }
   PrefillLaunch a;
   a.q_win = q_win;
@@ -359,7 +361,7 @@ int arkv_prefill_stats(arkv_cache* c, int32_t layer, const void* q_win, const vo
   if (c->layers[(size_t)layer].committed) return ARKV_ESTATE;
   return run_scorer(c, layer, static_cast<const uint16_t*>(q_win), (size_t)c->cfg.window * c->P.D,
                     static_cast<const uint16_t*>(k), T, softmax_scale, stats, static_cast<hipStream_t>(hip_stream),
-                    nullptr);
+                    nullptr, 1);
 }
 
 int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, const void* k, int32_t T,
@@ -369,7 +371,16 @@ int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, cons
   if (c->layers[(size_t)layer].committed) return ARKV_ESTATE;
   return run_scorer(c, layer, static_cast<const uint16_t*>(q_win), (size_t)c->cfg.window * c->P.D,
                     static_cast<const uint16_t*>(k), T, softmax_scale, stats, static_cast<hipStream_t>(hip_stream),
-                    nullptr, lse);
+                    nullptr, 1, lse);
+}
+
+// Scratch for the pieces of a prefill attention.  The attention needs none when it is not split, so a call that cannot
+// have it (its stream is being captured, when nothing may be allocated; no memory) runs unsplit.
+static bool attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
+  if (floats <= c->attn_part_cap) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return false; }
+  return grow(&c->attn_part, &c->attn_part_cap, floats) == ARKV_OK;
 }
 
 int arkv_prefill_attention(arkv_cache* c, int32_t layer, const void* q, const void* k, const void* v, int32_t T_q,
@@ -387,15 +398,24 @@ int arkv_prefill_attention(arkv_cache* c, int32_t layer, const void* q, const vo
   a.B = c->cfg.batch; a.Hq = c->cfg.n_q_heads; a.Hkv = c->cfg.n_kv_heads; a.D = c->P.D;
   a.T = T; a.Tq = T_q; a.W = c->cfg.window; a.MP = 0;
   a.scale2 = softmax_scale * 1.4426950408889634f;
-  if (!stats) {
-    HIP_TRY(launch_prefill_attn(a, s));
+  a.part = nullptr; a.piece_tiles = 0;
+  const bool with_stats = stats != nullptr;
+  if (with_stats) {
+    if (T_q < c->cfg.window || T <= c->cfg.window) return ARKV_EINVAL;
+    if (c->layers[(size_t)layer].committed) return ARKV_ESTATE;
+  }
+  int pieces = 1;
+  attn_split(a.D, c->P.G, c->U, T, T_q, &a.piece_tiles, &pieces);
+  if (pieces > 1 && !attn_scratch(c, attn_part_floats(a.D, c->P.G, c->U, T_q, pieces), s)) { pieces = 1; a.piece_tiles = 0; }
+  a.part = c->attn_part;
+  if (!with_stats) {
+    HIP_TRY(launch_prefill_attn(a, pieces, s));
     c->last_stream = s;
     return ARKV_OK;
   }
-  if (T_q < c->cfg.window || T <= c->cfg.window) return ARKV_EINVAL;
-  if (c->layers[(size_t)layer].committed) return ARKV_ESTATE;
   const size_t D = (size_t)c->P.D;
-  return run_scorer(c, layer, a.q + (size_t)(T_q - c->cfg.window) * D, (size_t)T_q * D, a.k, T, softmax_scale, stats, s, &a);
+  return run_scorer(c, layer, a.q + (size_t)(T_q - c->cfg.window) * D, (size_t)T_q * D, a.k, T, softmax_scale, stats, s, &a,
+                    pieces);
 }
 
 int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void* v, int32_t T,

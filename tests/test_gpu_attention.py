@@ -299,3 +299,71 @@ def test_scorer_with_the_callers_log_sum_exp(hq, hkv, d, T):
         sb.assert_within_tol()
     finally:
         sb.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,Tq,T", [
+    (4, 1, 128, 512, 4101),    # few workgroups: every workgroup in several pieces
+    (8, 1, 64, 33, 2048),      # group size 8, the second workgroup holds one row
+    (2, 2, 64, 129, 3001),     # 128-position workgroups, the second holds one row
+    (4, 2, 128, 65, 1025),     # 64-position workgroups at the smallest split
+    (4, 1, 64, 1100, 1100),    # a whole prompt: only the late workgroups are split
+])
+def test_attention_split_over_keys(hq, hkv, d, Tq, T):
+    """Launches too small for the chip cut a workgroup's keys into pieces and merge them: outputs against the oracle,
+    first and last rows of every block of positions among them, and the window rows' constants through the scorer
+    (same tolerances as the unsplit pass: the sums stay in fp32)."""
+    wl = synth.C1.scaled(name="split", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)[:, :, T - Tq:].contiguous()
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        kd, vd, qd = k.cuda(), v.cuda(), q.cuda()
+        alone, fused = (torch.zeros((1, 3), dtype=torch.float32, device="cuda") for _ in range(2))
+        A.arkv_prefill_stats(cache, 0, qw.cuda(), kd, T, scale, alone)
+        out = torch.zeros_like(qd)
+        _attention(cache, 0, qd, kd, vd, Tq, T, scale, out, fused)
+        pos = np.unique(np.clip(np.concatenate([np.arange(T - Tq, T, 32), np.arange(T - Tq + 31, T, 32), [T - 1]]), 0, T - 1))
+        assert _check_rows(out, q, k, v, scale, hq // hkv, pos, T - Tq) <= TOL
+        sa, sf = alone.cpu().numpy(), fused.cpu().numpy()
+        assert np.all(np.abs(sf - sa) <= TOL * np.abs(sa))
+        again = torch.zeros_like(out)
+        A.arkv_prefill_attention(cache, 0, qd, kd, vd, Tq, T, scale, again)
+        assert torch.equal(out, again)             # the cut depends on the shape alone
+    finally:
+        A.arkv_cache_destroy(cache)
+
+
+def test_attention_split_under_graph_capture():
+    """Nothing is allocated while a stream is being captured: before the scratch exists the call runs unsplit, after an
+    eager call has made it the captured call is split; every replay equals the eager result of its kind."""
+    T, Tq, d = 3000, 96, 128
+    wl = synth.C1.scaled(name="capture", n_q_heads=4, n_kv_heads=1, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)[:, :, T - Tq:].contiguous()
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        kd, vd, qd = k.cuda(), v.cuda(), q.cuda()
+        outs = [torch.zeros_like(qd) for _ in range(3)]
+        graphs = []
+        for i in (0, 1):
+            s = torch.cuda.Stream()
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                A.arkv_prefill_attention(cache, 0, qd, kd, vd, Tq, T, scale, outs[i])
+            graphs.append(g)
+            if i == 0:
+                A.arkv_prefill_attention(cache, 0, qd, kd, vd, Tq, T, scale, outs[2])
+                torch.cuda.synchronize()
+        for _ in range(3):
+            for i, g in enumerate(graphs):
+                outs[i].zero_()
+                g.replay()
+                torch.cuda.synchronize()
+                ref = outs[i].float().cpu()
+                assert torch.equal(outs[1], outs[2]) or i == 0
+                assert (ref - outs[2].float().cpu()).abs().max() <= 8e-3 * ref.abs().max()   # two bf16 roundings
+    finally:
+        A.arkv_cache_destroy(cache)
