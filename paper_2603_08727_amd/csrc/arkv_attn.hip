@@ -92,10 +92,25 @@ __host__ __device__ inline AttnPieces attn_pieces(int first_pos, int piece_tiles
 // [channel block][row group][lane] (unnormalised sums), then (reference maximum, sum) per row [32].
 template <int D> constexpr int kPieceFloats = 32 * D + 64;
 
+// Which block of query positions a workgroup takes.  grid (units, blocks, pieces; or units, up to kMaxGridY blocks, rest):
+// the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at the end,
+// and with a multiple of 8 units a unit's workgroups share the L2 of one XCD (workgroups go to the XCDs in turn).
+// With the block fastest, the last unit's long blocks started late: 4096 tokens x 8 units, d = 128, G = 4 205 -> 156 us,
+// x 24 units 551 -> 460 us, 2003 x 32, d = 64, G = 1 51.6 -> 43.5 us, 32768 x 8 9.02 -> 8.74 ms.
+// A launch of at most two workgroups per CU starts all at once: there the second half runs from the shortest up, so that
+// a CU that got a long one first gets a short one next (4096 x 8 units, G = 1: 65 -> 60 us; 1000 x 8, G = 4: 26.3 -> 25.7).
+constexpr int kMaxGridY = 65535;
+__device__ __forceinline__ int query_block(int nqb, bool split) {
+  const int rank = (int)blockIdx.y + (split ? 0 : (int)blockIdx.z * kMaxGridY);      // 0: the longest
+  const int half = (nqb + 1) / 2;
+  if ((int)gridDim.x * nqb <= 512 && rank >= half) return rank - half;
+  return nqb - 1 - rank;                                                              // negative past the last block
+}
+
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLaunch L) {
 #ifdef ARKV_PHASE_TRACE
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) { g_attn_clock[0] = clock64(); g_attn_clock[1] = wall_clock64(); }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) { g_attn_clock[0] = clock64(); g_attn_clock[1] = wall_clock64(); }
 #endif
   constexpr int KK = D / 16;          // k-steps of the logits MFMA
   constexpr int KH = KK / 2;          // operands carried from the previous phase
@@ -110,8 +125,9 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   constexpr int VPT = (VCH + NT - 1) / NT;
   static_assert(NPV >= KH, "operand prefetch pattern");
   __shared__ __align__(16) AttnLds<D> sm;
-  const int qb = gridDim.x - 1 - blockIdx.x;      // long rows first
-  const int u = blockIdx.y, b = u / L.Hkv, g = u % L.Hkv;
+  const int nqb = (L.Tq + 32 * QB - 1) / (32 * QB), qb = query_block(nqb, L.piece_tiles > 0);
+  if (qb < 0) return;
+  const int u = blockIdx.x, b = u / L.Hkv, g = u % L.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = wave % G, wq = QB * qb + wave / G; // head of the group, block of 32 query positions
@@ -123,7 +139,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   const int jmax = min(T, q0 + 32 * QB * (qb + 1));  // keys any row of this workgroup can see
   const int ntiles = (jmax + 31) / 32;
   const AttnPieces pc = attn_pieces(q0 + 32 * QB * qb, L.piece_tiles);
-  const int piece = blockIdx.z;
+  const int piece = L.piece_tiles > 0 ? (int)blockIdx.z : 0;
   if (piece >= pc.n) return;
   const int t0 = pc.visible * piece / pc.n, t1 = piece + 1 < pc.n ? pc.visible * (piece + 1) / pc.n : ntiles;
   const int jfull = q0 + 32 * wq - 31;             // tiles starting at or before this need no mask
@@ -336,11 +352,11 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   }
 
 #ifdef ARKV_PHASE_TRACE
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) { g_attn_clock[2] = clock64(); g_attn_clock[3] = wall_clock64(); }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) { g_attn_clock[2] = clock64(); g_attn_clock[3] = wall_clock64(); }
 #endif
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   if (pc.n > 1) {
-    float* part = L.part + ((((size_t)u * gridDim.x + qb) * gridDim.z + piece) * (G * QB) + wave) * kPieceFloats<D>;
+    float* part = L.part + ((((size_t)u * nqb + qb) * gridDim.z + piece) * (G * QB) + wave) * kPieceFloats<D>;
 #pragma unroll
     for (int cb = 0; cb < CBN; ++cb)
 #pragma unroll
@@ -372,7 +388,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
   constexpr int QB = kQBlocks<G>;
-  const int qb = gridDim.x - 1 - blockIdx.x, u = blockIdx.y, cb = blockIdx.z, b = u / L.Hkv, g = u % L.Hkv;
+  const int qb = blockIdx.x, u = blockIdx.y, cb = blockIdx.z, b = u / L.Hkv, g = u % L.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = wave % G, n = lane & 31, hh = lane >> 5;
   const int T = L.T, Tq = L.Tq, q0 = T - Tq, row = 32 * (QB * qb + wave / G) + n;
@@ -457,7 +473,8 @@ hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t 
   if (a.D == D_ && G == G_) {                                                                                        \
     constexpr int rows = 32 * kQBlocks<G_>, nt = 64 * G_ * kQBlocks<G_>;                                             \
     const int nqb = (a.Tq + rows - 1) / rows;                                                                        \
-    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), dim3(nqb, U, max_pieces), dim3(nt), 0, s, a);                       \
+    const dim3 grid(U, nqb < kMaxGridY ? nqb : kMaxGridY, max_pieces > 1 ? max_pieces : (nqb + kMaxGridY - 1) / kMaxGridY); \
+    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), grid, dim3(nt), 0, s, a);                                           \
     if (max_pieces > 1)                                                                                              \
       hipLaunchKernelGGL((k_prefill_attn_merge<D_, G_>), dim3(nqb, U, D_ / 32), dim3(nt), 0, s, a, max_pieces);      \
     return hipGetLastError();                                                                                        \
