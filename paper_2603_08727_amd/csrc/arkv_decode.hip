@@ -618,7 +618,8 @@ __device__ __forceinline__ unsigned long long ld_dev2(const float* p) {
 // adjacent channels (8-byte loads), and the partials of up to 64 splits are requested before the first is
 // used, so the merge costs one round trip to memory where a launch has many splits per unit.
 template <int D, int G>
-__device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunch& L, int lu, int gu, int tid) {
+__device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunch& L, const float* part, int S, int lu, int gu,
+                                               int tid) {
   __shared__ __align__(16) float cw[G][kMaxSplits];   // weight of split s for head h; 0 beyond the launch's splits
   __shared__ float cInv[G];
   constexpr int RS = G * (D + 2);                  // floats per split
@@ -626,8 +627,6 @@ __device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunc
   constexpr int NI = (NP + 255) / 256;             // pairs per thread
   constexpr int NB = (G <= 2 ? 32 : 64) / NI;      // splits per batch of loads (NI * NB * 2 registers)
   TRACE_M(0);
-  const float* part = P.part + (size_t)(gu - L.part_unit0) * P.max_splits * RS;
-  const int S = L.splits;
   int hh[NI], off[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -813,7 +812,9 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   // token counts: from the launch arguments when the host knows them, else from the unit's counters
   if (!known) {
     const volatile int* cnt = reinterpret_cast<const volatile int*>(P.cnt + gu);
-    cO = cnt[0]; cQ = cnt[1];
+    const int o = cnt[0], q = cnt[1];
+    // uniform, and told so: the row ranges that follow are then scalar arithmetic
+    cO = __builtin_amdgcn_readfirstlane(o); cQ = __builtin_amdgcn_readfirstlane(q);
   }
 
   int ao, bo, aq, bq;
@@ -852,6 +853,12 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   OTile ta, tb;
   if (ao < bo) load_o(ta, ao + 16 * w);
   TRACE(1);
+  // What the workgroup's end needs of the launch arguments is read here, while the first tile is on its way (pinned like
+  // the batch above): at their uses each was a scalar round trip in the chain from the last tile to the output, three of
+  // them between the tile loop and the merge's loads.
+  float* const part_ = P.part + (size_t)(gu - L.part_unit0) * P.max_splits * (G * (D + 2));   // the unit's partials
+  int* const ticket_ = P.ticket + (gu - L.part_unit0);
+  asm volatile("" ::"s"(part_), "s"(ticket_));
 
   // this step's query; on a launch that also updates the scores, the waiting steps' state goes to LDS
   uint4 qa[KK];
@@ -1216,33 +1223,42 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   __syncthreads();
 
   // ---------------- this split's partial ----------------
-  float* part = P.part + ((size_t)(gu - L.part_unit0) * P.max_splits + s) * G * (D + 2);
+  float* part = part_ + (size_t)s * G * (D + 2);
   for (int idx = tid; idx < G * D / 2; idx += 256) {
     const int h = idx / (D / 2), c = 2 * (idx % (D / 2));
-    float M = sm_m[0][h];
-#pragma unroll
-    for (int i = 1; i < 4; ++i) M = fmaxf(M, sm_m[i][h]);
-    float a0 = 0.f, a1 = 0.f, l = 0.f;
+    // every LDS read is requested before the first is used (a wait per wave's sums would be four LDS round trips in a
+    // row), the packed rows' sums behind one branch
+    float m[4], lw[4], f[4];
+    float2 t[4][RP], tq[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float cw_ = fexp2(sm_m[i][h] - M);
-      // the wave's value-row groups, added pairwise in the order a butterfly over the lanes would take
-      float2 t[RP];
+      m[i] = sm_m[i][h]; lw[i] = sm_l[i][h];
 #pragma unroll
-      for (int v = 0; v < RP; ++v) t[v] = *reinterpret_cast<const float2*>(&sm_a[i][v][h][c]);
+      for (int v = 0; v < RP; ++v) t[i][v] = *reinterpret_cast<const float2*>(&sm_a[i][v][h][c]);
+    }
+    if (hasq) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { tq[i] = *reinterpret_cast<const float2*>(&sm_q[i][h][c]); f[i] = sm_fo[i][h]; }
+    }
+    const float M = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+    // a wave's value-row groups, added pairwise in the order a butterfly over the lanes would take
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int st = 1; st < RP; st <<= 1)
 #pragma unroll
-        for (int v = 0; v < RP; v += 2 * st) { t[v].x += t[v + st].x; t[v].y += t[v + st].y; }
-      if (hasq) {
-        const float2 tq = *reinterpret_cast<const float2*>(&sm_q[i][h][c]);
-        const float f = sm_fo[i][h];
-        t[0].x = fmaf(t[0].x, f, tq.x);
-        t[0].y = fmaf(t[0].y, f, tq.y);
-      }
-      a0 = fmaf(t[0].x, cw_, a0);
-      a1 = fmaf(t[0].y, cw_, a1);
-      l = fmaf(sm_l[i][h], cw_, l);
+        for (int v = 0; v < RP; v += 2 * st) { t[i][v].x += t[i][v + st].x; t[i][v].y += t[i][v + st].y; }
+    if (hasq) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { t[i][0].x = fmaf(t[i][0].x, f[i], tq[i].x); t[i][0].y = fmaf(t[i][0].y, f[i], tq[i].y); }
+    }
+    float a0 = 0.f, a1 = 0.f, l = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float cw_ = fexp2(m[i] - M);
+      a0 = fmaf(t[i][0].x, cw_, a0);
+      a1 = fmaf(t[i][0].y, cw_, a1);
+      l = fmaf(lw[i], cw_, l);
     }
     st_dev2(part + h * (D + 2) + c, a0, a1);
     if (c == 0) st_dev2(part + h * (D + 2) + D, M, l);
@@ -1255,14 +1271,13 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (tid == 0) {
-    int* const ticket = P.ticket + (gu - L.part_unit0);
-    const int old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int old = __hip_atomic_fetch_add(ticket_, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = old == splits - 1;
-    if (last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
+    if (last) __hip_atomic_store(ticket_, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
     sm_last = last;
   }
   __syncthreads();
-  if (sm_last) combine_splits<D, G>(P, L, lu, gu, tid);
+  if (sm_last) combine_splits<D, G>(P, L, part_, splits, lu, gu, tid);
   TRACE(6);
 }
 
