@@ -165,14 +165,14 @@ int arkv_decode_step(arkv_cache* cache, int32_t layer, const void* q, const void
 
 /* arkv_decode_step for callers that must not allocate device memory while they run (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments, same result bit for bit when the
- * split-K factor is the same.  The split-K partials and the units' tickets of the launch live in a 4 MiB array in
+ * split-K factor is the same.  The split-K partials (4 MiB) and the units' tickets of the launch live in an array in
  * the library's static device memory (one per GPU, held until the process ends; its address is looked up by
  * arkv_cache_create on that GPU) instead of the cache's own buffers, and the call makes no hipMalloc / hipFree and
  * records no timing events.  Limits: B * H_kv <= 4096 units and B * H_kv * G * (d + 2) * 4 bytes <= 4 MiB - 16 KiB
  * (one split per unit must fit), else ARKV_ESCRATCH; the split-K factor is lowered to what fits (config of 32
  * units, G = 4, d = 128: up to 62 splits per unit).  Every call on a GPU shares that GPU's array: calls on
  * different streams (or different caches) that overlap in time on one GPU race; calls ordered on one stream do
- * not.  The tickets are zero between launches (the last workgroup of a unit clears its ticket); partials need
+ * not.  The tickets are zero between launches (the wave that draws a last ticket clears it); partials need
  * no clearing. */
 int arkv_decode_step_static(arkv_cache* cache, int32_t layer, const void* q, const void* k_new,
                             const void* v_new, float softmax_scale, void* out, void* hip_stream);
@@ -260,8 +260,8 @@ int arkv_debug_split_range(int32_t n_original, int32_t n_quantized, int32_t pack
  * which = 0: n_rows rows of 8 words, row = workgroup (unit-major, split-minor) of the latest decode launch:
  *   start, first tile requested, bf16 rows done, new token done, packed rows done, partial stored, end, and the
  *   XCC_ID hardware register (the XCD number is its low 4 bits); row 8190 holds the two markers' times in words 0 and 1;
- * which = 1: the same rows for the merge inside the unit's last workgroup: entered, loads issued, weights
- *   reduced, barrier passed, accumulated, stored (words 0..5; rows of other workgroups keep older values);
+ * which = 1: the same rows for the merge by wave 0 of the workgroup that ended last: entered, loads issued, weights
+ *   reduced, weights readable, accumulated, stored (words 0..5; rows of other workgroups keep older values);
  * which = 2: 4 words of the latest prefill-attention launch: shader clock and wall clock at the start and at the
  *   end of workgroup (0, 0) (n_rows is ignored, pass 1).
  * ARKV_EINVAL: null pointer, which outside 0..2, n_rows outside 1..8192. */

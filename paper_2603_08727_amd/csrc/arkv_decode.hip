@@ -602,7 +602,7 @@ __device__ unsigned long long g_trace_m[8192][8];
 // s_waitcnt vmcnt(0), and an acquire an L2 invalidate; the write-back and the invalidate exist for data that
 // ordinary stores left dirty in, or ordinary loads pulled into, an XCD's L2.  Nothing the merge consumes is
 // written or read by ordinary accesses, so only the wait remains: a wave's partial stores are acknowledged
-// (s_waitcnt 0) before the workgroup's barrier, and the ticket is taken after the barrier.
+// (s_waitcnt vmcnt(0)) before the wave takes its ticket, and only the wave that stored them counts for their ticket.
 // (two adjacent floats, 8-byte aligned, per access)
 __device__ __forceinline__ void st_dev2(float* p, float a, float b) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
@@ -613,24 +613,26 @@ __device__ __forceinline__ unsigned long long ld_dev2(const float* p) {
   return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Merge of a unit's split-K partials by the workgroup that finished last: output row, the step's
-// (max, 1/sum) per head, token count.  All 256 threads of that workgroup take part; a thread owns pairs of
-// adjacent channels (8-byte loads), and the partials of up to 64 splits are requested before the first is
-// used, so the merge costs one round trip to memory where a launch has many splits per unit.
+// Merge of a unit's split-K partials, wave by wave: wave w of every workgroup stores the channel pairs 64 w .. + 63
+// (+ 256 i) of the unit's heads, and the wave that stored them last (a ticket per unit and wave) merges exactly those:
+// output, the step's (max, 1/sum) of the heads in them, and with head 0 the token count.  Nothing here needs the other
+// waves, so no barrier stands between a wave's stores and the output.  A lane owns a pair of adjacent channels (8-byte
+// loads); the partials of up to 64 splits are requested before the first is used, so the merge costs one round trip to
+// memory.
 template <int D, int G>
 __device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunch& L, const float* part, int S, int lu, int gu,
-                                               int tid) {
+                                               int w, int lane) {
   __shared__ __align__(16) float cw[G][kMaxSplits];   // weight of split s for head h; 0 beyond the launch's splits
-  __shared__ float cInv[G];
   constexpr int RS = G * (D + 2);                  // floats per split
   constexpr int NP = G * D / 2;                    // channel pairs per split
-  constexpr int NI = (NP + 255) / 256;             // pairs per thread
+  constexpr int NI = (NP + 255) / 256;             // pairs per lane
+  constexpr int HW = 128 / D;                      // heads per 64 pairs
   constexpr int NB = (G <= 2 ? 32 : 64) / NI;      // splits per batch of loads (NI * NB * 2 registers)
   TRACE_M(0);
   int hh[NI], off[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const int idx = min(tid + 256 * i, NP - 1);
+    const int idx = min(64 * w + lane + 256 * i, NP - 1);
     hh[i] = idx / (D / 2);
     off[i] = hh[i] * (D + 2) + 2 * (idx % (D / 2));
   }
@@ -647,46 +649,47 @@ __device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunc
       }
     }
   };
-  // (max, sum) of the splits: wave w takes heads w and w + 4; a lane takes splits lane and lane + 64 and the
-  // wave reduces in a fixed order.  The pairs are requested first and the first batch of partial values right
-  // behind them, so that the weights are worked out while the values are on their way: one round trip.
+  // (max, sum) of the splits: a lane takes splits lane and lane + 64 and the wave reduces in a fixed order.  The pairs
+  // are requested first and the first batch of partial values right behind them, so that the weights are worked out
+  // while the values are on their way: one round trip.
+  float inv[NI][HW];
   {
-    constexpr int NH = (G + 3) / 4;
-    const int lane = tid & 63, w = tid >> 6;
-    float m0[NH], l0[NH], m1[NH], l1[NH];
+    float m0[NI][HW], l0[NI][HW], m1[NI][HW], l1[NI][HW];
 #pragma unroll
-    for (int k = 0; k < NH; ++k) {
-      const int h = min(w + 4 * k, G - 1);
-      m0[k] = m1[k] = kNegBig; l0[k] = l1[k] = 0.f;
-      if (lane < S) {
-        const unsigned long long ml = ld_dev2(part + (size_t)lane * RS + h * (D + 2) + D);
-        m0[k] = __uint_as_float((unsigned)ml); l0[k] = __uint_as_float((unsigned)(ml >> 32));
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int k = 0; k < HW; ++k) {
+        const int h = min((64 * w + 256 * i) / (D / 2) + k, G - 1);
+        m0[i][k] = m1[i][k] = kNegBig; l0[i][k] = l1[i][k] = 0.f;
+        if (lane < S) {
+          const unsigned long long ml = ld_dev2(part + (size_t)lane * RS + h * (D + 2) + D);
+          m0[i][k] = __uint_as_float((unsigned)ml); l0[i][k] = __uint_as_float((unsigned)(ml >> 32));
+        }
+        if (lane + 64 < S) {
+          const unsigned long long ml = ld_dev2(part + (size_t)(lane + 64) * RS + h * (D + 2) + D);
+          m1[i][k] = __uint_as_float((unsigned)ml); l1[i][k] = __uint_as_float((unsigned)(ml >> 32));
+        }
       }
-      if (lane + 64 < S) {
-        const unsigned long long ml = ld_dev2(part + (size_t)(lane + 64) * RS + h * (D + 2) + D);
-        m1[k] = __uint_as_float((unsigned)ml); l1[k] = __uint_as_float((unsigned)(ml >> 32));
-      }
-    }
     load_batch(0);
     TRACE_M(1);
 #pragma unroll
-    for (int k = 0; k < NH; ++k) {
-      const int h = w + 4 * k;
-      if (h < G) {                                 // uniform per wave
-        const float M = wave_max(fmaxf(m0[k], m1[k]));
-        const float w0 = lane < S ? exp2f(m0[k] - M) : 0.f, w1 = lane + 64 < S ? exp2f(m1[k] - M) : 0.f;
-        cw[h][lane] = w0;
-        cw[h][lane + 64] = w1;
-        const float l = wave_sum(fmaf(l0[k], w0, l1[k] * w1));
-        if (lane == 0) {
-          cInv[h] = 1.0f / l;
-          P.fin[(size_t)L.slot * P.fin_stride + (size_t)gu * G + h] = make_float2(M, 1.0f / l);
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int k = 0; k < HW; ++k) {
+        const int h = (64 * w + 256 * i) / (D / 2) + k;
+        if (h < G) {                               // uniform per wave
+          const float M = wave_max(fmaxf(m0[i][k], m1[i][k]));
+          const float w0 = lane < S ? exp2f(m0[i][k] - M) : 0.f, w1 = lane + 64 < S ? exp2f(m1[i][k] - M) : 0.f;
+          cw[h][lane] = w0;
+          cw[h][lane + 64] = w1;
+          const float l = wave_sum(fmaf(l0[i][k], w0, l1[i][k] * w1));
+          inv[i][k] = 1.0f / l;
+          if (lane == 0) P.fin[(size_t)L.slot * P.fin_stride + (size_t)gu * G + h] = make_float2(M, inv[i][k]);
         }
       }
-    }
   }
   TRACE_M(2);
-  __syncthreads();
+  __builtin_amdgcn_wave_barrier();                 // the weights are read by the wave that wrote them
   TRACE_M(3);
   float o[NI][2];
 #pragma unroll
@@ -718,15 +721,18 @@ __device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunc
   TRACE_M(4);
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const int idx = tid + 256 * i;
+    const int idx = 64 * w + lane + 256 * i;
     if (idx < NP) {
-      const float r0 = o[i][0] * cInv[hh[i]], r1 = o[i][1] * cInv[hh[i]];
+      float iv = inv[i][0];
+      if constexpr (HW == 2) iv = lane < 32 ? inv[i][0] : inv[i][1];
+      const float r0 = o[i][0] * iv, r1 = o[i][1] * iv;
       *reinterpret_cast<float2*>(P.outf + (size_t)gu * G * D + 2 * idx) = make_float2(r0, r1);
       *reinterpret_cast<uint32_t*>(L.out + (size_t)lu * G * D + 2 * idx) =
           (uint32_t)float_to_bf16_rne(r0) | ((uint32_t)float_to_bf16_rne(r1) << 16);
     }
   }
-  if (tid == 0) P.cnt[gu].x += 1;
+  // every workgroup of the unit has read the count: its wave 0 has passed the barrier in front of the partials
+  if (w == 0 && lane == 0) P.cnt[gu].x += 1;
   TRACE_M(5);
 }
 
@@ -781,7 +787,6 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   // 16-byte vectors fall into different bank groups)
   __shared__ __align__(16) _Float16 sm_p[4][16][kVBlock + 8];
   __shared__ _Float16 sm_pdump[4][16][8];
-  __shared__ int sm_last;
   __shared__ __align__(16) PendingLds<D, G> sm_pend;   // only touched when FOLD (16-byte alignment: its rows are read as 16-byte vectors)
   static_assert(!FOLD || sizeof(PendingLds<D, G>) >= sizeof(float) * 4 * G * D, "the packed rows' sums must fit the waiting steps' state");
   float (*sm_q)[G][D] = FOLD ? reinterpret_cast<float (*)[G][D]>(&sm_pend) : reinterpret_cast<float (*)[G][D]>(&sm_q_own[0][0][0]);
@@ -857,7 +862,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   // the batch above): at their uses each was a scalar round trip in the chain from the last tile to the output, three of
   // them between the tile loop and the merge's loads.
   float* const part_ = P.part + (size_t)(gu - L.part_unit0) * P.max_splits * (G * (D + 2));   // the unit's partials
-  int* const ticket_ = P.ticket + (gu - L.part_unit0);
+  int* const ticket_ = P.ticket + (size_t)(gu - L.part_unit0) * (kTicketWaves * kTicketPitch);
   asm volatile("" ::"s"(part_), "s"(ticket_));
 
   // this step's query; on a launch that also updates the scores, the waiting steps' state goes to LDS
@@ -1265,19 +1270,24 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   }
 
   TRACE(5);
-  // ---------------- the unit's last workgroup merges ----------------
-  // Every lane waits until its own stores are acknowledged, the barrier collects the workgroup, then one
-  // lane takes a ticket.  The workgroup that draws the last ticket of the unit sees all partials.
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (tid == 0) {
-    const int old = __hip_atomic_fetch_add(ticket_, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const int last = old == splits - 1;
-    if (last) __hip_atomic_store(ticket_, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next launch
-    sm_last = last;
+  // ---------------- the unit's last waves merge ----------------
+  // A wave waits until its own stores are acknowledged, then takes its ticket.  The wave that draws the last ticket sees
+  // all partials of its channels and clears the ticket for the next launch.  Every ticket has a cache line of its own:
+  // atomics on one line are served one after the other, and with the tickets of a unit's waves (or of a layer's units)
+  // side by side that queue was longer than the merge (one line per ticket against a layer's tickets side by side, per
+  // call: 16 units x 32 splits 15.2 -> 11.8 us with 2-bit rows, 12.8 -> 9.9 us at G = 1; 8 x 32 16.2 -> 15.4 us; 32 x 16
+  // bf16 26.2 -> 25.4 us).
+  constexpr int kMergeWaves = G * D / 2 >= 256 ? kTicketWaves : (G * D / 2 + 63) / 64;
+  if (w < kMergeWaves) {
+    int* const ticket = ticket_ + w * kTicketPitch;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    int old = 0;
+    if (lane == 0) old = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_readfirstlane(old) == splits - 1) {
+      if (lane == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);    // for the next launch
+      combine_splits<D, G>(P, L, part_, splits, lu, gu, __builtin_amdgcn_readfirstlane(w), lane);
+    }
   }
-  __syncthreads();
-  if (sm_last) combine_splits<D, G>(P, L, part_, splits, lu, gu, tid);
   TRACE(6);
 }
 
@@ -1384,10 +1394,11 @@ hipError_t launch_decode(const Pools& P, const DecodeLaunch& a, hipStream_t s, h
 }
 
 // ---- split-K scratch for callers that cannot allocate ---------------------------------------------
-// One file-scope array per GPU: the units' tickets first (zero between launches: the workgroup that draws a
-// unit's last ticket clears it), the splits' partials behind them.  The array's name is only a handle in host
+// One file-scope array per GPU: the units' tickets first (zero between launches: the wave that draws a last ticket
+// clears it), the splits' partials behind them.  The array's name is only a handle in host
 // code; its device address is looked up once per device and kept.
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+constexpr size_t kStaticTicketBytes = (size_t)kStaticUnits * kTicketWaves * kTicketPitch * sizeof(int);
+static __device__ __align__(256) unsigned char scratch[kStaticTicketBytes + kStaticPartBytes];
 constexpr int kMaxDevices = 64;
 static unsigned char* g_scratch_ptr[kMaxDevices] = {};
 
@@ -1406,8 +1417,8 @@ hipError_t static_scratch_setup() {
   e = hipGetSymbolAddress(reinterpret_cast<void**>(&ptr), HIP_SYMBOL(scratch));
   if (e != hipSuccess) return e;
   if (!ptr) return hipErrorInvalidSymbol;
-  hipLaunchKernelGGL(k_clear_words, dim3((kStaticUnits + 255) / 256), dim3(256), 0, nullptr,
-                     reinterpret_cast<unsigned*>(ptr), kStaticUnits);
+  constexpr int words = (int)(kStaticTicketBytes / sizeof(int));
+  hipLaunchKernelGGL(k_clear_words, dim3((words + 255) / 256), dim3(256), 0, nullptr, reinterpret_cast<unsigned*>(ptr), words);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) return e;
@@ -1422,8 +1433,8 @@ hipError_t static_scratch_get(float** part, int** ticket, size_t* part_floats) {
   if (dev < 0 || dev >= kMaxDevices || !g_scratch_ptr[dev]) return hipErrorNotInitialized;
   unsigned char* ptr = g_scratch_ptr[dev];
   *ticket = reinterpret_cast<int*>(ptr);
-  *part = reinterpret_cast<float*>(ptr + (size_t)kStaticUnits * sizeof(int));
-  *part_floats = (kStaticScratchBytes - (size_t)kStaticUnits * sizeof(int)) / sizeof(float);
+  *part = reinterpret_cast<float*>(ptr + kStaticTicketBytes);
+  *part_floats = kStaticPartBytes / sizeof(float);
   return hipSuccess;
 }
 

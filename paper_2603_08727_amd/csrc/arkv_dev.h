@@ -7,6 +7,7 @@ namespace arkv {
 
 constexpr int kGroup = 32;        // channels per (scale, zero) pair
 constexpr int kMaxSplits = 128;   // split-K factor of the decode attention, upper bound
+constexpr int kTicketWaves = 4, kTicketPitch = 32;   // tickets per unit, ints between them (a 128-byte line each)
 constexpr int kMaxLayersPerLaunch = 64;
 constexpr int kMaxUnitsKnown = 64;     // launches with at most this many units can carry host-known token counts
 
@@ -76,7 +77,8 @@ struct Pools {
   float*    qscale;     // [kRing][LU] softmax scale * log2(e) those queries were used with
   float*    part;       // [LU][max_splits][G][D+2] split-K partials: acc[D], max, sum
   int       max_splits;
-  int*      ticket;     // [LU] splits of the unit finished in the current launch (0 between launches)
+  int*      ticket;     // [LU][kTicketWaves][kTicketPitch] splits of the unit whose wave w is done in the current launch
+                        // (0 between launches), one per cache line
   float*    outf;       // [LU][G][D] fp32 output of the latest step (parity hook)
   int32_t*  n_o;        // [LU] Original target of the unit's layer/sequence
   int32_t*  nb;         // [LU] survivors outside the window (n_o + n_q) of the unit's layer/sequence
@@ -162,8 +164,8 @@ struct PrefillLaunch {
 hipError_t launch_decode(const Pools& P, const DecodeLaunch& a, hipStream_t s, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);  // ev0/ev1: recorded around the attention kernel
 // Split-K scratch in static device memory (for the entry point that must not allocate): one array per GPU.
-constexpr size_t kStaticScratchBytes = 4u << 20;   // tickets of up to kStaticUnits units, then partials
-constexpr int kStaticUnits = 4096;
+constexpr int kStaticUnits = 4096;                 // units with a ticket line
+constexpr size_t kStaticPartBytes = (4u << 20) - kStaticUnits * 4;   // partials
 hipError_t static_scratch_setup();                  // once per device, with that device current (synchronous)
 hipError_t static_scratch_get(float** part, int** ticket, size_t* part_floats);   // pointers for the current device
 // Profiling builds only (built = false otherwise): in-kernel timestamps of the latest launches.

@@ -249,7 +249,7 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   A(qkc, LU * P.capQ * CB) A(qvc, LU * P.capQv * CB)
   A(qkm, LU * P.capQ * NG) A(qvm, LU * P.capQv * MH)
   A(qpos, LU * P.capQ) A(qacc, LU * P.capQ)
-  A(cnt, LU) A(fin, kRing * LU * G) A(qprev, kRing * LU * G * D) A(qscale, kRing * LU) A(part, LU * (size_t)P.max_splits * G * (D + 2)) A(outf, LU * G * D) A(n_o, LU) A(nb, LU) A(ticket, LU)
+  A(cnt, LU) A(fin, kRing * LU * G) A(qprev, kRing * LU * G * D) A(qscale, kRing * LU) A(part, LU * (size_t)P.max_splits * G * (D + 2)) A(outf, LU * G * D) A(n_o, LU) A(nb, LU) A(ticket, LU * kTicketWaves * kTicketPitch)
   A(keys, LU * (size_t)(P.capO + P.capQ)) A(thr, LU * 2) A(plan, LU * (size_t)P.plan_stride)
 #undef A
   hipError_t e = hipSuccess;
@@ -261,7 +261,7 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   if (e == hipSuccess) e = hipMemset(P.qvc, 0, LU * P.capQv * CB);
   if (e == hipSuccess) e = hipMemset(P.qvm, 0, LU * P.capQv * MH * sizeof(uint16_t));
   if (e == hipSuccess) e = hipMemset(P.cnt, 0, LU * sizeof(int2));
-  if (e == hipSuccess) e = hipMemset(P.ticket, 0, LU * sizeof(int));
+  if (e == hipSuccess) e = hipMemset(P.ticket, 0, LU * kTicketWaves * kTicketPitch * sizeof(int));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->stat_ticket), (size_t)c->cfg.batch * sizeof(int));
   if (e == hipSuccess) e = hipMemset(c->stat_ticket, 0, (size_t)c->cfg.batch * sizeof(int));
   if (e == hipSuccess) e = hipMemset(P.fin, 0, kRing * LU * G * sizeof(float2));

@@ -27,7 +27,7 @@ from paper_2603_08727_amd import binding as A, synth   # noqa: E402
 PHASES = ["start", "first tile requested", "bf16 rows", "new token", "packed rows", "reduce + partial stored",
           "ticket (+ merge)"]
 MERGE_PHASES = ["partial stored -> merge entered (acknowledgements, ticket)", "loads issued", "weights reduced",
-                "barrier", "accumulated", "stored"]
+                "weights readable", "accumulated", "stored"]
 
 
 def dist(x):
