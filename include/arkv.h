@@ -236,7 +236,7 @@ int arkv_debug_time_attend(arkv_cache* cache, int32_t enable);
 int arkv_debug_attend_time(arkv_cache* cache, double* total_ms, int64_t* launches);
 
 /* Measurement hook: launch shape of the kernels, for sweeps.  wg_target: workgroups a decode launch aims at
- * when it picks its split-K factor (default 512 = two per compute unit); packed_weight: cost of a packed row in
+ * when it picks its split-K factor (default: one or two per compute unit, by units and budgets); packed_weight: cost of a packed row in
  * sixteenths of a bf16 row when rows are dealt to the splits (default: 10, or 16 for launches of at most 256
  * workgroups); prefill_chunk: keys per workgroup of the prefill scorer (multiple of 128, at most 8192; default:
  * 1024, halved while the grid would be small, or, with more than 256 query rows per kv-head, what makes the

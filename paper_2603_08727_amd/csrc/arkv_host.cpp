@@ -66,7 +66,7 @@ struct arkv_cache {
   // measurement hook: events around the attention kernel
   int prefill_chunk = 1024; // keys per workgroup of the prefill scorer (halved while the grid would be small)
   bool prefill_chunk_fixed = false;   // set through the launch-shape hook: taken as it is
-  int wg_target = 512;      // workgroups per decode launch the split-K factor aims at
+  int wg_target = 0;        // launch-shape hook: workgroups per decode launch the split-K factor aims at; 0 = split_factor
   int wq = 0;               // cost of a packed row in sixteenths of a bf16 row; 0 = by launch shape (decode_impl)
   float* attn_outf = nullptr;   // parity hook: fp32 copy of the prefill attention's output (caller's device buffer)
   bool timing = false;
@@ -475,6 +475,35 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
   return ARKV_OK;
 }
 
+// Split-K factor of a launch.  Whole workgroups per CU: a grid a little over one or two workgroups per CU runs a round
+// more (40 units, bf16: 25.0 us per call at 6 splits = 240 workgroups, 26.0 at 12 = 480, 32.2 at 7 = 280, 29.6 at 16 =
+// 640).  One workgroup per CU (8 to 24 units: 10-15 % faster than two, the merge has half the partials) unless packed
+// rows are many: their loop is bound by latency and needs the second workgroup once every CU has long ranges (32 units
+// x 8192, a third packed: 21.7 us at 16 splits, 23.5 at 8; all bf16: 22.2 us at 8, 23.3 at 16).  Whether a cache can hold
+// packed rows follows from its budgets, not from its counts: the factor decides the order of fp32 sums, so it must not
+// depend on when a count arrives.
+// At least 128 rows (two tiles per wave) per split: below that the merge of more partials costs more than the shorter
+// loops save (measured on the 8K-context shape).
+static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int n_units, int live) {
+  int splits;
+  if (c->wg_target > 0) {                          // launch-shape hook
+    splits = (c->wg_target + n_units / 2) / n_units;
+    if (splits > 32) splits = (splits + 1) / 2;
+  } else {
+    bool packed = false;
+    for (int i = 0; i < n; ++i) {
+      const LayerState& li = c->layers[(size_t)(layer_begin + i)];
+      if (li.n_tailors > 0 || c->cfg.capacity_tokens < li.T)
+        for (int32_t no : li.n_o) packed = packed || no < c->b;
+    }
+    const int one = 256 / n_units, two = 512 / n_units;
+    splits = (n_units < 32 || !packed) && one * n_units >= 232 ? one : two;
+    if (n_units < 8) splits = one;                  // (more than 32 splits: the merge outweighs a second workgroup)
+  }
+  splits = std::min(splits, std::max(1, live / 128));
+  return std::max(1, std::min(splits, c->P.max_splits));
+}
+
 // One decode step of n layers in the same state.  static_scratch: the split-K partials and tickets of this launch
 // live in the library's static device array instead of the cache's own buffers.
 static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void* q, const void* k_new,
@@ -500,14 +529,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   a.v_new = static_cast<const uint16_t*>(v_new);
   a.out = static_cast<uint16_t*>(out);
   a.unit_begin = layer_begin * U; a.n_units = n * U; a.units_per_layer = U;
-  // split-K factor: enough workgroups to fill the chip, at least 128 rows (two tiles per wave) each: below
-  // that the merge of more partials costs more than the shorter loops save (measured on the 8K-context shape)
-  int splits = (c->wg_target + a.n_units / 2) / a.n_units;
-  // few units: beyond 32 splits the merge (one workgroup pulls every partial of its unit) costs more than the
-  // second workgroup per CU gains, so such launches use one workgroup per CU
-  if (splits > 32) splits = (splits + 1) / 2;
-  splits = std::min(splits, std::max(1, l0.live / 128));
-  a.splits = std::max(1, std::min(splits, c->P.max_splits));
+  a.splits = split_factor(c, layer_begin, n, a.n_units, l0.live);
   a.part_unit0 = 0;
   Pools pools = c->P;                 // by value: the launch may point the split-K scratch elsewhere
   if (static_scratch) {
