@@ -83,9 +83,10 @@ struct Pools {
   int32_t*  n_o;        // [LU] Original target of the unit's layer/sequence
   int32_t*  nb;         // [LU] survivors outside the window (n_o + n_q) of the unit's layer/sequence
   // tailor scratch
-  uint64_t* keys;       // [LU][capO+capQ] selection keys of the latest tailor (0 = not eligible)
-  uint64_t* thr;        // [LU][2] keys of rank n_o and rank b
-  int32_t*  plan;       // [LU][kPlanHdr + 2*capO + 3*capQ... ] see arkv_tailor.hip
+  uint64_t* keys;       // [LU][capO+capQ] selection keys of the latest tailor's rows (0 = not eligible), O pool slots first; the
+                        // plan header says how many slots of either pool held a row
+  uint64_t* thr;        // [LU][2] a commit's keys of rank n_o and rank b
+  int32_t*  plan;       // [LU][plan_stride] see k_tailor_choose
   int       plan_stride;
 };
 
@@ -132,6 +133,8 @@ struct TailorLaunch {
   int window;
   float gamma;
   int n_pending, slot;  // pending steps to add to (s1,s2) before ranking; slot the NEXT step would write
+  int max_rows;         // no unit holds more rows than this
+  int few_moves;        // 1: a tailor at every step, which moves a few rows per unit
 };
 
 struct CommitLaunch {
@@ -173,10 +176,12 @@ hipError_t phase_trace_decode(int which, unsigned long long* host, int n_wg, boo
 hipError_t phase_trace_attn(unsigned long long* host, bool* built);
 hipError_t launch_flush_scores(const Pools& P, int unit_begin, int n_units, int n_pending, int slot, hipStream_t s);
 hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s);
-hipError_t launch_commit(const Pools& P, const CommitLaunch& a, uint64_t* commit_keys /*[U][T]*/, hipStream_t s);
-// n_o_seq, nb_seq: HOST [batch]; written to the units of one layer (unit_begin = layer * U) on the stream
-hipError_t launch_set_budgets(const Pools& P, int unit_begin, int hkv, int batch, const int32_t* n_o_seq,
-                              const int32_t* nb_seq, hipStream_t s);
+// n_o_seq, nb_seq: HOST [sequences], the layer's budgets, stored for the layer's units on the stream.  commit_keys: scratch of
+// commit_scratch_words words, only used when a.select: keys [U][T] (read by the debug hook), then per block of 1024
+// positions the rows in front of it
+hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
+                         uint64_t* commit_keys, hipStream_t s);
+size_t commit_scratch_words(int n_units, int T);
 // Causal prefill attention of T_q queries (positions [T - T_q, T)) over T keys.
 struct AttnLaunch {
   const uint16_t* q;      // [B][Hq][Tq][D]

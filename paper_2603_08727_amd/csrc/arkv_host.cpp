@@ -438,11 +438,10 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (T >= N) {      // the key scratch of the first tailor; sized before anything is launched or recorded
-    int rc = grow(&c->ckeys, &c->ckeys_cap, (size_t)U * T);
+    int rc = grow(&c->ckeys, &c->ckeys_cap, commit_scratch_words(U, T));
     if (rc != ARKV_OK) return rc;
   }
   for (int s = 0; s < cfg.batch; ++s) ls.n_o[(size_t)s] = no_seq[(size_t)s];
-  HIP_TRY(launch_set_budgets(c->P, layer * U, cfg.n_kv_heads, cfg.batch, no_seq.data(), nb_seq.data(), st));
   CommitLaunch a;
   a.k = static_cast<const uint16_t*>(k);
   a.v = static_cast<const uint16_t*>(v);
@@ -451,7 +450,7 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
   a.T = T; a.window = W; a.gamma = cfg.gamma;
   a.select = T >= N ? 1 : 0;
   if (a.select) { c->ckeys_layer = layer; c->ckeys_T = T; }
-  HIP_TRY(launch_commit(c->P, a, c->ckeys, st));
+  HIP_TRY(launch_commit(c->P, a, cfg.n_kv_heads, no_seq.data(), nb_seq.data(), c->ckeys, st));
   ls.committed = true; ls.T = T; ls.P = T - 1; ls.n_pending = 0; ls.slot = 0;
   if (a.select) {
     ls.live = std::min(c->b, T - W) + W;
@@ -595,6 +594,8 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     t.unit_begin = a.unit_begin; t.n_units = a.n_units;
     t.position = P; t.t_prefill = l0.T; t.window = W; t.gamma = cfg.gamma;
     t.n_pending = n_pending; t.slot = slot;
+    t.max_rows = cfg.budget_mode == 1 ? c->P.capO + c->P.capQ : N;      // live <= N in token mode
+    t.few_moves = cfg.tailor_policy == 1 ? 1 : 0;
     const hipError_t te = launch_tailor(c->P, t, st);
     if (te != hipSuccess) {
       // the attention of this step is on the stream, the tailor is not (or only partly): the device-side state of
@@ -757,6 +758,14 @@ int arkv_debug_last_tailor_scores(arkv_cache* c, int32_t layer, int32_t max_toke
   } else {
     per = (size_t)(c->P.capO + c->P.capQ);
     rc = fetch(keys, (const uint64_t*)c->P.keys + (size_t)layer * U * per, U * per);
+    // slots that held no row keep an older tailor's key
+    for (size_t u = 0; rc == ARKV_OK && u < U; ++u) {
+      std::vector<int32_t> hdr;
+      rc = fetch(hdr, (const int32_t*)c->P.plan + ((size_t)layer * U + u) * (size_t)c->P.plan_stride, (size_t)kPlanHdr);
+      if (rc != ARKV_OK) break;
+      for (size_t i = (size_t)hdr[PL_CO_OLD]; i < (size_t)c->P.capO; ++i) keys[u * per + i] = 0;
+      for (size_t i = (size_t)c->P.capO + (size_t)hdr[PL_CQ_OLD]; i < per; ++i) keys[u * per + i] = 0;
+    }
   }
   if (rc != ARKV_OK) return rc;
   for (size_t u = 0; u < U; ++u) {

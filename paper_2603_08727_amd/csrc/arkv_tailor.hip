@@ -1,15 +1,17 @@
 // Tri-state tailor (Sec. IV-F eq. 10, Alg. 1 "KV Cache Tailor") and the prompt commit.
 //
-//   keys    : heavy-hitter score S = mu + gamma*var (eq. 9) -> 64-bit selection key
+//   choose  : heavy-hitter score S = mu + gamma*var (eq. 9) -> 64-bit selection key
 //             (fp32 bits of S) << 32 | (0xFFFFFFFF - position); larger key = better rank, so ties in
 //             S go to the older token and the order is total.  0 marks "not eligible".
-//   select  : exact k-th largest key by an 8-pass radix select, for k = n_o and k = b
-//   plan    : classification of every slot and the lists that compact both pools in place
+//             exact k-th largest key by radix select, for k = n_o and k = b together;
+//             classification of every slot and the lists that compact both pools in place
 //   move    : quantise the demoted rows into free Q slots, fill holes with tail rows
 //
 // Everything that decides a state or a code is integer or single-rounded fp32 arithmetic in a fixed
 // order (this file must be compiled with -ffp-contract=off).
 #include <hip/hip_fp16.h>
+
+#include <type_traits>
 
 #include "arkv_dev.h"
 
@@ -30,257 +32,336 @@ __device__ __forceinline__ uint64_t make_key(float S, int pos) {
   return ((uint64_t)__float_as_uint(S) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos);
 }
 
-template <int G>
-__global__ __launch_bounds__(256) void k_tailor_keys(Pools P, TailorLaunch L) {
-  const int gu = L.unit_begin + blockIdx.y;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= P.capO + P.capQ) return;
-  const int2 cnt = P.cnt[gu];
-  uint64_t key = 0;
-  int pos = -1;
-  float2 acc;
-  if (i < P.capO) {
-    if (i < cnt.x) { pos = P.opos[(size_t)gu * P.capO + i]; acc = P.oacc[(size_t)gu * P.capO + i]; }
-  } else {
-    const int j = i - P.capO;
-    if (j < cnt.y) { pos = P.qpos[(size_t)gu * P.capQ + j]; acc = P.qacc[(size_t)gu * P.capQ + j]; }
-  }
-  if (pos >= 0 && pos < L.position + 1 - L.window) {
-    const int first = pos > L.t_prefill - L.window ? pos : L.t_prefill - L.window;
-    const int n = G * (L.position - first + 1);
-    key = make_key(hh_score(acc.x, acc.y, n, L.gamma), pos);
-  }
-  P.keys[(size_t)gu * (P.capO + P.capQ) + i] = key;
+// ------------------------------------------------------------------------------------------
+// exact k-th largest key for two ranks at once, by one workgroup of 1024 threads.
+//
+// Radix select, most significant digit first, on digits of 11, 11 and 10 bits of the score; the position is only looked
+// at where scores tie at a rank.  Bound by the one CU's instruction issue and the passes' barriers, not by bytes, hence:
+// the unit's scores as 32-bit words in LDS and rolled loops over them (in registers they took unrolled code with the
+// ballots of every round live at once: hundreds of spilled scalar registers), both ranks in the same passes, and wide
+// digits, which leave a handful of candidates after two passes.  Once the chosen bin holds a single candidate the
+// remaining passes are skipped.
+// ------------------------------------------------------------------------------------------
+constexpr uint32_t kNoScore = 0xFFFFFFFFu;   // not ranked (scores are >= 0)
+constexpr int kLdsRows = 32768;              // units of up to this many rows keep their scores in LDS (128 KB)
+constexpr int kRounds = 32;                  // rounds of 1024 rows per list chunk
+constexpr int kBins = 2048;
+template <typename Row>                      // Row: integer that holds a row index
+struct SelectLds {
+  int hist[2][kBins];
+  Row who[2][kBins];                         // a row that fell into the bin (the row, where only one did)
+  uint32_t wsum[2][16];
+  uint64_t thr[2];
+  int sel[2], k[2], cnt[2];
+};
+
+// inclusive sum over the wave's lanes up to this one (DPP: row shifts by 1, 2, 4, 8, then the rows' last lanes)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);
+  return dpp_add<0x143, 0xc>(v);
 }
 
-__global__ __launch_bounds__(256) void k_commit_keys(uint64_t* keys, CommitLaunch L, int G) {
-  const int lu = blockIdx.y;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= L.T) return;
-  uint64_t key = 0;
-  if (j < L.T - L.window) {
-    const float2 a = L.pre[(size_t)lu * L.T + j];
-    key = make_key(hh_score(a.x, a.y, G * L.window, L.gamma), j);
-  }
-  keys[(size_t)lu * L.T + j] = key;
+// A row's key against a threshold: score bits first, then the key's low word (asked for only where scores tie)
+template <typename Low>
+__device__ __forceinline__ bool key_ge(uint32_t sb, int row, uint64_t thr, Low&& low) {
+  const uint32_t ts = (uint32_t)(thr >> 32);
+  bool ge = sb > ts;
+  if (__any(sb == ts)) { if (sb == ts) ge = low(row) >= (uint32_t)thr; }
+  return ge;
 }
 
-// ------------------------------------------------------------------------------------------
-// exact k-th largest key.  grid (2, units): x = 0 -> k = n_o[unit], x = 1 -> k = nb[unit].
-// thr[unit][x] = that key, or ~0 when k = 0 (nothing qualifies).  k is clamped to the number of
-// eligible keys, so "fewer candidates than b" keeps everything.
-// ------------------------------------------------------------------------------------------
-// Radix select, most significant byte first.  The candidates of a pass often share their byte (scores of
-// one unit have the same exponent), which would serialise plain LDS atomics; lanes of a wave that hit the
-// same bin as the wave's first candidate are therefore counted with a ballot and added once.  The keys a thread owns stay in registers
-// for all passes when they fit (n <= 32 per thread), else they are re-read.  Keys are distinct (the position is part
-// of them), so once the chosen bin holds a single candidate the remaining passes are skipped: its owner writes it.
-constexpr int kSelKeys = 32;   // keys per thread held in registers
-__global__ __launch_bounds__(1024) void k_select(const uint64_t* keys_all, size_t stride, int n,
-                                                 const int32_t* n_o, const int32_t* nb, int unit_begin,
-                                                 uint64_t* thr) {
-  __shared__ int hist[256];
-  __shared__ int s_sel, s_k, s_tot, s_cnt;
-  const int lu = blockIdx.y, gu = unit_begin + lu, which = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-  const uint64_t* keys = keys_all + (size_t)lu * stride;
-  const bool in_regs = n <= 1024 * kSelKeys;
-  uint64_t mine[kSelKeys];
-  if (in_regs) {
-#pragma unroll
-    for (int j = 0; j < kSelKeys; ++j) {
-      const int i = tid + 1024 * j;
-      mine[j] = i < n ? keys[i] : 0;
+// each(f) must call f(score bits, row) for every row this thread owns (kNoScore: not a candidate); key(row) = a candidate's
+// key, for any thread.  sm.thr[x] = key of rank k_x, or ~0 when k_x = 0 or there
+// is no candidate (nothing qualifies); k_x is clamped to the number of candidates, so "fewer candidates than b" keeps
+// everything.  Ends with a barrier.
+template <typename Row, typename Each, typename Key>
+__device__ __forceinline__ void select_two(Each&& each, Key&& key, int k0, int k1, SelectLds<Row>& sm) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  uint32_t prefix[2] = {0, 0};               // digits found so far: of the score, then (tie) of the low word
+  uint32_t score[2] = {0, 0};                // passes 3..5: the rank's whole score
+  int k[2] = {k0, k1};
+  bool done[2] = {k0 <= 0, k1 <= 0};
+  if (tid < 2) sm.thr[tid] = ~0ull;
+  int shift = 32;
+  for (int pass = 0; pass < 6; ++pass) {
+    if (done[0] && done[1]) break;
+    const bool tie = pass >= 3;              // scores are used up: digits of the low word among equal scores
+    if (pass == 3) {
+      shift = 32;
+      for (int x = 0; x < 2; ++x) { score[x] = prefix[x]; prefix[x] = 0; }
     }
-  }
-  int k = which == 0 ? n_o[gu] : nb[gu];
-  uint64_t prefix = 0;
-  for (int pass = 0; pass < 8; ++pass) {
-    const int shift = 56 - 8 * pass;
-    if (tid < 256) hist[tid] = 0;
-    __syncthreads();
-    auto count = [&](uint64_t key) {
-      bool cand = key != 0 && (pass == 0 || (key >> (shift + 8)) == prefix);
-      const int bin = (int)((key >> shift) & 255);
-      const unsigned long long todo = __ballot(cand);
-      if (todo) {
-        // the bin of the wave's first candidate is counted once for all lanes that share it (the common
-        // case in the leading bytes); whoever differs adds for itself, to bins with little contention
-        const int leader = __ffsll((long long)todo) - 1;
-        const int lb = __shfl(bin, leader);
-        const unsigned long long same = __ballot(cand && bin == lb);
-        if (lane == leader) atomicAdd(&hist[lb], __popcll(same));
-        else if (cand && bin != lb) atomicAdd(&hist[bin], 1);
-      }
-    };
-    if (in_regs) {
-#pragma unroll
-      for (int j = 0; j < kSelKeys; ++j)
-        if (1024 * j < n) count(mine[j]);               // uniform: whole rounds past the end are skipped
-    } else {
-      for (int i0 = 0; i0 < n; i0 += 1024) count(i0 + tid < n ? keys[i0 + tid] : 0);
-    }
-    __syncthreads();
-    // wave 0: lane l owns bins 4l..4l+3; ge(bin) = candidates in bins >= bin
-    if (tid < 64) {
-      int h[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h[i] = hist[4 * tid + i];
-      const int own = h[0] + h[1] + h[2] + h[3];
-      int above = own;                                   // inclusive suffix sum over lanes
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_down(above, o);
-        if (tid + o < 64) above += t;
-      }
-      if (pass == 0 && tid == 0) s_tot = above;
-      const int total = __shfl(above, 0);
-      int kk = k;
-      if (pass == 0 && kk > total) kk = total;           // fewer candidates than k: keep them all
-      int ge = above - own;                              // candidates in bins of higher lanes
-#pragma unroll
-      for (int i = 3; i >= 0; --i) {
-        const int gt = ge;
-        ge += h[i];
-        if (kk > 0 && gt < kk && kk <= ge) { s_sel = 4 * tid + i; s_k = kk - gt; s_cnt = h[i]; }
-      }
-    }
+    const int width = pass % 3 == 2 ? 10 : 11;
+    shift -= width;
+    const bool shared = prefix[0] == prefix[1] && score[0] == score[1];    // both ranks still look at the same candidates
+    const bool use0 = !done[0] || shared, use1 = !done[1] && !shared;
+    const int top = kBins - 1 - 2 * tid;     // this thread's bins: top and top - 1
+    *reinterpret_cast<int2*>(&sm.hist[0][top - 1]) = make_int2(0, 0);
+    *reinterpret_cast<int2*>(&sm.hist[1][top - 1]) = make_int2(0, 0);
     __syncthreads();
     if (pass == 0) {
-      if (k > s_tot) k = s_tot;
-      if (k <= 0) {
-        if (tid == 0) thr[(size_t)gu * 2 + which] = ~0ull;
-        return;
-      }
+      // leading digits are often shared (scores of one unit have few exponents): the second histogram is free in this
+      // pass, so odd lanes count there and half as many lanes meet on a bin
+      each([&](uint32_t sb, int) {
+        if (sb != kNoScore) atomicAdd(&sm.hist[lane & 1][sb >> 21], 1);
+      });
+    } else if (!tie) {
+      const int up = shift + width;
+      each([&](uint32_t sb, int row) {
+        // (kNoScore never matches: a prefix comes from scores below 2^31)
+        const uint32_t hi = sb >> up;
+        if ((use0 && hi == prefix[0]) || (use1 && hi == prefix[1])) {
+          const int h = use0 && hi == prefix[0] ? 0 : 1, bin = (int)__builtin_amdgcn_ubfe(sb, shift, width);
+          atomicAdd(&sm.hist[h][bin], 1);
+          sm.who[h][bin] = (Row)row;
+        }
+      });
+    } else {
+      each([&](uint32_t sb, int row) {
+        const bool c0 = use0 && sb == score[0], c1 = use1 && sb == score[1];
+        if (c0 || c1) {
+          const uint32_t lw = (uint32_t)key(row), hi = pass == 3 ? 0u : lw >> (shift + width);
+          const int bin = (int)__builtin_amdgcn_ubfe(lw, shift, width);
+          if (c0 && hi == prefix[0]) { atomicAdd(&sm.hist[0][bin], 1); sm.who[0][bin] = (Row)row; }
+          if (c1 && hi == prefix[1]) { atomicAdd(&sm.hist[1][bin], 1); sm.who[1][bin] = (Row)row; }
+        }
+      });
     }
-    prefix = (prefix << 8) | (uint64_t)s_sel;
-    k = s_k;
-    const bool single = s_cnt == 1;                      // one candidate left: it is the answer
     __syncthreads();
-    if (single && pass < 7) {
-      auto claim = [&](uint64_t key) {
-        if (key != 0 && (key >> shift) == prefix) thr[(size_t)gu * 2 + which] = key;
-      };
-      if (in_regs) {
+    // ge = candidates in bins top - 1 and above
+    int2 a = *reinterpret_cast<const int2*>(&sm.hist[0][top - 1]);
+    const int2 b = *reinterpret_cast<const int2*>(&sm.hist[1][top - 1]);
+    if (pass == 0) { a.x += b.x; a.y += b.y; }
+    uint32_t ge0 = wave_prefix_sum((uint32_t)(a.x + a.y)), ge1 = wave_prefix_sum((uint32_t)(b.x + b.y));
+    if (lane == 63) { sm.wsum[0][w] = ge0; sm.wsum[1][w] = ge1; }
+    __syncthreads();
+    uint32_t tot0 = 0;
 #pragma unroll
-        for (int j = 0; j < kSelKeys; ++j)
-          if (1024 * j < n) claim(mine[j]);
-      } else {
-        for (int i0 = 0; i0 < n; i0 += 1024) claim(i0 + tid < n ? keys[i0 + tid] : 0);
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t s0 = sm.wsum[0][i], s1 = sm.wsum[1][i];
+      tot0 += s0;
+      if (i < w) { ge0 += s0; ge1 += s1; }
+    }
+    if (pass == 0) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        if (k[x] > (int)tot0) k[x] = (int)tot0;         // fewer candidates than k: keep them all
+        if (k[x] <= 0) done[x] = true;
       }
-      return;
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      if (done[x]) continue;
+      const bool first = x == 0 || shared;
+      const int hi_cnt = first ? a.y : b.y, lo_cnt = first ? a.x : b.x;
+      const int g = (int)(first ? ge0 : ge1);                         // >= bin top - 1
+      const int above = g - hi_cnt - lo_cnt;                          // > bin top
+      if (above < k[x] && k[x] <= above + hi_cnt) { sm.sel[x] = top; sm.k[x] = k[x] - above; sm.cnt[x] = hi_cnt; }
+      else if (above + hi_cnt < k[x] && k[x] <= g) { sm.sel[x] = top - 1; sm.k[x] = k[x] - above - hi_cnt; sm.cnt[x] = lo_cnt; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      if (done[x]) continue;
+      prefix[x] = (prefix[x] << width) | (uint32_t)sm.sel[x];
+      k[x] = sm.k[x];
+      if (sm.cnt[x] == 1 && pass > 0) {                  // one candidate left
+        if (tid == 0) sm.thr[x] = key((int)sm.who[x == 0 || shared ? 0 : 1][sm.sel[x]]);
+        done[x] = true;
+      }
     }
   }
-  if (tid == 0) thr[(size_t)gu * 2 + which] = prefix;
+  __syncthreads();
 }
 
 // ------------------------------------------------------------------------------------------
-// block-wide exclusive scan of a packed counter (five 12-bit fields), 1024 threads
+// block-wide exclusive scan of NF words of packed counters, 1024 threads; ends with a barrier
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t* sm /*[17]*/, uint64_t& total) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  uint64_t inc = v;
+template <int NF>
+__device__ __forceinline__ void block_excl_scan(uint32_t (&v)[NF], uint32_t (*sm)[16] /*[NF][16]*/, uint32_t (&total)[NF]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t inc[NF];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t t = __shfl_up(inc, o);
-    if (lane >= o) inc += t;
-  }
-  if (lane == 63) sm[w] = inc;
-  __syncthreads();
-  if (tid == 0) {
-    uint64_t run = 0;
-    for (int i = 0; i < 16; ++i) { const uint64_t t = sm[i]; sm[i] = run; run += t; }
-    sm[16] = run;
+  for (int f = 0; f < NF; ++f) {
+    inc[f] = wave_prefix_sum(v[f]);
+    if (lane == 63) sm[f][w] = inc[f];
   }
   __syncthreads();
-  const uint64_t res = sm[w] + inc - v;
-  total = sm[16];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    uint32_t before = 0;
+    total[f] = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t t = sm[f][i];
+      total[f] += t;
+      if (i < w) before += t;
+    }
+    v[f] = before + inc[f] - v[f];
+  }
   __syncthreads();
-  return res;
 }
 
-constexpr int F0 = 0, F1 = 12, F2 = 24, F3 = 36, F4 = 48;
-__device__ __forceinline__ int fld(uint64_t v, int f) { return (int)((v >> f) & 0xFFFu); }
+// Keys of a unit's rows and their list positions.  A workgroup goes through its rows in rounds of 1024 (thread t: row
+// 1024 j + t), so a wave's ballots of a round cover 64 consecutive rows; per (round, wave) the counts are kept in LDS,
+// scanned once per chunk of kRounds rounds, and every row then knows its place in each list.
+struct ListLds {
+  uint32_t c[3][kRounds * 16];               // two counts of 16 bits each (a chunk has at most 32768 rows), then their sums
+};
+
+// a row's place behind the rows before it in the wave that set the same flag
+__device__ __forceinline__ int place(unsigned long long flags, int lane) {
+  return __popcll(flags & ((1ull << lane) - 1ull));
+}
 
 // ------------------------------------------------------------------------------------------
-// in-place tailor plan.  One workgroup per unit.
+// in-place tailor: keys (eq. 9's score per row), the two thresholds, and the lists that compact both pools.
+// One workgroup per unit, one launch.  Keys, a select per rank and the lists were three (5 + 18 + 15 us at 32 units x 8192
+// rows, 26 us now; a step with a tailor 85 -> 68 us; 8 units x 32000 rows 182 -> 118 us).
 //   plan: header | ohole[capO] | omov[capO] | dem[capO] | qfree[capQ] | qmov[capQ]
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_tailor_plan(Pools P, TailorLaunch L) {
-  __shared__ uint64_t sm[17];
+template <int G, bool IN_LDS>
+__global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L) {
+  extern __shared__ uint32_t row_word[];                    // IN_LDS: score of row i, later its fate
+  __shared__ SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
+  __shared__ ListLds lists;
+  __shared__ uint32_t scan_sm[3][16];
   __shared__ int tot[3];
-  const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x;
+  const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int2 cnt = P.cnt[gu];
-  const int cO = cnt.x, cQ = cnt.y;
-  const uint64_t* keys = P.keys + (size_t)gu * (P.capO + P.capQ);
-  const uint64_t thr_o = P.thr[(size_t)gu * 2], thr_b = P.thr[(size_t)gu * 2 + 1];
-  int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  int32_t* ohole = plan + kPlanHdr;
-  int32_t* omov = ohole + P.capO;
-  int32_t* dem = omov + P.capO;
-  int32_t* qfree = dem + P.capO;
-  int32_t* qmov = qfree + P.capQ;
-
-  // totals
+  const int cO = cnt.x, cQ = cnt.y, n = cO + cQ;           // rows: the O pool's, then the Q pool's
+  uint64_t* keys = P.keys + (size_t)gu * (P.capO + P.capQ);
+  const int32_t* opos = P.opos + (size_t)gu * P.capO;
+  const int32_t* qpos = P.qpos + (size_t)gu * P.capQ;
+  const float2* oacc = P.oacc + (size_t)gu * P.capO;
+  const float2* qacc = P.qacc + (size_t)gu * P.capQ;
+  const int slot_q = P.capO - cO;                           // row i >= cO: key slot i + slot_q
+  const int rounds = (n + 1023) / 1024;
+  // (a barrier of the selection stands between these stores and another thread's read of a key)
+  constexpr int BATCH = 4;                                  // rows requested together (one by one, a memory round trip each)
+  for (int j0 = 0; j0 < rounds; j0 += BATCH) {
+    int pos[BATCH];
+    float2 acc[BATCH];
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = min(1024 * (j0 + j) + tid, n - 1);
+      pos[j] = i < cO ? opos[i] : qpos[i - cO];
+      acc[j] = i < cO ? oacc[i] : qacc[i - cO];
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int i = 1024 * (j0 + j) + tid;
+      uint64_t key = 0;
+      if (pos[j] < L.position + 1 - L.window) {
+        const int first = pos[j] > L.t_prefill - L.window ? pos[j] : L.t_prefill - L.window;
+        key = make_key(hh_score(acc[j].x, acc[j].y, G * (L.position - first + 1), L.gamma), pos[j]);
+      }
+      if (i < n) {
+        keys[i < cO ? i : i + slot_q] = key;
+        if constexpr (IN_LDS) row_word[i] = key ? (uint32_t)(key >> 32) : kNoScore;
+      }
+    }
+  }
+  auto key_of = [&](int i) -> uint64_t { return keys[i < cO ? i : i + slot_q]; };
+  auto score_of = [&](int i) -> uint32_t {
+    if constexpr (IN_LDS) return row_word[i];
+    const uint64_t k = key_of(i);
+    return k ? (uint32_t)(k >> 32) : kNoScore;
+  };
+  auto low = [&](int i) { return (uint32_t)key_of(i); };
+  auto each = [&](auto&& f) {
+    for (int j = 0; j < rounds; ++j) {
+      const int i = 1024 * j + tid;
+      f(i < n ? score_of(i) : kNoScore, i);
+    }
+  };
   if (tid < 3) tot[tid] = 0;
-  __syncthreads();
-  int keepO = 0, nDem = 0, keepQ = 0, nElig = 0;
-  for (int i = tid; i < cO; i += 1024) {
-    const uint64_t k = keys[i];
-    const bool keep = k == 0 || k >= thr_o;
-    keepO += keep;
-    nDem += (!keep && k >= thr_b);
-    nElig += k != 0;
+  select_two(each, key_of, P.n_o[gu], P.nb[gu], sel);
+  const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
+
+  // what becomes of a row: 1 stays in its pool, 2 is demoted, 0 is evicted (window rows stay)
+  auto classify = [&](int i) -> uint32_t {
+    if (i >= n) return 0;
+    const uint32_t sb = score_of(i);
+    const bool o = i < cO, cand = sb != kNoScore;
+    const bool geb = cand && key_ge(sb, i, thr_b, low), geo = cand && key_ge(sb, i, thr_o, low);
+    return (o ? !cand || geo : geb) ? 1u : (o && geb) ? 2u : 0u;
+  };
+  auto fate_of = [&](int i) -> uint32_t {
+    if constexpr (IN_LDS) return i < n ? row_word[i] : 0u;
+    else return classify(i);
+  };
+  // rows that stay Original, are demoted, stay Quantized
+  int keepO = 0, nDem = 0, keepQ = 0;
+  for (int j = 0; j < rounds; ++j) {
+    const int i = 1024 * j + tid;
+    const uint32_t f = classify(i);
+    if constexpr (IN_LDS) { if (i < n) row_word[i] = f; }
+    keepO += __popcll(__ballot(f == 1 && i < cO));
+    nDem += __popcll(__ballot(f == 2));
+    keepQ += __popcll(__ballot(f == 1 && i >= cO));
   }
-  for (int i = tid; i < cQ; i += 1024) {
-    const uint64_t k = keys[P.capO + i];
-    keepQ += (k >= thr_b);
-    nElig += 1;
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    keepO += __shfl_xor(keepO, o); nDem += __shfl_xor(nDem, o); keepQ += __shfl_xor(keepQ, o);
-  }
-  if ((tid & 63) == 0) { atomicAdd(&tot[0], keepO); atomicAdd(&tot[1], nDem); atomicAdd(&tot[2], keepQ); }
+  if (lane == 0) { atomicAdd(&tot[0], keepO); atomicAdd(&tot[1], nDem); atomicAdd(&tot[2], keepQ); }
   __syncthreads();
   const int cOn = tot[0], nD = tot[1], cQn = tot[2] + nD;
 
-  // O pool lists
-  int base_hole = 0, base_mov = 0, base_dem = 0;
-  for (int c0 = 0; c0 < cO; c0 += 1024) {
-    const int i = c0 + tid;
-    bool hole = false, mov = false, d = false;
-    if (i < cO) {
-      const uint64_t k = keys[i];
-      const bool keep = k == 0 || k >= thr_o;
-      d = !keep && k >= thr_b;
-      hole = i < cOn && !keep;
-      mov = i >= cOn && keep;
+  int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
+  int32_t* ohole = plan + kPlanHdr;
+  int32_t* omov = ohole + P.capO;
+  int32_t* dem_ = omov + P.capO;
+  int32_t* qfree = dem_ + P.capO;
+  int32_t* qmov = qfree + P.capQ;
+  int base_hole = 0, base_mov = 0, base_dem = 0, base_free = 0, base_qmov = 0;
+  struct Flags { bool hole, mov, dem, fr, qm; };
+  auto flags = [&](int i) {
+    const uint32_t fate_ = fate_of(i);
+    Flags f{false, false, fate_ == 2, false, false};
+    if (i < cO) { f.hole = i < cOn && fate_ != 1; f.mov = i >= cOn && fate_ == 1; }
+    else if (i < n) { f.fr = i - cO < cQn && fate_ != 1; f.qm = i - cO >= cQn && fate_ == 1; }
+    return f;
+  };
+  for (int j0 = 0; j0 < rounds; j0 += kRounds) {
+    const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds, entries = 16 * nj;
+    for (int j = 0; j < nj; ++j) {
+      const Flags f = flags(1024 * (j0 + j) + tid);
+      const uint32_t hm = (uint32_t)__popcll(__ballot(f.hole)) | ((uint32_t)__popcll(__ballot(f.mov)) << 16);
+      const uint32_t df = (uint32_t)__popcll(__ballot(f.dem)) | ((uint32_t)__popcll(__ballot(f.fr)) << 16);
+      const uint32_t qm = (uint32_t)__popcll(__ballot(f.qm));
+      if (lane == 0) { lists.c[0][16 * j + w] = hm; lists.c[1][16 * j + w] = df; lists.c[2][16 * j + w] = qm; }
     }
-    const uint64_t v = ((uint64_t)hole << F0) | ((uint64_t)mov << F1) | ((uint64_t)d << F2);
-    uint64_t total;
-    const uint64_t ex = block_excl_scan(v, sm, total);
-    if (hole) ohole[base_hole + fld(ex, F0)] = i;
-    if (mov) omov[base_mov + fld(ex, F1)] = i;
-    if (d) dem[base_dem + fld(ex, F2)] = i;
-    base_hole += fld(total, F0); base_mov += fld(total, F1); base_dem += fld(total, F2);
-  }
-  // Q pool lists
-  int base_free = 0, base_qmov = 0;
-  const int qhi = cQ > cQn ? cQ : cQn;
-  for (int c0 = 0; c0 < qhi; c0 += 1024) {
-    const int i = c0 + tid;
-    bool fr = false, mv = false;
-    if (i < qhi) {
-      const bool keep = i < cQ && keys[P.capO + i] >= thr_b;
-      fr = i < cQn && !keep;
-      mv = i >= cQn && keep;
+    __syncthreads();
+    uint32_t v[3], total[3];
+#pragma unroll
+    for (int f = 0; f < 3; ++f) v[f] = tid < entries ? lists.c[f][tid] : 0;
+    block_excl_scan<3>(v, scan_sm, total);
+    if (tid < entries) { lists.c[0][tid] = v[0]; lists.c[1][tid] = v[1]; lists.c[2][tid] = v[2]; }
+    __syncthreads();
+    for (int j = 0; j < nj; ++j) {
+      const int i = 1024 * (j0 + j) + tid;
+      const Flags f = flags(i);
+      const uint32_t hm = lists.c[0][16 * j + w], df = lists.c[1][16 * j + w], qm = lists.c[2][16 * j + w];
+      const int ph = place(__ballot(f.hole), lane), pm = place(__ballot(f.mov), lane), pd = place(__ballot(f.dem), lane);
+      const int pf = place(__ballot(f.fr), lane), pq = place(__ballot(f.qm), lane);
+      if (f.hole) ohole[base_hole + (int)(hm & 0xFFFF) + ph] = i;
+      if (f.mov) omov[base_mov + (int)(hm >> 16) + pm] = i;
+      if (f.dem) dem_[base_dem + (int)(df & 0xFFFF) + pd] = i;
+      if (f.fr) qfree[base_free + (int)(df >> 16) + pf] = i - cO;
+      if (f.qm) qmov[base_qmov + (int)qm + pq] = i - cO;
     }
-    const uint64_t v = ((uint64_t)fr << F3) | ((uint64_t)mv << F4);
-    uint64_t total;
-    const uint64_t ex = block_excl_scan(v, sm, total);
-    if (fr) qfree[base_free + fld(ex, F3)] = i;
-    if (mv) qmov[base_qmov + fld(ex, F4)] = i;
-    base_free += fld(total, F3); base_qmov += fld(total, F4);
+    base_hole += (int)(total[0] & 0xFFFF); base_mov += (int)(total[0] >> 16);
+    base_dem += (int)(total[1] & 0xFFFF); base_free += (int)(total[1] >> 16);
+    base_qmov += (int)total[2];
+    if (j0 + kRounds < rounds) __syncthreads();            // the next chunk's counts go into the same table
   }
+  // slots behind the Q pool's old end
+  for (int i = tid; i < cQn - cQ; i += 1024) qfree[base_free + i] = cQ + i;
   if (tid == 0) {
     plan[PL_CO_NEW] = cOn; plan[PL_CQ_NEW] = cQn; plan[PL_N_DEM] = nD;
     plan[PL_N_QMOV] = base_qmov; plan[PL_N_OMOV] = base_mov;
@@ -391,14 +472,15 @@ __device__ __forceinline__ void quantize8_fp8(const float (&x)[8], uint2& codes,
   meta = sh;
 }
 
-// One wave: lanes [0,LPR) quantise the K row, lanes [LPR,2LPR) the V row, into Q slot dst of unit gu.
+// 2 LPR adjacent lanes (lane = 0 .. 2 LPR - 1 among them) quantise a token into Q slot dst of unit gu: lanes [0, LPR) the
+// K row, the others the V row.  A wave takes 64 / (2 LPR) tokens at once; every lane runs the arithmetic (the lane
+// exchanges need them active), lanes without store write nothing.
 template <int D, int BITS>
 __device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, const uint16_t* krow,
-                                              const uint16_t* vrow, int lane) {
+                                              const uint16_t* vrow, int lane, bool store) {
   constexpr int LPR = D / 8, CB = D * BITS / 8, NG = metas_per_row(D, BITS);
   const bool isv = lane >= LPR;
   const int sub = lane % LPR;
-  // all 64 lanes run the arithmetic (the lane exchanges need them active); lanes >= 2LPR redo V
   const uint16_t* src = (isv ? vrow : krow) + sub * 8;
   const uint4 raw = *reinterpret_cast<const uint4*>(src);
   float x[8];
@@ -413,10 +495,11 @@ __device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, c
     uint2 codes;
     uint32_t meta;
     quantize8_fp8<LPR>(x, codes, meta);
+    if (!store) return;
     if (lane < LPR) {
       *reinterpret_cast<uint2*>(cdst + ((sub & 3) * (D / 32) + (sub >> 2)) * 8) = codes;     // see kcode_index
       if (sub == 0) mdst[0] = meta;
-    } else if (lane < 2 * LPR) {
+    } else {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         vcu[vcode_index(dst, 8 * sub + i, CB, BITS)] = (uint8_t)((i < 4 ? codes.x >> (8 * i) : codes.y >> (8 * (i - 4))) & 0xffu);
@@ -425,12 +508,13 @@ __device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, c
   } else {
     uint32_t codes, meta;
     quantize8<BITS>(x, codes, meta);
+    if (!store) return;
     if (lane < LPR) {
       const int chunk = (sub & 3) * (D / 32) + (sub >> 2);                                   // see kcode_index
       if (BITS == 4) *reinterpret_cast<uint32_t*>(cdst + chunk * 4) = codes;
       else *reinterpret_cast<uint16_t*>(cdst + chunk * 2) = (uint16_t)codes;
       if ((sub & 3) == 0) mdst[sub >> 2] = meta;
-    } else if (lane < 2 * LPR) {
+    } else {
 #pragma unroll
       for (int i = 0; i < BITS; ++i) vcu[vcode_index(dst, BITS * sub + i, CB, BITS)] = (uint8_t)((codes >> (8 * i)) & 0xffu);
       if ((sub & 3) == 0) {
@@ -441,142 +525,278 @@ __device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, c
   }
 }
 
+// The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
+// Demoted rows into free Q slots (TPW tokens per wave at once), tail rows of the Q pool into holes.
 template <int D, int BITS>
-__global__ __launch_bounds__(256) void k_tailor_move_q(Pools P, TailorLaunch L) {
+__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int first, int waves, int lane) {
   constexpr int CB = D * BITS / 8, NG = metas_per_row(D, BITS);
-  const int gu = L.unit_begin + blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int LPT = 2 * (D / 8), TPW = 64 / LPT;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
   const int nD = plan[PL_N_DEM], nM = plan[PL_N_QMOV];
   const int32_t* dem = plan + kPlanHdr + 2 * P.capO;
   const int32_t* qfree = dem + P.capO;
   const int32_t* qmov = qfree + P.capQ;
-  for (int item = blockIdx.x * 4 + w; item < nD + nM; item += gridDim.x * 4) {
-    const int dst = qfree[item];
-    if (item < nD) {
-      const int src = dem[item];
-      const size_t o = (size_t)gu * P.capO + src;
-      quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, lane);
-      if (lane == 0) {
-        P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
-        P.qacc[(size_t)gu * P.capQ + dst] = P.oacc[o];
-      }
-    } else {
-      const int src = qmov[item - nD];
-      const size_t so = (size_t)gu * P.capQ + src, d_ = (size_t)gu * P.capQ + dst;
-      // K: code bytes, 4 per lane; V: one byte column per lane (token-minor blocks)
-      for (int b = lane * 4; b < CB; b += 256)
-        *reinterpret_cast<uint32_t*>(P.qkc + d_ * CB + b) = *reinterpret_cast<const uint32_t*>(P.qkc + so * CB + b);
-      uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
-      for (int b = lane; b < CB; b += 64) vcu[vcode_index(dst, b, CB, BITS)] = vcu[vcode_index(src, b, CB, BITS)];
-      constexpr int MH = vmeta_per_row(D, BITS);
-      uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
-      if (lane < MH) vmu[vmeta_index(dst, lane, MH)] = vmu[vmeta_index(src, lane, MH)];
-      if (lane < NG) P.qkm[d_ * NG + lane] = P.qkm[so * NG + lane];
-      if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = P.qacc[so]; }
+  const int t = lane / LPT, sl = lane % LPT;
+  for (int i0 = first * TPW; i0 < nD; i0 += waves * TPW) {
+    const int item = min(i0 + t, nD - 1), dst = qfree[item];
+    const size_t o = (size_t)gu * P.capO + dem[item];
+    quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, sl, i0 + t < nD);
+    if (sl == 0 && i0 + t < nD) {
+      P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
+      P.qacc[(size_t)gu * P.capQ + dst] = P.oacc[o];
     }
+  }
+  for (int item = first; item < nM; item += waves) {
+    const int dst = qfree[nD + item], src = qmov[item];
+    const size_t so = (size_t)gu * P.capQ + src, d_ = (size_t)gu * P.capQ + dst;
+    // K: code bytes, 4 per lane; V: one byte column per lane (token-minor blocks)
+    for (int b = lane * 4; b < CB; b += 256)
+      *reinterpret_cast<uint32_t*>(P.qkc + d_ * CB + b) = *reinterpret_cast<const uint32_t*>(P.qkc + so * CB + b);
+    uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
+    for (int b = lane; b < CB; b += 64) vcu[vcode_index(dst, b, CB, BITS)] = vcu[vcode_index(src, b, CB, BITS)];
+    constexpr int MH = vmeta_per_row(D, BITS);
+    uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
+    if (lane < MH) vmu[vmeta_index(dst, lane, MH)] = vmu[vmeta_index(src, lane, MH)];
+    if (lane < NG) P.qkm[d_ * NG + lane] = P.qkm[so * NG + lane];
+    if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = P.qacc[so]; }
   }
 }
 
+// Tail rows of the O pool into holes: after every demoted row of the unit has been read.
 template <int D>
-__global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) {
-  constexpr int LPR = D / 8;
-  const int gu = L.unit_begin + blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int first, int waves, int lane) {
+  constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
   const int nM = plan[PL_N_OMOV];
   const int32_t* ohole = plan + kPlanHdr;
   const int32_t* omov = ohole + P.capO;
-  for (int item = blockIdx.x * 4 + w; item < nM; item += gridDim.x * 4) {
+  const int t = lane / LPT, sl = lane % LPT, sub = sl % LPR;
+  uint16_t* base = sl < LPR ? P.ok : P.ov;
+  for (int item = first * TPW + t; item < nM; item += waves * TPW) {
     const size_t so = (size_t)gu * P.capO + omov[item], d_ = (size_t)gu * P.capO + ohole[item];
-    if (lane < 2 * LPR) {
-      uint16_t* base = lane < LPR ? P.ok : P.ov;
-      const int sub = lane % LPR;
-      *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
-    }
-    if (lane == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = P.oacc[so]; }
+    *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
+    if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = P.oacc[so]; }
   }
+}
+
+template <int D, int BITS>
+__global__ __launch_bounds__(256) void k_tailor_move_q(Pools P, TailorLaunch L) {
+  tailor_move_q<D, BITS>(P, L.unit_begin + blockIdx.y, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
+}
+
+// Both kinds of moves of a unit by one workgroup, for tailors that move a few rows each (the tailor-at-every-step policy):
+// one launch instead of two (6.6 + 5.0 us -> 7 us for 32 units).
+template <int D, int BITS>
+__global__ __launch_bounds__(1024) void k_tailor_move_few(Pools P, TailorLaunch L) {
+  const int gu = L.unit_begin + blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
+  tailor_move_q<D, BITS>(P, gu, w, 16, lane);
+  __syncthreads();                           // every demoted row has been read
+  tailor_move_o<D>(P, gu, w, 16, lane);
+  if (threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) {
+  const int gu = L.unit_begin + blockIdx.y;
+  const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
+  tailor_move_o<D>(P, gu, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
   if (blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
 }
 
 // ------------------------------------------------------------------------------------------
-// prompt commit: classification of prompt positions and scatter into the empty pools
-//   plan: header | osrc[capO] | qsrc[capQ]
+// prompt commit: scores of the prompt's positions, the two thresholds, and the survivors' way into the empty pools
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_commit_plan(Pools P, CommitLaunch L, const uint64_t* keys_all) {
-  __shared__ uint64_t sm[17];
-  const int lu = blockIdx.x, gu = L.unit_begin + lu, tid = threadIdx.x;
-  const uint64_t* keys = keys_all + (size_t)lu * L.T;
-  const uint64_t thr_o = P.thr[(size_t)gu * 2], thr_b = P.thr[(size_t)gu * 2 + 1];
-  int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  int32_t* osrc = plan + kPlanHdr;
-  int32_t* qsrc = osrc + P.capO;
-  int bo = 0, bq = 0;
-  // eight consecutive positions per thread and round: one block scan per 8192 positions (the two counts are
-  // carried in the halves of one 64-bit word), positions stay in ascending order
-  constexpr int E = 8;
-  for (int c0 = 0; c0 < L.T; c0 += 1024 * E) {
-    const int j0 = c0 + E * tid;
-    unsigned om = 0, qm = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if (j0 + e < L.T) {
-        const uint64_t k = keys[j0 + e];
-        const bool o = k == 0 || k >= thr_o;          // key 0 = window position
-        om |= (unsigned)o << e;
-        qm |= (unsigned)(!o && k >= thr_b) << e;
-      }
-    }
-    const uint64_t v = (uint64_t)__popc(om) | ((uint64_t)__popc(qm) << 32);
-    uint64_t total;
-    const uint64_t ex = block_excl_scan(v, sm, total);
-    int io = bo + (int)(ex & 0xFFFFFFFFu), iq = bq + (int)(ex >> 32);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      if ((om >> e) & 1u) osrc[io++] = j0 + e;
-      if ((qm >> e) & 1u) qsrc[iq++] = j0 + e;
-    }
-    bo += (int)(total & 0xFFFFFFFFu); bq += (int)(total >> 32);
+struct BudgetArgs { int n_o[64], nb[64]; };       // per sequence
+
+// Scores of the prompt's positions, over the whole chip (two IEEE divisions per position: in the one workgroup that
+// selects they took longer than the selection), and the layer's budgets (a launch of their own took 5 us).
+__global__ __launch_bounds__(256) void k_commit_keys(Pools P, CommitLaunch L, uint64_t* keys, int hkv, BudgetArgs budgets) {
+  const int lu = blockIdx.y;
+  if (hkv > 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    P.n_o[L.unit_begin + lu] = budgets.n_o[lu / hkv];
+    P.nb[L.unit_begin + lu] = budgets.nb[lu / hkv];
   }
-  if (tid == 0) { plan[PL_CO_NEW] = bo; plan[PL_CQ_NEW] = bq; P.cnt[gu] = make_int2(bo, bq); }
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= L.T) return;
+  uint64_t key = 0;
+  if (j < L.T - L.window) {
+    const float2 a = L.pre[(size_t)lu * L.T + j];
+    key = make_key(hh_score(a.x, a.y, P.G * L.window, L.gamma), j);
+  }
+  keys[(size_t)lu * L.T + j] = key;
 }
 
-template <int D, int BITS>
-__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L) {
-  constexpr int LPR = D / 8;
-  const int lu = blockIdx.y, gu = L.unit_begin + lu, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  const int32_t* osrc = plan + kPlanHdr;
-  const int32_t* qsrc = osrc + P.capO;
-  const int cO = L.select ? plan[PL_CO_NEW] : L.T, cQ = L.select ? plan[PL_CQ_NEW] : 0;
-  const uint16_t* K = L.k + (size_t)lu * L.T * D;
-  const uint16_t* V = L.v + (size_t)lu * L.T * D;
-  const float2* pre = L.pre + (size_t)lu * L.T;
-  for (int item = blockIdx.x * 4 + w; item < cO + cQ; item += gridDim.x * 4) {
-    if (item < cO) {
-      const int j = L.select ? osrc[item] : item;
-      const size_t d_ = (size_t)gu * P.capO + item;
-      if (lane < 2 * LPR) {
-        const uint16_t* src = lane < LPR ? K : V;
-        uint16_t* dst = lane < LPR ? P.ok : P.ov;
-        const int sub = lane % LPR;
-        *reinterpret_cast<uint4*>(dst + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(src + (size_t)j * D + sub * 8);
-      }
-      if (lane == 0) { P.opos[d_] = j; P.oacc[d_] = pre[j]; }
-    } else {
-      const int dst = item - cO, j = qsrc[dst];
-      quantize_into<D, BITS>(P, gu, dst, K + (size_t)j * D, V + (size_t)j * D, lane);
-      if (lane == 0) { P.qpos[(size_t)gu * P.capQ + dst] = j; P.qacc[(size_t)gu * P.capQ + dst] = pre[j]; }
+// One workgroup per unit: 36 us for 32 units x 32768 positions, where a select per rank and a pass that wrote the lists of
+// survivors took 39 + 19 us.  The two thresholds of a unit, and how many rows in front of every block of 1024 positions become Original and
+// Quantized (base [units][rounds]), from which k_commit_scatter places its rows.
+template <bool IN_LDS>
+__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, const uint64_t* keys_all, int2* base_all) {
+  extern __shared__ uint32_t row_word[];     // IN_LDS: the positions' scores
+  __shared__ SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
+  __shared__ uint32_t cnt[kRounds][16];      // per (round, wave): Original | Quantized << 16
+  const int lu = blockIdx.x, gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int T = L.T, rounds = (T + 1023) / 1024;
+  const int n_cand = T - L.window;           // positions behind them are the window
+  const uint64_t* keys = keys_all + (size_t)lu * T;
+  if constexpr (IN_LDS) {
+    constexpr int BATCH = 8;                 // positions requested together; a thread only reads what it stores here
+    for (int i0 = tid; i0 < n_cand; i0 += 1024 * BATCH) {
+      uint32_t v[BATCH];
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) v[b] = (uint32_t)(keys[min(i0 + 1024 * b, T - 1)] >> 32);
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b)
+        if (i0 + 1024 * b < n_cand) row_word[i0 + 1024 * b] = v[b];
     }
   }
-  if (!L.select && blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(L.T, 0);
+  auto score_of = [&](int i) -> uint32_t {
+    if constexpr (IN_LDS) return row_word[i];
+    else return (uint32_t)(keys[i] >> 32);
+  };
+  auto each = [&](auto&& f) {
+    for (int j = 0; j < rounds; ++j) {
+      const int i = 1024 * j + tid;
+      f(i < n_cand ? score_of(i) : kNoScore, i);
+    }
+  };
+  auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
+  select_two(each, key_of, P.n_o[gu], P.nb[gu], sel);
+  const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
+  int2* base = base_all + (size_t)lu * rounds;
+  int bo = 0, bq = 0;
+  for (int j0 = 0; j0 < rounds; j0 += kRounds) {
+    const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds;
+    for (int j = 0; j < nj; ++j) {
+      const int i = 1024 * (j0 + j) + tid;
+      bool o = i >= n_cand && i < T, q = false;
+      if (i < n_cand) {
+        const uint64_t k = key_of(i);
+        o = k >= thr_o;
+        q = !o && k >= thr_b;
+      }
+      const uint32_t c = (uint32_t)__popcll(__ballot(o)) | ((uint32_t)__popcll(__ballot(q)) << 16);
+      if (lane == 0) cnt[j][w] = c;
+    }
+    __syncthreads();
+    // lane j of wave 0: round j (kRounds <= 64)
+    if (w == 0) {
+      uint32_t o = 0, q = 0;
+      if (lane < nj)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { o += cnt[lane][i] & 0xFFFFu; q += cnt[lane][i] >> 16; }
+      const uint32_t io = wave_prefix_sum(o), iq = wave_prefix_sum(q);
+      if (lane < nj) base[j0 + lane] = make_int2(bo + (int)(io - o), bq + (int)(iq - q));
+      bo += __builtin_amdgcn_readlane((int)io, 63);
+      bq += __builtin_amdgcn_readlane((int)iq, 63);
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    P.thr[(size_t)gu * 2] = thr_o; P.thr[(size_t)gu * 2 + 1] = thr_b;
+    P.cnt[gu] = make_int2(bo, bq);
+  }
+}
+
+// The survivors of 1024 prompt positions into the pools: a workgroup lists them in LDS (positions stay in ascending
+// order), then copies the Original rows, several in flight per wave, and quantises the others straight from the caller's
+// rows.  Bound by the gathered rows' bytes; one row per wave and round, its source read from a list in memory, was two
+// dependent round trips per 512 bytes (32 units x 6144 of 32768 rows, 200 MB: 69 us, now 63).
+template <int D, int BITS>
+__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, const uint64_t* keys_all, const int2* base_all) {
+  constexpr int LPR = D / 8, LPT = 2 * LPR;         // lanes per K (V) row, per token
+  constexpr int TPW = 64 / LPT;                     // tokens per wave and round
+  __shared__ uint16_t so[1024], sq[1024];
+  __shared__ uint32_t cnt[16];
+  const int lu = blockIdx.y, gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int T = L.T, j0 = 1024 * blockIdx.x;
+  const uint16_t* K = L.k + (size_t)lu * T * D;
+  const uint16_t* V = L.v + (size_t)lu * T * D;
+  const float2* pre = L.pre + (size_t)lu * T;
+  int no, nq = 0;
+  int2 base = make_int2(j0, 0);
+  if (L.select) {
+    base = base_all[(size_t)lu * gridDim.x + blockIdx.x];
+    const uint64_t thr_o = P.thr[(size_t)gu * 2], thr_b = P.thr[(size_t)gu * 2 + 1];
+    uint64_t key[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) key[r] = keys_all[(size_t)lu * T + min(j0 + 256 * r + tid, T - 1)];
+    bool o[4], q[4];
+    int po[4], pq[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool in = j0 + 256 * r + tid < T;
+      o[r] = in && (key[r] == 0 || key[r] >= thr_o);                 // key 0 = window position
+      q[r] = in && !o[r] && key[r] >= thr_b;
+      const unsigned long long bo = __ballot(o[r]), bq = __ballot(q[r]);
+      po[r] = place(bo, lane); pq[r] = place(bq, lane);
+      if (lane == 0) cnt[4 * r + w] = (uint32_t)__popcll(bo) | ((uint32_t)__popcll(bq) << 16);
+    }
+    __syncthreads();
+    uint32_t run = 0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if (e % 4 == w) {
+        const int r = e / 4;
+        if (o[r]) so[(run & 0xFFFFu) + po[r]] = (uint16_t)(256 * r + tid);
+        if (q[r]) sq[(run >> 16) + pq[r]] = (uint16_t)(256 * r + tid);
+      }
+      run += cnt[e];
+    }
+    no = (int)(run & 0xFFFFu); nq = (int)(run >> 16);
+  } else {
+    no = min(1024, T - j0);
+    for (int i = tid; i < no; i += 256) so[i] = (uint16_t)i;
+    if (blockIdx.x == 0 && tid == 0) P.cnt[gu] = make_int2(T, 0);
+  }
+  __syncthreads();
+  const size_t ob = (size_t)gu * P.capO + base.x, qb = (size_t)gu * P.capQ + base.y;
+  const int t = lane / LPT, sl = lane % LPT;        // token of the wave's round, lane inside it: K row, then V row
+  {
+    constexpr int U = 4;                            // rounds in flight
+    const uint16_t* src = (sl < LPR ? K : V) + (size_t)j0 * D + (sl % LPR) * 8;
+    uint16_t* dst = (sl < LPR ? P.ok : P.ov) + ob * D + (sl % LPR) * 8;
+    for (int i0 = w * TPW + t; i0 < no; i0 += 4 * TPW * U) {
+      uint4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4*>(src + (size_t)so[min(i0 + 4 * TPW * u, no - 1)] * D);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + 4 * TPW * u < no) *reinterpret_cast<uint4*>(dst + (size_t)(i0 + 4 * TPW * u) * D) = v[u];
+    }
+  }
+  for (int i = tid; i < no; i += 256) { const int j = j0 + so[i]; P.opos[ob + i] = j; P.oacc[ob + i] = pre[j]; }
+  // (all lanes of a wave stay together: the quantiser exchanges values between them)
+  for (int i0 = w * TPW; i0 < nq; i0 += 4 * TPW) {
+    const int i = i0 + t, j = j0 + sq[min(i, nq - 1)];
+    quantize_into<D, BITS>(P, gu, base.y + i, K + (size_t)j * D, V + (size_t)j * D, sl, i < nq);
+  }
+  for (int i = tid; i < nq; i += 256) { const int j = j0 + sq[i]; P.qpos[qb + i] = j; P.qacc[qb + i] = pre[j]; }
 }
 
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
+// One workgroup of 1024 threads per unit with a 32-bit word of LDS per row.
+template <typename... Params, typename... Args>
+static hipError_t launch_rows(void (*kernel)(Params...), int n_units, int lds_rows, hipStream_t s, Args... args) {
+  const size_t shm = (size_t)lds_rows * sizeof(uint32_t);
+  if (shm > 32 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(n_units), dim3(1024), shm, s, args...);
+  return hipGetLastError();
+}
+
 static int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
 template <int D, int BITS>
 static void launch_tailor_moves(const Pools& P, const TailorLaunch& a, hipStream_t s) {
+  if (a.few_moves) {
+    hipLaunchKernelGGL((k_tailor_move_few<D, BITS>), dim3(a.n_units), dim3(1024), 0, s, P, a);
+    return;
+  }
   dim3 gq(clampi((P.capQ + 3) / 4, 1, 256), a.n_units), go(clampi((P.capO + 3) / 4, 1, 256), a.n_units);
   hipLaunchKernelGGL((k_tailor_move_q<D, BITS>), gq, dim3(256), 0, s, P, a);
   hipLaunchKernelGGL((k_tailor_move_o<D>), go, dim3(256), 0, s, P, a);
@@ -587,18 +807,16 @@ hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
     hipError_t e = launch_flush_scores(P, a.unit_begin, a.n_units, a.n_pending, a.slot, s);
     if (e != hipSuccess) return e;
   }
-  const int ntot = P.capO + P.capQ;
-  dim3 gk((ntot + 255) / 256, a.n_units);
-  switch (P.G) {
-    case 1: hipLaunchKernelGGL((k_tailor_keys<1>), gk, dim3(256), 0, s, P, a); break;
-    case 2: hipLaunchKernelGGL((k_tailor_keys<2>), gk, dim3(256), 0, s, P, a); break;
-    case 4: hipLaunchKernelGGL((k_tailor_keys<4>), gk, dim3(256), 0, s, P, a); break;
-    case 8: hipLaunchKernelGGL((k_tailor_keys<8>), gk, dim3(256), 0, s, P, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  hipLaunchKernelGGL(k_select, dim3(2, a.n_units), dim3(1024), 0, s,
-                     P.keys + (size_t)a.unit_begin * ntot, (size_t)ntot, ntot, P.n_o, P.nb, a.unit_begin, P.thr);
-  hipLaunchKernelGGL(k_tailor_plan, dim3(a.n_units), dim3(1024), 0, s, P, a);
+  // the scores of a unit stay in LDS between the passes where they fit
+#define ARKV_CH(G_)                                                                                                     \
+  case G_:                                                                                                              \
+    e = a.max_rows <= kLdsRows ? launch_rows(k_tailor_choose<G_, true>, a.n_units, a.max_rows, s, P, a)                 \
+                               : launch_rows(k_tailor_choose<G_, false>, a.n_units, 0, s, P, a);                        \
+    break;
+  hipError_t e = hipErrorInvalidValue;
+  switch (P.G) { ARKV_CH(1) ARKV_CH(2) ARKV_CH(4) ARKV_CH(8) }
+  if (e != hipSuccess) return e;
+#undef ARKV_CH
   if (P.D == 128 && P.bits == 4) launch_tailor_moves<128, 4>(P, a, s);
   else if (P.D == 128 && P.bits == 2) launch_tailor_moves<128, 2>(P, a, s);
   else if (P.D == 64 && P.bits == 4) launch_tailor_moves<64, 4>(P, a, s);
@@ -610,14 +828,12 @@ hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
 }
 
 template <int D, int BITS>
-static void launch_commit_scatter(const Pools& P, const CommitLaunch& a, hipStream_t s) {
-  dim3 g(clampi((P.capO + P.capQ + 3) / 4, 1, 1024), a.n_units);
-  hipLaunchKernelGGL((k_commit_scatter<D, BITS>), g, dim3(256), 0, s, P, a);
+static void launch_commit_scatter(const Pools& P, const CommitLaunch& a, const uint64_t* keys, const int2* base, hipStream_t s) {
+  hipLaunchKernelGGL((k_commit_scatter<D, BITS>), dim3((a.T + 1023) / 1024, a.n_units), dim3(256), 0, s, P, a, keys, base);
 }
 
 // The layer's budgets (per sequence: Original target and survivor count) reach the device as launch
 // arguments, so that the commit stays ordered on the caller's stream without a staging buffer.
-struct BudgetArgs { int n_o[64], nb[64]; };
 __global__ void k_set_budgets(int32_t* n_o, int32_t* nb, int unit_begin, int hkv, int seq0, int n_seq, BudgetArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_seq * hkv) return;
@@ -626,31 +842,45 @@ __global__ void k_set_budgets(int32_t* n_o, int32_t* nb, int unit_begin, int hkv
   nb[u] = a.nb[i / hkv];
 }
 
-hipError_t launch_set_budgets(const Pools& P, int unit_begin, int hkv, int batch, const int32_t* n_o_seq,
-                              const int32_t* nb_seq, hipStream_t s) {
-  for (int s0 = 0; s0 < batch; s0 += 64) {
-    const int n = batch - s0 < 64 ? batch - s0 : 64;
-    BudgetArgs a;
-    for (int i = 0; i < n; ++i) { a.n_o[i] = n_o_seq[s0 + i]; a.nb[i] = nb_seq[s0 + i]; }
-    for (int i = n; i < 64; ++i) { a.n_o[i] = 0; a.nb[i] = 0; }
-    hipLaunchKernelGGL(k_set_budgets, dim3((n * hkv + 255) / 256), dim3(256), 0, s, P.n_o, P.nb, unit_begin, hkv, s0, n, a);
-  }
-  return hipGetLastError();
+static BudgetArgs budget_args(const int32_t* n_o_seq, const int32_t* nb_seq, int n) {
+  BudgetArgs a;
+  for (int i = 0; i < 64; ++i) { a.n_o[i] = i < n ? n_o_seq[i] : 0; a.nb[i] = i < n ? nb_seq[i] : 0; }
+  return a;
 }
 
-hipError_t launch_commit(const Pools& P, const CommitLaunch& a, uint64_t* ckeys, hipStream_t s) {
-  if (a.select) {
-    hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, ckeys, a, P.G);
-    hipLaunchKernelGGL(k_select, dim3(2, a.n_units), dim3(1024), 0, s, (const uint64_t*)ckeys, (size_t)a.T,
-                       a.T, P.n_o, P.nb, a.unit_begin, P.thr);
-    hipLaunchKernelGGL(k_commit_plan, dim3(a.n_units), dim3(1024), 0, s, P, a, (const uint64_t*)ckeys);
+static void launch_set_budgets(const Pools& P, int unit_begin, int hkv, int batch, const int32_t* n_o_seq,
+                               const int32_t* nb_seq, hipStream_t s) {
+  for (int s0 = 0; s0 < batch; s0 += 64) {
+    const int n = batch - s0 < 64 ? batch - s0 : 64;
+    hipLaunchKernelGGL(k_set_budgets, dim3((n * hkv + 255) / 256), dim3(256), 0, s, P.n_o, P.nb, unit_begin, hkv, s0, n,
+                       budget_args(n_o_seq + s0, nb_seq + s0, n));
   }
-  if (P.D == 128 && P.bits == 4) launch_commit_scatter<128, 4>(P, a, s);
-  else if (P.D == 128 && P.bits == 2) launch_commit_scatter<128, 2>(P, a, s);
-  else if (P.D == 64 && P.bits == 4) launch_commit_scatter<64, 4>(P, a, s);
-  else if (P.D == 64 && P.bits == 2) launch_commit_scatter<64, 2>(P, a, s);
-  else if (P.D == 128 && P.bits == 8) launch_commit_scatter<128, 8>(P, a, s);
-  else if (P.D == 64 && P.bits == 8) launch_commit_scatter<64, 8>(P, a, s);
+}
+
+size_t commit_scratch_words(int n_units, int T) { return (size_t)n_units * ((size_t)T + (size_t)((T + 1023) / 1024)); }
+
+hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
+                         uint64_t* ckeys, hipStream_t s) {
+  const int batch = a.n_units / hkv;
+  const bool with_keys = a.select && batch <= 64;           // the budgets ride with the keys' launch
+  if (!with_keys) launch_set_budgets(P, a.unit_begin, hkv, batch, n_o_seq, nb_seq, s);
+  int2* base = nullptr;
+  if (a.select) {
+    base = reinterpret_cast<int2*>(ckeys + (size_t)a.n_units * a.T);
+    hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, ckeys, with_keys ? hkv : 0,
+                       budget_args(n_o_seq, nb_seq, with_keys ? batch : 0));
+    const uint64_t* keys = ckeys;
+    const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, keys, base)
+                                         : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, keys, base);
+    if (e != hipSuccess) return e;
+  }
+  const uint64_t* keys = ckeys;
+  if (P.D == 128 && P.bits == 4) launch_commit_scatter<128, 4>(P, a, keys, base, s);
+  else if (P.D == 128 && P.bits == 2) launch_commit_scatter<128, 2>(P, a, keys, base, s);
+  else if (P.D == 64 && P.bits == 4) launch_commit_scatter<64, 4>(P, a, keys, base, s);
+  else if (P.D == 64 && P.bits == 2) launch_commit_scatter<64, 2>(P, a, keys, base, s);
+  else if (P.D == 128 && P.bits == 8) launch_commit_scatter<128, 8>(P, a, keys, base, s);
+  else if (P.D == 64 && P.bits == 8) launch_commit_scatter<64, 8>(P, a, keys, base, s);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

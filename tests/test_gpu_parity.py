@@ -264,3 +264,28 @@ def test_one_hot_attention_statistics():
         assert np.allclose(s[:, 1], m2, rtol=1e-6) and np.allclose(s[:, 2], m4 / m2 ** 2, rtol=1e-6)
     finally:
         A.arkv_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("T,N,every_step,steps", [
+    (2600, 900, False, 4),      # commit over three rounds of 1024 positions, the last one ragged
+    (2600, 2100, True, 6),      # tailors over three rounds, every step
+    (33200, 33000, True, 2),    # more rows than a unit's scores take in LDS: commit and tailor from memory
+])
+def test_selection_among_equal_scores(T, N, every_step, steps):
+    """Every key of the prompt is the same row, so the scores of all tokens outside the window tie and both ranks are
+    decided by the position alone (R15: the older token first); the new tokens differ.  States are compared exactly."""
+    def same_keys(layer, k, v, qw):
+        k[:] = k[:, :, :1]
+
+    wl = synth.C1.scaled(name="ties", n_q_heads=2, n_kv_heads=1, head_dim=64, prefill=T, budget_frac=(N + 0.5) / T, window=16,
+                         decode_steps=steps)
+    sb = SideBySide(wl, rho_override=0.4, every_step=every_step, mutate_prefill=same_keys)
+    try:
+        sb.prefill()
+        sb.commit()
+        sb.decode(check_every=steps)
+        # (a uniform distribution's variance is 0 up to rounding, so its relative error says nothing here; the statistics
+        # of uniform attention have a test of their own)
+        sb.assert_within_tol(stats=False)
+    finally:
+        sb.close()
