@@ -89,8 +89,9 @@ __host__ __device__ inline AttnPieces attn_pieces(int first_pos, int piece_tiles
   return {piece_tiles > 0 ? (visible + piece_tiles - 1) / piece_tiles : 1, visible};
 }
 // A piece's partial result per wave, in the order in which its lanes hold it: 4 * (D / 32) float4 per lane
-// [channel block][row group][lane] (unnormalised sums), then (reference maximum, sum) per row [32].
-template <int D> constexpr int kPieceFloats = 32 * D + 64;
+// [channel block][row group][lane] (unnormalised sums), then (reference maximum, sum) per row [32], then the sum of the
+// unrounded probabilities per row [32] (EXACT).
+template <int D> constexpr int kPieceFloats = 32 * D + 96;
 
 // Which block of query positions a workgroup takes.  grid (units, blocks, pieces; or units, up to kMaxGridY blocks, rest):
 // the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at the end,
@@ -107,7 +108,11 @@ __device__ __forceinline__ int query_block(int nqb, bool split) {
   return nqb - 1 - rank;                                                              // negative past the last block
 }
 
-template <int D, int G>
+// EXACT (a split launch that also hands the scorer its row constants): the window rows' normalisers are summed from the
+// probabilities before their rounding to fp16 as well.  The rounded sum is the right one for the outputs (numerator and
+// denominator then see the same numbers); as a normaliser it carries the roundings of few large probabilities, which
+// depend on the reference maximum and so on the cut.
+template <int D, int G, bool EXACT>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLaunch L) {
 #ifdef ARKV_PHASE_TRACE
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) { g_attn_clock[0] = clock64(); g_attn_clock[1] = wall_clock64(); }
@@ -228,7 +233,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   for (int cb = 0; cb < CBN; ++cb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[cb][i] = 0.f;
-  float m_run = kNegBigA, l_run = 0.f;
+  float m_run = kNegBigA, l_run = 0.f, le_run = 0.f;
   u32x4a kop[KK], vop[NPV];
   int kA = 1, kB = 2, kW = 0;       // LDS buffers of key tiles t + 1, t + 2 and t + 3 (= the one tile t leaves)
 
@@ -243,11 +248,12 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   };
   // probabilities of logits C against the running reference m_run, as fp16 pairs (ph[e]: elements 2e, 2e + 1),
   // and their sum as rounded (the same numbers the PV MFMA multiplies)
-  auto probs = [&](const f32x16a& C, int i, uint32_t (&ph)[8], float& lt) {
+  auto probs = [&](const f32x16a& C, int i, uint32_t (&ph)[8], float& lt, float& le) {
     const float p0 = aexp2(fmaf(C[i], scale2, -m_run)), p1 = aexp2(fmaf(C[i + 1], scale2, -m_run));
     const __half2 h2 = __floats2half2_rn(p0, p1);
     ph[i / 2] = *reinterpret_cast<const uint32_t*>(&h2);
     lt = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2a, ph[i / 2]), f16x2a{(_Float16)1.0f, (_Float16)1.0f}, lt, false);
+    if constexpr (EXACT) { le += p0; le += p1; }
   };
 
   // One step of the two-stage pipeline over tiles.  Phase A: the logits MFMAs of tile t + 1 (into Cn), each
@@ -263,7 +269,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
     fetch_k(j0 + 96);
     fetch_v(j0 + 32);
     uint32_t ph[8];
-    float lt0 = 0.f, lt1 = 0.f;
+    float lt0 = 0.f, lt1 = 0.f, le0 = 0.f, le1 = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) Cn[i] = 0.f;
 #pragma unroll
@@ -273,13 +279,13 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
       Cn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8a, kop[kk]), __builtin_bit_cast(bf16x8a, qreg[kk]), Cn, 0, 0, 0);
       constexpr int EPK = 16 / KK;                    // softmax elements per MFMA (2 at D = 128, 4 at D = 64)
 #pragma unroll
-      for (int e = 0; e < EPK; e += 2) probs(C, EPK * kk + e, ph, ((kk + e / 2) & 1) ? lt1 : lt0);
+      for (int e = 0; e < EPK; e += 2) probs(C, EPK * kk + e, ph, ((kk + e / 2) & 1) ? lt1 : lt0, ((kk + e / 2) & 1) ? le1 : le0);
     }
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
       __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
       __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSgValu, 6 * 16 / (2 * KK), 0);
+      __builtin_amdgcn_sched_group_barrier(kSgValu, (EXACT ? 8 : 6) * 16 / (2 * KK), 0);
     }
     float lt = lt0 + lt1;
     if (__any(!(lt <= kSumLimit))) {                  // rare after the first tile
@@ -294,16 +300,18 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
       const float f = aexp2(m_run - mn);
       m_run = mn;
       l_run *= f;
+      le_run *= f;
 #pragma unroll
       for (int cb = 0; cb < CBN; ++cb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[cb][i] *= f;
-      lt0 = 0.f; lt1 = 0.f;
+      lt0 = 0.f; lt1 = 0.f; le0 = 0.f; le1 = 0.f;
 #pragma unroll
-      for (int i = 0; i < 16; i += 2) probs(C, i, ph, lt0);
+      for (int i = 0; i < 16; i += 2) probs(C, i, ph, lt0, le0);
       lt = lt0;
     }
     l_run += lt;
+    if constexpr (EXACT) le_run += le0 + le1;
     // PV: probabilities eight per k-step: jj = 0 -> elements 0..7, jj = 1 -> 8..15
 #pragma unroll
     for (int r = 0; r < NPV; ++r) {
@@ -364,6 +372,10 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
         *reinterpret_cast<float4*>(part + ((cb * 4 + i4) * 64 + lane) * 4) =
             make_float4(acc[cb][4 * i4], acc[cb][4 * i4 + 1], acc[cb][4 * i4 + 2], acc[cb][4 * i4 + 3]);
     if (hh == 0) *reinterpret_cast<float2*>(part + 32 * D + 2 * n) = make_float2(m_run, l_tot);
+    if constexpr (EXACT) {
+      const float le = le_run + __shfl_xor(le_run, 32);
+      if (hh == 0) part[32 * D + 64 + n] = le;
+    }
     return;
   }
   const float inv = 1.0f / l_tot;
@@ -377,8 +389,10 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
         store_out4<D>(L, orow, 32 * cb + 8 * i4 + 4 * hh, val);
       }
     // the scorer's row constant c = max + log2(sum) of the window rows (row index: head-major, W per head)
+    float l_row = l_tot;
+    if constexpr (EXACT) l_row = le_run + __shfl_xor(le_run, 32);
     if (L.rowc && hh == 0 && pos >= T - L.W)
-      L.rowc[(size_t)u * L.MP + w * L.W + (pos - (T - L.W))] = m_run + log2f(l_tot);
+      L.rowc[(size_t)u * L.MP + w * L.W + (pos - (T - L.W))] = m_run + log2f(l_row);
   }
 }
 
@@ -398,7 +412,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(Att
   const size_t stride = (size_t)(G * QB) * kPieceFloats<D>;
   float M = kNegBigA;
   for (int p = 0; p < pc.n; ++p) M = fmaxf(M, part[p * stride + 32 * D + 2 * n]);
-  float l = 0.f, acc[16];
+  float l = 0.f, le = 0.f, acc[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
   for (int p = 0; p < pc.n; ++p) {
@@ -406,6 +420,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(Att
     const float2 ml = *reinterpret_cast<const float2*>(pp + 32 * D + 2 * n);
     const float f = aexp2(ml.x - M);
     l = fmaf(ml.y, f, l);
+    if (L.rowc && cb == 0) le = fmaf(pp[32 * D + 64 + n], f, le);
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
       const float4 v = *reinterpret_cast<const float4*>(pp + ((cb * 4 + i4) * 64 + lane) * 4);
@@ -423,7 +438,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(Att
     store_out4<D>(L, orow, 32 * cb + 8 * i4 + 4 * hh, val);
   }
   if (L.rowc && cb == 0 && hh == 0 && q0 + row >= T - L.W)
-    L.rowc[(size_t)u * L.MP + w * L.W + (q0 + row - (T - L.W))] = M + log2f(l);
+    L.rowc[(size_t)u * L.MP + w * L.W + (q0 + row - (T - L.W))] = M + log2f(le);
 }
 
 // Floats of scratch the pieces of such a launch take.
@@ -474,7 +489,8 @@ hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t 
     constexpr int rows = 32 * kQBlocks<G_>, nt = 64 * G_ * kQBlocks<G_>;                                             \
     const int nqb = (a.Tq + rows - 1) / rows;                                                                        \
     const dim3 grid(U, nqb < kMaxGridY ? nqb : kMaxGridY, max_pieces > 1 ? max_pieces : (nqb + kMaxGridY - 1) / kMaxGridY); \
-    hipLaunchKernelGGL((k_prefill_attn<D_, G_>), grid, dim3(nt), 0, s, a);                                           \
+    if (max_pieces > 1 && a.rowc) hipLaunchKernelGGL((k_prefill_attn<D_, G_, true>), grid, dim3(nt), 0, s, a);       \
+    else hipLaunchKernelGGL((k_prefill_attn<D_, G_, false>), grid, dim3(nt), 0, s, a);                               \
     if (max_pieces > 1)                                                                                              \
       hipLaunchKernelGGL((k_prefill_attn_merge<D_, G_>), dim3(nqb, U, D_ / 32), dim3(nt), 0, s, a, max_pieces);      \
     return hipGetLastError();                                                                                        \

@@ -325,8 +325,10 @@ def test_attention_split_over_keys(hq, hkv, d, Tq, T):
         _attention(cache, 0, qd, kd, vd, Tq, T, scale, out, fused)
         pos = np.unique(np.clip(np.concatenate([np.arange(T - Tq, T, 32), np.arange(T - Tq + 31, T, 32), [T - 1]]), 0, T - 1))
         assert _check_rows(out, q, k, v, scale, hq // hkv, pos, T - Tq) <= TOL
+        # a split pass sums the window rows' normalisers from fp32 probabilities, like the stand-alone scorer's first
+        # pass: sums of up to 4101 terms in another order (1e-7 seen; 4101 * 2^-24 = 2.4e-4 is the worst case)
         sa, sf = alone.cpu().numpy(), fused.cpu().numpy()
-        assert np.all(np.abs(sf - sa) <= TOL * np.abs(sa))
+        assert np.all(np.abs(sf - sa) <= 2.4e-4 * np.abs(sa))
         again = torch.zeros_like(out)
         A.arkv_prefill_attention(cache, 0, qd, kd, vd, Tq, T, scale, again)
         assert torch.equal(out, again)             # the cut depends on the shape alone
