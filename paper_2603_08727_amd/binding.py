@@ -112,16 +112,36 @@ def _np_ptr(a):
 
 
 def _dev_ptr(t, dtype=None):
-    import torch
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous GPU tensors"
     if dtype is not None:
         assert t.dtype == dtype, f"expected {dtype}, got {t.dtype}"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# torch is imported at the first call that takes a tensor; what every call needs of it is looked up once then.  A decode
+# step's host cost bounds small caches (their kernels take 6 to 9 us): with the current stream fetched as a
+# torch.cuda.Stream object (3.1 us against 0.2 us for its handle) and every pointer wrapped in a ctypes object, a call
+# took 9.3 us on the host; 4.6 us like this.
+_BF16 = _raw_stream = _device = None
+
+
+def _lookup_torch():
+    """Returns torch.bfloat16."""
+    global _BF16, _raw_stream, _device
+    import torch
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _device = getattr(torch._C, "_cuda_getDevice", None)
+    if _raw_stream is None or _device is None:      # (not part of torch's documented interface)
+        _raw_stream, _device = lambda _: torch.cuda.current_stream().cuda_stream, lambda: 0
+    _BF16 = torch.bfloat16
+    return _BF16
 
 
 def _stream():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on the current device (called behind the checks of GPU tensors)."""
+    if _raw_stream is None:
+        _lookup_torch()
+    return _raw_stream(_device())
 
 
 # ---- entry points, same names as the C ABI ---------------------------------------------------
@@ -203,17 +223,19 @@ def arkv_prefill_commit(cache, layer, k, v, T, rho):
 
 
 def arkv_decode_step(cache, layer, q, k_new, v_new, softmax_scale, out):
-    import torch
-    bf = torch.bfloat16
-    _check(load().arkv_decode_step(cache, layer, _dev_ptr(q, bf), _dev_ptr(k_new, bf), _dev_ptr(v_new, bf),
-                                   softmax_scale, _dev_ptr(out, bf), _stream()), "arkv_decode_step")
+    bf = _BF16 or _lookup_torch()
+    rc = (_lib or load()).arkv_decode_step(cache, layer, _dev_ptr(q, bf), _dev_ptr(k_new, bf), _dev_ptr(v_new, bf),
+                                           softmax_scale, _dev_ptr(out, bf), _stream())
+    if rc != OK:
+        raise ArkvError(rc, "arkv_decode_step")
 
 
 def arkv_decode_step_static(cache, layer, q, k_new, v_new, softmax_scale, out):
-    import torch
-    bf = torch.bfloat16
-    _check(load().arkv_decode_step_static(cache, layer, _dev_ptr(q, bf), _dev_ptr(k_new, bf), _dev_ptr(v_new, bf),
-                                          softmax_scale, _dev_ptr(out, bf), _stream()), "arkv_decode_step_static")
+    bf = _BF16 or _lookup_torch()
+    rc = (_lib or load()).arkv_decode_step_static(cache, layer, _dev_ptr(q, bf), _dev_ptr(k_new, bf), _dev_ptr(v_new, bf),
+                                                  softmax_scale, _dev_ptr(out, bf), _stream())
+    if rc != OK:
+        raise ArkvError(rc, "arkv_decode_step_static")
 
 
 def arkv_decode_step_layers(cache, layer_begin, n, q, k_new, v_new, softmax_scale, out):
