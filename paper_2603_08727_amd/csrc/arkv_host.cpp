@@ -481,8 +481,8 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
 // x 8192, a third packed: 21.7 us at 16 splits, 23.5 at 8; all bf16: 22.2 us at 8, 23.3 at 16).  Whether a cache can hold
 // packed rows follows from its budgets, not from its counts: the factor decides the order of fp32 sums, so it must not
 // depend on when a count arrives.
-// At least 128 rows (two tiles per wave) per split: below that the merge of more partials costs more than the shorter
-// loops save (measured on the 8K-context shape).
+// At least 64 rows (a tile per wave) per split (8 units x 800 bf16 rows: 7.2 us per call, 8.1 at 128 rows; x 390 rows,
+// a fifth packed: 9.0 and 9.9; x 1556 rows: the same).
 static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int n_units, int live) {
   int splits;
   if (c->wg_target > 0) {                          // launch-shape hook
@@ -499,7 +499,7 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
     splits = (n_units < 32 || !packed) && one * n_units >= 232 ? one : two;
     if (n_units < 8) splits = one;                  // (more than 32 splits: the merge outweighs a second workgroup)
   }
-  splits = std::min(splits, std::max(1, live / 128));
+  splits = std::min(splits, std::max(1, live / 64));
   return std::max(1, std::min(splits, c->P.max_splits));
 }
 
