@@ -269,6 +269,26 @@ __device__ __forceinline__ double block_sum_d(double v, double* sm) {
   return t;
 }
 
+// the same for N values at once: one pair of barriers
+template <int N>
+__device__ __forceinline__ void block_sums_d(double (&v)[N], double* sm /*[N][4]*/) {
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    for (int o = 32; o > 0; o >>= 1) v[k] += __shfl_xor(v[k], o);
+  const int w = threadIdx.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int k = 0; k < N; ++k) sm[4 * k + w] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    v[k] = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[k] += sm[4 * k + i];
+  }
+}
+
 // Second pass.  Here the MFMA is turned round (query rows on the M side, keys on the N side) so that a
 // lane owns ONE key and the sums over the M = G*W query rows are in-register additions: C[i] is row
 // rt*32 + 8(i/4) + 4(lane/32) + i%4 against key j0 + lane%32.  The row constants c_r come from LDS.
@@ -374,45 +394,57 @@ __device__ __forceinline__ double ld_dev_d(const double* p) { return __hip_atomi
 // of -p ln p, (p - 1/n)^2, (p - 1/n)^4; the workgroup of a sequence that finishes last (a ticket) adds the
 // chunks up and writes the statistics.
 constexpr int kStatChunk = 512;    // keys per workgroup
+// Bound by its chain of round trips and barriers (keys' loads, normaliser, sums, ticket, sums): the keys' loads go out
+// before the normaliser is reduced and the three sums share their barriers (2000 keys x 8 heads: 13 -> 8 us).
 
 __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const double* zpart, double* mpart) {
   __shared__ double sm[16];
   __shared__ int last;
   const int b = blockIdx.y, ch = blockIdx.x, n = L.T - L.W, nch = gridDim.x;
   const float2* pre = L.pre + (size_t)b * L.Hkv * L.T;
+  // the keys' sums over the heads do not wait for the normaliser: their loads are on the way while it is reduced
+  constexpr int KPT = kStatChunk / 256;
+  double c[KPT];
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) c[i] = 0;
+#pragma unroll 8
+  for (int g = 0; g < L.Hkv; ++g)
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+      c[i] += (double)pre[(size_t)g * L.T + min(ch * kStatChunk + (int)threadIdx.x + 256 * i, n - 1)].x;
   double Z = 0;
   for (int i = threadIdx.x; i < L.Hkv * L.n_chunks; i += 256) Z += zpart[(size_t)b * L.Hkv * L.n_chunks + i];
   Z = block_sum_d(Z, sm);
   const double pbar = 1.0 / (double)n;
-  const int j1 = min(n, (ch + 1) * kStatChunk);
-  double h = 0, m2 = 0, m4 = 0;
-  for (int j = ch * kStatChunk + threadIdx.x; j < j1; j += 256) {
-    double c = 0;
-    for (int g = 0; g < L.Hkv; ++g) c += (double)pre[(size_t)g * L.T + j].x;
-    const double p = c / Z;
-    if (p > 0) h -= p * log(p);
-    const double d = p - pbar, d2 = d * d;
-    m2 += d2; m4 += d2 * d2;
+  double m[3] = {0, 0, 0};            // sums of -p ln p, (p - pbar)^2, (p - pbar)^4
+#pragma unroll
+  for (int i = 0; i < KPT; ++i) {
+    if (ch * kStatChunk + (int)threadIdx.x + 256 * i < n) {
+      const double p = c[i] / Z;
+      if (p > 0) m[0] -= p * log(p);
+      const double d = p - pbar, d2 = d * d;
+      m[1] += d2; m[2] += d2 * d2;
+    }
   }
-  h = block_sum_d(h, sm); m2 = block_sum_d(m2, sm); m4 = block_sum_d(m4, sm);
+  block_sums_d(m, sm);
   if (threadIdx.x == 0) {
     double* o = mpart + ((size_t)b * nch + ch) * 3;
-    st_dev_d(o, h); st_dev_d(o + 1, m2); st_dev_d(o + 2, m4);
+    st_dev_d(o, m[0]); st_dev_d(o + 1, m[1]); st_dev_d(o + 2, m[2]);
     __builtin_amdgcn_s_waitcnt(0);                    // the partials are at the device's coherence point
     last = __hip_atomic_fetch_add(L.stat_ticket + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nch - 1;
   }
   __syncthreads();
   if (!last) return;
-  h = 0; m2 = 0; m4 = 0;
+  m[0] = m[1] = m[2] = 0;
   for (int i = threadIdx.x; i < nch; i += 256) {
     const double* o = mpart + ((size_t)b * nch + i) * 3;
-    h += ld_dev_d(o); m2 += ld_dev_d(o + 1); m4 += ld_dev_d(o + 2);
+    m[0] += ld_dev_d(o); m[1] += ld_dev_d(o + 1); m[2] += ld_dev_d(o + 2);
   }
-  h = block_sum_d(h, sm); m2 = block_sum_d(m2, sm); m4 = block_sum_d(m4, sm);
+  block_sums_d(m, sm);
   if (threadIdx.x != 0) return;
   __hip_atomic_store(L.stat_ticket + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-  m2 /= (double)n; m4 /= (double)n;
-  L.stats[b * 3 + 0] = (float)h;
+  const double m2 = m[1] / (double)n, m4 = m[2] / (double)n;
+  L.stats[b * 3 + 0] = (float)m[0];
   L.stats[b * 3 + 1] = (float)m2;
   L.stats[b * 3 + 2] = m2 > 0 ? (float)(m4 / (m2 * m2)) : 0.f;
 }
