@@ -159,6 +159,7 @@ struct PrefillLaunch {
   int have_rowc;          // 1: the row constants are already in the scratch (attention pass), skip the first pass
   const float* lse;       // not null: the caller's log-sum-exp [U][G][W] (natural log), from which the column pass
                           // takes its row constants itself (have_rowc is 1 then, and the scratch rows are not read)
+  int merge_rows;         // 1: the column pass forms the row constants from rowstat itself
   int chunk;              // keys per workgroup
   int n_chunks;
   float scale2;
