@@ -134,7 +134,7 @@ struct TailorLaunch {
   float gamma;
   int n_pending, slot;  // pending steps to add to (s1,s2) before ranking; slot the NEXT step would write
   int max_rows;         // no unit holds more rows than this
-  int few_moves;        // 1: a tailor at every step, which moves a few rows per unit
+  int few_moves;        // 1: each unit moves a few rows, one workgroup per unit does it
 };
 
 struct CommitLaunch {

@@ -595,7 +595,10 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     t.position = P; t.t_prefill = l0.T; t.window = W; t.gamma = cfg.gamma;
     t.n_pending = n_pending; t.slot = slot;
     t.max_rows = cfg.budget_mode == 1 ? c->P.capO + c->P.capQ : N;      // live <= N in token mode
-    t.few_moves = cfg.tailor_policy == 1 ? 1 : 0;
+    // A tailor at every step settles to a few moved rows per unit: one launch, a workgroup per unit.  The first ones
+    // after a commit move many (32 units x 8192 rows: 41 us in that one workgroup at the first, 17 at the twelfth, 8 in
+    // the long run, against 12 us for the two launches over the whole chip).
+    t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
     const hipError_t te = launch_tailor(c->P, t, st);
     if (te != hipSuccess) {
       // the attention of this step is on the stream, the tailor is not (or only partly): the device-side state of
