@@ -93,19 +93,40 @@ __host__ __device__ inline AttnPieces attn_pieces(int first_pos, int piece_tiles
 // unrounded probabilities per row [32] (EXACT).
 template <int D> constexpr int kPieceFloats = 32 * D + 96;
 
-// Which block of query positions a workgroup takes.  grid (units, blocks, pieces; or units, up to kMaxGridY blocks, rest):
-// the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at the end,
-// and with a multiple of 8 units a unit's workgroups share the L2 of one XCD (workgroups go to the XCDs in turn).
+// Which unit and block of query positions a workgroup takes.  grid (units, blocks, pieces; or units, up to kMaxGridY
+// blocks, rest): the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at
+// the end, and with a multiple of 8 units a unit's workgroups share the L2 of one XCD (workgroups go to the XCDs in turn).
 // With the block fastest, the last unit's long blocks started late: 4096 tokens x 8 units, d = 128, G = 4 205 -> 156 us,
-// x 24 units 551 -> 460 us, 2003 x 32, d = 64, G = 1 51.6 -> 43.5 us, 32768 x 8 9.02 -> 8.74 ms.
+// x 24 units 551 -> 460 us, 2003 x 32, d = 64, G = 1 51.6 -> 43.5 us.
+// Units whose keys and values together exceed the last-level cache go in groups that fit (L.group units, see
+// attn_group), one group after the other: 32 units x 32768 tokens (537 MB) 36.7 ms all at once, 35.0 one unit at a time,
+// 34.3 in groups of eight; 64 x 8192 4.73 -> 4.49 ms against one at a time.
 // A launch of at most two workgroups per CU starts all at once: there the second half runs from the shortest up, so that
 // a CU that got a long one first gets a short one next (4096 x 8 units, G = 1: 65 -> 60 us; 1000 x 8, G = 4: 26.3 -> 25.7).
 constexpr int kMaxGridY = 65535;
-__device__ __forceinline__ int query_block(int nqb, bool split) {
-  const int rank = (int)blockIdx.y + (split ? 0 : (int)blockIdx.z * kMaxGridY);      // 0: the longest
-  const int half = (nqb + 1) / 2;
-  if ((int)gridDim.x * nqb <= 512 && rank >= half) return rank - half;
-  return nqb - 1 - rank;                                                              // negative past the last block
+__device__ __forceinline__ bool query_block(int nqb, int group, bool split, int& u, int& qb) {
+  const unsigned units = gridDim.x;
+  unsigned rank = blockIdx.y + (split ? 0u : blockIdx.z * (unsigned)kMaxGridY);          // 0: the longest
+  if (rank >= (unsigned)nqb) return false;
+  u = (int)blockIdx.x;
+  if ((unsigned)group < units) {
+    const unsigned id = blockIdx.x + units * rank, per = (unsigned)group * (unsigned)nqb;
+    const unsigned g = id / per, rem = id % per, first = g * (unsigned)group;
+    const unsigned n = first + (unsigned)group < units ? (unsigned)group : units - first;  // units of this group
+    u = (int)(first + rem % n);
+    rank = rem / n;
+  } else if (units * (unsigned)nqb <= 512u && (int)rank >= (nqb + 1) / 2) {
+    qb = (int)rank - (nqb + 1) / 2;
+    return true;
+  }
+  qb = nqb - 1 - (int)rank;
+  return true;
+}
+// Units that run side by side: as many as 128 MB of keys and values, in eights (one per XCD), at least eight.
+static int attn_group(int D, int T, int units) {
+  const long long per_unit = 4ll * D * T;
+  const long long n = (128ll << 20) / per_unit / 8 * 8;
+  return (int)(n < 8 ? (units < 8 ? units : 8) : (n < units ? n : units));
 }
 
 // EXACT (a split launch that also hands the scorer its row constants): the window rows' normalisers are summed from the
@@ -130,9 +151,10 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   constexpr int VPT = (VCH + NT - 1) / NT;
   static_assert(NPV >= KH, "operand prefetch pattern");
   __shared__ __align__(16) AttnLds<D> sm;
-  const int nqb = (L.Tq + 32 * QB - 1) / (32 * QB), qb = query_block(nqb, L.piece_tiles > 0);
-  if (qb < 0) return;
-  const int u = blockIdx.x, b = u / L.Hkv, g = u % L.Hkv;
+  const int nqb = (L.Tq + 32 * QB - 1) / (32 * QB);
+  int u, qb;
+  if (!query_block(nqb, L.group, L.piece_tiles > 0, u, qb)) return;
+  const int b = u / L.Hkv, g = u % L.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int w = wave % G, wq = QB * qb + wave / G; // head of the group, block of 32 query positions
@@ -482,8 +504,10 @@ void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* m
   }
 }
 
-hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s) {
+hipError_t launch_prefill_attn(const AttnLaunch& launch, int max_pieces, hipStream_t s) {
+  AttnLaunch a = launch;
   const int U = a.B * a.Hkv, G = a.Hq / a.Hkv;
+  a.group = max_pieces > 1 ? U : attn_group(a.D, a.T, U);
 #define ARKV_AT(D_, G_)                                                                                              \
   if (a.D == D_ && G == G_) {                                                                                        \
     constexpr int rows = 32 * kQBlocks<G_>, nt = 64 * G_ * kQBlocks<G_>;                                             \
