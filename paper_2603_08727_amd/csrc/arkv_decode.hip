@@ -1,7 +1,7 @@
 // Decode step kernels (Alg. 1 "Decoding Phase" + "Reconstruction Before Attention", fused):
 //   k_decode_attend : append + split-K attention of one query per head over the bf16 pool and the
 //                     packed pool (dequantisation inside the QK and PV loops)
-//                     + the merge of the split-K partials by the unit's last workgroup (partials
+//                     + the merge of the split-K partials by the unit's last waves (partials
 //                     move through device-scope atomics, see st_dev2; a device-scope fence per
 //                     workgroup instead was measured 3-6x slower, a second kernel costs a launch gap
 //                     per step)

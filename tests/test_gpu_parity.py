@@ -289,3 +289,17 @@ def test_selection_among_equal_scores(T, N, every_step, steps):
         sb.assert_within_tol(stats=False)
     finally:
         sb.close()
+
+
+@pytest.mark.parametrize("batch,hkv,g,rho", [
+    (3, 3, 1, 0.5),     # 9 units: one workgroup per CU allows 28 splits, the rows allow 6; one merging wave per split
+    (5, 5, 2, 1.0),     # 25 units
+    (5, 8, 4, 1.0),     # 40 units without packed rows: one workgroup per CU
+    (5, 8, 4, 0.4),     # 40 units with packed rows: two
+    (9, 8, 1, 0.4),     # 72 units: more than the launch carries counts for
+])
+def test_split_factors_by_units(batch, hkv, g, rho):
+    """Unit counts at which the split factor rounds differently, over eight steps (one of them updates the scores)."""
+    wl = synth.C1.scaled(name=f"units{batch * hkv}", batch=batch, n_q_heads=hkv * g, n_kv_heads=hkv, head_dim=128, prefill=700,
+                         budget_frac=0.7, window=16, decode_steps=9)
+    _run(wl, rho=rho, check_every=9)
