@@ -469,7 +469,6 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
   return max_pieces < 2 ? 0 : (size_t)units * ((Tq + qb_rows - 1) / qb_rows) * max_pieces * (G < 4 ? 4 : G) *
                               (size_t)(D == 64 ? kPieceFloats<64> : kPieceFloats<128>);
 }
-constexpr size_t kAttnPartFloats = 32u << 20;   // no split that would take more than 128 MB of scratch
 
 // How far to split over the keys: tiles per piece (0: no split) and the largest number of pieces of a workgroup.
 // Measured at d = 128 (d = 64: about 0.65 of it): a tile step takes 0.75 us in a workgroup that has its CU to itself and

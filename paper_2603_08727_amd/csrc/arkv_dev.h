@@ -200,6 +200,7 @@ struct AttnLaunch {
 // split of a launch over the keys: a.piece_tiles and the max_pieces of launch_prefill_attn; floats of scratch it needs
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces);
 size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces);
+constexpr size_t kAttnPartFloats = 32u << 20;   // no split that would take more than 128 MB of scratch
 hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s);
 hipError_t launch_prefill_stats(const PrefillLaunch& a, float* rowc /*[U][MP] scratch*/, hipStream_t s);
 

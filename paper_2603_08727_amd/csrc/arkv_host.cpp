@@ -49,6 +49,11 @@ struct LayerState {
   int cnt_refresh_P = 0;        // position of the step whose tailor the snapshot follows
 };
 
+// Sizes of the blocks a split prefill attention keeps its pieces in: 4 MB << i, up to the largest split's 128 MB.
+constexpr size_t kAttnBlockFloats = 1u << 20;
+constexpr int kAttnBlocks = 6;
+static_assert((kAttnBlockFloats << (kAttnBlocks - 1)) >= kAttnPartFloats, "the largest block must hold the largest split");
+
 struct arkv_cache {
   arkv_config cfg;
   Pools P;
@@ -60,7 +65,7 @@ struct arkv_cache {
   float* rowc = nullptr; size_t rowc_cap = 0;
   int* stat_ticket = nullptr;     // [batch], zero between scorer calls
   uint64_t* ckeys = nullptr; size_t ckeys_cap = 0;
-  float* attn_part = nullptr; size_t attn_part_cap = 0;   // pieces of a prefill attention that is split over the keys
+  float* attn_block[kAttnBlocks] = {};   // pieces of a prefill attention that is split over the keys (attn_scratch)
   int ckeys_layer = -1, ckeys_T = 0;
   hipStream_t last_stream = nullptr;
   // measurement hook: events around the attention kernel
@@ -287,7 +292,8 @@ int arkv_cache_destroy(arkv_cache* c) {
   if (c->rowc) (void)hipFree(c->rowc);
   if (c->stat_ticket) (void)hipFree(c->stat_ticket);
   if (c->ckeys) (void)hipFree(c->ckeys);
-  if (c->attn_part) (void)hipFree(c->attn_part);
+  for (float* p : c->attn_block)
+    if (p) (void)hipFree(p);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   delete c;
   return ARKV_OK;
@@ -374,13 +380,23 @@ int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, cons
                     nullptr, 1, lse);
 }
 
-// Scratch for the pieces of a prefill attention.  The attention needs none when it is not split, so a call that cannot
-// have it (its stream is being captured, when nothing may be allocated; no memory) runs unsplit.
-static bool attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
-  if (floats <= c->attn_part_cap) return true;
+// Scratch for the pieces of a prefill attention: the smallest block that holds them, allocated if there is none.  A call
+// that is captured leaves its block's address in the graph, so no block is freed before the cache is; the sizes double, so
+// the blocks of a cache are 252 MB at most.
+// nullptr where there can be none (this call's own stream is being captured; no memory): such a call runs unsplit.
+static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
+  int i = 0;
+  while (i < kAttnBlocks && (kAttnBlockFloats << i) < floats) ++i;
+  for (int j = i; j < kAttnBlocks; ++j)
+    if (c->attn_block[j]) return c->attn_block[j];
+  if (i == kAttnBlocks) return nullptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) { (void)hipGetLastError(); return false; }
-  return grow(&c->attn_part, &c->attn_part_cap, floats) == ARKV_OK;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  void* p = nullptr;
+  const hipError_t e = hipMalloc(&p, (kAttnBlockFloats << i) * sizeof(float));
+  if (e != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
+  return c->attn_block[i] = static_cast<float*>(p);
 }
 
 int arkv_prefill_attention(arkv_cache* c, int32_t layer, const void* q, const void* k, const void* v, int32_t T_q,
@@ -406,8 +422,10 @@ int arkv_prefill_attention(arkv_cache* c, int32_t layer, const void* q, const vo
   }
   int pieces = 1;
   attn_split(a.D, c->P.G, c->U, T, T_q, &a.piece_tiles, &pieces);
-  if (pieces > 1 && !attn_scratch(c, attn_part_floats(a.D, c->P.G, c->U, T_q, pieces), s)) { pieces = 1; a.piece_tiles = 0; }
-  a.part = c->attn_part;
+  if (pieces > 1) {
+    a.part = attn_scratch(c, attn_part_floats(a.D, c->P.G, c->U, T_q, pieces), s);
+    if (!a.part) { pieces = 1; a.piece_tiles = 0; }
+  }
   if (!with_stats) {
     HIP_TRY(launch_prefill_attn(a, pieces, s));
     c->last_stream = s;

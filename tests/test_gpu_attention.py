@@ -369,3 +369,42 @@ def test_attention_split_under_graph_capture():
                 assert (ref - outs[2].float().cpu()).abs().max() <= 8e-3 * ref.abs().max()   # two bf16 roundings
     finally:
         A.arkv_cache_destroy(cache)
+
+
+def _chunk(wl, Tq):
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)[:, :, wl.prefill - Tq:].contiguous()
+    return q.cuda(), k.cuda(), v.cuda()
+
+
+def test_captured_split_attention_outlives_larger_calls():
+    """A graph of a split call holds the address of its scratch: larger calls afterwards take other memory, and what they
+    leave for the allocator is not what the replay writes to.  Every replay equals the eager result."""
+    T, d = 3000, 128
+    wl = synth.C1.scaled(name="outlive", n_q_heads=4, n_kv_heads=1, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        (q, k, v), (qb, _, _), (qc, _, _) = _chunk(wl, 96), _chunk(wl, 512), _chunk(wl, 1200)
+        eager, out = torch.zeros_like(q), torch.zeros_like(q)
+        A.arkv_prefill_attention(cache, 0, q, k, v, 96, T, scale, eager)          # the scratch of this size
+        s = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            A.arkv_prefill_attention(cache, 0, q, k, v, 96, T, scale, out)
+        for big in (qb, qc):
+            ref = torch.zeros_like(big)
+            A.arkv_prefill_attention(cache, 0, big, k, v, big.shape[2], T, scale, ref)
+            torch.cuda.synchronize()
+            # the rows both calls have differ by their cut only
+            assert (ref[:, :, -96:].float() - eager.float()).abs().max() <= 8e-3 * eager.float().abs().max()
+            spare = torch.full((8 << 20,), 7.0, device="cuda")                     # would reuse a freed block
+            out.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager)
+            assert bool((spare == 7.0).all())
+            del spare
+    finally:
+        A.arkv_cache_destroy(cache)
