@@ -382,7 +382,8 @@ int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, cons
 
 // Scratch for the pieces of a prefill attention: the smallest block that holds them, allocated if there is none.  A call
 // that is captured leaves its block's address in the graph, so no block is freed before the cache is; the sizes double, so
-// the blocks of a cache are 252 MB at most.
+// the blocks of a cache are 252 MB at most.  The allocation must not break a capture on another stream (in the default
+// mode every thread's allocations do), so it is made in the relaxed mode.
 // nullptr where there can be none (this call's own stream is being captured; no memory): such a call runs unsplit.
 static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
   int i = 0;
@@ -393,9 +394,12 @@ static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   if (cap != hipStreamCaptureStatusNone) return nullptr;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   void* p = nullptr;
   const hipError_t e = hipMalloc(&p, (kAttnBlockFloats << i) * sizeof(float));
   if (e != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
+  (void)hipThreadExchangeStreamCaptureMode(&mode);       // the caller's mode again
   return c->attn_block[i] = static_cast<float*>(p);
 }
 

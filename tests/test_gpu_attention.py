@@ -408,3 +408,33 @@ def test_captured_split_attention_outlives_larger_calls():
             del spare
     finally:
         A.arkv_cache_destroy(cache)
+
+
+def test_split_attention_beside_a_capture_on_another_stream():
+    """The first split call of a cache allocates its scratch.  It may do so while another stream is being captured (in
+    torch's default mode, which forbids the allocations of every thread): the capture stays whole, the call is split."""
+    T, Tq, d = 3000, 96, 128
+    wl = synth.C1.scaled(name="beside", n_q_heads=4, n_kv_heads=1, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        q, k, v = _chunk(wl, Tq)
+        first, later = torch.zeros_like(q), torch.zeros_like(q)
+        x = torch.zeros(1000, device="cuda")
+        captured, other = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=captured):
+            x += 1
+            with torch.cuda.stream(other):
+                A.arkv_prefill_attention(cache, 0, q, k, v, Tq, T, scale, first)
+            x += 1
+        torch.cuda.synchronize()
+        A.arkv_prefill_attention(cache, 0, q, k, v, Tq, T, scale, later)
+        for i in range(3):
+            g.replay()
+            torch.cuda.synchronize()
+            assert bool((x == 2 * (i + 1)).all())
+        assert torch.equal(first, later)
+    finally:
+        A.arkv_cache_destroy(cache)
