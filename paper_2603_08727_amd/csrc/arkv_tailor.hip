@@ -28,8 +28,10 @@ __device__ __forceinline__ float hh_score(float s1, float s2, int n, float gamma
   return mu + gamma * var;
 }
 
+// A score's first digit in the radix select (11 bits) is never all ones: those are the first digit of kNoScore, which must
+// not match a ranked row's.  Scores are >= 0 or NaN; negative NaNs with that digit count as the largest one below it.
 __device__ __forceinline__ uint64_t make_key(float S, int pos) {
-  return ((uint64_t)__float_as_uint(S) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos);
+  return ((uint64_t)min(__float_as_uint(S), 0xFFDFFFFFu) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -42,7 +44,7 @@ __device__ __forceinline__ uint64_t make_key(float S, int pos) {
 // digits, which leave a handful of candidates after two passes.  Once the chosen bin holds a single candidate the
 // remaining passes are skipped.
 // ------------------------------------------------------------------------------------------
-constexpr uint32_t kNoScore = 0xFFFFFFFFu;   // not ranked (scores are >= 0)
+constexpr uint32_t kNoScore = 0xFFFFFFFFu;   // not ranked (above every score, see make_key)
 constexpr int kLdsRows = 32768;              // units of up to this many rows keep their scores in LDS (128 KB)
 constexpr int kRounds = 32;                  // rounds of 1024 rows per list chunk
 constexpr int kBins = 2048;
@@ -115,8 +117,7 @@ __device__ __forceinline__ void select_two(Each&& each, Key&& key, int k0, int k
     } else if (!tie) {
       const int up = shift + width;
       each([&](uint32_t sb, int row) {
-        // (kNoScore never matches: a prefix comes from scores below 2^31)
-        const uint32_t hi = sb >> up;
+        const uint32_t hi = sb >> up;        // (kNoScore never matches: no score shares its first digit)
         if ((use0 && hi == prefix[0]) || (use1 && hi == prefix[1])) {
           const int h = use0 && hi == prefix[0] ? 0 : 1, bin = (int)__builtin_amdgcn_ubfe(sb, shift, width);
           atomicAdd(&sm.hist[h][bin], 1);

@@ -3,9 +3,11 @@ the same seeded inputs.  Integer results (positions, states, codes, fp16 scale/z
 bf16 rows) must be identical; floating-point results within 2e-3 (helpers.TOL)."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2603_08727_amd import binding as A
 from paper_2603_08727_amd import synth
-from helpers import SideBySide
+from helpers import SideBySide, make_cfg
 
 pytestmark = pytest.mark.gpu
 
@@ -303,3 +305,47 @@ def test_split_factors_by_units(batch, hkv, g, rho):
     wl = synth.C1.scaled(name=f"units{batch * hkv}", batch=batch, n_q_heads=hkv * g, n_kv_heads=hkv, head_dim=128, prefill=700,
                          budget_frac=0.7, window=16, decode_steps=9)
     _run(wl, rho=rho, check_every=9)
+
+
+@pytest.mark.parametrize("bits", [0x7FC00000, 0xFFC00000, 0x7FFFFFFF, 0xFFFFFFFF])
+def test_selection_among_nan_scores(bits):
+    """A window row without a finite normaliser (here a caller's NaN log-sum-exp) makes every score of its kv-head a NaN.
+    The scores are then ranked by their bits, the older token first, whatever sign and payload they carry: a NaN must not
+    be mistaken for a row that is not ranked.  Counts and states follow from the scores that were ranked on."""
+    T, N, W, rho, steps = 2300, 1100, 16, 0.5, 20
+    wl = synth.C1.scaled(name="nan", n_q_heads=4, n_kv_heads=2, head_dim=64, prefill=T, budget_frac=(N + 0.5) / T, window=W,
+                         decode_steps=steps)
+    cfg = make_cfg(wl, every_step=True)
+    n_o, n_q, b = A.arkv_budget_counts(cfg, rho)
+    k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+    q, kn, vn = (t.cuda() for t in synth.decode_inputs(wl, 0, steps))
+    scale = synth.softmax_scale(wl, 0)
+    lse = torch.full((1, 4, W), 8.0, device="cuda")
+    lse.view(torch.int32)[0, 1, 3] = bits - (1 << 32) if bits >> 31 else bits           # a head of kv-head 0
+    stats = torch.zeros((1, 3), device="cuda")
+    cache = A.arkv_cache_create(cfg)
+    try:
+        A.arkv_prefill_stats_lse(cache, 0, qw, k, T, scale, lse, stats)
+        A.arkv_prefill_commit(cache, 0, k, v, T, [rho])
+        cnt, pos, score = A.arkv_debug_last_tailor_scores(cache, 0, 2, T)
+        ex = A.arkv_cache_export(cache, 0, cfg, rows=False, codes=False)
+        for u in range(2):
+            assert cnt[u] == T - W and bool(np.isnan(score[u, :cnt[u]]).all()) == (u == 0)
+            order = np.lexsort((pos[u, :cnt[u]], -score[u, :cnt[u]].view(np.uint32).astype(np.int64)))
+            want = {int(p): 0 for p in range(T - W, T)}
+            want.update({int(pos[u, i]): 0 for i in order[:n_o]})
+            want.update({int(pos[u, i]): 1 for i in order[n_o:b]})
+            assert ex["n_live"][u] == b + W
+            assert dict(zip(ex["pos"][u, : b + W].tolist(), ex["state"][u, : b + W].tolist())) == want
+        out = torch.zeros((1, 4, 64), dtype=torch.bfloat16, device="cuda")
+        for t in range(steps):
+            A.arkv_decode_step(cache, 0, q[t], kn[t], vn[t], scale, out)
+        orig, quant, evicted, _ = A.arkv_cache_counters(cache, 0, 2)
+        assert (orig + quant == b + W).all() and (orig >= W).all() and (evicted == T + steps - b - W).all()
+        ex = A.arkv_cache_export(cache, 0, cfg, rows=False, codes=False)
+        for u in range(2):
+            p, st = ex["pos"][u, : b + W], ex["state"][u, : b + W]
+            assert len(set(p.tolist())) == b + W and (p[-W:] == np.arange(T + steps - W, T + steps)).all()
+            assert (st[-W:] == 0).all() and (st == 0).sum() == orig[u]
+    finally:
+        A.arkv_cache_destroy(cache)
