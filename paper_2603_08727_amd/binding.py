@@ -126,13 +126,15 @@ _BF16 = _raw_stream = _device = None
 
 
 def _lookup_torch():
-    """Returns torch.bfloat16."""
+    """Returns torch.bfloat16.  (Several threads may be here at once: what _stream looks at is set last.)"""
     global _BF16, _raw_stream, _device
     import torch
-    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    _device = getattr(torch._C, "_cuda_getDevice", None)
-    if _raw_stream is None or _device is None:      # (not part of torch's documented interface)
-        _raw_stream, _device = lambda _: torch.cuda.current_stream().cuda_stream, lambda: 0
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:               # (not part of torch's documented interface)
+        raw, device = lambda _: torch.cuda.current_stream().cuda_stream, lambda: 0
+    _device = device
+    _raw_stream = raw
     _BF16 = torch.bfloat16
     return _BF16
 

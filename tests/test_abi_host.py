@@ -163,3 +163,35 @@ def test_product_path_does_not_import_the_oracle():
                 text = open(os.path.join(dirpath, f), encoding="utf-8").read()
                 assert not re.search(r"^\s*(from|import)\s+oracle\b", text, re.M), f
                 assert "arkv_oracle" not in text, f
+
+
+@pytest.mark.parametrize("documented_only", [False, True])
+def test_stream_lookup_is_whole_for_every_thread(monkeypatch, documented_only):
+    """The binding looks torch's stream functions up at the first call that needs them.  A thread that comes while another
+    is in the middle of that must find either nothing yet or all of it: seen here from inside the lookup itself."""
+    import sys
+    import types
+    seen = []
+
+    def look():
+        seen.append((A._raw_stream, A._device))
+
+    class Half:
+        def __getattr__(self, name):
+            look()
+            if documented_only and name == "_cuda_getDevice":
+                raise AttributeError(name)
+            return lambda *a: 7
+
+    class Stream:
+        cuda_stream = 9
+
+    fake = types.ModuleType("torch")
+    fake._C, fake.bfloat16 = Half(), "bf16"
+    fake.cuda = types.SimpleNamespace(current_stream=lambda: Stream)
+    monkeypatch.setitem(sys.modules, "torch", fake)
+    for name in ("_BF16", "_raw_stream", "_device"):
+        monkeypatch.setattr(A, name, None)
+    assert A._stream() == (9 if documented_only else 7)
+    assert seen and all((raw is None) or (callable(raw) and callable(device)) for raw, device in seen)
+    assert callable(A._raw_stream) and callable(A._device) and A._BF16 == "bf16"
