@@ -50,11 +50,12 @@ constexpr int kRounds = 32;                  // rounds of 1024 rows per list chu
 constexpr int kBins = 2048;
 template <typename Row>                      // Row: integer that holds a row index
 struct SelectLds {
-  int hist[2][kBins];
-  Row who[2][kBins];                         // a row that fell into the bin (the row, where only one did)
+  int hist[2 * kBins];                       // one histogram per rank
+  Row who[2 * kBins];                        // a row that fell into the bin (the row, where only one did)
   uint32_t wsum[2][16];
   uint64_t thr[2];
   int sel[2], k[2], cnt[2];
+  int crowded[6];                            // per pass
 };
 
 // inclusive sum over the wave's lanes up to this one (DPP: row shifts by 1, 2, 4, 8, then the rows' last lanes)
@@ -80,18 +81,26 @@ __device__ __forceinline__ bool key_ge(uint32_t sb, int row, uint64_t thr, Low&&
   return ge;
 }
 
-// each(f) must call f(score bits, row) for every row this thread owns (kNoScore: not a candidate); key(row) = a candidate's
-// key, for any thread.  sm.thr[x] = key of rank k_x, or ~0 when k_x = 0 or there
+// The lanes of a wave that share the first adding lane's bin (all lanes of the wave must be here).
+struct Shared { int first, bin, lanes; };
+__device__ __forceinline__ Shared shared_bin(int bin, bool add, unsigned long long adding) {
+  const int first = __ffsll(adding) - 1, b = __builtin_amdgcn_readlane(bin, first);
+  return {first, b, (int)__popcll(__ballot(add && bin == b))};
+}
+
+// each(j0, j1, f) must call f(score bits, row) for this thread's row of every round j0 .. j1 - 1 (kNoScore: not a candidate);
+// key(row) = a candidate's key, for any thread.  sm.thr[x] = key of rank k_x, or ~0 when k_x = 0 or there
 // is no candidate (nothing qualifies); k_x is clamped to the number of candidates, so "fewer candidates than b" keeps
 // everything.  Ends with a barrier.
 template <typename Row, typename Each, typename Key>
-__device__ __forceinline__ void select_two(Each&& each, Key&& key, int k0, int k1, SelectLds<Row>& sm) {
+__device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, int k0, int k1, SelectLds<Row>& sm) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   uint32_t prefix[2] = {0, 0};               // digits found so far: of the score, then (tie) of the low word
   uint32_t score[2] = {0, 0};                // passes 3..5: the rank's whole score
   int k[2] = {k0, k1};
   bool done[2] = {k0 <= 0, k1 <= 0};
   if (tid < 2) sm.thr[tid] = ~0ull;
+  if (tid < 6) sm.crowded[tid] = 0;
   int shift = 32;
   for (int pass = 0; pass < 6; ++pass) {
     if (done[0] && done[1]) break;
@@ -105,40 +114,76 @@ __device__ __forceinline__ void select_two(Each&& each, Key&& key, int k0, int k
     const bool shared = prefix[0] == prefix[1] && score[0] == score[1];    // both ranks still look at the same candidates
     const bool use0 = !done[0] || shared, use1 = !done[1] && !shared;
     const int top = kBins - 1 - 2 * tid;     // this thread's bins: top and top - 1
-    *reinterpret_cast<int2*>(&sm.hist[0][top - 1]) = make_int2(0, 0);
-    *reinterpret_cast<int2*>(&sm.hist[1][top - 1]) = make_int2(0, 0);
-    __syncthreads();
+    *reinterpret_cast<int2*>(&sm.hist[top - 1]) = make_int2(0, 0);
+    *reinterpret_cast<int2*>(&sm.hist[kBins + top - 1]) = make_int2(0, 0);
+    // bin_of(score, row, bin): whether the row is counted in this pass, and in which bin, which remembers a row.
+    // Accesses to one LDS word are served lane by lane, and equal scores (or the leading digits of neighbouring positions)
+    // put whole waves on one bin.  So every wave looks at one of its rounds, spread over the unit; if any finds more than 24
+    // lanes on one bin, the pass counts the lanes that share the first one's at once.  Otherwise it does not: that costs ten
+    // instructions per round (32 units x 32768 positions: 3 us a pass).  All scores equal: a tailor step of 32 units x 8192
+    // rows 91 -> 77 us; 0.3 us more where nothing is equal.
+    auto count = [&](auto&& bin_of) {
+      const int js = (w * rounds) >> 4;
+      each(js, js + 1, [&](uint32_t sb, int row) {
+        int bin = 0;
+        const bool add = bin_of(sb, row, bin);
+        const unsigned long long adding = __ballot(add);
+        if (adding != 0 && shared_bin(bin, add, adding).lanes > 24 && lane == 0) sm.crowded[pass] = 1;
+      });
+      __syncthreads();
+      if (sm.crowded[pass]) {
+        each(0, rounds, [&](uint32_t sb, int row) {
+          int bin = 0;
+          const bool add = bin_of(sb, row, bin);
+          const unsigned long long adding = __ballot(add);
+          if (adding == 0) return;
+          const Shared s = shared_bin(bin, add, adding);
+          if (lane == s.first || (add && bin != s.bin)) {
+            atomicAdd(&sm.hist[bin], lane == s.first ? s.lanes : 1);
+            sm.who[bin] = (Row)row;
+          }
+        });
+      } else {
+        each(0, rounds, [&](uint32_t sb, int row) {
+          int bin = 0;
+          if (bin_of(sb, row, bin)) {
+            atomicAdd(&sm.hist[bin], 1);
+            sm.who[bin] = (Row)row;
+          }
+        });
+      }
+    };
     if (pass == 0) {
       // leading digits are often shared (scores of one unit have few exponents): the second histogram is free in this
       // pass, so odd lanes count there and half as many lanes meet on a bin
-      each([&](uint32_t sb, int) {
-        if (sb != kNoScore) atomicAdd(&sm.hist[lane & 1][sb >> 21], 1);
+      __syncthreads();
+      each(0, rounds, [&](uint32_t sb, int) {
+        if (sb != kNoScore) atomicAdd(&sm.hist[(lane & 1) * kBins + (int)(sb >> 21)], 1);
       });
     } else if (!tie) {
       const int up = shift + width;
-      each([&](uint32_t sb, int row) {
+      count([&](uint32_t sb, int, int& bin) {
         const uint32_t hi = sb >> up;        // (kNoScore never matches: no score shares its first digit)
-        if ((use0 && hi == prefix[0]) || (use1 && hi == prefix[1])) {
-          const int h = use0 && hi == prefix[0] ? 0 : 1, bin = (int)__builtin_amdgcn_ubfe(sb, shift, width);
-          atomicAdd(&sm.hist[h][bin], 1);
-          sm.who[h][bin] = (Row)row;
-        }
+        const bool c0 = use0 && hi == prefix[0], c1 = use1 && hi == prefix[1];
+        bin = (int)__builtin_amdgcn_ubfe(sb, shift, width) + (c0 ? 0 : kBins);
+        return c0 || c1;
       });
     } else {
-      each([&](uint32_t sb, int row) {
-        const bool c0 = use0 && sb == score[0], c1 = use1 && sb == score[1];
+      count([&](uint32_t sb, int row, int& bin) {
+        bool c0 = use0 && sb == score[0], c1 = use1 && sb == score[1];
         if (c0 || c1) {
           const uint32_t lw = (uint32_t)key(row), hi = pass == 3 ? 0u : lw >> (shift + width);
-          const int bin = (int)__builtin_amdgcn_ubfe(lw, shift, width);
-          if (c0 && hi == prefix[0]) { atomicAdd(&sm.hist[0][bin], 1); sm.who[0][bin] = (Row)row; }
-          if (c1 && hi == prefix[1]) { atomicAdd(&sm.hist[1][bin], 1); sm.who[1][bin] = (Row)row; }
+          c0 = c0 && hi == prefix[0];
+          c1 = c1 && hi == prefix[1];        // (not both: two ranks with the same digits share the first histogram)
+          bin = (int)__builtin_amdgcn_ubfe(lw, shift, width) + (c0 ? 0 : kBins);
         }
+        return c0 || c1;
       });
     }
     __syncthreads();
     // ge = candidates in bins top - 1 and above
-    int2 a = *reinterpret_cast<const int2*>(&sm.hist[0][top - 1]);
-    const int2 b = *reinterpret_cast<const int2*>(&sm.hist[1][top - 1]);
+    int2 a = *reinterpret_cast<const int2*>(&sm.hist[top - 1]);
+    const int2 b = *reinterpret_cast<const int2*>(&sm.hist[kBins + top - 1]);
     if (pass == 0) { a.x += b.x; a.y += b.y; }
     uint32_t ge0 = wave_prefix_sum((uint32_t)(a.x + a.y)), ge1 = wave_prefix_sum((uint32_t)(b.x + b.y));
     if (lane == 63) { sm.wsum[0][w] = ge0; sm.wsum[1][w] = ge1; }
@@ -174,7 +219,7 @@ __device__ __forceinline__ void select_two(Each&& each, Key&& key, int k0, int k
       prefix[x] = (prefix[x] << width) | (uint32_t)sm.sel[x];
       k[x] = sm.k[x];
       if (sm.cnt[x] == 1 && pass > 0) {                  // one candidate left
-        if (tid == 0) sm.thr[x] = key((int)sm.who[x == 0 || shared ? 0 : 1][sm.sel[x]]);
+        if (tid == 0) sm.thr[x] = key((int)sm.who[(x == 0 || shared ? 0 : kBins) + sm.sel[x]]);
         done[x] = true;
       }
     }
@@ -277,14 +322,14 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     return k ? (uint32_t)(k >> 32) : kNoScore;
   };
   auto low = [&](int i) { return (uint32_t)key_of(i); };
-  auto each = [&](auto&& f) {
-    for (int j = 0; j < rounds; ++j) {
+  auto each = [&](int j0, int j1, auto&& f) {
+    for (int j = j0; j < j1; ++j) {
       const int i = 1024 * j + tid;
       f(i < n ? score_of(i) : kNoScore, i);
     }
   };
   if (tid < 3) tot[tid] = 0;
-  select_two(each, key_of, P.n_o[gu], P.nb[gu], sel);
+  select_two(rounds, each, key_of, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
 
   // what becomes of a row: 1 stays in its pool, 2 is demoted, 0 is evicted (window rows stay)
@@ -655,14 +700,14 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
     if constexpr (IN_LDS) return row_word[i];
     else return (uint32_t)(keys[i] >> 32);
   };
-  auto each = [&](auto&& f) {
-    for (int j = 0; j < rounds; ++j) {
+  auto each = [&](int j0, int j1, auto&& f) {
+    for (int j = j0; j < j1; ++j) {
       const int i = 1024 * j + tid;
       f(i < n_cand ? score_of(i) : kNoScore, i);
     }
   };
   auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
-  select_two(each, key_of, P.n_o[gu], P.nb[gu], sel);
+  select_two(rounds, each, key_of, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
   int2* base = base_all + (size_t)lu * rounds;
   int bo = 0, bq = 0;

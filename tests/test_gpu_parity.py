@@ -349,3 +349,29 @@ def test_selection_among_nan_scores(bits):
             assert (st[-W:] == 0).all() and (st == 0).sum() == orig[u]
     finally:
         A.arkv_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("kind,every_step", [("two", False), ("mostly", False), ("mostly", True), ("late", True)])
+def test_selection_among_few_distinct_scores(kind, every_step):
+    """Few distinct keys: whole waves meet on one or two bins of the selection, in all of its rounds or in some, with the
+    two ranks in the same bin and in different ones.  States are compared exactly."""
+    T, N, steps = 3100, 1300, 4
+
+    def few_keys(layer, k, v, qw):
+        i = torch.arange(T)
+        if kind == "two":
+            k[:] = k[:, :, :2].repeat(1, 1, T // 2 + 1, 1)[:, :, :T]
+        else:
+            same = i % 10 != 3 if kind == "mostly" else i >= 1100
+            k[:, :, same] = k[:, :, :1]
+
+    wl = synth.C1.scaled(name="few", n_q_heads=4, n_kv_heads=2, head_dim=64, prefill=T, budget_frac=(N + 0.5) / T, window=16,
+                         decode_steps=steps)
+    sb = SideBySide(wl, rho_override=0.3, every_step=every_step, mutate_prefill=few_keys)
+    try:
+        sb.prefill()
+        sb.commit()
+        sb.decode(check_every=steps)
+        sb.assert_within_tol(stats=False)
+    finally:
+        sb.close()
