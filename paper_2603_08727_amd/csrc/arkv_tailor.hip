@@ -11,11 +11,14 @@
 // order (this file must be compiled with -ffp-contract=off).
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "arkv_dev.h"
 
 namespace arkv {
+
+typedef uint32_t u32x4t __attribute__((ext_vector_type(4)));   // 16 bytes; arrays of it stay in registers (arrays of uint4 do not)
 
 // ------------------------------------------------------------------------------------------
 // score -> key
@@ -673,11 +676,18 @@ __global__ __launch_bounds__(256) void k_commit_keys(Pools P, CommitLaunch L, ui
   keys[(size_t)lu * L.T + j] = key;
 }
 
+// Parts into which a block with that many survivors is cut.
+__device__ __forceinline__ uint32_t commit_parts(uint32_t survivors, int share_rows) {
+  return (survivors + (uint32_t)share_rows - 1) / (uint32_t)share_rows;
+}
+
 // One workgroup per unit: 36 us for 32 units x 32768 positions, where a select per rank and a pass that wrote the lists of
-// survivors took 39 + 19 us.  The two thresholds of a unit, and how many rows in front of every block of 1024 positions become Original and
-// Quantized (base [units][rounds]), from which k_commit_scatter places its rows.
+// survivors took 39 + 19 us.  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
+// last one the totals) the rows in front of it that become Original and Quantized and the parts in front of it into which
+// k_commit_scatter cuts blocks: as many as hold share_rows survivors each, wherever in the prompt the survivors sit.
 template <bool IN_LDS>
-__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, const uint64_t* keys_all, int2* base_all) {
+__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, const uint64_t* keys_all, int4* blocks_all,
+                                                         int share_rows) {
   extern __shared__ uint32_t row_word[];     // IN_LDS: the positions' scores
   __shared__ SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
   __shared__ uint32_t cnt[kRounds][16];      // per (round, wave): Original | Quantized << 16
@@ -709,8 +719,8 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
   auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
   select_two(rounds, each, key_of, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
-  int2* base = base_all + (size_t)lu * rounds;
-  int bo = 0, bq = 0;
+  int4* blocks = blocks_all + (size_t)lu * (rounds + 1);
+  int bo = 0, bq = 0, bp = 0;
   for (int j0 = 0; j0 < rounds; j0 += kRounds) {
     const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds;
     for (int j = 0; j < nj; ++j) {
@@ -731,38 +741,81 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
       if (lane < nj)
 #pragma unroll
         for (int i = 0; i < 16; ++i) { o += cnt[lane][i] & 0xFFFFu; q += cnt[lane][i] >> 16; }
-      const uint32_t io = wave_prefix_sum(o), iq = wave_prefix_sum(q);
-      if (lane < nj) base[j0 + lane] = make_int2(bo + (int)(io - o), bq + (int)(iq - q));
+      const uint32_t p = commit_parts(o + q, share_rows);
+      const uint32_t io = wave_prefix_sum(o), iq = wave_prefix_sum(q), ip = wave_prefix_sum(p);
+      if (lane < nj) blocks[j0 + lane] = make_int4(bo + (int)(io - o), bq + (int)(iq - q), bp + (int)(ip - p), 0);
       bo += __builtin_amdgcn_readlane((int)io, 63);
       bq += __builtin_amdgcn_readlane((int)iq, 63);
+      bp += __builtin_amdgcn_readlane((int)ip, 63);
     }
     __syncthreads();
   }
   if (tid == 0) {
     P.thr[(size_t)gu * 2] = thr_o; P.thr[(size_t)gu * 2 + 1] = thr_b;
     P.cnt[gu] = make_int2(bo, bq);
+    blocks[rounds] = make_int4(bo, bq, bp, 0);
   }
 }
 
-// The survivors of 1024 prompt positions into the pools: a workgroup lists them in LDS (positions stay in ascending
-// order), then copies the Original rows, several in flight per wave, and quantises the others straight from the caller's
-// rows.  Bound by the gathered rows' bytes; one row per wave and round, its source read from a list in memory, was two
-// dependent round trips per 512 bytes (32 units x 6144 of 32768 rows, 200 MB: 69 us, now 63).
+// A prompt that fits its cache: every row becomes Original.  The workgroups of a unit go through its rows side by side, a
+// wave two (d = 64: four) tokens at a time.  Bound by the bytes (32 units x 16384 rows, 537 MB in and out, with the budgets'
+// launch: 104 us; 8 units x 1000 rows 10.0).  Several rows in flight per lane, 512 to 8192 workgroups: slower or the same.
+template <int D>
+__global__ __launch_bounds__(256) void k_commit_copy(Pools P, CommitLaunch L) {
+  constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;      // as in k_commit_scatter
+  const int lu = blockIdx.y, gu = L.unit_begin + lu, lane = threadIdx.x & 63, w = threadIdx.x >> 6, T = L.T;
+  const int t = lane / LPT, sl = lane % LPT;
+  const uint16_t* src = (sl < LPR ? L.k : L.v) + (size_t)lu * T * D + (sl % LPR) * 8;
+  uint16_t* dst = (sl < LPR ? P.ok : P.ov) + (size_t)gu * P.capO * D + (sl % LPR) * 8;
+  for (int i = (4 * blockIdx.x + w) * TPW + t; i < T; i += 4 * TPW * gridDim.x) {
+    *reinterpret_cast<uint4*>(dst + (size_t)i * D) = *reinterpret_cast<const uint4*>(src + (size_t)i * D);
+    if (sl == 0) {
+      P.opos[(size_t)gu * P.capO + i] = i;
+      P.oacc[(size_t)gu * P.capO + i] = L.pre[(size_t)lu * T + i];
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(T, 0);
+}
+
+// The survivors of a selection into the pools: a workgroup takes one part of a block of 1024 positions (see k_commit_select).
+// It lists the block's survivors in LDS (positions stay in ascending order), copies its share of the Original rows, several
+// in flight per wave, and quantises its share of the others straight from the caller's rows.  Bound by the gathered rows'
+// bytes where the grid fills the chip (32 units x 6152 of 32768 rows, 200 MB: 43 us), by a workgroup's chain of rounds where it
+// does not, hence the parts: with one workgroup per block a whole commit of 16 units x 2200 positions (1100 kept, all packed)
+// takes 62 us instead of 26, and one of 32 x 32768 whose survivors sit in few blocks (equal scores) 335 instead of 132.
 template <int D, int BITS>
-__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, const uint64_t* keys_all, const int2* base_all) {
+__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, const uint64_t* keys_all, const int4* blocks_all,
+                                                        int share_rows) {
   constexpr int LPR = D / 8, LPT = 2 * LPR;         // lanes per K (V) row, per token
   constexpr int TPW = 64 / LPT;                     // tokens per wave and round
   __shared__ uint16_t so[1024], sq[1024];
   __shared__ uint32_t cnt[16];
-  const int lu = blockIdx.y, gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int T = L.T, j0 = 1024 * blockIdx.x;
+  // the units run fastest: workgroups behind a unit's last part end at once, and with the slots fastest they left the CUs
+  // with unequal shares of the others (32 units x 32768 positions, total of the commit: 105 to 128 us by their number)
+  const int lu = (int)(blockIdx.x % (unsigned)L.n_units), slot = (int)(blockIdx.x / (unsigned)L.n_units);
+  const int gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, T = L.T;
+  // the block whose parts this workgroup falls among: the last one with no more parts in front of it (lane = block)
+  const int n_blocks = (T + 1023) / 1024;
+  const int4* blocks = blocks_all + (size_t)lu * (n_blocks + 1);
+  int block = 0, part = 0;
+  int2 base = make_int2(0, 0);
+  for (int b0 = 0; b0 <= n_blocks; b0 += 64) {
+    const int4 e = blocks[min(b0 + lane, n_blocks)];
+    const int in_front = __popcll(__ballot(b0 + lane <= n_blocks && e.z <= slot));
+    if (in_front > 0) {
+      block = b0 + in_front - 1;
+      base = make_int2(__builtin_amdgcn_readlane(e.x, in_front - 1), __builtin_amdgcn_readlane(e.y, in_front - 1));
+      part = slot - __builtin_amdgcn_readlane(e.z, in_front - 1);
+    }
+    if (in_front < 64) break;
+  }
+  if (block == n_blocks) return;                    // behind the last part
+  const int j0 = 1024 * block;
   const uint16_t* K = L.k + (size_t)lu * T * D;
   const uint16_t* V = L.v + (size_t)lu * T * D;
   const float2* pre = L.pre + (size_t)lu * T;
-  int no, nq = 0;
-  int2 base = make_int2(j0, 0);
-  if (L.select) {
-    base = base_all[(size_t)lu * gridDim.x + blockIdx.x];
+  int no, nq, parts;
+  {
     const uint64_t thr_o = P.thr[(size_t)gu * 2], thr_b = P.thr[(size_t)gu * 2 + 1];
     uint64_t key[4];
 #pragma unroll
@@ -790,34 +843,34 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
       run += cnt[e];
     }
     no = (int)(run & 0xFFFFu); nq = (int)(run >> 16);
-  } else {
-    no = min(1024, T - j0);
-    for (int i = tid; i < no; i += 256) so[i] = (uint16_t)i;
-    if (blockIdx.x == 0 && tid == 0) P.cnt[gu] = make_int2(T, 0);
+    parts = (int)commit_parts((uint32_t)(no + nq), share_rows);
   }
   __syncthreads();
+  const int o0 = no * part / parts, o1 = no * (part + 1) / parts, q0 = nq * part / parts, q1 = nq * (part + 1) / parts;
   const size_t ob = (size_t)gu * P.capO + base.x, qb = (size_t)gu * P.capQ + base.y;
   const int t = lane / LPT, sl = lane % LPT;        // token of the wave's round, lane inside it: K row, then V row
+  constexpr int ROUND = 4 * TPW;                    // tokens of the workgroup's round
   {
-    constexpr int U = 4;                            // rounds in flight
     const uint16_t* src = (sl < LPR ? K : V) + (size_t)j0 * D + (sl % LPR) * 8;
     uint16_t* dst = (sl < LPR ? P.ok : P.ov) + ob * D + (sl % LPR) * 8;
-    for (int i0 = w * TPW + t; i0 < no; i0 += 4 * TPW * U) {
-      uint4 v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const uint4*>(src + (size_t)so[min(i0 + 4 * TPW * u, no - 1)] * D);
+    constexpr int U = 4;                            // rounds in flight
+    for (int i0 = o0 + w * TPW + t; i0 < o1; i0 += ROUND * U) {
+      u32x4t v[U];
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (i0 + 4 * TPW * u < no) *reinterpret_cast<uint4*>(dst + (size_t)(i0 + 4 * TPW * u) * D) = v[u];
+        if (i0 + ROUND * u < o1) v[u] = *reinterpret_cast<const u32x4t*>(src + (size_t)so[i0 + ROUND * u] * D);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + ROUND * u < o1) *reinterpret_cast<u32x4t*>(dst + (size_t)(i0 + ROUND * u) * D) = v[u];
     }
   }
-  for (int i = tid; i < no; i += 256) { const int j = j0 + so[i]; P.opos[ob + i] = j; P.oacc[ob + i] = pre[j]; }
+  for (int i = o0 + tid; i < o1; i += 256) { const int j = j0 + so[i]; P.opos[ob + i] = j; P.oacc[ob + i] = pre[j]; }
   // (all lanes of a wave stay together: the quantiser exchanges values between them)
-  for (int i0 = w * TPW; i0 < nq; i0 += 4 * TPW) {
-    const int i = i0 + t, j = j0 + sq[min(i, nq - 1)];
-    quantize_into<D, BITS>(P, gu, base.y + i, K + (size_t)j * D, V + (size_t)j * D, sl, i < nq);
+  for (int i0 = q0 + w * TPW; i0 < q1; i0 += ROUND) {
+    const int i = i0 + t, j = j0 + sq[min(i, q1 - 1)];
+    quantize_into<D, BITS>(P, gu, base.y + i, K + (size_t)j * D, V + (size_t)j * D, sl, i < q1);
   }
-  for (int i = tid; i < nq; i += 256) { const int j = j0 + sq[i]; P.qpos[qb + i] = j; P.qacc[qb + i] = pre[j]; }
+  for (int i = q0 + tid; i < q1; i += 256) { const int j = j0 + sq[i]; P.qpos[qb + i] = j; P.qacc[qb + i] = pre[j]; }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -873,11 +926,6 @@ hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, int BITS>
-static void launch_commit_scatter(const Pools& P, const CommitLaunch& a, const uint64_t* keys, const int2* base, hipStream_t s) {
-  hipLaunchKernelGGL((k_commit_scatter<D, BITS>), dim3((a.T + 1023) / 1024, a.n_units), dim3(256), 0, s, P, a, keys, base);
-}
-
 // The layer's budgets (per sequence: Original target and survivor count) reach the device as launch
 // arguments, so that the commit stays ordered on the caller's stream without a staging buffer.
 __global__ void k_set_budgets(int32_t* n_o, int32_t* nb, int unit_begin, int hkv, int seq0, int n_seq, BudgetArgs a) {
@@ -903,32 +951,45 @@ static void launch_set_budgets(const Pools& P, int unit_begin, int hkv, int batc
   }
 }
 
-size_t commit_scratch_words(int n_units, int T) { return (size_t)n_units * ((size_t)T + (size_t)((T + 1023) / 1024)); }
+static int commit_blocks(int T) { return (T + 1023) / 1024; }
+size_t commit_scratch_words(int n_units, int T) { return (size_t)n_units * ((size_t)T + 2 * ((size_t)commit_blocks(T) + 1)) + 1; }
 
 hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
-                         uint64_t* ckeys, hipStream_t s) {
+                         uint64_t* keys, hipStream_t s) {
   const int batch = a.n_units / hkv;
   const bool with_keys = a.select && batch <= 64;           // the budgets ride with the keys' launch
   if (!with_keys) launch_set_budgets(P, a.unit_begin, hkv, batch, n_o_seq, nb_seq, s);
-  int2* base = nullptr;
-  if (a.select) {
-    base = reinterpret_cast<int2*>(ckeys + (size_t)a.n_units * a.T);
-    hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, ckeys, with_keys ? hkv : 0,
-                       budget_args(n_o_seq, nb_seq, with_keys ? batch : 0));
-    const uint64_t* keys = ckeys;
-    const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, keys, base)
-                                         : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, keys, base);
-    if (e != hipSuccess) return e;
+  if (!a.select) {
+    const int rounds = (a.T + 4 * (256 / P.D) - 1) / (4 * (256 / P.D));     // of the four waves' rows
+    const dim3 grid(clampi(rounds, 1, std::max(1, 16384 / a.n_units)), a.n_units);
+    if (P.D == 128) hipLaunchKernelGGL(k_commit_copy<128>, grid, dim3(256), 0, s, P, a);
+    else hipLaunchKernelGGL(k_commit_copy<64>, grid, dim3(256), 0, s, P, a);
+    return hipGetLastError();
   }
-  const uint64_t* keys = ckeys;
-  if (P.D == 128 && P.bits == 4) launch_commit_scatter<128, 4>(P, a, keys, base, s);
-  else if (P.D == 128 && P.bits == 2) launch_commit_scatter<128, 2>(P, a, keys, base, s);
-  else if (P.D == 64 && P.bits == 4) launch_commit_scatter<64, 4>(P, a, keys, base, s);
-  else if (P.D == 64 && P.bits == 2) launch_commit_scatter<64, 2>(P, a, keys, base, s);
-  else if (P.D == 128 && P.bits == 8) launch_commit_scatter<128, 8>(P, a, keys, base, s);
-  else if (P.D == 64 && P.bits == 8) launch_commit_scatter<64, 8>(P, a, keys, base, s);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  // (16-byte entries behind the keys)
+  int4* blocks = reinterpret_cast<int4*>(keys + ((size_t)a.n_units * a.T + 1) / 2 * 2);
+  hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, keys, with_keys ? hkv : 0,
+                     budget_args(n_o_seq, nb_seq, with_keys ? batch : 0));
+  int kept = 0;                                             // the most rows that a unit keeps
+  for (int i = 0; i < batch; ++i) kept = std::max(kept, std::min(nb_seq[i], a.T - a.window) + a.window);
+  // about four workgroups per CU; below 8 rows a workgroup's lists cost more than its rows (8 units x 1000 positions, 500
+  // kept: 21 us for the whole commit, 52 in one part per block), above 96 nothing is gained (32 units x 32768 positions,
+  // 6152 kept: 89 to 95 us at 64 to 1024 rows)
+  const int share_rows = clampi((int)((long long)a.n_units * kept / 1024 + 7) / 8 * 8, 8, 96);
+  const uint64_t* ckeys = keys;
+  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, ckeys, blocks, share_rows)
+                                       : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, ckeys, blocks, share_rows);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)a.n_units * (unsigned)(kept / share_rows + commit_blocks(a.T)));   // (a block's last part may be short)
+  const int4* cblocks = blocks;
+#define ARKV_SC(D_, B_)                                                                                                      \
+  if (P.D == D_ && P.bits == B_) {                                                                                           \
+    hipLaunchKernelGGL((k_commit_scatter<D_, B_>), grid, dim3(256), 0, s, P, a, ckeys, cblocks, share_rows);                 \
+    return hipGetLastError();                                                                                                \
+  }
+  ARKV_SC(128, 4) ARKV_SC(128, 2) ARKV_SC(128, 8) ARKV_SC(64, 4) ARKV_SC(64, 2) ARKV_SC(64, 8)
+#undef ARKV_SC
+  return hipErrorInvalidValue;
 }
 
 }  // namespace arkv

@@ -375,3 +375,25 @@ def test_selection_among_few_distinct_scores(kind, every_step):
         sb.assert_within_tol(stats=False)
     finally:
         sb.close()
+
+
+@pytest.mark.parametrize("T,N,g,d,bits,batch,rho", [
+    (1024, 700, 4, 128, 4, 1, 0.0),      # one whole block, in parts of eight rows, all packed
+    (1025, 900, 2, 64, 8, 3, 1.0),       # the last block holds one position (window)
+    (2049, 2049, 1, 128, 2, 1, 0.5),     # T = N: nothing but the slack is evicted, parts larger than their block's last
+    (65536, 2000, 1, 64, 4, 1, 0.4),     # 64 blocks and the totals: one entry more than a wave looks at together
+    (66100, 9000, 2, 64, 4, 2, 0.7),     # 65 blocks
+])
+def test_commit_in_parts(T, N, g, d, bits, batch, rho):
+    """Survivors by parts of blocks of 1024 positions: positions, states, rows and codes are compared exactly."""
+    wl = synth.C1.scaled(name="parts", batch=batch, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, bits=bits, prefill=T,
+                         budget_frac=(N + 0.5) / T, window=16, decode_steps=2)
+    _run(wl, rho=rho, check_every=2, stats=False)
+
+
+@pytest.mark.parametrize("T,g,d,batch", [(17, 1, 64, 1), (1000, 4, 128, 1), (1025, 2, 64, 3), (4099, 8, 128, 2)])
+def test_commit_of_a_prompt_that_fits(T, g, d, batch):
+    """Every row is copied as it lies, the last round of a workgroup's rows ragged: compared exactly."""
+    wl = synth.C1.scaled(name="fits", batch=batch, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, prefill=T, budget_frac=(T + 60.5) / T,
+                         window=16, decode_steps=2)
+    _run(wl, check_every=2)
