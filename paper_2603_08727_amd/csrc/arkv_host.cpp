@@ -519,7 +519,10 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
     }
     const int one = 256 / n_units, two = 512 / n_units;
     splits = (n_units < 32 || !packed) && one * n_units >= 232 ? one : two;
-    if (n_units < 8) splits = one;                  // (more than 32 splits: the merge outweighs a second workgroup)
+    // Few units: one workgroup per CU is more than 32 splits, where every wave that merges reads that many partials.  More
+    // than 48 only pay with long ranges (2 units, G = 8, bf16: 7500 rows 12.9 us per call at 48 splits, 13.7 at 64, 16.1 at
+    // 117; 32000 rows 18.3, 17.7 and 20.2 at 128; 1 unit x 120000 rows, G = 4: 25.6 at 48, 21.6 at 64, 18.0 at 128).
+    if (n_units < 8) splits = std::min(one, std::max(live < 20000 ? 48 : 64, live / 640));
   }
   splits = std::min(splits, std::max(1, live / 64));
   return std::max(1, std::min(splits, c->P.max_splits));

@@ -397,3 +397,11 @@ def test_commit_of_a_prompt_that_fits(T, g, d, batch):
     wl = synth.C1.scaled(name="fits", batch=batch, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, prefill=T, budget_frac=(T + 60.5) / T,
                          window=16, decode_steps=2)
     _run(wl, check_every=2)
+
+
+@pytest.mark.parametrize("hkv,g,d,T", [(2, 8, 128, 5000), (1, 1, 64, 20100), (1, 4, 64, 45000)])
+def test_split_factors_of_few_units(hkv, g, d, T):
+    """Launches of one and two units, whose splits are limited by their number (48, 64) or by the rows per split."""
+    wl = synth.C1.scaled(name=f"few{hkv}", n_q_heads=hkv * g, n_kv_heads=hkv, head_dim=d, prefill=T, budget_frac=1.01, window=16,
+                         decode_steps=9)
+    _run(wl, check_every=9)
