@@ -254,6 +254,18 @@ int arkv_debug_set_launch_shape(arkv_cache* cache, int32_t wg_target, int32_t pa
 int arkv_debug_split_range(int32_t n_original, int32_t n_quantized, int32_t packed_weight, int32_t n_splits,
                            int32_t split, int32_t* range);
 
+/* Parity hook, HOST, pure: how arkv_prefill_attention cuts a call of T_q queries against T keys for units = B H_kv and
+ * group = H_q / H_kv.  out[0] = key tiles (of 32 keys) per piece, 0: the call is not split; out[1] = the most pieces of a
+ * workgroup; out[2], out[3] = pieces of the first and of the last block of query positions.  ARKV_EINVAL: null pointer,
+ * head_dim or group not built, units < 1, T_q outside [1, T]. */
+int arkv_debug_attention_split(int32_t head_dim, int32_t group, int32_t units, int32_t T, int32_t T_q, int32_t* out);
+
+/* Parity hook, HOST, pure: out[0] = unit and out[1] = block of query positions that the index-th of a prefill-attention
+ * launch's units * n_blocks workgroups takes (index runs over the units first; split != 0: one piece of a split launch).
+ * ARKV_EINVAL: null pointer, head_dim not built, sizes < 1, index outside [0, units * n_blocks). */
+int arkv_debug_attention_block(int32_t head_dim, int32_t units, int32_t T, int32_t n_blocks, int32_t split, int32_t index,
+                               int32_t* out);
+
 /* Measurement hook of profiling builds (the library compiled with -DARKV_PHASE_TRACE, see the package's build
  * script; the product build returns ARKV_EUNSUPPORTED and its kernels carry none of this).  In such a build
  * thread 0 of every workgroup of the decode kernel stores the 100 MHz wall clock at its phase boundaries, and a

@@ -16,6 +16,7 @@
 // beyond fp16's range are not supported), accumulation fp32.
 #include <hip/hip_fp16.h>
 
+#include "arkv.h"
 #include "arkv_dev.h"
 
 namespace arkv {
@@ -104,13 +105,12 @@ template <int D> constexpr int kPieceFloats = 32 * D + 96;
 // A launch of at most two workgroups per CU starts all at once: there the second half runs from the shortest up, so that
 // a CU that got a long one first gets a short one next (4096 x 8 units, G = 1: 65 -> 60 us; 1000 x 8, G = 4: 26.3 -> 25.7).
 constexpr int kMaxGridY = 65535;
-__device__ __forceinline__ bool query_block(int nqb, int group, bool split, int& u, int& qb) {
-  const unsigned units = gridDim.x;
-  unsigned rank = blockIdx.y + (split ? 0u : blockIdx.z * (unsigned)kMaxGridY);          // 0: the longest
+// x of units workgroups side by side, rank of the blocks (0: the longest)
+__host__ __device__ __forceinline__ bool query_block(unsigned units, unsigned x, unsigned rank, int nqb, int group, int& u, int& qb) {
   if (rank >= (unsigned)nqb) return false;
-  u = (int)blockIdx.x;
+  u = (int)x;
   if ((unsigned)group < units) {
-    const unsigned id = blockIdx.x + units * rank, per = (unsigned)group * (unsigned)nqb;
+    const unsigned id = x + units * rank, per = (unsigned)group * (unsigned)nqb;
     const unsigned g = id / per, rem = id % per, first = g * (unsigned)group;
     const unsigned n = first + (unsigned)group < units ? (unsigned)group : units - first;  // units of this group
     u = (int)(first + rem % n);
@@ -153,7 +153,8 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   __shared__ __align__(16) AttnLds<D> sm;
   const int nqb = (L.Tq + 32 * QB - 1) / (32 * QB);
   int u, qb;
-  if (!query_block(nqb, L.group, L.piece_tiles > 0, u, qb)) return;
+  const bool split = L.piece_tiles > 0;
+  if (!query_block(gridDim.x, blockIdx.x, blockIdx.y + (split ? 0u : blockIdx.z * (unsigned)kMaxGridY), nqb, L.group, u, qb)) return;
   const int b = u / L.Hkv, g = u % L.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -166,7 +167,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   const int jmax = min(T, q0 + 32 * QB * (qb + 1));  // keys any row of this workgroup can see
   const int ntiles = (jmax + 31) / 32;
   const AttnPieces pc = attn_pieces(q0 + 32 * QB * qb, L.piece_tiles);
-  const int piece = L.piece_tiles > 0 ? (int)blockIdx.z : 0;
+  const int piece = split ? (int)blockIdx.z : 0;
   if (piece >= pc.n) return;
   const int t0 = pc.visible * piece / pc.n, t1 = piece + 1 < pc.n ? pc.visible * (piece + 1) / pc.n : ntiles;
   const int jfull = q0 + 32 * wq - 31;             // tiles starting at or before this need no mask
@@ -525,6 +526,32 @@ hipError_t launch_prefill_attn(const AttnLaunch& launch, int max_pieces, hipStre
 }
 
 }  // namespace arkv
+
+extern "C" int arkv_debug_attention_split(int32_t head_dim, int32_t group, int32_t units, int32_t T, int32_t T_q, int32_t* out) {
+  if (!out || (head_dim != 64 && head_dim != 128) || (group != 1 && group != 2 && group != 4 && group != 8) || units < 1 ||
+      T_q < 1 || T_q > T)
+    return ARKV_EINVAL;
+  int tiles, pieces;
+  arkv::attn_split(head_dim, group, units, T, T_q, &tiles, &pieces);
+  const int rows = 32 * (group < 4 ? 4 / group : 1), last = (T_q - 1) / rows;
+  out[0] = tiles; out[1] = pieces;
+  out[2] = arkv::attn_pieces(T - T_q, tiles).n;
+  out[3] = arkv::attn_pieces(T - T_q + rows * last, tiles).n;
+  return ARKV_OK;
+}
+
+extern "C" int arkv_debug_attention_block(int32_t head_dim, int32_t units, int32_t T, int32_t n_blocks, int32_t split, int32_t index,
+                                          int32_t* out) {
+  if (!out || (head_dim != 64 && head_dim != 128) || units < 1 || T < 1 || n_blocks < 1 || index < 0 ||
+      (long long)index >= (long long)units * n_blocks)
+    return ARKV_EINVAL;
+  const unsigned x = (unsigned)index % (unsigned)units, rank = (unsigned)index / (unsigned)units;
+  int u = -1, qb = -1;
+  if (!arkv::query_block((unsigned)units, x, rank, n_blocks, split ? units : arkv::attn_group(head_dim, T, units), u, qb))
+    return ARKV_EINVAL;
+  out[0] = u; out[1] = qb;
+  return ARKV_OK;
+}
 
 namespace arkv {
 // the prefill attention's four clock words (shader clock and 100 MHz counter at the start and the end of workgroup 0)

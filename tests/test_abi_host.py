@@ -195,3 +195,38 @@ def test_stream_lookup_is_whole_for_every_thread(monkeypatch, documented_only):
     assert A._stream() == (9 if documented_only else 7)
     assert seen and all((raw is None) or (callable(raw) and callable(device)) for raw, device in seen)
     assert callable(A._raw_stream) and callable(A._device) and A._BF16 == "bf16"
+
+
+@pytest.mark.parametrize("units,T,n_blocks,split", [
+    (1, 100, 1, 0), (3, 500, 7, 0), (8, 4096, 64, 0), (8, 4096, 65, 0),      # at most 512 workgroups (second half reversed) and more
+    (12, 16500, 129, 0), (24, 16384, 33, 0), (24, 8200, 5, 0), (17, 40000, 9, 0), (7, 40000, 3, 0),   # groups, the last one ragged
+    (12, 16500, 129, 1),                                                      # a split launch has no groups
+])
+def test_attention_workgroups_cover_every_block_once(units, T, n_blocks, split):
+    """Host logic of the prefill attention's launch order: every (unit, block of positions) is taken by exactly one
+    workgroup, and a group's longest blocks come first."""
+    order = [A.arkv_debug_attention_block(128, units, T, n_blocks, split, i) for i in range(units * n_blocks)]
+    assert sorted(order) == [(u, b) for u in range(units) for b in range(n_blocks)]
+    assert order[0][1] == n_blocks - 1
+    fits = units * T * 512 <= 128 << 20
+    if not split and not fits and units > 8:
+        group = max(8, (128 << 20) // (512 * T) // 8 * 8)
+        assert {u for u, _ in order[: group * n_blocks]} == set(range(group))
+    with pytest.raises(A.ArkvError):
+        A.arkv_debug_attention_block(128, units, T, n_blocks, split, units * n_blocks)
+
+
+def test_attention_split_pieces():
+    """Host logic of the split over the keys: never more pieces than the scratch is sized for, none for short prompts or
+    launches that fill the chip."""
+    for d in (64, 128):
+        for g in (1, 2, 4, 8):
+            for units in (1, 2, 8, 32):
+                for T, T_q in [(1, 1), (992, 992), (1025, 65), (3000, 32), (16411, 512), (16411, 16411), (50000, 300)]:
+                    tiles, most, first, last = A.arkv_debug_attention_split(d, g, units, T, T_q)
+                    assert 1 <= first <= last <= most <= 16 and (tiles == 0) == (most == 1)
+                    if T <= 900:
+                        assert most == 1
+    for bad in [(96, 4, 1, 10, 1), (64, 3, 1, 10, 1), (64, 4, 0, 10, 1), (64, 4, 1, 10, 11), (64, 4, 1, 10, 0)]:
+        with pytest.raises(A.ArkvError):
+            A.arkv_debug_attention_split(*bad)

@@ -301,17 +301,21 @@ def test_scorer_with_the_callers_log_sum_exp(hq, hkv, d, T):
         sb.close()
 
 
-@pytest.mark.parametrize("hq,hkv,d,Tq,T", [
-    (4, 1, 128, 512, 4101),    # few workgroups: every workgroup in several pieces
-    (8, 1, 64, 33, 2048),      # group size 8, the second workgroup holds one row
-    (2, 2, 64, 129, 3001),     # 128-position workgroups, the second holds one row
-    (4, 2, 128, 65, 1025),     # 64-position workgroups at the smallest split
-    (4, 1, 64, 1100, 1100),    # a whole prompt: only the late workgroups are split
+@pytest.mark.parametrize("hq,hkv,d,Tq,T,pieces", [
+    (4, 1, 128, 512, 4101, (15, 16)),  # few workgroups: every workgroup in several pieces (first and last block's number)
+    (8, 1, 64, 33, 2048, (8, 8)),      # group size 8, the second workgroup holds one row
+    (2, 2, 64, 129, 3001, (12, 12)),   # 128-position workgroups, the second holds one row
+    (4, 2, 128, 65, 1025, (4, 4)),     # 64-position workgroups at the smallest split
+    (4, 1, 64, 1100, 1100, (1, 1)),    # a whole prompt too short to be split
+    (4, 1, 128, 1100, 1100, (1, 4)),   # whole prompts: only the late workgroups are split
+    (4, 1, 64, 2000, 2000, (1, 7)),
+    (2, 1, 128, 1500, 1500, (1, 6)),   # the same with 64-position workgroups
 ])
-def test_attention_split_over_keys(hq, hkv, d, Tq, T):
+def test_attention_split_over_keys(hq, hkv, d, Tq, T, pieces):
     """Launches too small for the chip cut a workgroup's keys into pieces and merge them: outputs against the oracle,
     first and last rows of every block of positions among them, and the window rows' constants through the scorer
     (same tolerances as the unsplit pass: the sums stay in fp32)."""
+    assert A.arkv_debug_attention_split(d, hq // hkv, hkv, T, Tq)[2:] == pieces
     wl = synth.C1.scaled(name="split", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
     k, v, qw = synth.prefill_inputs(wl, 0)
     q = _full_queries(wl, 0, qw)[:, :, T - Tq:].contiguous()
@@ -386,6 +390,7 @@ def test_captured_split_attention_outlives_larger_calls():
     cache = A.arkv_cache_create(make_cfg(wl))
     try:
         (q, k, v), (qb, _, _), (qc, _, _) = _chunk(wl, 96), _chunk(wl, 512), _chunk(wl, 1200)
+        assert all(A.arkv_debug_attention_split(d, 4, 1, T, n)[1] > 1 for n in (96, 512, 1200))
         eager, out = torch.zeros_like(q), torch.zeros_like(q)
         A.arkv_prefill_attention(cache, 0, q, k, v, 96, T, scale, eager)          # the scratch of this size
         s = torch.cuda.Stream()
@@ -436,5 +441,27 @@ def test_split_attention_beside_a_capture_on_another_stream():
             torch.cuda.synchronize()
             assert bool((x == 2 * (i + 1)).all())
         assert torch.equal(first, later)
+    finally:
+        A.arkv_cache_destroy(cache)
+
+
+def test_attention_units_in_groups():
+    """Units whose keys and values together exceed the last-level cache go in groups, here of eight and of four of the
+    twelve: every row is written, sampled rows of every unit (first and last of a block of positions) against the oracle."""
+    T, d, batch, hkv = 16500, 128, 3, 4
+    units, rows = batch * hkv, 128                       # group size 1: workgroups of 128 positions
+    n_blocks = (T + rows - 1) // rows
+    assert A.arkv_debug_attention_split(d, 1, units, T, T)[0] == 0
+    assert A.arkv_debug_attention_block(d, units, T, n_blocks, 0, 8)[0] == 0       # the ninth workgroup: the first unit again
+    wl = synth.C1.scaled(name="groups", n_q_heads=hkv, n_kv_heads=hkv, head_dim=d, prefill=T, batch=batch, budget_frac=0.1)
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        out = torch.full_like(q, float("nan"), device="cuda")
+        _attention(cache, 0, q.cuda(), k.cuda(), v.cuda(), T, T, scale, out)
+        assert bool(torch.isfinite(out).all())
+        assert _check_rows(out, q, k, v, scale, 1, np.array([0, 127, 128, 4095, 8000, 16383, 16384, T - 1]), 0) <= TOL
     finally:
         A.arkv_cache_destroy(cache)
