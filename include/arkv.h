@@ -116,8 +116,8 @@ int arkv_prefill_stats_lse(arkv_cache* cache, int32_t layer, const void* q_win, 
  * sums of those rows come out of the attention pass, so the scorer reads the keys once instead of twice.
  * Calls with few query rows against many keys split a row's keys over workgroups and merge the parts in fp32 (from
  * about 1000 keys; by shape alone): such a row differs from the same row of an unsplit call by the order of its fp32
- * sums.  The parts' scratch belongs to the cache: blocks of 4 to 128 MB (252 MB at most), allocated on first use and
- * when a larger call comes (an allocation may synchronise the device) and freed by arkv_cache_destroy only.  While the
+ * sums.  The parts' scratch belongs to the cache: blocks of up to 128 MB (less than 256 MB together), allocated on first use
+ * and when a larger call comes (an allocation may synchronise the device) and freed by arkv_cache_destroy only.  While the
  * call's stream is being captured nothing is allocated, and a call whose scratch is not there yet runs unsplit; a captured
  * call without stats can be replayed as long as the cache lives, whatever is called in between.
  * Arithmetic: bf16 logits MFMA, probabilities and values as fp16 in the PV MFMA, fp32 accumulation; values

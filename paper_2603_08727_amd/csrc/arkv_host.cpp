@@ -49,10 +49,12 @@ struct LayerState {
   int cnt_refresh_P = 0;        // position of the step whose tailor the snapshot follows
 };
 
-// Sizes of the blocks a split prefill attention keeps its pieces in: 4 MB << i, up to the largest split's 128 MB.
-constexpr size_t kAttnBlockFloats = 1u << 20;
-constexpr int kAttnBlocks = 6;
-static_assert((kAttnBlockFloats << (kAttnBlocks - 1)) >= kAttnPartFloats, "the largest block must hold the largest split");
+// Blocks in which a split prefill attention keeps its pieces: the first one at least this large, every later one at least
+// twice the one before it, up to the largest split's size.
+constexpr size_t kAttnBlockFloats = 1u << 16;
+constexpr int kAttnBlocks = 10;
+static_assert((kAttnBlockFloats << (kAttnBlocks - 1)) >= kAttnPartFloats, "the last block must hold the largest split");
+struct AttnBlock { float* p; size_t floats; };
 
 struct arkv_cache {
   arkv_config cfg;
@@ -65,7 +67,7 @@ struct arkv_cache {
   float* rowc = nullptr; size_t rowc_cap = 0;
   int* stat_ticket = nullptr;     // [batch], zero between scorer calls
   uint64_t* ckeys = nullptr; size_t ckeys_cap = 0;
-  float* attn_block[kAttnBlocks] = {};   // pieces of a prefill attention that is split over the keys (attn_scratch)
+  AttnBlock attn_block[kAttnBlocks] = {};   // pieces of a prefill attention that is split over the keys (attn_scratch)
   int ckeys_layer = -1, ckeys_T = 0;
   hipStream_t last_stream = nullptr;
   // measurement hook: events around the attention kernel
@@ -292,8 +294,8 @@ int arkv_cache_destroy(arkv_cache* c) {
   if (c->rowc) (void)hipFree(c->rowc);
   if (c->stat_ticket) (void)hipFree(c->stat_ticket);
   if (c->ckeys) (void)hipFree(c->ckeys);
-  for (float* p : c->attn_block)
-    if (p) (void)hipFree(p);
+  for (const AttnBlock& b : c->attn_block)
+    if (b.p) (void)hipFree(b.p);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
   delete c;
   return ARKV_OK;
@@ -382,14 +384,16 @@ int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, cons
 
 // Scratch for the pieces of a prefill attention: the smallest block that holds them, allocated if there is none.  A call
 // that is captured leaves its block's address in the graph, so no block is freed before the cache is; the sizes double, so
-// the blocks of a cache are 252 MB at most.  The allocation must not break a capture on another stream (in the default
-// mode every thread's allocations do), so it is made in the relaxed mode.
+// the blocks of a cache are less than 256 MB together.  The allocation must not break a capture on another stream (in the
+// default mode every thread's allocations do), so it is made in the relaxed mode.
 // nullptr where there can be none (this call's own stream is being captured; no memory): such a call runs unsplit.
 static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
   int i = 0;
-  while (i < kAttnBlocks && (kAttnBlockFloats << i) < floats) ++i;
-  for (int j = i; j < kAttnBlocks; ++j)
-    if (c->attn_block[j]) return c->attn_block[j];
+  size_t size = std::max(floats, kAttnBlockFloats);
+  for (; i < kAttnBlocks && c->attn_block[i].p; ++i) {
+    if (c->attn_block[i].floats >= floats) return c->attn_block[i].p;
+    size = std::max(floats, std::min(2 * c->attn_block[i].floats, kAttnPartFloats));
+  }
   if (i == kAttnBlocks) return nullptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
@@ -397,10 +401,11 @@ static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   void* p = nullptr;
-  const hipError_t e = hipMalloc(&p, (kAttnBlockFloats << i) * sizeof(float));
+  const hipError_t e = hipMalloc(&p, size * sizeof(float));
   if (e != hipSuccess) { (void)hipGetLastError(); p = nullptr; }
   (void)hipThreadExchangeStreamCaptureMode(&mode);       // the caller's mode again
-  return c->attn_block[i] = static_cast<float*>(p);
+  if (p) c->attn_block[i] = {static_cast<float*>(p), size};
+  return static_cast<float*>(p);
 }
 
 int arkv_prefill_attention(arkv_cache* c, int32_t layer, const void* q, const void* k, const void* v, int32_t T_q,
