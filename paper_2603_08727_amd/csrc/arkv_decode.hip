@@ -356,7 +356,6 @@ struct ValueFmt {
     const uint32_t fill = n == NG ? kOnesF16 : 0u;
     b.z = n < NG ? zl : make_uint4(fill, fill, fill, fill);
   }
-  static __device__ __forceinline__ int group_of(int a) { return a / APG; }
   // B operand of accumulator a
   static __device__ __forceinline__ uint4 operand(const Blk& b, int a, int n) {
     uint32_t mask;
@@ -408,7 +407,6 @@ struct ValueFmt<D, 8> {
     const uint32_t fill = n == 0 ? kOnesF16 : 0u;
     b.z = make_uint4(fill, fill, fill, fill);
   }
-  static __device__ __forceinline__ int group_of(int) { return 0; }
   static __device__ __forceinline__ uint4 operand(const Blk& b, int a, int) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     const uint2 w = b.cw[a];

@@ -92,7 +92,7 @@ struct Pools {
 
 constexpr int kPlanHdr = 16;
 // plan header fields (int32 each)
-enum { PL_CO_NEW = 0, PL_CQ_NEW, PL_N_DEM, PL_N_QMOV, PL_N_OMOV, PL_N_ELIG, PL_CO_OLD, PL_CQ_OLD };
+enum { PL_CO_NEW = 0, PL_CQ_NEW, PL_N_DEM, PL_N_QMOV, PL_N_OMOV, PL_CO_OLD, PL_CQ_OLD };
 
 // Reciprocals for the decode kernel's split cut points (see split_range)
 struct SplitRecip { unsigned inv_s, inv_wq; };          // ceil(2^32 / S), ceil(2^32 / wq) (unused when S or wq is 1)

@@ -519,7 +519,7 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
     bool packed = false;
     for (int i = 0; i < n; ++i) {
       const LayerState& li = c->layers[(size_t)(layer_begin + i)];
-      if (li.n_tailors > 0 || c->cfg.capacity_tokens < li.T)
+      if (li.n_tailors > 0)
         for (int32_t no : li.n_o) packed = packed || no < c->b;
     }
     const int one = 256 / n_units, two = 512 / n_units;
