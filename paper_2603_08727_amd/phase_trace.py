@@ -6,8 +6,9 @@ Usage (GPU; build first with `python -m paper_2603_08727_amd.build --phase-trace
 Runs the prompt phase and K decode steps of N layers of the workload on the profiling library, then reads the
 100 MHz timestamps that thread 0 of every workgroup of the LAST decode launch stored at its phase boundaries
 (arkv_debug_phase_trace) and prints, per phase, the distribution over the workgroups, per XCD the tile loop's
-duration, and the merge's own phases in the merging workgroups.  The last launch is a read-only one when K % 8 != 0
-and one that also updates the scores when K % 8 == 0 (the update runs on every 8th step after the commit).
+duration, and the merge's own phases in the merging workgroups.  The last launch also updates the scores when K = 9, 17,
+25, ... (the update adds the eight steps that wait, from the ninth step after the commit on; a tailor, which none of these
+runs reaches, starts the count again), else it is a read-only one.
 """
 from __future__ import annotations
 
@@ -28,6 +29,11 @@ PHASES = ["start", "first tile requested", "bf16 rows", "new token", "packed row
           "ticket (+ merge)"]
 MERGE_PHASES = ["partial stored -> merge entered (acknowledgements, ticket)", "loads issued", "weights reduced",
                 "weights readable", "accumulated", "stored"]
+
+
+def updates_scores(step):
+    """Whether the step-th decode step after a commit also updates the scores."""
+    return step > 1 and (step - 1) % 8 == 0
 
 
 def dist(x):
@@ -78,7 +84,7 @@ def main():
     rel = (t - t[:, 0].min()) * 0.01    # microseconds
     print("workload %s, %d layers, rho %s, last launch of step %d (%s): %d workgroups = %d units x %d splits" % (
         wl.name, L, "scored" if args.rho is None else args.rho, args.steps,
-        "with score update" if args.steps % 8 == 0 else "read-only", n, U, n // U))
+        "with score update" if updates_scores(args.steps) else "read-only", n, U, n // U))
     print("marker kernel before -> first workgroup starts %.2f us; last workgroup ends -> marker kernel after %.2f us; "
           "marker to marker %.2f us" % ((t[:, 0].min() - mk[0]) * 0.01, (mk[1] - t[:, 6].max()) * 0.01,
                                        (mk[1] - mk[0]) * 0.01))

@@ -230,3 +230,19 @@ def test_attention_split_pieces():
     for bad in [(96, 4, 1, 10, 1), (64, 3, 1, 10, 1), (64, 4, 0, 10, 1), (64, 4, 1, 10, 11), (64, 4, 1, 10, 0)]:
         with pytest.raises(A.ArkvError):
             A.arkv_debug_attention_split(*bad)
+
+
+def test_phase_trace_names_the_launches_that_update_the_scores():
+    """The library adds the waiting steps when kRing - 1 of them wait (and then the step itself waits)."""
+    import subprocess
+    import sys
+    ring = int(re.search(r"constexpr int kRing = (\d+)", open(os.path.join(ROOT, "paper_2603_08727_amd", "csrc", "arkv_dev.h")).read()).group(1))
+    want, waiting = [], 0
+    for step in range(1, 60):
+        fold = waiting == ring - 1
+        want += [step] if fold else []
+        waiting = (0 if fold else waiting) + 1
+    got = subprocess.run([sys.executable, "-c", "from paper_2603_08727_amd import phase_trace as p\n"
+                          "print([s for s in range(1, 60) if p.updates_scores(s)])"], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert got.returncode == 0, got.stderr
+    assert got.stdout.strip() == str(want)
