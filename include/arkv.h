@@ -115,8 +115,10 @@ int arkv_prefill_stats_lse(arkv_cache* cache, int32_t layer, const void* q_win, 
  * committed): the call also does what arkv_prefill_stats does for the last W queries; the softmax maxima and
  * sums of those rows come out of the attention pass, so the scorer reads the keys once instead of twice.
  * Calls with few query rows against many keys split a row's keys over workgroups and merge the parts in fp32 (from
- * about 1000 keys; by shape alone): such a row differs from the same row of an unsplit call by the order of its fp32
- * sums.  The parts' scratch belongs to the cache: blocks of up to 128 MB (less than 256 MB together), allocated on first use
+ * about 1000 keys; by shape alone).  A part has a softmax reference of its own, against which its probabilities are rounded
+ * to fp16, so such a row differs from the same row of an unsplit call by the roundings of its probabilities and by the
+ * order of its fp32 sums (2e-4 of the output's 2-norm at 512 queries x 16411 keys; equally far from the exact result).
+ * The parts' scratch belongs to the cache: blocks of up to 128 MB (less than 256 MB together), allocated on first use
  * and when a larger call comes (an allocation may synchronise the device) and freed by arkv_cache_destroy only.  While the
  * call's stream is being captured nothing is allocated, and a call whose scratch is not there yet runs unsplit; a captured
  * call without stats can be replayed as long as the cache lives, whatever is called in between.
@@ -242,7 +244,8 @@ int arkv_debug_attend_time(arkv_cache* cache, double* total_ms, int64_t* launche
  * workgroups); prefill_chunk: keys per workgroup of the prefill scorer (multiple of 128, at most 8192; default:
  * 1024, halved while the grid would be small, or, with more than 256 query rows per kv-head, what makes the
  * grid one round of the chip; a value given here is taken as it is).  A value <= 0 leaves that setting as it
- * is.  Results do not depend on these beyond the order of floating-point additions.  ARKV_EINVAL: null cache,
+ * is.  Results do not depend on these beyond the order of floating-point additions and, with packed rows, the softmax
+ * reference against which a split's probabilities are rounded to fp16.  ARKV_EINVAL: null cache,
  * packed_weight above 16, prefill_chunk not a multiple of 128 or above 8192. */
 int arkv_debug_set_launch_shape(arkv_cache* cache, int32_t wg_target, int32_t packed_weight, int32_t prefill_chunk);
 

@@ -98,7 +98,7 @@ template <int D> constexpr int kPieceFloats = 32 * D + 96;
 // blocks, rest): the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at
 // the end, and with a multiple of 8 units a unit's workgroups share the L2 of one XCD (workgroups go to the XCDs in turn).
 // With the block fastest, the last unit's long blocks started late: 4096 tokens x 8 units, d = 128, G = 4 205 -> 156 us,
-// x 24 units 551 -> 460 us, 2003 x 32, d = 64, G = 1 51.6 -> 43.5 us.
+// x 24 units 551 -> 450 us, 2003 x 32, d = 64, G = 1 51.6 -> 43.5 us.
 // Units whose keys and values together exceed the last-level cache go in groups that fit (L.group units, see
 // attn_group), one group after the other: 32 units x 32768 tokens (537 MB) 36.7 ms all at once, 35.0 one unit at a time,
 // 34.3 in groups of eight; 64 x 8192 4.73 -> 4.49 ms against one at a time.
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 
 // Adds up the pieces of the workgroups that have more than one.  grid (query blocks, units, D / 32), the same waves and
 // lanes as above; a wave takes one block of 32 channels.  Bound by the partials' bytes (34 MB written and read at 512
-// queries x 16411 keys x 32 heads: 9 us of 148).
+// queries x 16411 keys x 32 heads: 9 us of 164).
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
   constexpr int QB = kQBlocks<G>;
@@ -475,7 +475,7 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
 // Measured at d = 128 (d = 64: about 0.65 of it): a tile step takes 0.75 us in a workgroup that has its CU to itself and
 // 1.06 us where two share it, so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU,
 // whichever is more; the merge costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where
-// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 158 us (4 pieces), 32 x 3000 x 16 units
+// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 164 us (4 pieces), 32 x 3000 x 16 units
 // (d = 64, G = 1) 66 -> 16 us.  It does not pay for a whole short prompt, whose imbalance is only the causal triangle
 // (1000 tokens x 8 kv-heads: 30 us unsplit, 37 us in 2 pieces), hence the margin and the floor of 32 tiles.
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {

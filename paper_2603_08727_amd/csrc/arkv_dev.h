@@ -179,7 +179,7 @@ hipError_t launch_flush_scores(const Pools& P, int unit_begin, int n_units, int 
 hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s);
 // n_o_seq, nb_seq: HOST [sequences], the layer's budgets, stored for the layer's units on the stream.  commit_keys: scratch of
 // commit_scratch_words words, only used when a.select: keys [U][T] (read by the debug hook), then per block of 1024
-// positions the rows in front of it
+// positions the rows and the scatter's parts in front of it
 hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
                          uint64_t* commit_keys, hipStream_t s);
 size_t commit_scratch_words(int n_units, int T);

@@ -506,8 +506,8 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
 // 640).  One workgroup per CU (8 to 24 units: 10-15 % faster than two, the merge has half the partials) unless packed
 // rows are many: their loop is bound by latency and needs the second workgroup once every CU has long ranges (32 units
 // x 8192, a third packed: 21.7 us at 16 splits, 23.5 at 8; all bf16: 22.2 us at 8, 23.3 at 16).  Whether a cache can hold
-// packed rows follows from its budgets, not from its counts: the factor decides the order of fp32 sums, so it must not
-// depend on when a count arrives.
+// packed rows follows from its budgets, not from its counts: the factor decides the order of fp32 sums and, for packed
+// rows, the reference against which a split's fp16 probabilities are rounded, so it must not depend on when a count arrives.
 // At least 64 rows (a tile per wave) per split (8 units x 800 bf16 rows: 7.2 us per call, 8.1 at 128 rows; x 390 rows,
 // a fifth packed: 9.0 and 9.9; x 1556 rows: the same).
 static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int n_units, int live) {

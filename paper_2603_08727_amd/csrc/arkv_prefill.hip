@@ -473,6 +473,8 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
 // Up to this many key chunks the column pass merges the first pass's partials itself (one batch of loads in its prologue)
 // and k_prefill_rowfinal, a launch of 5 us, is left out: 2000 keys x 8 units 20.6 -> 18.5 us.  With more chunks every
 // workgroup of the column pass reads more than the launch costs to save (32 chunks: 130 us either way).
+// The two add a row's partials in different orders, so a row constant, and with it a score, can differ in its last bit from
+// what the other gives.
 constexpr int kMergeChunks = 16;
 
 template <int D, int RT>
