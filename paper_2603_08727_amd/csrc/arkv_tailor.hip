@@ -124,7 +124,7 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
     // put whole waves on one bin.  So every wave looks at one of its rounds, spread over the unit; if any finds more than 24
     // lanes on one bin, the pass counts the lanes that share the first one's at once.  Otherwise it does not: that costs ten
     // instructions per round (32 units x 32768 positions: 3 us a pass).  All scores equal: a tailor step of 32 units x 8192
-    // rows 91 -> 77 us; 0.3 us more where nothing is equal.
+    // rows 91 -> 78 us; 0.3 us more where nothing is equal.
     auto count = [&](auto&& bin_of) {
       const int js = (w * rounds) >> 4;
       each(js, js + 1, [&](uint32_t sb, int row) {
@@ -960,7 +960,9 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
   const bool with_keys = a.select && batch <= 64;           // the budgets ride with the keys' launch
   if (!with_keys) launch_set_budgets(P, a.unit_begin, hkv, batch, n_o_seq, nb_seq, s);
   if (!a.select) {
-    const int rounds = (a.T + 4 * (256 / P.D) - 1) / (4 * (256 / P.D));     // of the four waves' rows
+    // a workgroup per round of its four waves while they are few, then 64 per CU that go through the rows side by side (32
+    // units x 16384 rows: 99 us at 16384 workgroups, 103 at 8192, 111 at 2048; 8 x 16384: 28.6, 27.9, 29.4)
+    const int rounds = (a.T + 4 * (256 / P.D) - 1) / (4 * (256 / P.D));
     const dim3 grid(clampi(rounds, 1, std::max(1, 16384 / a.n_units)), a.n_units);
     if (P.D == 128) hipLaunchKernelGGL(k_commit_copy<128>, grid, dim3(256), 0, s, P, a);
     else hipLaunchKernelGGL(k_commit_copy<64>, grid, dim3(256), 0, s, P, a);
