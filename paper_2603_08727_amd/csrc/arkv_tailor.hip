@@ -58,7 +58,7 @@ struct SelectLds {
   uint32_t wsum[2][16];
   uint64_t thr[2];
   int sel[2], k[2], cnt[2];
-  int crowded[6];                            // per pass
+  int crowded[3];                            // per pass over the scores
 };
 
 // inclusive sum over the wave's lanes up to this one (DPP: row shifts by 1, 2, 4, 8, then the rows' last lanes)
@@ -102,8 +102,9 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
   uint32_t score[2] = {0, 0};                // passes 3..5: the rank's whole score
   int k[2] = {k0, k1};
   bool done[2] = {k0 <= 0, k1 <= 0};
+  int left[2] = {0, 0}, total = 0;           // candidates of a rank after the last pass, and at the start
   if (tid < 2) sm.thr[tid] = ~0ull;
-  if (tid < 6) sm.crowded[tid] = 0;
+  if (tid < 3) sm.crowded[tid] = 0;
   int shift = 32;
   for (int pass = 0; pass < 6; ++pass) {
     if (done[0] && done[1]) break;
@@ -116,6 +117,7 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
     shift -= width;
     const bool shared = prefix[0] == prefix[1] && score[0] == score[1];    // both ranks still look at the same candidates
     const bool use0 = !done[0] || shared, use1 = !done[1] && !shared;
+    const bool few = 3 * ((use0 ? left[0] : 0) + (use1 ? left[1] : 0)) <= total;
     const int top = kBins - 1 - 2 * tid;     // this thread's bins: top and top - 1
     *reinterpret_cast<int2*>(&sm.hist[top - 1]) = make_int2(0, 0);
     *reinterpret_cast<int2*>(&sm.hist[kBins + top - 1]) = make_int2(0, 0);
@@ -123,29 +125,33 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
     // Accesses to one LDS word are served lane by lane, and equal scores (or the leading digits of neighbouring positions)
     // put whole waves on one bin.  So every wave looks at one of its rounds, spread over the unit; if any finds more than 24
     // lanes on one bin, the pass counts the lanes that share the first one's at once.  Otherwise it does not: that costs ten
-    // instructions per round (32 units x 32768 positions: 3 us a pass).  All scores equal: a tailor step of 32 units x 8192
-    // rows 91 -> 78 us; 0.3 us more where nothing is equal.
+    // instructions per round (32 units x 32768 positions: 3 us a pass).  Nor does it look where less than a third of the
+    // rows are candidates (a wave then has 21 of them).  All scores equal: a tailor step of 32 units x 8192 rows 91 -> 77 us;
+    // nothing equal: 64.0 -> 64.1, 8 units x 2048 33.5 -> 33.6 (33.8 if every pass looks).
+    auto count_shared = [&](auto&& bin_of) {
+      each(0, rounds, [&](uint32_t sb, int row) {
+        int bin = 0;
+        const bool add = bin_of(sb, row, bin);
+        const unsigned long long adding = __ballot(add);
+        if (adding == 0) return;
+        const Shared s = shared_bin(bin, add, adding);
+        if (lane == s.first || (add && bin != s.bin)) {
+          atomicAdd(&sm.hist[bin], lane == s.first ? s.lanes : 1);
+          sm.who[bin] = (Row)row;
+        }
+      });
+    };
     auto count = [&](auto&& bin_of) {
       const int js = (w * rounds) >> 4;
-      each(js, js + 1, [&](uint32_t sb, int row) {
+      if (!few) each(js, js + 1, [&](uint32_t sb, int row) {
         int bin = 0;
         const bool add = bin_of(sb, row, bin);
         const unsigned long long adding = __ballot(add);
         if (adding != 0 && shared_bin(bin, add, adding).lanes > 24 && lane == 0) sm.crowded[pass] = 1;
       });
       __syncthreads();
-      if (sm.crowded[pass]) {
-        each(0, rounds, [&](uint32_t sb, int row) {
-          int bin = 0;
-          const bool add = bin_of(sb, row, bin);
-          const unsigned long long adding = __ballot(add);
-          if (adding == 0) return;
-          const Shared s = shared_bin(bin, add, adding);
-          if (lane == s.first || (add && bin != s.bin)) {
-            atomicAdd(&sm.hist[bin], lane == s.first ? s.lanes : 1);
-            sm.who[bin] = (Row)row;
-          }
-        });
+      if (!few && sm.crowded[pass]) {
+        count_shared(bin_of);
       } else {
         each(0, rounds, [&](uint32_t sb, int row) {
           int bin = 0;
@@ -172,7 +178,8 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
         return c0 || c1;
       });
     } else {
-      count([&](uint32_t sb, int row, int& bin) {
+      __syncthreads();
+      count_shared([&](uint32_t sb, int row, int& bin) {
         bool c0 = use0 && sb == score[0], c1 = use1 && sb == score[1];
         if (c0 || c1) {
           const uint32_t lw = (uint32_t)key(row), hi = pass == 3 ? 0u : lw >> (shift + width);
@@ -199,6 +206,7 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
       if (i < w) { ge0 += s0; ge1 += s1; }
     }
     if (pass == 0) {
+      total = (int)tot0;
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         if (k[x] > (int)tot0) k[x] = (int)tot0;         // fewer candidates than k: keep them all
@@ -221,6 +229,7 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
       if (done[x]) continue;
       prefix[x] = (prefix[x] << width) | (uint32_t)sm.sel[x];
       k[x] = sm.k[x];
+      left[x] = sm.cnt[x];
       if (sm.cnt[x] == 1 && pass > 0) {                  // one candidate left
         if (tid == 0) sm.thr[x] = key((int)sm.who[(x == 0 || shared ? 0 : kBins) + sm.sel[x]]);
         done[x] = true;
