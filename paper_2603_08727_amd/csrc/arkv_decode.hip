@@ -611,6 +611,12 @@ __device__ __forceinline__ unsigned long long ld_dev2(const float* p) {
   return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// two adjacent channels of a unit's output (rows begin at element of of outf, ou of the caller's buffer)
+__device__ __forceinline__ void store_out2(const Pools& P, const DecodeLaunch& L, size_t of, size_t ou, int e, float r0, float r1) {
+  *reinterpret_cast<float2*>(P.outf + of + e) = make_float2(r0, r1);
+  *reinterpret_cast<uint32_t*>(L.out + ou + e) = (uint32_t)float_to_bf16_rne(r0) | ((uint32_t)float_to_bf16_rne(r1) << 16);
+}
+
 // Merge of a unit's split-K partials, wave by wave: wave w of every workgroup stores the channel pairs 64 w .. + 63
 // (+ 256 i) of the unit's heads, and the wave that stored them last (a ticket per unit and wave) merges exactly those:
 // output, the step's (max, 1/sum) of the heads in them, and with head 0 the token count.  Nothing here needs the other
@@ -723,10 +729,7 @@ __device__ __forceinline__ void combine_splits(const Pools& P, const DecodeLaunc
     if (idx < NP) {
       float iv = inv[i][0];
       if constexpr (HW == 2) iv = lane < 32 ? inv[i][0] : inv[i][1];
-      const float r0 = o[i][0] * iv, r1 = o[i][1] * iv;
-      *reinterpret_cast<float2*>(P.outf + (size_t)gu * G * D + 2 * idx) = make_float2(r0, r1);
-      *reinterpret_cast<uint32_t*>(L.out + (size_t)lu * G * D + 2 * idx) =
-          (uint32_t)float_to_bf16_rne(r0) | ((uint32_t)float_to_bf16_rne(r1) << 16);
+      store_out2(P, L, (size_t)gu * G * D, (size_t)lu * G * D, 2 * idx, o[i][0] * iv, o[i][1] * iv);
     }
   }
   // every workgroup of the unit has read the count: its wave 0 has passed the barrier in front of the partials
@@ -1263,8 +1266,19 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
       a1 = fmaf(t[i][0].y, cw_, a1);
       l = fmaf(lw[i], cw_, l);
     }
+    if (splits == 1) {
+      // the only split: its sums are the unit's (same arithmetic as a merge of one)
+      const float inv = 1.0f / l;
+      store_out2(P, L, (size_t)gu * G * D, (size_t)lu * G * D, 2 * idx, a0 * inv, a1 * inv);
+      if (c == 0) P.fin[(size_t)L.slot * P.fin_stride + (size_t)gu * G + h] = make_float2(M, inv);
+      continue;
+    }
     st_dev2(part + h * (D + 2) + c, a0, a1);
     if (c == 0) st_dev2(part + h * (D + 2) + D, M, l);
+  }
+  if (splits == 1) {
+    if (tid == 0) P.cnt[gu].x += 1;                // (every wave has read the count: the barrier above)
+    return;
   }
 
   TRACE(5);

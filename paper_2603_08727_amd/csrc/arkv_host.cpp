@@ -530,6 +530,11 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
     if (n_units < 8) splits = std::min(one, std::max(live < 20000 ? 48 : 64, live / 640));
   }
   splits = std::min(splits, std::max(1, live / 64));
+  // Few rows: one workgroup per unit writes the output itself and the partials' way through memory, the ticket and the
+  // merge fall away, against a longer row loop (us per call, one split / the best of more; d = 128, 8 units: G = 4, 128
+  // rows 6.2 / 7.4, 256 rows 7.4 / 7.3, G = 1 256 rows 6.4 / 6.1, G = 8 256 rows 10.6 / 10.6, a third packed 158 rows 6.9 /
+  // 8.8, 263 rows 8.6 / 8.5; d = 64: 128 rows 5.5 / 7.1, 320 rows 7.0 / 7.1, 384 rows 7.3 / 7.0).
+  if (c->wg_target <= 0 && live <= (c->P.D == 64 ? 336 : 240)) splits = 1;
   return std::max(1, std::min(splits, c->P.max_splits));
 }
 

@@ -405,3 +405,17 @@ def test_split_factors_of_few_units(hkv, g, d, T):
     wl = synth.C1.scaled(name=f"few{hkv}", n_q_heads=hkv * g, n_kv_heads=hkv, head_dim=d, prefill=T, budget_frac=1.01, window=16,
                          decode_steps=9)
     _run(wl, check_every=9)
+
+
+@pytest.mark.parametrize("g,d,T,budget,rho,bits", [
+    (4, 128, 234, 2.0, 0.5, 4),       # grows over 240 rows: one split, then more; all bf16
+    (8, 64, 330, 2.0, 0.5, 4),        # 336 rows at d = 64
+    (1, 64, 20, 3.0, 0.5, 4),         # waves without rows
+    (2, 128, 500, 0.42, 0.3, 2),      # packed rows in the only split
+    (8, 128, 500, 0.42, 0.3, 8),
+])
+def test_single_split(g, d, T, budget, rho, bits):
+    """Units of few rows are one workgroup's work, output included: over 18 steps, two of which update the scores."""
+    wl = synth.C1.scaled(name="single", batch=2, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, prefill=T, budget_frac=budget,
+                         bits=bits, window=16, decode_steps=18)
+    _run(wl, rho=rho, check_every=6)
