@@ -177,11 +177,13 @@ hipError_t phase_trace_decode(int which, unsigned long long* host, int n_wg, boo
 hipError_t phase_trace_attn(unsigned long long* host, bool* built);
 hipError_t launch_flush_scores(const Pools& P, int unit_begin, int n_units, int n_pending, int slot, hipStream_t s);
 hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s);
-// n_o_seq, nb_seq: HOST [sequences], the layer's budgets, stored for the layer's units on the stream.  commit_keys: scratch of
-// commit_scratch_words words, only used when a.select: keys [U][T] (read by the debug hook), then per block of 1024
-// positions the rows and the scatter's parts in front of it
+// n_o_seq, nb_seq: HOST [sequences], the layer's budgets, stored for the layer's units on the stream.  scratch: of
+// commit_scratch_words words, only used when a.select: the positions' scores come first, commit_score_pitch 32-bit words per
+// unit (commit_key: the selection key that a score stands for), then what the commit's kernels tell each other
 hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
-                         uint64_t* commit_keys, hipStream_t s);
+                         uint64_t* scratch, hipStream_t s);
+int commit_score_pitch(int T);
+uint64_t commit_key(const uint32_t* scores, int i);
 size_t commit_scratch_words(int n_units, int T);
 // Causal prefill attention of T_q queries (positions [T - T_q, T)) over T keys.
 struct AttnLaunch {

@@ -792,7 +792,12 @@ int arkv_debug_last_tailor_scores(arkv_cache* c, int32_t layer, int32_t max_toke
   if (ls.last_tailor == 1) {
     if (c->ckeys_layer != layer) return ARKV_ESTATE;   // scratch reused by another layer's commit
     per = (size_t)c->ckeys_T;
-    rc = fetch(keys, (const uint64_t*)c->ckeys, U * per);
+    const size_t pitch = (size_t)commit_score_pitch(c->ckeys_T);
+    std::vector<uint32_t> scores;
+    rc = fetch(scores, reinterpret_cast<const uint32_t*>(c->ckeys), U * pitch);
+    keys.assign(U * per, 0);
+    for (size_t u = 0; rc == ARKV_OK && u < U; ++u)
+      for (size_t i = 0; i < per; ++i) keys[u * per + i] = commit_key(&scores[u * pitch], (int)i);
   } else {
     per = (size_t)(c->P.capO + c->P.capQ);
     rc = fetch(keys, (const uint64_t*)c->P.keys + (size_t)layer * U * per, U * per);

@@ -40,25 +40,35 @@ __device__ __forceinline__ uint64_t make_key(float S, int pos) {
 // ------------------------------------------------------------------------------------------
 // exact k-th largest key for two ranks at once, by one workgroup of 1024 threads.
 //
-// Radix select, most significant digit first, on digits of 11, 11 and 10 bits of the score; the position is only looked
-// at where scores tie at a rank.  Bound by the one CU's instruction issue and the passes' barriers, not by bytes, hence:
-// the unit's scores as 32-bit words in LDS and rolled loops over them (in registers they took unrolled code with the
-// ballots of every round live at once: hundreds of spilled scalar registers), both ranks in the same passes, and wide
-// digits, which leave a handful of candidates after two passes.  Once the chosen bin holds a single candidate the
-// remaining passes are skipped.
+// Radix select, most significant digit first, on digits of up to 11 bits of (score - smallest score): the scores of a unit
+// share most of their leading bits, so digits of the difference spread them over the bins from the first pass on, and two
+// passes usually leave one candidate per rank (digits of the score itself: three passes, the first one held up by lanes that
+// met on the few exponents' bins).  The position is only looked at where scores tie at a rank.  Bound by the one CU's
+// instruction issue and the passes' barriers, not by bytes, hence: the unit's scores as 32-bit words in LDS, four to a read,
+// and rolled loops over them (in registers they took unrolled code with the ballots of every round live at once: hundreds of
+// spilled scalar registers), and both ranks in the same passes.  Once the chosen bin holds a single candidate the remaining
+// passes are skipped.
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kNoScore = 0xFFFFFFFFu;   // not ranked (above every score, see make_key)
 constexpr int kLdsRows = 32768;              // units of up to this many rows keep their scores in LDS (128 KB)
 constexpr int kRounds = 32;                  // rounds of 1024 rows per list chunk
-constexpr int kBins = 2048;
+constexpr int kBins = 2048, kDigit = 11;
+constexpr int kQuad = 4096;                  // rows of a round of the selection: four adjacent ones per thread
+__host__ __device__ constexpr int quads(int rows) { return (rows + kQuad - 1) / kQuad; }
 template <typename Row>                      // Row: integer that holds a row index
 struct SelectLds {
-  int hist[2 * kBins];                       // one histogram per rank
+  union {
+    int hist[2 * kBins];                     // one histogram per rank
+    struct {                                 // behind the selection, per 64 rows of a list chunk (see k_tailor_choose)
+      uint64_t stay[kRounds * 16], dem[kRounds * 16];
+      uint32_t off[3][kRounds * 16];         // places of the rows' first entries in the lists, two of 16 bits each
+    };
+  };
   Row who[2 * kBins];                        // a row that fell into the bin (the row, where only one did)
-  uint32_t wsum[2][16];
+  uint32_t wsum[2][16], lo[16], hi[16];
   uint64_t thr[2];
   int sel[2], k[2], cnt[2];
-  int crowded[3];                            // per pass over the scores
+  int crowded[6];                            // per pass over the scores
 };
 
 // inclusive sum over the wave's lanes up to this one (DPP: row shifts by 1, 2, 4, 8, then the rows' last lanes)
@@ -75,14 +85,35 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t v) {
   return dpp_add<0x143, 0xc>(v);
 }
 
-// A row's key against a threshold: score bits first, then the key's low word (asked for only where scores tie)
-template <typename Low>
-__device__ __forceinline__ bool key_ge(uint32_t sb, int row, uint64_t thr, Low&& low) {
-  const uint32_t ts = (uint32_t)(thr >> 32);
-  bool ge = sb > ts;
-  if (__any(sb == ts)) { if (sb == ts) ge = low(row) >= (uint32_t)thr; }
-  return ge;
+// Sums of 16 waves' values in LDS: of the waves before this one (w, uniform), and of all.
+struct WaveSums { uint32_t before, total; };
+__device__ __forceinline__ WaveSums wave_sums(const uint32_t* sums /*[16]*/, int lane, int w) {
+  uint32_t v = sums[lane & 15];
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  const uint32_t up_to = (uint32_t)__builtin_amdgcn_readlane((int)v, w), own = sums[w];
+  return {up_to - own, (uint32_t)__builtin_amdgcn_readlane((int)v, 15)};
 }
+
+// Smallest and largest score seen so far; over the wave's lanes.
+struct ScoreRange {
+  uint32_t lo = kNoScore, hi = 0;
+  __device__ __forceinline__ void add(uint32_t sb) {
+    lo = min(lo, sb);
+    hi = max(hi, sb == kNoScore ? 0u : sb);
+  }
+  // over the wave's lanes, in the last one (the steps of wave_prefix_sum)
+  template <int CTRL, int ROWS>
+  __device__ __forceinline__ void step() {
+    lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp((int)kNoScore, (int)lo, CTRL, ROWS, 0xf, false));
+    hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, ROWS, 0xf, false));
+  }
+  __device__ __forceinline__ void wave() {
+    step<0x111, 0xf>(); step<0x112, 0xf>(); step<0x114, 0xf>(); step<0x118, 0xf>(); step<0x142, 0xa>(); step<0x143, 0xc>();
+  }
+};
 
 // The lanes of a wave that share the first adding lane's bin (all lanes of the wave must be here).
 struct Shared { int first, bin, lanes; };
@@ -91,101 +122,141 @@ __device__ __forceinline__ Shared shared_bin(int bin, bool add, unsigned long lo
   return {first, b, (int)__popcll(__ballot(add && bin == b))};
 }
 
-// each(j0, j1, f) must call f(score bits, row) for this thread's row of every round j0 .. j1 - 1 (kNoScore: not a candidate);
-// key(row) = a candidate's key, for any thread.  sm.thr[x] = key of rank k_x, or ~0 when k_x = 0 or there
-// is no candidate (nothing qualifies); k_x is clamped to the number of candidates, so "fewer candidates than b" keeps
-// everything.  Ends with a barrier.
-template <typename Row, typename Each, typename Key>
-__device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, int k0, int k1, SelectLds<Row>& sm) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+// Barrier for what the workgroup keeps in LDS only: it does not wait for the wave's stores to memory, as __syncthreads does
+// (about a microsecond behind a phase that wrote there).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// load(q, s) must give the scores s[0 .. 3] of rows 4096 q + 4 * thread .. + 3, q < nq (kNoScore: not a candidate);
+// score(row), key(row) = a candidate's, for any thread; range: of the scores this thread has seen, all threads' together of
+// all candidates.  sm.thr[x]: the candidates whose key is at least that are the best k_x.  It is the key of rank k_x, its low
+// word left out (0) where no other candidate has that score, or ~0 when k_x = 0 or there is no candidate (nothing
+// qualifies); k_x is clamped to the number of candidates, so "fewer candidates than b" keeps everything.  Ends with a barrier.
+template <typename Row, typename Load, typename Score, typename Key>
+__device__ __forceinline__ void select_two(int nq, Load&& load, Score&& score_at, Key&& key, ScoreRange range, int k0, int k1,
+                                           SelectLds<Row>& sm) {
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t prefix[2] = {0, 0};               // digits found so far: of the score, then (tie) of the low word
-  uint32_t score[2] = {0, 0};                // passes 3..5: the rank's whole score
+  uint32_t base = 0, score[2] = {0, 0};      // the smallest score; tie passes: the rank's whole score
   int k[2] = {k0, k1};
   bool done[2] = {k0 <= 0, k1 <= 0};
   int left[2] = {0, 0}, total = 0;           // candidates of a rank after the last pass, and at the start
+  range.wave();
+  if (lane == 63) { sm.lo[w] = range.lo; sm.hi[w] = range.hi; }
   if (tid < 2) sm.thr[tid] = ~0ull;
-  if (tid < 3) sm.crowded[tid] = 0;
-  int shift = 32;
-  for (int pass = 0; pass < 6; ++pass) {
+  if (tid < 6) sm.crowded[tid] = 0;
+  bool tie = false;                          // scores are used up: digits of the low word among equal scores
+  int rest = 0;                              // bits of the score (low word) not looked at yet
+  for (int pass = 0;; ++pass) {
     if (done[0] && done[1]) break;
-    const bool tie = pass >= 3;              // scores are used up: digits of the low word among equal scores
-    if (pass == 3) {
-      shift = 32;
-      for (int x = 0; x < 2; ++x) { score[x] = prefix[x]; prefix[x] = 0; }
-    }
-    const int width = pass % 3 == 2 ? 10 : 11;
-    shift -= width;
-    const bool shared = prefix[0] == prefix[1] && score[0] == score[1];    // both ranks still look at the same candidates
-    const bool use0 = !done[0] || shared, use1 = !done[1] && !shared;
-    const bool few = 3 * ((use0 ? left[0] : 0) + (use1 ? left[1] : 0)) <= total;
     const int top = kBins - 1 - 2 * tid;     // this thread's bins: top and top - 1
     *reinterpret_cast<int2*>(&sm.hist[top - 1]) = make_int2(0, 0);
     *reinterpret_cast<int2*>(&sm.hist[kBins + top - 1]) = make_int2(0, 0);
+    if (pass == 0) {
+      lds_barrier();
+      uint32_t lo = kNoScore, hi = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { lo = min(lo, sm.lo[i]); hi = max(hi, sm.hi[i]); }
+      base = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+      hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+      rest = hi > base ? 32 - __builtin_clz(hi - base) : 0;
+    }
+    if (rest == 0) {
+      if (tie) break;                        // (positions are distinct: a bin of the last pass holds one candidate)
+      tie = true;
+      rest = 32;
+      for (int x = 0; x < 2; ++x) { score[x] = base + prefix[x]; prefix[x] = 0; }
+    }
+    const bool low_first = tie && rest == 32;
+    const int width = min(rest, kDigit);
+    rest -= width;
+    const bool shared = prefix[0] == prefix[1] && score[0] == score[1];    // both ranks still look at the same candidates
+    const bool use0 = !done[0] || shared, use1 = !done[1] && !shared;
+    const bool few = 3 * ((use0 ? left[0] : 0) + (use1 ? left[1] : 0)) <= total;
     // bin_of(score, row, bin): whether the row is counted in this pass, and in which bin, which remembers a row.
     // Accesses to one LDS word are served lane by lane, and equal scores (or the leading digits of neighbouring positions)
-    // put whole waves on one bin.  So every wave looks at one of its rounds, spread over the unit; if any finds more than 24
+    // put whole waves on one bin.  So every wave looks at a row per lane, spread over the unit; if any finds more than 24
     // lanes on one bin, the pass counts the lanes that share the first one's at once.  Otherwise it does not: that costs ten
-    // instructions per round (32 units x 32768 positions: 3 us a pass).  Nor does it look where less than a third of the
-    // rows are candidates (a wave then has 21 of them).  All scores equal: a tailor step of 32 units x 8192 rows 91 -> 77 us;
-    // nothing equal: 64.0 -> 64.1, 8 units x 2048 33.5 -> 33.6 (33.8 if every pass looks).
+    // instructions per round.  Nor does it look where less than a third of the rows are candidates (a wave then has 21 of
+    // them).
     auto count_shared = [&](auto&& bin_of) {
-      each(0, rounds, [&](uint32_t sb, int row) {
-        int bin = 0;
-        const bool add = bin_of(sb, row, bin);
-        const unsigned long long adding = __ballot(add);
-        if (adding == 0) return;
-        const Shared s = shared_bin(bin, add, adding);
-        if (lane == s.first || (add && bin != s.bin)) {
-          atomicAdd(&sm.hist[bin], lane == s.first ? s.lanes : 1);
-          sm.who[bin] = (Row)row;
+      for (int q = 0; q < nq; ++q) {
+        uint32_t s4[4];
+        load(q, s4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = kQuad * q + 4 * tid + e;
+          int bin = 0;
+          const bool add = bin_of(s4[e], row, bin);
+          const unsigned long long adding = __ballot(add);
+          if (adding == 0) continue;
+          const Shared s = shared_bin(bin, add, adding);
+          if (lane == s.first || (add && bin != s.bin)) {
+            atomicAdd(&sm.hist[bin], lane == s.first ? s.lanes : 1);
+            sm.who[bin] = (Row)row;
+          }
         }
-      });
+      }
     };
     auto count = [&](auto&& bin_of) {
-      const int js = (w * rounds) >> 4;
-      if (!few) each(js, js + 1, [&](uint32_t sb, int row) {
+      if (!few) {
+        const int q = (w * nq) >> 4;
+        uint32_t s4[4];
+        load(q, s4);
         int bin = 0;
-        const bool add = bin_of(sb, row, bin);
+        const bool add = bin_of(s4[0], kQuad * q + 4 * tid, bin);
         const unsigned long long adding = __ballot(add);
         if (adding != 0 && shared_bin(bin, add, adding).lanes > 24 && lane == 0) sm.crowded[pass] = 1;
-      });
+      }
       __syncthreads();
       if (!few && sm.crowded[pass]) {
         count_shared(bin_of);
       } else {
-        each(0, rounds, [&](uint32_t sb, int row) {
-          int bin = 0;
-          if (bin_of(sb, row, bin)) {
-            atomicAdd(&sm.hist[bin], 1);
-            sm.who[bin] = (Row)row;
+        for (int q = 0; q < nq; ++q) {
+          uint32_t s4[4];
+          load(q, s4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int row = kQuad * q + 4 * tid + e;
+            int bin = 0;
+            if (bin_of(s4[e], row, bin)) {
+              atomicAdd(&sm.hist[bin], 1);
+              sm.who[bin] = (Row)row;
+            }
           }
-        });
+        }
       }
     };
-    if (pass == 0) {
-      // leading digits are often shared (scores of one unit have few exponents): the second histogram is free in this
-      // pass, so odd lanes count there and half as many lanes meet on a bin
-      __syncthreads();
-      each(0, rounds, [&](uint32_t sb, int) {
-        if (sb != kNoScore) atomicAdd(&sm.hist[(lane & 1) * kBins + (int)(sb >> 21)], 1);
-      });
+    if (pass == 0 && !tie) {
+      if (rest + width <= 6) {               // (nearly) equal scores: whole waves meet on a bin
+        count_shared([&](uint32_t sb, int, int& bin) { bin = (int)((sb - base) >> rest); return sb != kNoScore; });
+      } else {
+        // the second histogram is free in this pass, so odd lanes count there and half as many lanes meet on a bin
+        const int odd = (lane & 1) * kBins;
+        for (int q = 0; q < nq; ++q) {
+          uint32_t s4[4];
+          load(q, s4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (s4[e] != kNoScore) atomicAdd(&sm.hist[odd + (int)((s4[e] - base) >> rest)], 1);
+        }
+      }
     } else if (!tie) {
-      const int up = shift + width;
+      const int up = rest + width;
       count([&](uint32_t sb, int, int& bin) {
-        const uint32_t hi = sb >> up;        // (kNoScore never matches: no score shares its first digit)
+        const uint32_t v = sb - base, hi = v >> up;    // (kNoScore never matches: it lies at least 2^21 above every score)
         const bool c0 = use0 && hi == prefix[0], c1 = use1 && hi == prefix[1];
-        bin = (int)__builtin_amdgcn_ubfe(sb, shift, width) + (c0 ? 0 : kBins);
+        bin = (int)__builtin_amdgcn_ubfe(v, rest, width) + (c0 ? 0 : kBins);
         return c0 || c1;
       });
     } else {
-      __syncthreads();
+      __syncthreads();                       // (the keys may lie in memory)
       count_shared([&](uint32_t sb, int row, int& bin) {
         bool c0 = use0 && sb == score[0], c1 = use1 && sb == score[1];
         if (c0 || c1) {
-          const uint32_t lw = (uint32_t)key(row), hi = pass == 3 ? 0u : lw >> (shift + width);
+          const uint32_t lw = (uint32_t)key(row), hi = low_first ? 0u : lw >> (rest + width);
           c0 = c0 && hi == prefix[0];
           c1 = c1 && hi == prefix[1];        // (not both: two ranks with the same digits share the first histogram)
-          bin = (int)__builtin_amdgcn_ubfe(lw, shift, width) + (c0 ? 0 : kBins);
+          bin = (int)__builtin_amdgcn_ubfe(lw, rest, width) + (c0 ? 0 : kBins);
         }
         return c0 || c1;
       });
@@ -194,17 +265,14 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
     // ge = candidates in bins top - 1 and above
     int2 a = *reinterpret_cast<const int2*>(&sm.hist[top - 1]);
     const int2 b = *reinterpret_cast<const int2*>(&sm.hist[kBins + top - 1]);
-    if (pass == 0) { a.x += b.x; a.y += b.y; }
+    if (pass == 0 && !tie) { a.x += b.x; a.y += b.y; }
     uint32_t ge0 = wave_prefix_sum((uint32_t)(a.x + a.y)), ge1 = wave_prefix_sum((uint32_t)(b.x + b.y));
     if (lane == 63) { sm.wsum[0][w] = ge0; sm.wsum[1][w] = ge1; }
     __syncthreads();
-    uint32_t tot0 = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t s0 = sm.wsum[0][i], s1 = sm.wsum[1][i];
-      tot0 += s0;
-      if (i < w) { ge0 += s0; ge1 += s1; }
-    }
+    const WaveSums w0 = wave_sums(sm.wsum[0], lane, w), w1 = wave_sums(sm.wsum[1], lane, w);
+    const uint32_t tot0 = w0.total;
+    ge0 += w0.before;
+    ge1 += w1.before;
     if (pass == 0) {
       total = (int)tot0;
 #pragma unroll
@@ -230,8 +298,9 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
       prefix[x] = (prefix[x] << width) | (uint32_t)sm.sel[x];
       k[x] = sm.k[x];
       left[x] = sm.cnt[x];
-      if (sm.cnt[x] == 1 && pass > 0) {                  // one candidate left
-        if (tid == 0) sm.thr[x] = key((int)sm.who[(x == 0 || shared ? 0 : kBins) + sm.sel[x]]);
+      if (sm.cnt[x] == 1 && (pass > 0 || tie)) {         // one candidate left
+        const int row = (int)sm.who[(x == 0 || shared ? 0 : kBins) + sm.sel[x]];
+        if (tid == 0) sm.thr[x] = tie ? key(row) : (uint64_t)score_at(row) << 32;
         done[x] = true;
       }
     }
@@ -244,7 +313,7 @@ __device__ __forceinline__ void select_two(int rounds, Each&& each, Key&& key, i
 // ------------------------------------------------------------------------------------------
 template <int NF>
 __device__ __forceinline__ void block_excl_scan(uint32_t (&v)[NF], uint32_t (*sm)[16] /*[NF][16]*/, uint32_t (&total)[NF]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t inc[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
@@ -254,25 +323,12 @@ __device__ __forceinline__ void block_excl_scan(uint32_t (&v)[NF], uint32_t (*sm
   __syncthreads();
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    uint32_t before = 0;
-    total[f] = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t t = sm[f][i];
-      total[f] += t;
-      if (i < w) before += t;
-    }
-    v[f] = before + inc[f] - v[f];
+    const WaveSums ws = wave_sums(sm[f], lane, w);
+    total[f] = ws.total;
+    v[f] = ws.before + inc[f] - v[f];
   }
   __syncthreads();
 }
-
-// Keys of a unit's rows and their list positions.  A workgroup goes through its rows in rounds of 1024 (thread t: row
-// 1024 j + t), so a wave's ballots of a round cover 64 consecutive rows; per (round, wave) the counts are kept in LDS,
-// scanned once per chunk of kRounds rounds, and every row then knows its place in each list.
-struct ListLds {
-  uint32_t c[3][kRounds * 16];               // two counts of 16 bits each (a chunk has at most 32768 rows), then their sums
-};
 
 // a row's place behind the rows before it in the wave that set the same flag
 __device__ __forceinline__ int place(unsigned long long flags, int lane) {
@@ -281,18 +337,33 @@ __device__ __forceinline__ int place(unsigned long long flags, int lane) {
 
 // ------------------------------------------------------------------------------------------
 // in-place tailor: keys (eq. 9's score per row), the two thresholds, and the lists that compact both pools.
-// One workgroup per unit, one launch.  Keys, a select per rank and the lists were three (5 + 18 + 15 us at 32 units x 8192
-// rows, 26 us now; a step with a tailor 85 -> 68 us; 8 units x 32000 rows 182 -> 118 us).
+// One workgroup per unit, one launch, bound by one CU's instruction issue and round trips (32 units x 8192 rows, one moved per
+// step: 14 us inside the kernel, of which keys 3, selection 6, fates 3, lists 2; a step with a tailor 64.3 -> 56.5 us against
+// digits of the plain score, scalar LDS reads, a fate word per row and thresholds fetched from memory).  Fates are kept as a
+// bit per row (two words per 64 rows), so that the lists' counts are one thread's work per 64 rows and words with nothing to
+// list are skipped.
 //   plan: header | ohole[capO] | omov[capO] | dem[capO] | qfree[capQ] | qmov[capQ]
 // ------------------------------------------------------------------------------------------
+// bits 0 .. n - 1 of a word whose first bit is row `row0`: the rows below `end`
+__device__ __forceinline__ uint64_t rows_below(int row0, int end) {
+  const int n = end - row0;
+  return n <= 0 ? 0ull : n >= 64 ? ~0ull : (1ull << n) - 1ull;
+}
+// What a list gets of 64 rows: Original rows to fill (hole), Original rows behind the new end that stay (mov), demoted rows
+// (dem), free Quantized slots below the new end (fr), Quantized rows behind it that stay (qm).
+struct ListFlags { uint64_t hole, mov, dem, fr, qm; };
+__device__ __forceinline__ ListFlags list_flags(uint64_t stay, uint64_t dem, int row0, int cO, int n, int cOn, int cQn) {
+  const uint64_t o = rows_below(row0, cO), on = rows_below(row0, cOn), all = rows_below(row0, n), q = rows_below(row0, cO + cQn);
+  return {~stay & on, stay & o & ~on, dem, ~stay & all & q & ~o, stay & all & ~o & ~q};
+}
+
 template <int G, bool IN_LDS>
 __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L) {
-  extern __shared__ uint32_t row_word[];                    // IN_LDS: score of row i, later its fate
-  __shared__ SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
-  __shared__ ListLds lists;
+  extern __shared__ __align__(16) uint32_t row_word[];      // IN_LDS: score of row i
+  __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
   __shared__ uint32_t scan_sm[3][16];
   __shared__ int tot[3];
-  const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int2 cnt = P.cnt[gu];
   const int cO = cnt.x, cQ = cnt.y, n = cO + cQ;           // rows: the O pool's, then the Q pool's
   uint64_t* keys = P.keys + (size_t)gu * (P.capO + P.capQ);
@@ -301,30 +372,46 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   const float2* oacc = P.oacc + (size_t)gu * P.capO;
   const float2* qacc = P.qacc + (size_t)gu * P.capQ;
   const int slot_q = P.capO - cO;                           // row i >= cO: key slot i + slot_q
-  const int rounds = (n + 1023) / 1024;
+  const int nq = quads(n), rounds = (n + 1023) / 1024;
+  ScoreRange range;
   // (a barrier of the selection stands between these stores and another thread's read of a key)
-  constexpr int BATCH = 4;                                  // rows requested together (one by one, a memory round trip each)
-  for (int j0 = 0; j0 < rounds; j0 += BATCH) {
-    int pos[BATCH];
-    float2 acc[BATCH];
+  constexpr int BATCH = 4;                                  // rows requested together, one batch ahead of their use
+  struct Rows { int pos[BATCH]; float2 acc[BATCH]; };
+  auto fetch = [&](int q, Rows& r) {
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
-      const int i = min(1024 * (j0 + j) + tid, n - 1);
-      pos[j] = i < cO ? opos[i] : qpos[i - cO];
-      acc[j] = i < cO ? oacc[i] : qacc[i - cO];
+      const int i = min(kQuad * q + 1024 * j + tid, n - 1);
+      r.pos[j] = i < cO ? opos[i] : qpos[i - cO];
+      r.acc[j] = i < cO ? oacc[i] : qacc[i - cO];
     }
+  };
+  auto score_rows = [&](int q, const Rows& r) {
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
-      const int i = 1024 * (j0 + j) + tid;
+      const int i = kQuad * q + 1024 * j + tid;
+      if (kQuad * q + 1024 * j >= n) {                      // a round without rows
+        if constexpr (IN_LDS) row_word[i] = kNoScore;
+        continue;
+      }
       uint64_t key = 0;
-      if (pos[j] < L.position + 1 - L.window) {
-        const int first = pos[j] > L.t_prefill - L.window ? pos[j] : L.t_prefill - L.window;
-        key = make_key(hh_score(acc[j].x, acc[j].y, G * (L.position - first + 1), L.gamma), pos[j]);
+      if (i < n && r.pos[j] < L.position + 1 - L.window) {
+        const int first = r.pos[j] > L.t_prefill - L.window ? r.pos[j] : L.t_prefill - L.window;
+        key = make_key(hh_score(r.acc[j].x, r.acc[j].y, G * (L.position - first + 1), L.gamma), r.pos[j]);
       }
-      if (i < n) {
-        keys[i < cO ? i : i + slot_q] = key;
-        if constexpr (IN_LDS) row_word[i] = key ? (uint32_t)(key >> 32) : kNoScore;
-      }
+      const uint32_t sb = key ? (uint32_t)(key >> 32) : kNoScore;
+      range.add(sb);
+      if (i < n) keys[i < cO ? i : i + slot_q] = key;
+      if constexpr (IN_LDS) row_word[i] = sb;               // (whole quads)
+    }
+  };
+  Rows ra, rb;
+  fetch(0, ra);
+  for (int q = 0; q < nq; q += 2) {
+    fetch(min(q + 1, nq - 1), rb);
+    score_rows(q, ra);
+    if (q + 1 < nq) {
+      fetch(min(q + 2, nq - 1), ra);
+      score_rows(q + 1, rb);
     }
   }
   auto key_of = [&](int i) -> uint64_t { return keys[i < cO ? i : i + slot_q]; };
@@ -333,38 +420,63 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     const uint64_t k = key_of(i);
     return k ? (uint32_t)(k >> 32) : kNoScore;
   };
-  auto low = [&](int i) { return (uint32_t)key_of(i); };
-  auto each = [&](int j0, int j1, auto&& f) {
-    for (int j = j0; j < j1; ++j) {
-      const int i = 1024 * j + tid;
-      f(i < n ? score_of(i) : kNoScore, i);
+  auto load = [&](int q, uint32_t (&s)[4]) {
+    const int i = kQuad * q + 4 * tid;
+    if constexpr (IN_LDS) {
+      const uint4 v = *reinterpret_cast<const uint4*>(row_word + i);
+      s[0] = v.x; s[1] = v.y; s[2] = v.z; s[3] = v.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] = i + e < n ? score_of(i + e) : kNoScore;
     }
   };
   if (tid < 3) tot[tid] = 0;
-  select_two(rounds, each, key_of, P.n_o[gu], P.nb[gu], sel);
+  select_two(nq, load, score_of, key_of, range, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
 
-  // what becomes of a row: 1 stays in its pool, 2 is demoted, 0 is evicted (window rows stay)
-  auto classify = [&](int i) -> uint32_t {
-    if (i >= n) return 0;
-    const uint32_t sb = score_of(i);
-    const bool o = i < cO, cand = sb != kNoScore;
-    const bool geb = cand && key_ge(sb, i, thr_b, low), geo = cand && key_ge(sb, i, thr_o, low);
-    return (o ? !cand || geo : geb) ? 1u : (o && geb) ? 2u : 0u;
+  // What becomes of the 64 rows of a wave's round: whether they stay in their pool (window rows do), are demoted, or (neither)
+  // are evicted.
+  const uint32_t so = (uint32_t)(thr_o >> 32), sq = (uint32_t)(thr_b >> 32);
+  const bool ties = __builtin_amdgcn_readfirstlane((uint32_t)thr_o | (uint32_t)thr_b) != 0;
+  auto classify = [&](int i, uint32_t sb, uint64_t& stay, uint64_t& dem) {
+    bool geo = sb >= so, geb = sb >= sq;
+    if (ties && __any(sb != kNoScore && (sb == so || sb == sq))) {     // scores that tie with a threshold: the whole key decides
+      if (sb != kNoScore) {
+        const uint64_t key = key_of(i);
+        geo = key >= thr_o; geb = key >= thr_b;
+      }
+    }
+    const bool o = i < cO, none = sb == kNoScore;
+    stay = __ballot(o ? none || geo : geb && !none);
+    dem = __ballot(o && !none && geb && !geo);
   };
-  auto fate_of = [&](int i) -> uint32_t {
-    if constexpr (IN_LDS) return i < n ? row_word[i] : 0u;
-    else return classify(i);
+  // four rounds of 1024 rows: a row's word, a wave's 64 rows at a time (kNoScore behind the last row)
+  auto words = [&](int q, uint32_t (&s)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = kQuad * q + 1024 * e + tid;
+      if constexpr (IN_LDS) s[e] = row_word[i];
+      else s[e] = i < n ? score_of(i) : kNoScore;
+    }
   };
   // rows that stay Original, are demoted, stay Quantized
   int keepO = 0, nDem = 0, keepQ = 0;
-  for (int j = 0; j < rounds; ++j) {
-    const int i = 1024 * j + tid;
-    const uint32_t f = classify(i);
-    if constexpr (IN_LDS) { if (i < n) row_word[i] = f; }
-    keepO += __popcll(__ballot(f == 1 && i < cO));
-    nDem += __popcll(__ballot(f == 2));
-    keepQ += __popcll(__ballot(f == 1 && i >= cO));
+  const bool one_chunk = rounds <= kRounds;
+  for (int q = 0; q < nq; ++q) {
+    uint32_t s4[4];
+    words(q, s4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = 4 * q + e;
+      if (j >= rounds) continue;
+      uint64_t stay, dem;
+      classify(1024 * j + tid, s4[e], stay, dem);
+      const uint64_t o = rows_below(1024 * j + 64 * w, cO);
+      keepO += __popcll(stay & o);
+      nDem += __popcll(dem);
+      keepQ += __popcll(stay & ~o);
+      if (one_chunk && lane == 0) { sel.stay[16 * j + w] = stay; sel.dem[16 * j + w] = dem; }
+    }
   }
   if (lane == 0) { atomicAdd(&tot[0], keepO); atomicAdd(&tot[1], nDem); atomicAdd(&tot[2], keepQ); }
   __syncthreads();
@@ -377,46 +489,60 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   int32_t* qfree = dem_ + P.capO;
   int32_t* qmov = qfree + P.capQ;
   int base_hole = 0, base_mov = 0, base_dem = 0, base_free = 0, base_qmov = 0;
-  struct Flags { bool hole, mov, dem, fr, qm; };
-  auto flags = [&](int i) {
-    const uint32_t fate_ = fate_of(i);
-    Flags f{false, false, fate_ == 2, false, false};
-    if (i < cO) { f.hole = i < cOn && fate_ != 1; f.mov = i >= cOn && fate_ == 1; }
-    else if (i < n) { f.fr = i - cO < cQn && fate_ != 1; f.qm = i - cO >= cQn && fate_ == 1; }
-    return f;
-  };
   for (int j0 = 0; j0 < rounds; j0 += kRounds) {
     const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds, entries = 16 * nj;
-    for (int j = 0; j < nj; ++j) {
-      const Flags f = flags(1024 * (j0 + j) + tid);
-      const uint32_t hm = (uint32_t)__popcll(__ballot(f.hole)) | ((uint32_t)__popcll(__ballot(f.mov)) << 16);
-      const uint32_t df = (uint32_t)__popcll(__ballot(f.dem)) | ((uint32_t)__popcll(__ballot(f.fr)) << 16);
-      const uint32_t qm = (uint32_t)__popcll(__ballot(f.qm));
-      if (lane == 0) { lists.c[0][16 * j + w] = hm; lists.c[1][16 * j + w] = df; lists.c[2][16 * j + w] = qm; }
-    }
-    __syncthreads();
-    uint32_t v[3], total[3];
+    if (!one_chunk) {
+      for (int q = 0; q < quads(1024 * nj); ++q) {
+        uint32_t s4[4];
+        words(j0 / 4 + q, s4);
 #pragma unroll
-    for (int f = 0; f < 3; ++f) v[f] = tid < entries ? lists.c[f][tid] : 0;
+        for (int e = 0; e < 4; ++e) {
+          const int j = 4 * q + e;
+          if (j >= nj) continue;
+          uint64_t stay, dem;
+          classify(1024 * (j0 + j) + tid, s4[e], stay, dem);
+          if (lane == 0) { sel.stay[16 * j + w] = stay; sel.dem[16 * j + w] = dem; }
+        }
+      }
+      __syncthreads();
+    }
+    uint32_t v[3] = {0, 0, 0}, total[3];
+    if (tid < entries) {                                    // thread = 64 rows
+      const ListFlags f = list_flags(sel.stay[tid], sel.dem[tid], 1024 * j0 + 64 * tid, cO, n, cOn, cQn);
+      v[0] = (uint32_t)__popcll(f.hole) | ((uint32_t)__popcll(f.mov) << 16);
+      v[1] = (uint32_t)__popcll(f.dem) | ((uint32_t)__popcll(f.fr) << 16);
+      v[2] = (uint32_t)__popcll(f.qm);
+    }
     block_excl_scan<3>(v, scan_sm, total);
-    if (tid < entries) { lists.c[0][tid] = v[0]; lists.c[1][tid] = v[1]; lists.c[2][tid] = v[2]; }
+    if (tid < entries) { sel.off[0][tid] = v[0]; sel.off[1][tid] = v[1]; sel.off[2][tid] = v[2]; }
     __syncthreads();
-    for (int j = 0; j < nj; ++j) {
-      const int i = 1024 * (j0 + j) + tid;
-      const Flags f = flags(i);
-      const uint32_t hm = lists.c[0][16 * j + w], df = lists.c[1][16 * j + w], qm = lists.c[2][16 * j + w];
-      const int ph = place(__ballot(f.hole), lane), pm = place(__ballot(f.mov), lane), pd = place(__ballot(f.dem), lane);
-      const int pf = place(__ballot(f.fr), lane), pq = place(__ballot(f.qm), lane);
-      if (f.hole) ohole[base_hole + (int)(hm & 0xFFFF) + ph] = i;
-      if (f.mov) omov[base_mov + (int)(hm >> 16) + pm] = i;
-      if (f.dem) dem_[base_dem + (int)(df & 0xFFFF) + pd] = i;
-      if (f.fr) qfree[base_free + (int)(df >> 16) + pf] = i - cO;
-      if (f.qm) qmov[base_qmov + (int)qm + pq] = i - cO;
+    // wave: its share of the entries, a lane each, of which most have nothing to list in the long run
+    const int mine = 16 * lane + w;
+    uint64_t m_stay = 0, m_dem = 0;
+    bool some = false;
+    if (mine < entries) {
+      m_stay = sel.stay[mine]; m_dem = sel.dem[mine];
+      const ListFlags f = list_flags(m_stay, m_dem, 1024 * j0 + 64 * mine, cO, n, cOn, cQn);
+      some = (f.hole | f.mov | f.dem | f.fr | f.qm) != 0;
+    }
+    for (unsigned long long todo = __ballot(some); todo; todo &= todo - 1) {
+      const int l = __ffsll(todo) - 1, e = 16 * l + w, row0 = 1024 * j0 + 64 * e, i = row0 + lane;
+      auto of = [&](uint64_t m) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)m, l) | ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(m >> 32), l) << 32);
+      };
+      const ListFlags f = list_flags(of(m_stay), of(m_dem), row0, cO, n, cOn, cQn);
+      const uint32_t hm = sel.off[0][e], df = sel.off[1][e], qm = sel.off[2][e];
+      auto has = [&](uint64_t m) { return ((m >> lane) & 1) != 0; };
+      if (has(f.hole)) ohole[base_hole + (int)(hm & 0xFFFF) + place(f.hole, lane)] = i;
+      if (has(f.mov)) omov[base_mov + (int)(hm >> 16) + place(f.mov, lane)] = i;
+      if (has(f.dem)) dem_[base_dem + (int)(df & 0xFFFF) + place(f.dem, lane)] = i;
+      if (has(f.fr)) qfree[base_free + (int)(df >> 16) + place(f.fr, lane)] = i - cO;
+      if (has(f.qm)) qmov[base_qmov + (int)qm + place(f.qm, lane)] = i - cO;
     }
     base_hole += (int)(total[0] & 0xFFFF); base_mov += (int)(total[0] >> 16);
     base_dem += (int)(total[1] & 0xFFFF); base_free += (int)(total[1] >> 16);
     base_qmov += (int)total[2];
-    if (j0 + kRounds < rounds) __syncthreads();            // the next chunk's counts go into the same table
+    if (j0 + kRounds < rounds) __syncthreads();            // the next chunk's flags go into the same table
   }
   // slots behind the Q pool's old end
   for (int i = tid; i < cQn - cQ; i += 1024) qfree[base_free + i] = cQ + i;
@@ -666,23 +792,32 @@ __global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) 
 // prompt commit: scores of the prompt's positions, the two thresholds, and the survivors' way into the empty pools
 // ------------------------------------------------------------------------------------------
 struct BudgetArgs { int n_o[64], nb[64]; };       // per sequence
+// Scratch of a commit: scores [units][pitch] (rows of a whole number of 16-byte vectors), each 64 positions' range of them
+// [units][commit_ranges], and what k_commit_select says of the blocks of 1024 positions.
+struct CommitScratch { uint32_t* scores; int pitch; uint2* ranges; int4* blocks; };
+__host__ __device__ constexpr int commit_ranges(int T) { return (T + 63) / 64; }
+__host__ __device__ constexpr int commit_blocks(int T) { return (T + 1023) / 1024; }
 
-// Scores of the prompt's positions, over the whole chip (two IEEE divisions per position: in the one workgroup that
-// selects they took longer than the selection), and the layer's budgets (a launch of their own took 5 us).
-__global__ __launch_bounds__(256) void k_commit_keys(Pools P, CommitLaunch L, uint64_t* keys, int hkv, BudgetArgs budgets) {
+// Scores of the prompt's positions (kNoScore: window, and what fills the pitch), over the whole chip (two IEEE divisions per
+// position: in the one workgroup that selects they took longer than the selection), each 64 positions' range of scores, and
+// the layer's budgets (a launch of their own took 5 us).
+__global__ __launch_bounds__(256) void k_commit_keys(Pools P, CommitLaunch L, CommitScratch C, int hkv, BudgetArgs budgets) {
   const int lu = blockIdx.y;
   if (hkv > 0 && blockIdx.x == 0 && threadIdx.x == 0) {
     P.n_o[L.unit_begin + lu] = budgets.n_o[lu / hkv];
     P.nb[L.unit_begin + lu] = budgets.nb[lu / hkv];
   }
   const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= L.T) return;
-  uint64_t key = 0;
+  uint32_t sb = kNoScore;
   if (j < L.T - L.window) {
     const float2 a = L.pre[(size_t)lu * L.T + j];
-    key = make_key(hh_score(a.x, a.y, P.G * L.window, L.gamma), j);
+    sb = (uint32_t)(make_key(hh_score(a.x, a.y, P.G * L.window, L.gamma), j) >> 32);
   }
-  keys[(size_t)lu * L.T + j] = key;
+  if (j < C.pitch) C.scores[(size_t)lu * C.pitch + j] = sb;
+  ScoreRange r;
+  r.add(sb);
+  r.wave();
+  if ((threadIdx.x & 63) == 63 && j - 63 < C.pitch) C.ranges[(size_t)lu * commit_ranges(L.T) + j / 64] = make_uint2(r.lo, r.hi);
 }
 
 // Parts into which a block with that many survivors is cut.
@@ -690,58 +825,70 @@ __device__ __forceinline__ uint32_t commit_parts(uint32_t survivors, int share_r
   return (survivors + (uint32_t)share_rows - 1) / (uint32_t)share_rows;
 }
 
-// One workgroup per unit: 36 us for 32 units x 32768 positions, where a select per rank and a pass that wrote the lists of
-// survivors took 39 + 19 us.  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
+// One workgroup per unit (15 us inside the kernel for 32 units x 32768 positions; 31 us with digits of the plain score, one
+// score per LDS read and 64-bit keys in memory; whole commits of 32 x 32768 88 -> 75 us, 8 x 131072 159 -> 96 us, 8 x 1000 20.2
+// -> 19.6 us).  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
 // last one the totals) the rows in front of it that become Original and Quantized and the parts in front of it into which
 // k_commit_scatter cuts blocks: as many as hold share_rows survivors each, wherever in the prompt the survivors sit.
 template <bool IN_LDS>
-__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, const uint64_t* keys_all, int4* blocks_all,
-                                                         int share_rows) {
-  extern __shared__ uint32_t row_word[];     // IN_LDS: the positions' scores
-  __shared__ SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
-  __shared__ uint32_t cnt[kRounds][16];      // per (round, wave): Original | Quantized << 16
-  const int lu = blockIdx.x, gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int T = L.T, rounds = (T + 1023) / 1024;
+__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, CommitScratch C, int share_rows) {
+  extern __shared__ __align__(16) uint32_t row_word[];     // IN_LDS: the positions' scores
+  __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
+  __shared__ uint32_t cnt[kRounds / 4][16];  // per (round of 4096 positions, wave): Original | Quantized << 16
+  const int lu = blockIdx.x, gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int T = L.T, rounds = commit_blocks(T), nq = quads(T);
   const int n_cand = T - L.window;           // positions behind them are the window
-  const uint64_t* keys = keys_all + (size_t)lu * T;
-  if constexpr (IN_LDS) {
-    constexpr int BATCH = 8;                 // positions requested together; a thread only reads what it stores here
-    for (int i0 = tid; i0 < n_cand; i0 += 1024 * BATCH) {
-      uint32_t v[BATCH];
-#pragma unroll
-      for (int b = 0; b < BATCH; ++b) v[b] = (uint32_t)(keys[min(i0 + 1024 * b, T - 1)] >> 32);
-#pragma unroll
-      for (int b = 0; b < BATCH; ++b)
-        if (i0 + 1024 * b < n_cand) row_word[i0 + 1024 * b] = v[b];
-    }
+  const uint32_t* scores = C.scores + (size_t)lu * C.pitch;
+  auto fetch = [&](int q) -> u32x4t {
+    const int i = kQuad * q + 4 * tid;
+    const u32x4t none = {kNoScore, kNoScore, kNoScore, kNoScore};
+    return i < C.pitch ? *reinterpret_cast<const u32x4t*>(scores + i) : none;
+  };
+  ScoreRange range;
+  for (int i = tid; i < commit_ranges(T); i += 1024) {
+    const uint2 r = C.ranges[(size_t)lu * commit_ranges(T) + i];
+    range.lo = min(range.lo, r.x);
+    range.hi = max(range.hi, r.y);
   }
+  if constexpr (IN_LDS) {
+    u32x4t v[kLdsRows / kQuad];              // (all requested together; a thread only reads what it stores here)
+#pragma unroll
+    for (int q = 0; q < kLdsRows / kQuad; ++q)
+      if (q < nq) v[q] = fetch(q);
+#pragma unroll
+    for (int q = 0; q < kLdsRows / kQuad; ++q)
+      if (q < nq) *reinterpret_cast<u32x4t*>(row_word + kQuad * q + 4 * tid) = v[q];
+  }
+  auto load = [&](int q, uint32_t (&s)[4]) {
+    u32x4t v;
+    if constexpr (IN_LDS) v = *reinterpret_cast<const u32x4t*>(row_word + kQuad * q + 4 * tid);
+    else v = fetch(q);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = v[e];
+  };
   auto score_of = [&](int i) -> uint32_t {
     if constexpr (IN_LDS) return row_word[i];
-    else return (uint32_t)(keys[i] >> 32);
-  };
-  auto each = [&](int j0, int j1, auto&& f) {
-    for (int j = j0; j < j1; ++j) {
-      const int i = 1024 * j + tid;
-      f(i < n_cand ? score_of(i) : kNoScore, i);
-    }
+    else return scores[i];
   };
   auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
-  select_two(rounds, each, key_of, P.n_o[gu], P.nb[gu], sel);
+  select_two(nq, load, score_of, key_of, range, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
-  int4* blocks = blocks_all + (size_t)lu * (rounds + 1);
+  int4* blocks = C.blocks + (size_t)lu * (rounds + 1);
   int bo = 0, bq = 0, bp = 0;
   for (int j0 = 0; j0 < rounds; j0 += kRounds) {
     const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds;
-    for (int j = 0; j < nj; ++j) {
-      const int i = 1024 * (j0 + j) + tid;
-      bool o = i >= n_cand && i < T, q = false;
-      if (i < n_cand) {
-        const uint64_t k = key_of(i);
-        o = k >= thr_o;
-        q = !o && k >= thr_b;
+    for (int q = 0; q < quads(1024 * nj); ++q) {
+      uint32_t s[4], no = 0, nb = 0;         // a wave's positions of the round are a quarter of a block
+      load(j0 / 4 + q, s);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = 1024 * j0 + kQuad * q + 4 * tid + e;
+        const uint64_t k = ((uint64_t)s[e] << 32) | (0xFFFFFFFFu - (uint32_t)i);
+        no += (uint32_t)__popcll(__ballot(i < n_cand ? k >= thr_o : i < T));
+        nb += (uint32_t)__popcll(__ballot(i < n_cand ? k >= thr_b : i < T));     // (n_o <= b)
       }
-      const uint32_t c = (uint32_t)__popcll(__ballot(o)) | ((uint32_t)__popcll(__ballot(q)) << 16);
-      if (lane == 0) cnt[j][w] = c;
+      if (lane == 0) cnt[q][w] = no | ((nb - no) << 16);
     }
     __syncthreads();
     // lane j of wave 0: round j (kRounds <= 64)
@@ -749,7 +896,7 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
       uint32_t o = 0, q = 0;
       if (lane < nj)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) { o += cnt[lane][i] & 0xFFFFu; q += cnt[lane][i] >> 16; }
+        for (int i = 0; i < 4; ++i) { const uint32_t c = cnt[lane / 4][4 * (lane % 4) + i]; o += c & 0xFFFFu; q += c >> 16; }
       const uint32_t p = commit_parts(o + q, share_rows);
       const uint32_t io = wave_prefix_sum(o), iq = wave_prefix_sum(q), ip = wave_prefix_sum(p);
       if (lane < nj) blocks[j0 + lane] = make_int4(bo + (int)(io - o), bq + (int)(iq - q), bp + (int)(ip - p), 0);
@@ -793,8 +940,7 @@ __global__ __launch_bounds__(256) void k_commit_copy(Pools P, CommitLaunch L) {
 // does not, hence the parts: with one workgroup per block a whole commit of 16 units x 2200 positions (1100 kept, all packed)
 // takes 62 us instead of 26, and one of 32 x 32768 whose survivors sit in few blocks (equal scores) 335 instead of 132.
 template <int D, int BITS>
-__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, const uint64_t* keys_all, const int4* blocks_all,
-                                                        int share_rows) {
+__global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, CommitScratch C, int share_rows) {
   constexpr int LPR = D / 8, LPT = 2 * LPR;         // lanes per K (V) row, per token
   constexpr int TPW = 64 / LPT;                     // tokens per wave and round
   __shared__ uint16_t so[1024], sq[1024];
@@ -804,8 +950,8 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
   const int lu = (int)(blockIdx.x % (unsigned)L.n_units), slot = (int)(blockIdx.x / (unsigned)L.n_units);
   const int gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, T = L.T;
   // the block whose parts this workgroup falls among: the last one with no more parts in front of it (lane = block)
-  const int n_blocks = (T + 1023) / 1024;
-  const int4* blocks = blocks_all + (size_t)lu * (n_blocks + 1);
+  const int n_blocks = commit_blocks(T);
+  const int4* blocks = C.blocks + (size_t)lu * (n_blocks + 1);
   int block = 0, part = 0;
   int2 base = make_int2(0, 0);
   for (int b0 = 0; b0 <= n_blocks; b0 += 64) {
@@ -826,16 +972,17 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
   int no, nq, parts;
   {
     const uint64_t thr_o = P.thr[(size_t)gu * 2], thr_b = P.thr[(size_t)gu * 2 + 1];
-    uint64_t key[4];
+    uint32_t sb[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) key[r] = keys_all[(size_t)lu * T + min(j0 + 256 * r + tid, T - 1)];
+    for (int r = 0; r < 4; ++r) sb[r] = C.scores[(size_t)lu * C.pitch + min(j0 + 256 * r + tid, T - 1)];
     bool o[4], q[4];
     int po[4], pq[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool in = j0 + 256 * r + tid < T;
-      o[r] = in && (key[r] == 0 || key[r] >= thr_o);                 // key 0 = window position
-      q[r] = in && !o[r] && key[r] >= thr_b;
+      const int i = j0 + 256 * r + tid;
+      const uint64_t key = ((uint64_t)sb[r] << 32) | (0xFFFFFFFFu - (uint32_t)i);
+      o[r] = i < T && (sb[r] == kNoScore || key >= thr_o);           // kNoScore: window position
+      q[r] = i < T && !o[r] && key >= thr_b;
       const unsigned long long bo = __ballot(o[r]), bq = __ballot(q[r]);
       po[r] = place(bo, lane); pq[r] = place(bq, lane);
       if (lane == 0) cnt[4 * r + w] = (uint32_t)__popcll(bo) | ((uint32_t)__popcll(bq) << 16);
@@ -885,10 +1032,10 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
-// One workgroup of 1024 threads per unit with a 32-bit word of LDS per row.
+// One workgroup of 1024 threads per unit with a 32-bit word of LDS per row (whole rounds of the selection).
 template <typename... Params, typename... Args>
 static hipError_t launch_rows(void (*kernel)(Params...), int n_units, int lds_rows, hipStream_t s, Args... args) {
-  const size_t shm = (size_t)lds_rows * sizeof(uint32_t);
+  const size_t shm = (size_t)quads(lds_rows) * kQuad * sizeof(uint32_t);
   if (shm > 32 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
@@ -960,11 +1107,27 @@ static void launch_set_budgets(const Pools& P, int unit_begin, int hkv, int batc
   }
 }
 
-static int commit_blocks(int T) { return (T + 1023) / 1024; }
-size_t commit_scratch_words(int n_units, int T) { return (size_t)n_units * ((size_t)T + 2 * ((size_t)commit_blocks(T) + 1)) + 1; }
+static int commit_pitch(int T) { return (T + 3) / 4 * 4; }
+size_t commit_scratch_words(int n_units, int T) {       // 8-byte words; the blocks' entries are 16-byte aligned
+  return (size_t)n_units * ((size_t)commit_pitch(T) / 2 + (size_t)commit_ranges(T) + 2 * ((size_t)commit_blocks(T) + 1)) + 1;
+}
+static CommitScratch commit_scratch(uint64_t* p, int n_units, int T) {
+  CommitScratch c;
+  c.pitch = commit_pitch(T);
+  c.scores = reinterpret_cast<uint32_t*>(p);
+  uint64_t* ranges = p + (size_t)n_units * c.pitch / 2;
+  c.ranges = reinterpret_cast<uint2*>(ranges);
+  c.blocks = reinterpret_cast<int4*>(p + (((size_t)(ranges - p) + (size_t)n_units * commit_ranges(T) + 1) / 2 * 2));
+  return c;
+}
+// the key of the unit's i-th position in a commit's scratch (0: not ranked)
+uint64_t commit_key(const uint32_t* scores, int i) {
+  return scores[i] == kNoScore ? 0 : ((uint64_t)scores[i] << 32) | (0xFFFFFFFFu - (uint32_t)i);
+}
+int commit_score_pitch(int T) { return commit_pitch(T); }
 
 hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const int32_t* n_o_seq, const int32_t* nb_seq,
-                         uint64_t* keys, hipStream_t s) {
+                         uint64_t* scratch, hipStream_t s) {
   const int batch = a.n_units / hkv;
   const bool with_keys = a.select && batch <= 64;           // the budgets ride with the keys' launch
   if (!with_keys) launch_set_budgets(P, a.unit_begin, hkv, batch, n_o_seq, nb_seq, s);
@@ -977,9 +1140,8 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
     else hipLaunchKernelGGL(k_commit_copy<64>, grid, dim3(256), 0, s, P, a);
     return hipGetLastError();
   }
-  // (16-byte entries behind the keys)
-  int4* blocks = reinterpret_cast<int4*>(keys + ((size_t)a.n_units * a.T + 1) / 2 * 2);
-  hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, keys, with_keys ? hkv : 0,
+  const CommitScratch c = commit_scratch(scratch, a.n_units, a.T);
+  hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, c, with_keys ? hkv : 0,
                      budget_args(n_o_seq, nb_seq, with_keys ? batch : 0));
   int kept = 0;                                             // the most rows that a unit keeps
   for (int i = 0; i < batch; ++i) kept = std::max(kept, std::min(nb_seq[i], a.T - a.window) + a.window);
@@ -987,15 +1149,13 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
   // kept: 21 us for the whole commit, 52 in one part per block), above 96 nothing is gained (32 units x 32768 positions,
   // 6152 kept: 89 to 95 us at 64 to 1024 rows)
   const int share_rows = clampi((int)((long long)a.n_units * kept / 1024 + 7) / 8 * 8, 8, 96);
-  const uint64_t* ckeys = keys;
-  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, ckeys, blocks, share_rows)
-                                       : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, ckeys, blocks, share_rows);
+  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, c, share_rows)
+                                       : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, c, share_rows);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)a.n_units * (unsigned)(kept / share_rows + commit_blocks(a.T)));   // (a block's last part may be short)
-  const int4* cblocks = blocks;
 #define ARKV_SC(D_, B_)                                                                                                      \
   if (P.D == D_ && P.bits == B_) {                                                                                           \
-    hipLaunchKernelGGL((k_commit_scatter<D_, B_>), grid, dim3(256), 0, s, P, a, ckeys, cblocks, share_rows);                 \
+    hipLaunchKernelGGL((k_commit_scatter<D_, B_>), grid, dim3(256), 0, s, P, a, c, share_rows);                              \
     return hipGetLastError();                                                                                                \
   }
   ARKV_SC(128, 4) ARKV_SC(128, 2) ARKV_SC(128, 8) ARKV_SC(64, 4) ARKV_SC(64, 2) ARKV_SC(64, 8)

@@ -419,3 +419,33 @@ def test_single_split(g, d, T, budget, rho, bits):
     wl = synth.C1.scaled(name="single", batch=2, n_q_heads=2 * g, n_kv_heads=2, head_dim=d, prefill=T, budget_frac=budget,
                          bits=bits, window=16, decode_steps=18)
     _run(wl, rho=rho, check_every=6)
+
+
+@pytest.mark.parametrize("T,N,gain,steps", [
+    (3100, 1300, 2.0 ** -17, 4),       # scores a few units in the last place apart: most tie, the range takes few bits
+    (3100, 1300, 2.0 ** -10, 4),       # one digit and a little more
+    (4097, 1025, 2.0 ** -5, 0),        # a position behind a whole round of the selection
+    (33000, 900, 2.0 ** -12, 0),       # scores read back from memory
+])
+def test_selection_in_a_narrow_range_of_scores(T, N, gain, steps):
+    """Nearly uniform attention: all scores of a unit lie within few representable values, so the selection starts with
+    short digits and reaches the positions early.  States are compared exactly, of the commit and of a tailor per step.  (No
+    steps over long caches: there the mean of many values nearly cancels, and the 2e-3 of its maximum is less than the fp16
+    weights of packed rows give, with any selection.)"""
+    def flat(layer, k, v, qw):
+        qw *= gain
+
+    def flat_steps(layer, q, kn, vn):
+        q *= gain
+
+    wl = synth.C1.scaled(name="narrow", n_q_heads=4, n_kv_heads=2, head_dim=64, prefill=T, budget_frac=(N + 0.5) / T, window=16,
+                         decode_steps=steps)
+    sb = SideBySide(wl, rho_override=0.3, every_step=steps > 0, mutate_prefill=flat, mutate_decode=flat_steps)
+    try:
+        sb.prefill()
+        sb.commit()
+        if steps:
+            sb.decode(check_every=4)
+        sb.assert_within_tol(stats=False)
+    finally:
+        sb.close()
