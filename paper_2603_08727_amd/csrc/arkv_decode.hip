@@ -756,7 +756,10 @@ struct DecodeHot {
   unsigned inv_s, inv_wq;
 };
 
-template <int D, int G, int BITS, bool FOLD>
+// KEEP launches (a tailor follows at once, which ranks on scores that include this step) store the rows' logits for it: 4 G
+// bytes per row, where a pass of its own over the keys (k_flush_scores) read 2 D (32 units x 8192 rows, G = 4: that launch's
+// 12.4 us against 0.7 here and 1 in k_tailor_choose).
+template <int D, int G, int BITS, bool FOLD, bool KEEP>
 __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, DecodeLaunch L) {
   constexpr int KK = D / 32;           // MFMA k-steps = quantisation groups per row
   constexpr int LPR = D / 8;           // lanes per value row
@@ -865,6 +868,15 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   float* const part_ = P.part + (size_t)(gu - L.part_unit0) * P.max_splits * (G * (D + 2));   // the unit's partials
   int* const ticket_ = P.ticket + (size_t)(gu - L.part_unit0) * (kTicketWaves * kTicketPitch);
   asm volatile("" ::"s"(part_), "s"(ticket_));
+  float* const logit_ = KEEP ? P.logit + (size_t)gu * ((size_t)P.capO + P.capQ) * G : nullptr;
+  auto keep_logits = [&](bool own, int row, const float (&x)[HPL]) {
+    if (!own) return;
+    float* dst = logit_ + (size_t)row * G + 4 * blk;
+    if constexpr (HPL == 4) *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+    else
+#pragma unroll
+      for (int i = 0; i < HPL; ++i) dst[i] = x[i];
+  };
 
   // this step's query; on a launch that also updates the scores, the waiting steps' state goes to LDS
   uint4 qa[KK];
@@ -944,6 +956,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
     float x[HPL];
 #pragma unroll
     for (int i = 0; i < HPL; ++i) x[i] = own ? C[i] * scale2 : kNegBig;
+    if constexpr (KEEP) keep_logits(own, row0 + tok, x);
     if constexpr (FOLD) {
       // the token appended by waiting step j sits at row cO - npend + j: older steps did not see it
       const int row = min(row0 + tok, bo - 1);
@@ -991,6 +1004,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
     float x[HPL];
 #pragma unroll
     for (int i = 0; i < HPL; ++i) x[i] = own ? C[i] * scale2 : kNegBig;
+    if constexpr (KEEP) keep_logits(own, cO, x);
     softmax_pv(own, x, [&](int, float (&f)[8]) { unpack_bf16x8(vr, f); });
     uint16_t* dk = P.ok + ((size_t)gu * P.capO + cO) * D;
     uint16_t* dv = P.ov + ((size_t)gu * P.capO + cO) * D;
@@ -1105,6 +1119,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
           Fmt::dots(pqa, t.k[tl], x[tl]);
 #pragma unroll
         for (int i = 0; i < HPL; ++i) x[tl][i] = own[tl] ? x[tl][i] * scale2 : kNegBig;
+        if constexpr (KEEP) keep_logits(own[tl], capO + row, x[tl]);
         if constexpr (FOLD) {
           const float2 ac = fold_pending<D, G>(sm_pend, npend, 0, t.ac[tl], lane, [&](int r, const uint4 (&qop)[KK], float (&xp)[HPL]) {
             if constexpr (BITS == 8) {
@@ -1373,8 +1388,9 @@ static hipError_t launch_decode_t(const Pools& P, const DecodeLaunch& a, hipStre
   h.fin_stride = P.fin_stride;
   h.capO = P.capO; h.capQ = P.capQ; h.splits = a.splits; h.wq = a.wq; h.known = a.cnt_known; h.npend = a.n_pending;
   h.upl = a.units_per_layer; h.ubeg = a.unit_begin; h.inv_s = a.inv_splits; h.inv_wq = a.inv_wq;
-  if (a.fold) hipLaunchKernelGGL((k_decode_attend<D, G, BITS, true>), grid, dim3(256), 0, s, h, P, a);
-  else hipLaunchKernelGGL((k_decode_attend<D, G, BITS, false>), grid, dim3(256), 0, s, h, P, a);
+  if (a.fold) hipLaunchKernelGGL((k_decode_attend<D, G, BITS, true, false>), grid, dim3(256), 0, s, h, P, a);
+  else if (a.keep) hipLaunchKernelGGL((k_decode_attend<D, G, BITS, false, true>), grid, dim3(256), 0, s, h, P, a);
+  else hipLaunchKernelGGL((k_decode_attend<D, G, BITS, false, false>), grid, dim3(256), 0, s, h, P, a);
 #ifdef ARKV_PHASE_TRACE
   hipLaunchKernelGGL(k_trace_mark, dim3(1), dim3(64), 0, s, 1);
 #endif

@@ -80,6 +80,8 @@ struct Pools {
   int*      ticket;     // [LU][kTicketWaves][kTicketPitch] splits of the unit whose wave w is done in the current launch
                         // (0 between launches), one per cache line
   float*    outf;       // [LU][G][D] fp32 output of the latest step (parity hook)
+  float*    logit;      // [LU][capO+capQ][G] a step's logits (base-2 units) per row, O pool slots first, where a tailor follows it
+                        // at once (tailor_policy 1); null with the other policy
   int32_t*  n_o;        // [LU] Original target of the unit's layer/sequence
   int32_t*  nb;         // [LU] survivors outside the window (n_o + n_q) of the unit's layer/sequence
   // tailor scratch
@@ -117,6 +119,7 @@ struct DecodeLaunch {
                           // of them used ring slot (slot - n_pending + j) mod kRing
   int slot;               // ring slot of fin/qprev/qscale this step writes
   int fold;               // 1: this launch adds the pending steps to (s1,s2)
+  int keep;               // 1: the rows' logits go to Pools::logit (no steps pending, a tailor follows; never with fold)
   int wq;                 // cost of a packed row in sixteenths of a bf16 row (split balancing)
   unsigned inv_splits, inv_wq;   // ceil(2^32 / splits), ceil(2^32 / wq): the split cut points without divisions
   int part_unit0;         // global unit whose partials and ticket come first in Pools::part / ticket (0: arrays of the
@@ -134,7 +137,8 @@ struct TailorLaunch {
   float gamma;
   int n_pending, slot;  // pending steps to add to (s1,s2) before ranking; slot the NEXT step would write
   int max_rows;         // no unit holds more rows than this
-  int few_moves;        // 1: each unit moves a few rows, one workgroup per unit does it
+  int kept;             // 1: the one pending step's logits are in Pools::logit
+  int few_moves;        // 1: each unit moves a few rows, its choosing workgroup does it (with kept)
 };
 
 struct CommitLaunch {

@@ -257,6 +257,7 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   A(qkm, LU * P.capQ * NG) A(qvm, LU * P.capQv * MH)
   A(qpos, LU * P.capQ) A(qacc, LU * P.capQ)
   A(cnt, LU) A(fin, kRing * LU * G) A(qprev, kRing * LU * G * D) A(qscale, kRing * LU) A(part, LU * (size_t)P.max_splits * G * (D + 2)) A(outf, LU * G * D) A(n_o, LU) A(nb, LU) A(ticket, LU * kTicketWaves * kTicketPitch)
+  if (cfg->tailor_policy == 1) A(logit, LU * (size_t)(P.capO + P.capQ) * G)
   A(keys, LU * (size_t)(P.capO + P.capQ)) A(thr, LU * 2) A(plan, LU * (size_t)P.plan_stride)
 #undef A
   hipError_t e = hipSuccess;
@@ -606,6 +607,9 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   a.n_pending = l0.n_pending;
   a.slot = l0.slot;
   a.fold = l0.n_pending == kRing - 1 ? 1 : 0;   // the ring is full: add the waiting steps now
+  const bool tailor = l0.live + 1 >= N;
+  // a tailor that ranks on this step alone takes its logits from this launch
+  a.keep = tailor && l0.n_pending == 0 && pools.logit ? 1 : 0;
   for (int i = 0; i < n; ++i) a.scale2[i] = softmax_scale[i] * 1.4426950408889634f;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->timing && !static_scratch) {        // the event pool grows by allocation
@@ -622,7 +626,6 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   HIP_TRY(launch_decode(pools, a, st, e0, e1));
   const int P = l0.P + 1, live = l0.live + 1;
   const int n_pending = (a.fold ? 0 : l0.n_pending) + 1, slot = (l0.slot + 1) % kRing;
-  bool tailor = live >= N;
   int live_after = live;
   if (tailor) {
     TailorLaunch t;
@@ -630,10 +633,11 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     t.position = P; t.t_prefill = l0.T; t.window = W; t.gamma = cfg.gamma;
     t.n_pending = n_pending; t.slot = slot;
     t.max_rows = cfg.budget_mode == 1 ? c->P.capO + c->P.capQ : N;      // live <= N in token mode
-    // A tailor at every step settles to a few moved rows per unit: one launch, a workgroup per unit.  The first ones
-    // after a commit move many (32 units x 8192 rows: 41 us in that one workgroup at the first, 17 at the twelfth, 8 in
-    // the long run, against 12 us for the two launches over the whole chip).
+    // A tailor at every step settles to a few moved rows per unit: the choosing workgroup moves them (3 us instead of a
+    // launch's 7.6).  The first ones after a commit move many (32 units x 8192 rows, one workgroup per unit: 41 us at the
+    // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
     t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
+    t.kept = a.keep;
     const hipError_t te = launch_tailor(c->P, t, st);
     if (te != hipSuccess) {
       // the attention of this step is on the stream, the tailor is not (or only partly): the device-side state of

@@ -336,6 +336,212 @@ __device__ __forceinline__ int place(unsigned long long flags, int lane) {
 }
 
 // ------------------------------------------------------------------------------------------
+// quantiser: one K or V row held by LPR lanes, 8 channels each (fp32 from bf16)
+// ------------------------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ float dppf(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                               0xf, 0xf, true));
+}
+
+__device__ __forceinline__ uint16_t f2h(float x) { return __half_as_ushort(__float2half_rn(x)); }
+__device__ __forceinline__ float h2f(uint16_t h) { return __half2float(__ushort_as_half(h)); }
+__device__ __forceinline__ uint16_t h_next_down(uint16_t h) {
+  if ((h & 0x7fffu) == 0) return 0x8001u;
+  return (h & 0x8000u) ? (uint16_t)(h + 1) : (uint16_t)(h - 1);
+}
+__device__ __forceinline__ uint16_t h_next_up(uint16_t h) {
+  if ((h & 0x7fffu) == 0) return 0x0001u;
+  return (h & 0x8000u) ? (uint16_t)(h - 1) : (uint16_t)(h + 1);
+}
+
+// x: the 8 channels of this lane; the 4 lanes of an aligned quad form one group of 32 channels.
+// Returns the lane's packed codes (8*BITS bits) and the group's meta word (scale | zero << 16).
+template <int BITS>
+__device__ __forceinline__ void quantize8(const float (&x)[8], uint32_t& codes, uint32_t& meta) {
+  const float qmax = (float)((1 << BITS) - 1);
+  float mn = x[0], mx = x[0];
+#pragma unroll
+  for (int c = 1; c < 8; ++c) { mn = fminf(mn, x[c]); mx = fmaxf(mx, x[c]); }
+  mn = fminf(mn, dppf<0xB1>(mn)); mx = fmaxf(mx, dppf<0xB1>(mx));
+  mn = fminf(mn, dppf<0x4E>(mn)); mx = fmaxf(mx, dppf<0x4E>(mx));
+  uint16_t zh = f2h(mn);
+  float z = h2f(zh);
+  if (z > mn) { zh = h_next_down(zh); z = h2f(zh); }
+  const float r = mx - z;
+  uint16_t sh = 0;
+  codes = 0;
+  if (r != 0.0f) {
+    const float s = r / qmax;
+    sh = f2h(s);
+    float sc = h2f(sh);
+    if (sc * qmax < r) { sh = h_next_up(sh); sc = h2f(sh); }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      float t = rintf((x[c] - z) / sc);
+      t = fminf(fmaxf(t, 0.0f), qmax);
+      codes |= (uint32_t)t << (BITS * c);
+    }
+  }
+  meta = (uint32_t)sh | ((uint32_t)zh << 16);
+}
+
+__device__ __forceinline__ void unpack8(const uint4& r, float (&f)[8]) {
+  f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
+  f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
+  f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xffff0000u);
+  f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xffff0000u);
+}
+
+// fp8 rows with one scale per token (Alg. 1 "Reconstruction Before Attention": x~ = q^ * s).
+// |t| <= 448 -> nearest E4M3 code (sign, 4 exponent bits with bias 7, 3 mantissa bits, subnormals below
+// 2^-6, no infinities), ties to the even code, in integer arithmetic on the fp32 bits.
+__device__ __forceinline__ uint32_t e4m3_code(float t) {
+  const float a = fminf(fabsf(t), 448.0f);
+  uint32_t code;
+  if (a < 0.015625f) {
+    code = (uint32_t)rintf(a * 512.0f);             // subnormals are multiples of 2^-9; 8 = the smallest normal
+  } else {
+    uint32_t b = __float_as_uint(a);
+    b += 0x7FFFFu + ((b >> 20) & 1u);               // round to 3 mantissa bits, ties to even
+    code = (((b >> 23) - 120u) << 3) | ((b >> 20) & 7u);
+  }
+  return code;
+}
+
+// x: the 8 channels of this lane; the LPR lanes of a row share one scale.
+// Returns the lane's 8 codes (byte c = channel c) and the row's scale (fp16 bits).
+template <int LPR>
+__device__ __forceinline__ void quantize8_fp8(const float (&x)[8], uint2& codes, uint32_t& meta) {
+  float amax = fabsf(x[0]);
+#pragma unroll
+  for (int c = 1; c < 8; ++c) amax = fmaxf(amax, fabsf(x[c]));
+  amax = fmaxf(amax, dppf<0xB1>(amax));
+  amax = fmaxf(amax, dppf<0x4E>(amax));
+  amax = fmaxf(amax, dppf<0x141>(amax));             // 8 lanes
+  if (LPR == 16) amax = fmaxf(amax, dppf<0x140>(amax));
+  uint16_t sh = 0;
+  codes = make_uint2(0, 0);
+  if (amax != 0.0f) {
+    const float s = amax / 448.0f;
+    sh = f2h(s);
+    float sc = h2f(sh);
+    if (sc * 448.0f < amax) { sh = h_next_up(sh); sc = h2f(sh); }
+    uint32_t w[2] = {0, 0};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const uint32_t code = e4m3_code(x[c] / sc) | (x[c] < 0.0f ? 0x80u : 0u);
+      w[c >> 2] |= code << (8 * (c & 3));
+    }
+    codes = make_uint2(w[0], w[1]);
+  }
+  meta = sh;
+}
+
+// 2 LPR adjacent lanes (lane = 0 .. 2 LPR - 1 among them) quantise a token into Q slot dst of unit gu: lanes [0, LPR) the
+// K row, the others the V row.  A wave takes 64 / (2 LPR) tokens at once; every lane runs the arithmetic (the lane
+// exchanges need them active), lanes without store write nothing.
+template <int D, int BITS>
+__device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, const uint16_t* krow,
+                                              const uint16_t* vrow, int lane, bool store) {
+  constexpr int LPR = D / 8, CB = D * BITS / 8, NG = metas_per_row(D, BITS);
+  const bool isv = lane >= LPR;
+  const int sub = lane % LPR;
+  const uint16_t* src = (isv ? vrow : krow) + sub * 8;
+  const uint4 raw = *reinterpret_cast<const uint4*>(src);
+  float x[8];
+  unpack8(raw, x);
+  // K: canonical row-major packing.  V: the same bytes, token-minor in blocks of kVBlock tokens (see Pools).
+  uint8_t* cdst = P.qkc + ((size_t)gu * P.capQ + dst) * CB;
+  uint32_t* mdst = P.qkm + ((size_t)gu * P.capQ + dst) * NG;
+  uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
+  constexpr int MH = vmeta_per_row(D, BITS);
+  uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
+  if constexpr (BITS == 8) {
+    uint2 codes;
+    uint32_t meta;
+    quantize8_fp8<LPR>(x, codes, meta);
+    if (!store) return;
+    if (lane < LPR) {
+      *reinterpret_cast<uint2*>(cdst + ((sub & 3) * (D / 32) + (sub >> 2)) * 8) = codes;     // see kcode_index
+      if (sub == 0) mdst[0] = meta;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        vcu[vcode_index(dst, 8 * sub + i, CB, BITS)] = (uint8_t)((i < 4 ? codes.x >> (8 * i) : codes.y >> (8 * (i - 4))) & 0xffu);
+      if (sub == 0) vmu[vmeta_index(dst, 0, MH)] = (uint16_t)meta;
+    }
+  } else {
+    uint32_t codes, meta;
+    quantize8<BITS>(x, codes, meta);
+    if (!store) return;
+    if (lane < LPR) {
+      const int chunk = (sub & 3) * (D / 32) + (sub >> 2);                                   // see kcode_index
+      if (BITS == 4) *reinterpret_cast<uint32_t*>(cdst + chunk * 4) = codes;
+      else *reinterpret_cast<uint16_t*>(cdst + chunk * 2) = (uint16_t)codes;
+      if ((sub & 3) == 0) mdst[sub >> 2] = meta;
+    } else {
+#pragma unroll
+      for (int i = 0; i < BITS; ++i) vcu[vcode_index(dst, BITS * sub + i, CB, BITS)] = (uint8_t)((codes >> (8 * i)) & 0xffu);
+      if ((sub & 3) == 0) {
+        vmu[vmeta_index(dst, sub >> 2, MH)] = (uint16_t)(meta & 0xffffu);              // scale
+        vmu[vmeta_index(dst, D / kGroup + (sub >> 2), MH)] = (uint16_t)(meta >> 16);   // zero point
+      }
+    }
+  }
+}
+
+// The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
+// nD demoted rows into free Q slots (TPW tokens per wave at once), nM tail rows of the Q pool into holes.
+template <int D, int BITS>
+__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, int nM, int first, int waves, int lane) {
+  constexpr int CB = D * BITS / 8, NG = metas_per_row(D, BITS);
+  constexpr int LPT = 2 * (D / 8), TPW = 64 / LPT;
+  const int32_t* dem = P.plan + (size_t)gu * P.plan_stride + kPlanHdr + 2 * P.capO;
+  const int32_t* qfree = dem + P.capO;
+  const int32_t* qmov = qfree + P.capQ;
+  const int t = lane / LPT, sl = lane % LPT;
+  for (int i0 = first * TPW; i0 < nD; i0 += waves * TPW) {
+    const int item = min(i0 + t, nD - 1), dst = qfree[item];
+    const size_t o = (size_t)gu * P.capO + dem[item];
+    quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, sl, i0 + t < nD);
+    if (sl == 0 && i0 + t < nD) {
+      P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
+      P.qacc[(size_t)gu * P.capQ + dst] = P.oacc[o];
+    }
+  }
+  for (int item = first; item < nM; item += waves) {
+    const int dst = qfree[nD + item], src = qmov[item];
+    const size_t so = (size_t)gu * P.capQ + src, d_ = (size_t)gu * P.capQ + dst;
+    // K: code bytes, 4 per lane; V: one byte column per lane (token-minor blocks)
+    for (int b = lane * 4; b < CB; b += 256)
+      *reinterpret_cast<uint32_t*>(P.qkc + d_ * CB + b) = *reinterpret_cast<const uint32_t*>(P.qkc + so * CB + b);
+    uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
+    for (int b = lane; b < CB; b += 64) vcu[vcode_index(dst, b, CB, BITS)] = vcu[vcode_index(src, b, CB, BITS)];
+    constexpr int MH = vmeta_per_row(D, BITS);
+    uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
+    if (lane < MH) vmu[vmeta_index(dst, lane, MH)] = vmu[vmeta_index(src, lane, MH)];
+    if (lane < NG) P.qkm[d_ * NG + lane] = P.qkm[so * NG + lane];
+    if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = P.qacc[so]; }
+  }
+}
+
+// nM tail rows of the O pool into holes: after every demoted row of the unit has been read.
+template <int D>
+__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, int first, int waves, int lane) {
+  constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;
+  const int32_t* ohole = P.plan + (size_t)gu * P.plan_stride + kPlanHdr;
+  const int32_t* omov = ohole + P.capO;
+  const int t = lane / LPT, sl = lane % LPT, sub = sl % LPR;
+  uint16_t* base = sl < LPR ? P.ok : P.ov;
+  for (int item = first * TPW + t; item < nM; item += waves * TPW) {
+    const size_t so = (size_t)gu * P.capO + omov[item], d_ = (size_t)gu * P.capO + ohole[item];
+    *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
+    if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = P.oacc[so]; }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // in-place tailor: keys (eq. 9's score per row), the two thresholds, and the lists that compact both pools.
 // One workgroup per unit, one launch, bound by one CU's instruction issue and round trips (32 units x 8192 rows, one moved per
 // step: 14 us inside the kernel, of which keys 3, selection 6, fates 3, lists 2; a step with a tailor 64.3 -> 56.5 us against
@@ -357,7 +563,29 @@ __device__ __forceinline__ ListFlags list_flags(uint64_t stay, uint64_t dem, int
   return {~stay & on, stay & o & ~on, dem, ~stay & all & q & ~o, stay & all & ~o & ~q};
 }
 
-template <int G, bool IN_LDS>
+// Sum and sum of squares of a step's probabilities of one row over the unit's heads, added up as k_flush_scores does.
+// fin: the step's final (max, 1/sum) per head.
+template <int G>
+__device__ __forceinline__ float2 step_moments(const float (&x)[G], const float2 (&fin)[G]) {
+  constexpr int HB = (G + 3) / 4, HPL = G < 4 ? G : 4;
+  float2 m[HB];
+#pragma unroll
+  for (int b = 0; b < HB; ++b) {
+    m[b] = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int i = 0; i < HPL; ++i) {
+      const float p = __builtin_amdgcn_exp2f(x[4 * b + i] - fin[4 * b + i].x) * fin[4 * b + i].y;
+      m[b].x += p;
+      m[b].y = fmaf(p, p, m[b].y);
+    }
+  }
+  if constexpr (HB == 2) { m[0].x += m[1].x; m[0].y += m[1].y; }
+  return m[0];
+}
+
+// KEPT: the pending step's logits are in Pools::logit (see k_decode_attend); its probabilities are added to the sums here,
+// and few moved rows (L.few_moves) are moved here as well.
+template <int G, bool IN_LDS, bool KEPT>
 __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L) {
   extern __shared__ __align__(16) uint32_t row_word[];      // IN_LDS: score of row i
   __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
@@ -369,29 +597,53 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   uint64_t* keys = P.keys + (size_t)gu * (P.capO + P.capQ);
   const int32_t* opos = P.opos + (size_t)gu * P.capO;
   const int32_t* qpos = P.qpos + (size_t)gu * P.capQ;
-  const float2* oacc = P.oacc + (size_t)gu * P.capO;
-  const float2* qacc = P.qacc + (size_t)gu * P.capQ;
+  float2* oacc = P.oacc + (size_t)gu * P.capO;
+  float2* qacc = P.qacc + (size_t)gu * P.capQ;
+  const float* logit = KEPT ? P.logit + (size_t)gu * ((size_t)P.capO + P.capQ) * G : nullptr;
+  float2 fin[G];
+  if constexpr (KEPT) {
+    const float2* f = P.fin + (size_t)((L.slot + kRing - 1) % kRing) * P.fin_stride + (size_t)gu * G;
+#pragma unroll
+    for (int h = 0; h < G; ++h) fin[h] = f[h];
+  }
   const int slot_q = P.capO - cO;                           // row i >= cO: key slot i + slot_q
   const int nq = quads(n), rounds = (n + 1023) / 1024;
   ScoreRange range;
   // (a barrier of the selection stands between these stores and another thread's read of a key)
   constexpr int BATCH = 4;                                  // rows requested together, one batch ahead of their use
-  struct Rows { int pos[BATCH]; float2 acc[BATCH]; };
+  struct Rows { int pos[BATCH]; float2 acc[BATCH]; float x[KEPT ? BATCH : 1][G]; };
   auto fetch = [&](int q, Rows& r) {
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
       const int i = min(kQuad * q + 1024 * j + tid, n - 1);
       r.pos[j] = i < cO ? opos[i] : qpos[i - cO];
       r.acc[j] = i < cO ? oacc[i] : qacc[i - cO];
+      if constexpr (KEPT) {
+        typedef float Vec __attribute__((ext_vector_type(G < 4 ? G : 4)));
+        const Vec* p = reinterpret_cast<const Vec*>(logit + (size_t)(i < cO ? i : i + slot_q) * G);
+        if constexpr (G == 1) r.x[j][0] = *reinterpret_cast<const float*>(p);
+        else
+#pragma unroll
+          for (int v = 0; v < (G + 3) / 4; ++v) {
+            const Vec t = p[v];
+#pragma unroll
+            for (int h = 0; h < (G < 4 ? G : 4); ++h) r.x[j][4 * v + h] = t[h];
+          }
+      }
     }
   };
-  auto score_rows = [&](int q, const Rows& r) {
+  auto score_rows = [&](int q, Rows& r) {
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
       const int i = kQuad * q + 1024 * j + tid;
       if (kQuad * q + 1024 * j >= n) {                      // a round without rows
         if constexpr (IN_LDS) row_word[i] = kNoScore;
         continue;
+      }
+      if constexpr (KEPT) {
+        const float2 m = step_moments<G>(r.x[j], fin);
+        r.acc[j].x += m.x; r.acc[j].y += m.y;
+        if (i < n) *(i < cO ? oacc + i : qacc + (i - cO)) = r.acc[j];
       }
       uint64_t key = 0;
       if (i < n && r.pos[j] < L.position + 1 - L.window) {
@@ -551,240 +803,38 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     plan[PL_N_QMOV] = base_qmov; plan[PL_N_OMOV] = base_mov;
     plan[PL_CO_OLD] = cO; plan[PL_CQ_OLD] = cQ;
   }
-}
-
-// ------------------------------------------------------------------------------------------
-// quantiser: one K or V row held by LPR lanes, 8 channels each (fp32 from bf16)
-// ------------------------------------------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ float dppf(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               0xf, 0xf, true));
-}
-
-__device__ __forceinline__ uint16_t f2h(float x) { return __half_as_ushort(__float2half_rn(x)); }
-__device__ __forceinline__ float h2f(uint16_t h) { return __half2float(__ushort_as_half(h)); }
-__device__ __forceinline__ uint16_t h_next_down(uint16_t h) {
-  if ((h & 0x7fffu) == 0) return 0x8001u;
-  return (h & 0x8000u) ? (uint16_t)(h + 1) : (uint16_t)(h - 1);
-}
-__device__ __forceinline__ uint16_t h_next_up(uint16_t h) {
-  if ((h & 0x7fffu) == 0) return 0x0001u;
-  return (h & 0x8000u) ? (uint16_t)(h - 1) : (uint16_t)(h + 1);
-}
-
-// x: the 8 channels of this lane; the 4 lanes of an aligned quad form one group of 32 channels.
-// Returns the lane's packed codes (8*BITS bits) and the group's meta word (scale | zero << 16).
-template <int BITS>
-__device__ __forceinline__ void quantize8(const float (&x)[8], uint32_t& codes, uint32_t& meta) {
-  const float qmax = (float)((1 << BITS) - 1);
-  float mn = x[0], mx = x[0];
-#pragma unroll
-  for (int c = 1; c < 8; ++c) { mn = fminf(mn, x[c]); mx = fmaxf(mx, x[c]); }
-  mn = fminf(mn, dppf<0xB1>(mn)); mx = fmaxf(mx, dppf<0xB1>(mx));
-  mn = fminf(mn, dppf<0x4E>(mn)); mx = fmaxf(mx, dppf<0x4E>(mx));
-  uint16_t zh = f2h(mn);
-  float z = h2f(zh);
-  if (z > mn) { zh = h_next_down(zh); z = h2f(zh); }
-  const float r = mx - z;
-  uint16_t sh = 0;
-  codes = 0;
-  if (r != 0.0f) {
-    const float s = r / qmax;
-    sh = f2h(s);
-    float sc = h2f(sh);
-    if (sc * qmax < r) { sh = h_next_up(sh); sc = h2f(sh); }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      float t = rintf((x[c] - z) / sc);
-      t = fminf(fmaxf(t, 0.0f), qmax);
-      codes |= (uint32_t)t << (BITS * c);
-    }
-  }
-  meta = (uint32_t)sh | ((uint32_t)zh << 16);
-}
-
-__device__ __forceinline__ void unpack8(const uint4& r, float (&f)[8]) {
-  f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
-  f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
-  f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xffff0000u);
-  f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xffff0000u);
-}
-
-// fp8 rows with one scale per token (Alg. 1 "Reconstruction Before Attention": x~ = q^ * s).
-// |t| <= 448 -> nearest E4M3 code (sign, 4 exponent bits with bias 7, 3 mantissa bits, subnormals below
-// 2^-6, no infinities), ties to the even code, in integer arithmetic on the fp32 bits.
-__device__ __forceinline__ uint32_t e4m3_code(float t) {
-  const float a = fminf(fabsf(t), 448.0f);
-  uint32_t code;
-  if (a < 0.015625f) {
-    code = (uint32_t)rintf(a * 512.0f);             // subnormals are multiples of 2^-9; 8 = the smallest normal
-  } else {
-    uint32_t b = __float_as_uint(a);
-    b += 0x7FFFFu + ((b >> 20) & 1u);               // round to 3 mantissa bits, ties to even
-    code = (((b >> 23) - 120u) << 3) | ((b >> 20) & 7u);
-  }
-  return code;
-}
-
-// x: the 8 channels of this lane; the LPR lanes of a row share one scale.
-// Returns the lane's 8 codes (byte c = channel c) and the row's scale (fp16 bits).
-template <int LPR>
-__device__ __forceinline__ void quantize8_fp8(const float (&x)[8], uint2& codes, uint32_t& meta) {
-  float amax = fabsf(x[0]);
-#pragma unroll
-  for (int c = 1; c < 8; ++c) amax = fmaxf(amax, fabsf(x[c]));
-  amax = fmaxf(amax, dppf<0xB1>(amax));
-  amax = fmaxf(amax, dppf<0x4E>(amax));
-  amax = fmaxf(amax, dppf<0x141>(amax));             // 8 lanes
-  if (LPR == 16) amax = fmaxf(amax, dppf<0x140>(amax));
-  uint16_t sh = 0;
-  codes = make_uint2(0, 0);
-  if (amax != 0.0f) {
-    const float s = amax / 448.0f;
-    sh = f2h(s);
-    float sc = h2f(sh);
-    if (sc * 448.0f < amax) { sh = h_next_up(sh); sc = h2f(sh); }
-    uint32_t w[2] = {0, 0};
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const uint32_t code = e4m3_code(x[c] / sc) | (x[c] < 0.0f ? 0x80u : 0u);
-      w[c >> 2] |= code << (8 * (c & 3));
-    }
-    codes = make_uint2(w[0], w[1]);
-  }
-  meta = sh;
-}
-
-// 2 LPR adjacent lanes (lane = 0 .. 2 LPR - 1 among them) quantise a token into Q slot dst of unit gu: lanes [0, LPR) the
-// K row, the others the V row.  A wave takes 64 / (2 LPR) tokens at once; every lane runs the arithmetic (the lane
-// exchanges need them active), lanes without store write nothing.
-template <int D, int BITS>
-__device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, const uint16_t* krow,
-                                              const uint16_t* vrow, int lane, bool store) {
-  constexpr int LPR = D / 8, CB = D * BITS / 8, NG = metas_per_row(D, BITS);
-  const bool isv = lane >= LPR;
-  const int sub = lane % LPR;
-  const uint16_t* src = (isv ? vrow : krow) + sub * 8;
-  const uint4 raw = *reinterpret_cast<const uint4*>(src);
-  float x[8];
-  unpack8(raw, x);
-  // K: canonical row-major packing.  V: the same bytes, token-minor in blocks of kVBlock tokens (see Pools).
-  uint8_t* cdst = P.qkc + ((size_t)gu * P.capQ + dst) * CB;
-  uint32_t* mdst = P.qkm + ((size_t)gu * P.capQ + dst) * NG;
-  uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
-  constexpr int MH = vmeta_per_row(D, BITS);
-  uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
-  if constexpr (BITS == 8) {
-    uint2 codes;
-    uint32_t meta;
-    quantize8_fp8<LPR>(x, codes, meta);
-    if (!store) return;
-    if (lane < LPR) {
-      *reinterpret_cast<uint2*>(cdst + ((sub & 3) * (D / 32) + (sub >> 2)) * 8) = codes;     // see kcode_index
-      if (sub == 0) mdst[0] = meta;
+  if constexpr (KEPT) {
+    if (!L.few_moves) return;
+    __syncthreads();                                        // the lists
+    auto moves = [&](auto d, auto bits) {
+      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane);
+      __syncthreads();                                      // every demoted row has been read
+      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane);
+    };
+    using std::integral_constant;
+    if (P.D == 128) {
+      const integral_constant<int, 128> d;
+      if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
     } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        vcu[vcode_index(dst, 8 * sub + i, CB, BITS)] = (uint8_t)((i < 4 ? codes.x >> (8 * i) : codes.y >> (8 * (i - 4))) & 0xffu);
-      if (sub == 0) vmu[vmeta_index(dst, 0, MH)] = (uint16_t)meta;
+      const integral_constant<int, 64> d;
+      if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
     }
-  } else {
-    uint32_t codes, meta;
-    quantize8<BITS>(x, codes, meta);
-    if (!store) return;
-    if (lane < LPR) {
-      const int chunk = (sub & 3) * (D / 32) + (sub >> 2);                                   // see kcode_index
-      if (BITS == 4) *reinterpret_cast<uint32_t*>(cdst + chunk * 4) = codes;
-      else *reinterpret_cast<uint16_t*>(cdst + chunk * 2) = (uint16_t)codes;
-      if ((sub & 3) == 0) mdst[sub >> 2] = meta;
-    } else {
-#pragma unroll
-      for (int i = 0; i < BITS; ++i) vcu[vcode_index(dst, BITS * sub + i, CB, BITS)] = (uint8_t)((codes >> (8 * i)) & 0xffu);
-      if ((sub & 3) == 0) {
-        vmu[vmeta_index(dst, sub >> 2, MH)] = (uint16_t)(meta & 0xffffu);              // scale
-        vmu[vmeta_index(dst, D / kGroup + (sub >> 2), MH)] = (uint16_t)(meta >> 16);   // zero point
-      }
-    }
-  }
-}
-
-// The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
-// Demoted rows into free Q slots (TPW tokens per wave at once), tail rows of the Q pool into holes.
-template <int D, int BITS>
-__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int first, int waves, int lane) {
-  constexpr int CB = D * BITS / 8, NG = metas_per_row(D, BITS);
-  constexpr int LPT = 2 * (D / 8), TPW = 64 / LPT;
-  const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  const int nD = plan[PL_N_DEM], nM = plan[PL_N_QMOV];
-  const int32_t* dem = plan + kPlanHdr + 2 * P.capO;
-  const int32_t* qfree = dem + P.capO;
-  const int32_t* qmov = qfree + P.capQ;
-  const int t = lane / LPT, sl = lane % LPT;
-  for (int i0 = first * TPW; i0 < nD; i0 += waves * TPW) {
-    const int item = min(i0 + t, nD - 1), dst = qfree[item];
-    const size_t o = (size_t)gu * P.capO + dem[item];
-    quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, sl, i0 + t < nD);
-    if (sl == 0 && i0 + t < nD) {
-      P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
-      P.qacc[(size_t)gu * P.capQ + dst] = P.oacc[o];
-    }
-  }
-  for (int item = first; item < nM; item += waves) {
-    const int dst = qfree[nD + item], src = qmov[item];
-    const size_t so = (size_t)gu * P.capQ + src, d_ = (size_t)gu * P.capQ + dst;
-    // K: code bytes, 4 per lane; V: one byte column per lane (token-minor blocks)
-    for (int b = lane * 4; b < CB; b += 256)
-      *reinterpret_cast<uint32_t*>(P.qkc + d_ * CB + b) = *reinterpret_cast<const uint32_t*>(P.qkc + so * CB + b);
-    uint8_t* vcu = P.qvc + (size_t)gu * P.capQv * CB;
-    for (int b = lane; b < CB; b += 64) vcu[vcode_index(dst, b, CB, BITS)] = vcu[vcode_index(src, b, CB, BITS)];
-    constexpr int MH = vmeta_per_row(D, BITS);
-    uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
-    if (lane < MH) vmu[vmeta_index(dst, lane, MH)] = vmu[vmeta_index(src, lane, MH)];
-    if (lane < NG) P.qkm[d_ * NG + lane] = P.qkm[so * NG + lane];
-    if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = P.qacc[so]; }
-  }
-}
-
-// Tail rows of the O pool into holes: after every demoted row of the unit has been read.
-template <int D>
-__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int first, int waves, int lane) {
-  constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;
-  const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  const int nM = plan[PL_N_OMOV];
-  const int32_t* ohole = plan + kPlanHdr;
-  const int32_t* omov = ohole + P.capO;
-  const int t = lane / LPT, sl = lane % LPT, sub = sl % LPR;
-  uint16_t* base = sl < LPR ? P.ok : P.ov;
-  for (int item = first * TPW + t; item < nM; item += waves * TPW) {
-    const size_t so = (size_t)gu * P.capO + omov[item], d_ = (size_t)gu * P.capO + ohole[item];
-    *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
-    if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = P.oacc[so]; }
+    if (tid == 0) P.cnt[gu] = make_int2(cOn, cQn);
   }
 }
 
 template <int D, int BITS>
 __global__ __launch_bounds__(256) void k_tailor_move_q(Pools P, TailorLaunch L) {
-  tailor_move_q<D, BITS>(P, L.unit_begin + blockIdx.y, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
-}
-
-// Both kinds of moves of a unit by one workgroup, for tailors that move a few rows each (the tailor-at-every-step policy):
-// one launch instead of two (6.6 + 5.0 us -> 7 us for 32 units).
-template <int D, int BITS>
-__global__ __launch_bounds__(1024) void k_tailor_move_few(Pools P, TailorLaunch L) {
-  const int gu = L.unit_begin + blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int gu = L.unit_begin + blockIdx.y;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  tailor_move_q<D, BITS>(P, gu, w, 16, lane);
-  __syncthreads();                           // every demoted row has been read
-  tailor_move_o<D>(P, gu, w, 16, lane);
-  if (threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
+  tailor_move_q<D, BITS>(P, gu, plan[PL_N_DEM], plan[PL_N_QMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) {
   const int gu = L.unit_begin + blockIdx.y;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  tailor_move_o<D>(P, gu, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
+  tailor_move_o<D>(P, gu, plan[PL_N_OMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
   if (blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
 }
 
@@ -1048,30 +1098,31 @@ static int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v
 
 template <int D, int BITS>
 static void launch_tailor_moves(const Pools& P, const TailorLaunch& a, hipStream_t s) {
-  if (a.few_moves) {
-    hipLaunchKernelGGL((k_tailor_move_few<D, BITS>), dim3(a.n_units), dim3(1024), 0, s, P, a);
-    return;
-  }
   dim3 gq(clampi((P.capQ + 3) / 4, 1, 256), a.n_units), go(clampi((P.capO + 3) / 4, 1, 256), a.n_units);
   hipLaunchKernelGGL((k_tailor_move_q<D, BITS>), gq, dim3(256), 0, s, P, a);
   hipLaunchKernelGGL((k_tailor_move_o<D>), go, dim3(256), 0, s, P, a);
 }
 
 hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
-  if (a.n_pending > 0) {
+  if (a.n_pending > 0 && !a.kept) {
     hipError_t e = launch_flush_scores(P, a.unit_begin, a.n_units, a.n_pending, a.slot, s);
     if (e != hipSuccess) return e;
   }
   // the scores of a unit stay in LDS between the passes where they fit
+  const bool lds = a.max_rows <= kLdsRows;
+  const int rows = lds ? a.max_rows : 0;
 #define ARKV_CH(G_)                                                                                                     \
   case G_:                                                                                                              \
-    e = a.max_rows <= kLdsRows ? launch_rows(k_tailor_choose<G_, true>, a.n_units, a.max_rows, s, P, a)                 \
-                               : launch_rows(k_tailor_choose<G_, false>, a.n_units, 0, s, P, a);                        \
+    e = a.kept ? (lds ? launch_rows(k_tailor_choose<G_, true, true>, a.n_units, rows, s, P, a)                          \
+                      : launch_rows(k_tailor_choose<G_, false, true>, a.n_units, rows, s, P, a))                        \
+               : (lds ? launch_rows(k_tailor_choose<G_, true, false>, a.n_units, rows, s, P, a)                         \
+                      : launch_rows(k_tailor_choose<G_, false, false>, a.n_units, rows, s, P, a));                      \
     break;
   hipError_t e = hipErrorInvalidValue;
   switch (P.G) { ARKV_CH(1) ARKV_CH(2) ARKV_CH(4) ARKV_CH(8) }
   if (e != hipSuccess) return e;
 #undef ARKV_CH
+  if (a.kept && a.few_moves) return hipSuccess;             // done by the choosing workgroups
   if (P.D == 128 && P.bits == 4) launch_tailor_moves<128, 4>(P, a, s);
   else if (P.D == 128 && P.bits == 2) launch_tailor_moves<128, 2>(P, a, s);
   else if (P.D == 64 && P.bits == 4) launch_tailor_moves<64, 4>(P, a, s);

@@ -449,3 +449,19 @@ def test_selection_in_a_narrow_range_of_scores(T, N, gain, steps):
         sb.assert_within_tol(stats=False)
     finally:
         sb.close()
+
+
+@pytest.mark.parametrize("g,d,bits,T,N,rho,byte_budget", [
+    (1, 128, 8, 600, 300, 0.3, False),
+    (2, 64, 2, 1500, 1100, 0.0, False),       # rows of both pools in every round, all candidates packed
+    (8, 128, 4, 700, 90, 0.5, False),         # one split per unit
+    (8, 64, 8, 900, 400, 0.4, True),          # more rows than the token rule keeps
+    (4, 128, 4, 5000, 4200, 0.6, False),      # two rounds of 4096 rows
+    (2, 64, 4, 33400, 33000, 0.9, False),     # rows' scores in memory
+])
+def test_tailor_from_kept_logits(g, d, bits, T, N, rho, byte_budget):
+    """With a tailor at every step the scores' update takes the step's logits from the attention launch, and from the 17th
+    tailor on the choosing workgroup moves the rows: 19 steps against the oracle, states and rows exactly."""
+    wl = synth.C1.scaled(name="kept", n_q_heads=2 * g, n_kv_heads=2, head_dim=d, bits=bits, prefill=T, budget_frac=(N + 0.5) / T,
+                         window=16, decode_steps=19)
+    _run(wl, rho=rho, check_every=6, stats=False, every_step=True, byte_budget=byte_budget)
