@@ -377,6 +377,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 #pragma unroll
     for (int kk = 0; kk < KH; ++kk) kop[kk] = k_operand(1, kk);
   }
+  __syncthreads();       // the first step stages into buffer 0: every wave, also one whose query rows came late, has read it
   for (int t = t0; t < t1; t += 2) {
     step(C0, C1, t, 0);
     if (t + 1 < t1) step(C1, C0, t + 1, 1);
