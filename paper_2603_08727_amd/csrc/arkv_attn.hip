@@ -5,7 +5,11 @@
 // One workgroup = 32 QB query positions of one (sequence, kv-head) x the G heads of its group; a wave takes 32
 // positions of one head.  QB = 4 / G for G < 4 (else 1), so that at least four waves share every key and value tile,
 // which is fetched from HBM once per workgroup and staged
-// in LDS (keys in three buffers, values in two, one barrier per 32-key tile).  Keys are on the M side of the
+// in LDS (keys in three buffers, values in two, one barrier per 32-key tile); the loads of a tile have two steps to
+// arrive (a step takes 0.4-1.1 us, a load that misses the L2 0.5-1 us), and their conversion and way into LDS is
+// dealt out between the PV MFMAs of the second.  With one step to arrive and the staging behind the MFMAs: 32768 tokens x
+// 8 units 8736 -> 8206 us, 512 x 16411 x 8 units 164 -> 152 us, 2003 x 32 units (d = 64, G = 1) 43.1 -> 33.0 us;
+// the earlier loads alone gave 1 / 4 / 15 %.  Keys are on the M side of the
 // logits MFMA (v_mfma_f32_32x32x16_bf16, S^T = K Q^T), which leaves ONE query row per lane: the online softmax
 // is per-lane arithmetic (the two lane halves of a row talk only when the row's reference maximum moves, which
 // is rare: see the step below).  The probabilities a lane then holds
@@ -25,6 +29,19 @@ typedef __bf16 bf16x8a __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8a __attribute__((ext_vector_type(8)));
 typedef float f32x16a __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4a __attribute__((ext_vector_type(4)));   // a 16-byte chunk the compiler keeps in registers
+// N dwords that one load or store moves
+template <int N> struct WordsOf { typedef uint32_t type __attribute__((ext_vector_type(N))); };
+template <> struct WordsOf<1> { typedef uint32_t type; };
+template <int N> using Words = typename WordsOf<N>::type;
+template <int N> __device__ __forceinline__ Words<N> buffer_words(__amdgpu_buffer_rsrc_t r, uint32_t byte) {
+  if constexpr (N == 4) return __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, 0);
+  else if constexpr (N == 2) return __builtin_amdgcn_raw_buffer_load_b64(r, byte, 0, 0);
+  else return __builtin_amdgcn_raw_buffer_load_b32(r, byte, 0, 0);
+}
+template <typename V> __device__ __forceinline__ uint32_t word(const V& v, int i) {
+  if constexpr (sizeof(V) == 4) return v;
+  else return v[i];
+}
 
 constexpr float kNegBigA = -1.0e30f;
 constexpr int kVtPitch = 40;   // halves per channel row of the transposed value tile: 32 keys + 8 (16-byte reads, 20-dword stride)
@@ -49,7 +66,7 @@ struct AttnLds {
 };
 
 // sched_group_barrier classes
-constexpr int kSgValu = 0x2, kSgMfma = 0x8, kSgDsRead = 0x100;
+constexpr int kSgValu = 0x2, kSgMfma = 0x8, kSgDsRead = 0x100, kSgDsWrite = 0x200;
 typedef _Float16 f16x2a __attribute__((ext_vector_type(2)));
 constexpr float kSumLimit = 16384.0f;   // a lane's 16 probabilities may sum to this before the reference maximum moves
 
@@ -144,12 +161,14 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   constexpr int NPV = 2 * CBN;        // PV MFMAs per tile
   constexpr int QB = kQBlocks<G>;     // blocks of 32 query positions per workgroup
   constexpr int NT = 64 * G * QB;
-  constexpr int CPR = D / 8;          // 16-byte chunks per row
-  constexpr int KCH = 32 * CPR;       // key chunks per tile
-  constexpr int VCH = 16 * CPR;       // value chunk pairs (two adjacent keys, eight channels) per tile
-  constexpr int KPT = (KCH + NT - 1) / NT;
-  constexpr int VPT = (VCH + NT - 1) / NT;
-  static_assert(NPV >= KH, "operand prefetch pattern");
+  // Staging items of a tile, the same number for every thread (a branch would end the region in which they are
+  // dealt out between MFMAs): KW channels of a key; VW channels of a pair of adjacent keys' values.
+  constexpr int KW = 32 * D / NT < 8 ? 32 * D / NT : 8, KPR = D / KW, KPT = 32 * KPR / NT;
+  constexpr int VW = 16 * D / NT;
+  static_assert(KW * KPR == D && KPT * NT == 32 * KPR && VW >= 2 && VW <= 8, "equal shares");
+  static_assert(NPV >= KH && NPV >= KPT + VW / 2, "operand prefetch pattern; one staging item per PV MFMA at most");
+  using KItem = Words<KW / 2>;
+  using VItem = Words<VW / 2>;
   __shared__ __align__(16) AttnLds<D> sm;
   const int nqb = (L.Tq + 32 * QB - 1) / (32 * QB);
   int u, qb;
@@ -182,67 +201,35 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) qreg[kk] = *reinterpret_cast<const u32x4a*>(qp + 16 * kk);
   }
-  // global -> registers -> LDS staging of one tile.  A tile that ends inside the prompt is addressed as a
-  // uniform base plus a per-thread constant; the last, partial one (and the prefetch past it) clamps its rows
-  // to the prompt: the surplus keys are masked or never read.
-  u32x4a ks[KPT], vs[VPT][2];
-  auto fetch_k = [&](int j0) {
-    if (j0 + 32 <= T) {
-      const uint16_t* base = kbase + (size_t)j0 * D;
-#pragma unroll
-      for (int c = 0; c < KPT; ++c) {
-        const int ch = min(tid + NT * c, KCH - 1);
-        ks[c] = *reinterpret_cast<const u32x4a*>(base + (ch / CPR) * D + 8 * (ch % CPR));
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < KPT; ++c) {
-        const int ch = min(tid + NT * c, KCH - 1);
-        const int key = min(j0 + ch / CPR, T - 1);
-        ks[c] = *reinterpret_cast<const u32x4a*>(kbase + (size_t)key * D + 8 * (ch % CPR));
-      }
-    }
+  // global -> registers -> LDS staging of one tile.  A tile is a buffer of its own: a uniform base, a per-thread constant
+  // offset, and as many rows as the prompt still has (none for the prefetch past it), so that the last, partial tile needs
+  // no branch and no clamped address (1-3 %); the rows it lacks read as zero and are masked.
+  KItem ks[2][KPT];
+  VItem vs[2][2];
+  const uint32_t koff = 2 * KW * tid, voff = 2 * (2 * (tid % 16) * D + VW * (tid / 16));
+  auto rows_from = [&](const uint16_t* base, int j0) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base) + (size_t)j0 * D, 0,
+                                             2 * D * __builtin_amdgcn_readfirstlane(min(max(T - j0, 0), 32)), 0x00027000);
   };
-  auto fetch_v = [&](int j0) {
-    if (j0 + 32 <= T) {
-      const uint16_t* base = vbase + (size_t)j0 * D;
+  auto fetch_k = [&](int j0, KItem (&to)[KPT]) {
+    const __amdgpu_buffer_rsrc_t r = rows_from(kbase, j0);
 #pragma unroll
-      for (int c = 0; c < VPT; ++c) {
-        const int ch = min(tid + NT * c, VCH - 1);
-        const uint16_t* p = base + 2 * (ch % 16) * D + 8 * (ch / 16);
-        vs[c][0] = *reinterpret_cast<const u32x4a*>(p);
-        vs[c][1] = *reinterpret_cast<const u32x4a*>(p + D);
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < VPT; ++c) {
-        const int ch = min(tid + NT * c, VCH - 1);
-        const int k0 = min(j0 + 2 * (ch % 16), T - 1), k1 = min(j0 + 2 * (ch % 16) + 1, T - 1);
-        vs[c][0] = *reinterpret_cast<const u32x4a*>(vbase + (size_t)k0 * D + 8 * (ch / 16));
-        vs[c][1] = *reinterpret_cast<const u32x4a*>(vbase + (size_t)k1 * D + 8 * (ch / 16));
-      }
-    }
+    for (int c = 0; c < KPT; ++c) to[c] = buffer_words<KW / 2>(r, koff + 2 * KW * NT * c);
   };
-  auto stage_k = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < KPT; ++c) {
-      const int ch = tid + NT * c;
-      if (KCH % NT == 0 || ch < KCH) *reinterpret_cast<u32x4a*>(&sm.k[buf][ch / CPR][8 * (ch % CPR)]) = ks[c];
-    }
+  auto fetch_v = [&](int j0, VItem (&to)[2]) {
+    const __amdgpu_buffer_rsrc_t r = rows_from(vbase, j0);
+    to[0] = buffer_words<VW / 2>(r, voff);
+    to[1] = buffer_words<VW / 2>(r, voff + 2 * D);
   };
-  auto stage_v = [&](int buf) {
-#pragma unroll
-    for (int c = 0; c < VPT; ++c) {
-      const int ch = tid + NT * c;
-      if (VCH % NT == 0 || ch < VCH) {
-        const int col = vt_col(2 * (ch % 16)), c0 = 8 * (ch / 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          *reinterpret_cast<uint32_t*>(&sm.vt[buf][c0 + 2 * e][col]) = bf16_pair_to_f16x2(vs[c][0][e], vs[c][1][e]);
-          *reinterpret_cast<uint32_t*>(&sm.vt[buf][c0 + 2 * e + 1][col]) = bf16_pair_to_f16x2(vs[c][0][e] >> 16, vs[c][1][e] >> 16);
-        }
-      }
-    }
+  auto stage_k1 = [&](int buf, int c, const KItem (&from)[KPT]) {
+    const int ch = tid + NT * c;
+    *reinterpret_cast<KItem*>(&sm.k[buf][ch / KPR][KW * (ch % KPR)]) = from[c];
+  };
+  auto stage_v1 = [&](int buf, int e, const VItem (&from)[2]) {      // channels 2 e, 2 e + 1 of the thread's share
+    const int col = vt_col(2 * (tid % 16)), c0 = VW * (tid / 16);
+    const uint32_t a = word(from[0], e), b = word(from[1], e);
+    *reinterpret_cast<uint32_t*>(&sm.vt[buf][c0 + 2 * e][col]) = bf16_pair_to_f16x2(a, b);
+    *reinterpret_cast<uint32_t*>(&sm.vt[buf][c0 + 2 * e + 1][col]) = bf16_pair_to_f16x2(a >> 16, b >> 16);
   };
   auto k_operand = [&](int buf, int kk) { return *reinterpret_cast<const u32x4a*>(&sm.k[buf][n][16 * kk + 8 * hh]); };
   // A of O^T = V^T P^T, PV MFMA r = jj * CBN + cb: channel 32 cb + n, keys 16 jj + 4 hh + (0..3) and
@@ -283,14 +270,16 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   // followed in issue order by one LDS operand read for a later MFMA and by its share of tile t's softmax
   // arithmetic (from C): the matrix pipe works in the background of the same wave's vector instructions only
   // if the two alternate.  Phase B: the PV MFMAs of tile t between operand reads for the next step and the
-  // conversion of the tiles fetched at the top, which are staged into LDS at the end.
+  // conversion and staging of the tiles fetched at the top of the step before: one item behind each MFMA, pinned there by
+  // an empty asm that takes an operand of the next MFMA (group barriers alone let the MFMAs run together at the end).
   // The reference maximum is lazy: probabilities are taken against the row's current m_run, and only when a
   // lane's sum shows that they grew large (or the reference is still unset) does the row move its reference
   // to the tile's maximum and redo the tile.  A row decides from its own numbers only.
   auto step = [&](f32x16a& C, f32x16a& Cn, int t, const int vb) {     // vb: the buffer that holds the value tile
     const int j0 = 32 * t;
-    fetch_k(j0 + 96);
-    fetch_v(j0 + 32);
+    fetch_k(j0 + 128, ks[vb]);
+    fetch_v(j0 + 64, vs[vb]);
+    __builtin_amdgcn_sched_barrier(0);
     uint32_t ph[8];
     float lt0 = 0.f, lt1 = 0.f, le0 = 0.f, le1 = 0.f;
 #pragma unroll
@@ -343,28 +332,30 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
       const int jj = r / CBN, cb = r % CBN;
       const u32x4a pb = {ph[4 * jj], ph[4 * jj + 1], ph[4 * jj + 2], ph[4 * jj + 3]};
       acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8a, vop[r]), __builtin_bit_cast(f16x8a, pb), acc[cb], 0, 0, 0);
+      if (r < VW / 2) stage_v1(vb ^ 1, r, vs[vb ^ 1]);                  // tile t + 1; that buffer was last read one step ago
+      else if (r < VW / 2 + KPT) stage_k1(kW, r - VW / 2, ks[vb ^ 1]);  // tile t + 3 into the buffer tile t's logits came from
+      if (r + 1 < NPV) asm volatile("" : "+v"(ph[4 * ((r + 1) / CBN)]) : : "memory");
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int r = 0; r < NPV; ++r) {
-      __builtin_amdgcn_sched_group_barrier(kSgMfma, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kSgDsRead, 1, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);                // the staging waits for this step's loads: keep it behind the MFMAs
-    stage_k(kW);                                      // tile t + 3 into the buffer tile t's logits came from
-    stage_v(vb ^ 1);                                  // tile t + 1; that buffer was last read one step ago
     mask(Cn, j0 + 32);
     const int k0 = kA; kA = kB; kB = kW; kW = k0;
     __syncthreads();
   };
 
-  fetch_k(32 * t0);
-  fetch_v(32 * t0);
-  stage_k(0);
-  stage_v(0);
-  fetch_k(32 * t0 + 32);
-  stage_k(1);
-  fetch_k(32 * t0 + 64);
-  stage_k(2);
+  fetch_k(32 * t0, ks[0]);
+  fetch_v(32 * t0, vs[0]);
+  fetch_k(32 * t0 + 32, ks[1]);
+  fetch_v(32 * t0 + 32, vs[1]);
+#pragma unroll
+  for (int c = 0; c < KPT; ++c) stage_k1(0, c, ks[0]);
+#pragma unroll
+  for (int e = 0; e < VW / 2; ++e) stage_v1(0, e, vs[0]);
+  fetch_k(32 * t0 + 64, ks[0]);
+#pragma unroll
+  for (int c = 0; c < KPT; ++c) stage_k1(1, c, ks[1]);
+  fetch_k(32 * t0 + 96, ks[1]);
+#pragma unroll
+  for (int c = 0; c < KPT; ++c) stage_k1(2, c, ks[0]);
   __syncthreads();
   f32x16a C0, C1;
   {
