@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 
 // Adds up the pieces of the workgroups that have more than one.  grid (query blocks, units, D / 32), the same waves and
 // lanes as above; a wave takes one block of 32 channels.  Bound by the partials' bytes (34 MB written and read at 512
-// queries x 16411 keys x 32 heads: 9 us of 164).
+// queries x 16411 keys x 32 heads: 9 us of 152).
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
   constexpr int QB = kQBlocks<G>;
@@ -467,7 +467,7 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
 // Measured at d = 128 (d = 64: about 0.65 of it): a tile step takes 0.75 us in a workgroup that has its CU to itself and
 // 1.06 us where two share it, so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU,
 // whichever is more; the merge costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where
-// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 164 us (4 pieces), 32 x 3000 x 16 units
+// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 152 us (4 pieces), 32 x 3000 x 16 units
 // (d = 64, G = 1) 66 -> 16 us.  It does not pay for a whole short prompt, whose imbalance is only the causal triangle
 // (1000 tokens x 8 kv-heads: 30 us unsplit, 37 us in 2 pieces), hence the margin and the floor of 32 tiles.
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {

@@ -51,6 +51,29 @@ def _check_rows(out, q, k, v, scale, group, positions, q0):
     return worst
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group", [1, 2, 4, 8])
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 64, 95, 129])
+def test_attention_ends_of_tiles(d, group, T):
+    """Prompts of one to five key tiles, most with a partial last one, for every shape of a thread's staging share:
+    tiles are requested up to four ahead of the one in work, past the prompt's end as well, and what lies behind it
+    (here NaN) takes no part."""
+    hkv = 2
+    cfg = make_cfg(synth.C1.scaled(name="ends", n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=d, batch=1))
+    g = torch.Generator().manual_seed(1000 * T + 10 * group + d)
+    q, k, v = (torch.randn((1, h, T, d), generator=g).to(torch.bfloat16) for h in (hkv * group, hkv, hkv))
+    behind = torch.full((2, hkv * T * d + 256 * d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    kd, vd = (behind[i, : hkv * T * d].view(1, hkv, T, d).copy_(x) for i, x in enumerate((k, v)))
+    scale = d ** -0.5
+    cache = A.arkv_cache_create(cfg)
+    try:
+        out = torch.zeros_like(q, device="cuda")
+        _attention(cache, 0, q.cuda(), kd, vd, T, T, scale, out)
+        assert _check_rows(out, q, k, v, scale, group, np.arange(T), 0) <= TOL
+    finally:
+        A.arkv_cache_destroy(cache)
+
+
 @pytest.mark.parametrize("hq,hkv,d,T", [(8, 2, 64, 200), (4, 4, 128, 97), (2, 1, 128, 160), (8, 1, 64, 131), (8, 2, 128, 33)])
 def test_attention_small_all_rows(hq, hkv, d, T):
     wl = synth.C1.scaled(name="attn", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=2, budget_frac=2.0)
