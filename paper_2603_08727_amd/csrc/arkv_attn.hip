@@ -8,7 +8,7 @@
 // in LDS (keys in three buffers, values in two, one barrier per 32-key tile); the loads of a tile have two steps to
 // arrive (a step takes 0.4-1.1 us, a load that misses the L2 0.5-1 us), and their conversion and way into LDS is
 // dealt out between the PV MFMAs of the second.  With one step to arrive and the staging behind the MFMAs: 32768 tokens x
-// 8 units 8736 -> 8206 us, 512 x 16411 x 8 units 164 -> 152 us, 2003 x 32 units (d = 64, G = 1) 43.1 -> 33.0 us;
+// 8 units 8736 -> 8206 us, 512 x 16411 x 8 units 164 -> 152 us (147 since, see kPrio), 2003 x 32 units (d = 64, G = 1) 43.1 -> 33.0 us;
 // the earlier loads alone gave 1 / 4 / 15 %.  Keys are on the M side of the
 // logits MFMA (v_mfma_f32_32x32x16_bf16, S^T = K Q^T), which leaves ONE query row per lane: the online softmax
 // is per-lane arithmetic (the two lane halves of a row talk only when the row's reference maximum moves, which
@@ -166,6 +166,10 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   constexpr int KW = 32 * D / NT < 8 ? 32 * D / NT : 8, KPR = D / KW, KPT = 32 * KPR / NT;
   constexpr int VW = 16 * D / NT;
   static_assert(KW * KPR == D && KPT * NT == 32 * KPR && VW >= 2 && VW <= 8, "equal shares");
+  // Of the two waves on a SIMD the one in phase A issues first, then the one in phase B: they share the issue port, and the
+  // phase with vector work beside its MFMAs is the longer one.  512 queries x 16411 keys x 8 units 160-164 -> 147-156 us, 8192
+  // tokens x 8 units 533 -> 527, the same at G = 8; nothing at G = 1 (164.4, 165.3) or d = 64 (321, 323).
+  constexpr bool kPrio = D == 128 && G >= 4;
   static_assert(NPV >= KH && NPV >= KPT + VW / 2, "operand prefetch pattern; one staging item per PV MFMA at most");
   using KItem = Words<KW / 2>;
   using VItem = Words<VW / 2>;
@@ -280,6 +284,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
     fetch_k(j0 + 128, ks[vb]);
     fetch_v(j0 + 64, vs[vb]);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(2);
     uint32_t ph[8];
     float lt0 = 0.f, lt1 = 0.f, le0 = 0.f, le1 = 0.f;
 #pragma unroll
@@ -324,6 +329,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
     }
     l_run += lt;
     if constexpr (EXACT) le_run += le0 + le1;
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(1);
     // PV: probabilities eight per k-step: jj = 0 -> elements 0..7, jj = 1 -> 8..15
 #pragma unroll
     for (int r = 0; r < NPV; ++r) {
@@ -337,6 +343,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
       if (r + 1 < NPV) asm volatile("" : "+v"(ph[4 * ((r + 1) / CBN)]) : : "memory");
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (kPrio) __builtin_amdgcn_s_setprio(0);
     mask(Cn, j0 + 32);
     const int k0 = kA; kA = kB; kB = kW; kW = k0;
     __syncthreads();
