@@ -257,6 +257,13 @@ int arkv_debug_set_launch_shape(arkv_cache* cache, int32_t wg_target, int32_t pa
 int arkv_debug_split_range(int32_t n_original, int32_t n_quantized, int32_t packed_weight, int32_t n_splits,
                            int32_t split, int32_t* range);
 
+/* Parity hook, HOST arrays, synchronous: the selection that tailors and commits make, on its own.  scores [n]: fp32 bits of
+ * the rows' scores, not above 0xFFDFFFFF, or 0xFFFFFFFF for a row that is not ranked; a row's key is score << 32 |
+ * (0xFFFFFFFF - row).  thr[x]: the ranked rows whose key is at least that are the k_x with the largest keys (all, where fewer
+ * are ranked); 2^64 - 1 where k_x <= 0 or no row is ranked.  in_memory: 0 = scores kept in LDS (n <= 32768), 1 = read back from
+ * memory.  ARKV_EINVAL: null pointers, n outside [1, 2^22], a score in between, in_memory not 0 or 1. */
+int arkv_debug_select(const uint32_t* scores, int32_t n, int32_t k0, int32_t k1, int32_t in_memory, uint64_t* thr);
+
 /* Parity hook, HOST, pure: how arkv_prefill_attention cuts a call of T_q queries against T keys for units = B H_kv and
  * group = H_q / H_kv.  out[0] = key tiles (of 32 keys) per piece, 0: the call is not split; out[1] = the most pieces of a
  * workgroup; out[2], out[3] = pieces of the first and of the last block of query positions.  ARKV_EINVAL: null pointer,

@@ -23,7 +23,7 @@ EXPORTED = [
     "arkv_decode_step", "arkv_decode_step_static", "arkv_decode_step_layers", "arkv_cache_counters", "arkv_cache_export",
     "arkv_debug_last_tailor_scores", "arkv_debug_last_out_f32", "arkv_debug_prefill_attention_f32", "arkv_cache_progress",
     "arkv_debug_time_attend", "arkv_debug_attend_time", "arkv_debug_set_launch_shape", "arkv_debug_split_range", "arkv_debug_phase_trace",
-    "arkv_debug_attention_split", "arkv_debug_attention_block",
+    "arkv_debug_attention_split", "arkv_debug_attention_block", "arkv_debug_select",
     "arkv_strerror",
     "arkv_last_hip_error",
 ]
@@ -373,6 +373,17 @@ def arkv_debug_split_range(n_original, n_quantized, packed_weight, n_splits, spl
     lib.arkv_debug_split_range.restype = C.c_int
     _check(lib.arkv_debug_split_range(n_original, n_quantized, packed_weight, n_splits, split, r), "arkv_debug_split_range")
     return tuple(r)
+
+
+def arkv_debug_select(scores, k0, k1, in_memory=False):
+    """Thresholds of the two ranks (see the header) for an array of uint32 scores."""
+    scores = np.ascontiguousarray(scores, dtype=np.uint32)
+    thr = (C.c_uint64 * 2)()
+    lib = load()
+    lib.arkv_debug_select.argtypes = [C.c_void_p] + [C.c_int32] * 4 + [C.POINTER(C.c_uint64)]
+    lib.arkv_debug_select.restype = C.c_int
+    _check(lib.arkv_debug_select(_np_ptr(scores), len(scores), k0, k1, int(in_memory), thr), "arkv_debug_select")
+    return int(thr[0]), int(thr[1])
 
 
 def arkv_debug_attention_split(head_dim, group, units, T, T_q):

@@ -189,6 +189,10 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
 int commit_score_pitch(int T);
 uint64_t commit_key(const uint32_t* scores, int i);
 size_t commit_scratch_words(int n_units, int T);
+// The selection of tailors and commits on its own (parity hook): thr[2] of n scores in device memory; in_lds only where
+// select_in_lds(n)
+bool select_in_lds(int n);
+hipError_t launch_select_probe(const uint32_t* scores, int n, int k0, int k1, bool in_lds, uint64_t* thr, hipStream_t s);
 // Causal prefill attention of T_q queries (positions [T - T_q, T)) over T keys.
 struct AttnLaunch {
   const uint16_t* q;      // [B][Hq][Tq][D]

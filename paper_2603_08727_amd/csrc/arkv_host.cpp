@@ -877,6 +877,23 @@ int arkv_debug_attend_time(arkv_cache* c, double* total_ms, int64_t* launches) {
   return ARKV_OK;
 }
 
+int arkv_debug_select(const uint32_t* scores, int32_t n, int32_t k0, int32_t k1, int32_t in_memory, uint64_t* thr) {
+  if (!scores || !thr || n < 1 || n > (1 << 22) || in_memory < 0 || in_memory > 1 || (!in_memory && !select_in_lds(n)))
+    return ARKV_EINVAL;
+  for (int32_t i = 0; i < n; ++i)            // make_key's scores
+    if (scores[i] > 0xFFDFFFFFu && scores[i] != 0xFFFFFFFFu) return ARKV_EINVAL;
+  uint32_t* d = nullptr;
+  const size_t words = ((size_t)n + 1) / 2 * 2;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), (words + 4) * sizeof(uint32_t));
+  if (e != hipSuccess) { hip_fail(e, "hipMalloc"); return e == hipErrorOutOfMemory ? ARKV_ENOMEM : ARKV_EHIP; }
+  uint64_t* dthr = reinterpret_cast<uint64_t*>(d + words);
+  e = hipMemcpy(d, scores, (size_t)n * sizeof(uint32_t), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = launch_select_probe(d, n, k0, k1, in_memory == 0, dthr, nullptr);
+  if (e == hipSuccess) e = hipMemcpy(thr, dthr, 2 * sizeof(uint64_t), hipMemcpyDeviceToHost);
+  (void)hipFree(d);
+  return e == hipSuccess ? ARKV_OK : hip_fail(e, "arkv_debug_select");
+}
+
 int arkv_debug_phase_trace(int32_t which, unsigned long long* host_words, int32_t n_rows) {
   if (!host_words || which < 0 || which > 2 || n_rows < 1 || n_rows > 8192) return ARKV_EINVAL;
   bool built = false;

@@ -158,6 +158,7 @@ __device__ __forceinline__ void select_two(int nq, Load&& load, Score&& score_at
       for (int i = 0; i < 16; ++i) { lo = min(lo, sm.lo[i]); hi = max(hi, sm.hi[i]); }
       base = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
       hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)hi);
+      if (base == kNoScore) break;           // no candidate: rows that are not ranked must not count as equal scores
       rest = hi > base ? 32 - __builtin_clz(hi - base) : 0;
     }
     if (rest == 0) {
@@ -1079,6 +1080,32 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
   for (int i = q0 + tid; i < q1; i += 256) { const int j = j0 + sq[i]; P.qpos[qb + i] = j; P.qacc[qb + i] = pre[j]; }
 }
 
+// The selection by itself (parity hook): thresholds of a list of scores whose keys are a commit's.
+template <bool IN_LDS>
+__global__ __launch_bounds__(1024) void k_select_probe(const uint32_t* scores, int n, int k0, int k1, uint64_t* thr) {
+  extern __shared__ __align__(16) uint32_t row_word[];
+  __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
+  const int tid = threadIdx.x, nq = quads(n);
+  ScoreRange range;
+  for (int i = tid; i < kQuad * nq; i += 1024) {
+    const uint32_t sb = i < n ? scores[i] : kNoScore;
+    range.add(sb);
+    if constexpr (IN_LDS) row_word[i] = sb;
+  }
+  __syncthreads();
+  auto score_of = [&](int i) -> uint32_t {
+    if constexpr (IN_LDS) return row_word[i];
+    else return i < n ? scores[i] : kNoScore;
+  };
+  auto load = [&](int q, uint32_t (&s)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] = score_of(kQuad * q + 4 * tid + e);
+  };
+  auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
+  select_two(nq, load, score_of, key_of, range, k0, k1, sel);
+  if (tid < 2) thr[tid] = sel.thr[tid];
+}
+
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
@@ -1212,6 +1239,12 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
   ARKV_SC(128, 4) ARKV_SC(128, 2) ARKV_SC(128, 8) ARKV_SC(64, 4) ARKV_SC(64, 2) ARKV_SC(64, 8)
 #undef ARKV_SC
   return hipErrorInvalidValue;
+}
+
+bool select_in_lds(int n) { return n <= kLdsRows; }
+hipError_t launch_select_probe(const uint32_t* scores, int n, int k0, int k1, bool in_lds, uint64_t* thr, hipStream_t s) {
+  return in_lds ? launch_rows(k_select_probe<true>, 1, n, s, scores, n, k0, k1, thr)
+                : launch_rows(k_select_probe<false>, 1, 0, s, scores, n, k0, k1, thr);
 }
 
 }  // namespace arkv

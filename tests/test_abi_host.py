@@ -246,3 +246,16 @@ def test_phase_trace_names_the_launches_that_update_the_scores():
                           "print([s for s in range(1, 60) if p.updates_scores(s)])"], cwd=ROOT, capture_output=True, text=True, timeout=120)
     assert got.returncode == 0, got.stderr
     assert got.stdout.strip() == str(want)
+
+
+def test_select_hook_rejects_what_it_cannot_rank():
+    """Arguments of the selection hook are checked before anything is allocated."""
+    import ctypes as C
+    good = np.zeros(8, np.uint32)
+    for bad in ((good[:0], 0), (np.zeros(32769, np.uint32), 0), (good, 2), (good, -1),
+                (np.array([0xFFE00000], np.uint32), 0), (np.array([0xFFFFFFFE], np.uint32), 1)):
+        with pytest.raises(A.ArkvError) as e:
+            A.arkv_debug_select(bad[0], 1, 1, bad[1])
+        assert e.value.code == A.EINVAL
+    thr = (C.c_uint64 * 2)()
+    assert A.load().arkv_debug_select(None, 8, 1, 1, 0, thr) == A.EINVAL

@@ -465,3 +465,47 @@ def test_tailor_from_kept_logits(g, d, bits, T, N, rho, byte_budget):
     wl = synth.C1.scaled(name="kept", n_q_heads=2 * g, n_kv_heads=2, head_dim=d, bits=bits, prefill=T, budget_frac=(N + 0.5) / T,
                          window=16, decode_steps=19)
     _run(wl, rho=rho, check_every=6, stats=False, every_step=True, byte_budget=byte_budget)
+
+
+def _scores(kind, n):
+    """fp32 bits of n scores (0xFFFFFFFF: not ranked)."""
+    r = np.random.default_rng(n)
+    s = r.random(n).astype(np.float32)
+    if kind == "infinite and NaN":
+        s[r.random(n) < 0.3] = np.inf
+        s[r.random(n) < 0.1] = np.nan
+    bits = s.view(np.uint32).copy()
+    if kind == "equal":
+        bits[:] = np.float32(0.25).view(np.uint32)
+    if kind == "few values":
+        bits = (np.uint32(0x3E000000) + r.integers(0, 3, n).astype(np.uint32))
+    if kind == "widest range":
+        bits[1 : 3] = (0, 0xFFDFFFFF)[: max(n - 1, 0)]
+    if kind == "none":
+        bits[:] = 0xFFFFFFFF
+    elif kind == "one":
+        bits[np.arange(n) != n // 2] = 0xFFFFFFFF
+    else:
+        bits[r.random(n) < 0.2] = 0xFFFFFFFF
+        bits[0] = 0x3DCCCCCD                         # at least one
+    return bits
+
+
+@pytest.mark.parametrize("in_memory", [False, True])
+@pytest.mark.parametrize("n", [1, 1023, 4096, 4097, 32768])
+@pytest.mark.parametrize("kind", ["spread", "none", "one", "equal", "few values", "widest range", "infinite and NaN"])
+def test_selection_alone(kind, n, in_memory):
+    """The thresholds of two ranks let exactly the best rows through, whatever the scores; where no row is ranked nothing
+    qualifies (rows that are not ranked, and those that fill the last round of 4096, are no candidates)."""
+    bits = _scores(kind, n)
+    ranked = np.nonzero(bits != 0xFFFFFFFF)[0]
+    keys = (bits.astype(np.uint64) << np.uint64(32)) | (np.uint64(0xFFFFFFFF) - np.arange(n, dtype=np.uint64))
+    best = np.sort(keys[ranked])[::-1]
+    for k0, k1 in ((0, 1), (1, n), (n // 3, n // 2), (n // 2, n // 2), (0, 0), (n, n + 5)):
+        thr = A.arkv_debug_select(bits, k0, k1, in_memory)
+        for k, t in zip((k0, k1), thr):
+            if k == 0 or len(ranked) == 0:
+                assert t == 2 ** 64 - 1
+            else:
+                assert np.count_nonzero(keys[ranked] >= np.uint64(t)) == min(k, len(ranked))
+                assert (best[: k] >= np.uint64(t)).all()
