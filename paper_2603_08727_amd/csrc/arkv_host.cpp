@@ -37,6 +37,8 @@ struct LayerState {
   float2* pre = nullptr;        // [U][T] window sums from the prefill scorer
   size_t pre_cap = 0;
   std::vector<int32_t> n_o;     // [B] Original target per sequence
+  int extra = 0;                // rows that a unit can hold beyond `live` once a tailor has run: a byte budget books every
+                                // survivor as Original and keeps more of them than that
   // host mirror of the units' (Original, Quantized) token counts: exact after a commit and while only
   // appends happen; a decode-time tailor makes the split data dependent and invalidates it
   bool cnt_valid = false;
@@ -469,7 +471,11 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
     int rc = grow(&c->ckeys, &c->ckeys_cap, commit_scratch_words(U, T));
     if (rc != ARKV_OK) return rc;
   }
-  for (int s = 0; s < cfg.batch; ++s) ls.n_o[(size_t)s] = no_seq[(size_t)s];
+  ls.extra = 0;
+  for (int s = 0; s < cfg.batch; ++s) {
+    ls.n_o[(size_t)s] = no_seq[(size_t)s];
+    ls.extra = std::max(ls.extra, nb_seq[(size_t)s] - c->b);
+  }
   CommitLaunch a;
   a.k = static_cast<const uint16_t*>(k);
   a.v = static_cast<const uint16_t*>(v);
@@ -512,7 +518,7 @@ int arkv_prefill_commit(arkv_cache* c, int32_t layer, const void* k, const void*
 // At least 64 rows (a tile per wave) per split (8 units x 800 bf16 rows: 7.2 us per call, 8.1 at 128 rows; x 390 rows,
 // a fifth packed: 9.0 and 9.9; x 1556 rows: the same).
 static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int n_units, int live) {
-  int splits;
+  int splits, rows = live;                         // rows: no unit holds more
   if (c->wg_target > 0) {                          // launch-shape hook
     splits = (c->wg_target + n_units / 2) / n_units;
     if (splits > 32) splits = (splits + 1) / 2;
@@ -520,8 +526,9 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
     bool packed = false;
     for (int i = 0; i < n; ++i) {
       const LayerState& li = c->layers[(size_t)(layer_begin + i)];
-      if (li.n_tailors > 0)
-        for (int32_t no : li.n_o) packed = packed || no < c->b;
+      if (li.n_tailors == 0) continue;
+      for (int32_t no : li.n_o) packed = packed || no < c->b;
+      rows = std::max(rows, live + li.extra);
     }
     const int one = 256 / n_units, two = 512 / n_units;
     splits = (n_units < 32 || !packed) && one * n_units >= 232 ? one : two;
@@ -534,8 +541,11 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
   // Few rows: one workgroup per unit writes the output itself and the partials' way through memory, the ticket and the
   // merge fall away, against a longer row loop (us per call, one split / the best of more; d = 128, 8 units: G = 4, 128
   // rows 6.2 / 7.4, 256 rows 7.4 / 7.3, G = 1 256 rows 6.4 / 6.1, G = 8 256 rows 10.6 / 10.6, a third packed 158 rows 6.9 /
-  // 8.8, 263 rows 8.6 / 8.5; d = 64: 128 rows 5.5 / 7.1, 320 rows 7.0 / 7.1, 384 rows 7.3 / 7.0).
-  if (c->wg_target <= 0 && live <= (c->P.D == 64 ? 336 : 240)) splits = 1;
+  // 8.8, 263 rows 8.6 / 8.5; d = 64: 128 rows 5.5 / 7.1, 320 rows 7.0 / 7.1, 384 rows 7.3 / 7.0).  Under a byte budget a unit
+  // holds more rows than are booked, packed ones; there the line lies at 340 of them all (d = 64: 480): one split / live / 64
+  // of them, 8 units, G = 4: fp8, 290-340 rows 8.1 / 8.9, 350-400 8.3 / 8.4; 4-bit, 300-340 8.4 / 8.9, 460-510 10.3 / 9.5, 2-bit,
+  // 1000 14.8 / 11.4; d = 64: 4-bit, 360-420 8.0 / 8.6, 500-600 9.0 / 8.1, 2-bit, 440-480 8.2 / 9.2, 530-590 9.4 / 8.9.
+  if (c->wg_target <= 0 && live <= (c->P.D == 64 ? 336 : 240) && rows <= (c->P.D == 64 ? 480 : 340)) splits = 1;
   return std::max(1, std::min(splits, c->P.max_splits));
 }
 

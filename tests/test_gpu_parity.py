@@ -421,6 +421,43 @@ def test_single_split(g, d, T, budget, rho, bits):
     _run(wl, rho=rho, check_every=6)
 
 
+@pytest.mark.parametrize("g,d,bits,N,rho,one", [
+    (4, 128, 2, 240, 0.0, False),     # 184 to 239 rows booked, about 1000 held
+    (1, 128, 4, 230, 0.1, False),
+    (8, 64, 2, 330, 0.2, False),
+    (4, 128, 8, 190, 0.2, True),      # up to 282 rows held
+    (2, 64, 4, 250, 0.4, True),       # up to 429
+    (4, 128, 4, 230, 1.0, True),      # none packed: 230
+])
+def test_split_of_a_byte_budget(g, d, bits, N, rho, one):
+    """Under a byte budget a unit holds more rows than are booked for it: whether one workgroup takes all of them goes by
+    what it can hold.  A step's output is, bit for bit, that of a cache whose split factor is set to the one expected."""
+    hkv, W, T = 4, 16, 1500
+    wl = synth.C1.scaled(name="bytes", n_q_heads=hkv * g, n_kv_heads=hkv, head_dim=d, prefill=T, budget_frac=(N + 0.5) / T,
+                         window=W, bits=bits, batch=1, n_layers=1, decode_steps=N - int(0.75 * (N - W)) - W - 1)
+    k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+    q, kn, vn = (t.cuda() for t in synth.decode_inputs(wl, 0, wl.decode_steps))
+    out = torch.empty((1, hkv * g, d), dtype=torch.bfloat16, device="cuda")
+    caches = [A.arkv_cache_create(make_cfg(wl, byte_budget=True)) for _ in range(2)]
+    try:
+        for c in caches:
+            A.arkv_prefill_stats(c, 0, qw, k, T, d ** -0.5, torch.zeros((1, 3), device="cuda"))
+            A.arkv_prefill_commit(c, 0, k, v, T, np.full(1, rho, np.float32))
+        for t in range(wl.decode_steps):
+            splits = 1 if one else max(1, A.arkv_cache_progress(caches[1], 0)[1] // 64)
+            A.arkv_debug_set_launch_shape(caches[1], splits * hkv)
+            f32 = []
+            for c in caches:
+                A.arkv_decode_step(c, 0, q[t], kn[t], vn[t], d ** -0.5, out)
+                f32.append(A.arkv_debug_last_out_f32(c, 0, tuple(out.shape)))
+            assert np.array_equal(f32[0].view(np.uint32), f32[1].view(np.uint32)), t
+        assert splits == (1 if one else (N - 2) // 64)
+        assert A.arkv_cache_progress(caches[0], 0)[0] == 1          # the commit's tailor only
+    finally:
+        for c in caches:
+            A.arkv_cache_destroy(c)
+
+
 @pytest.mark.parametrize("T,N,gain,steps", [
     (3100, 1300, 2.0 ** -17, 4),       # scores a few units in the last place apart: most tie, the range takes few bits
     (3100, 1300, 2.0 ** -10, 4),       # one digit and a little more
