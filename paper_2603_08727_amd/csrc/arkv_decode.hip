@@ -868,7 +868,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
   float* const part_ = P.part + (size_t)(gu - L.part_unit0) * P.max_splits * (G * (D + 2));   // the unit's partials
   int* const ticket_ = P.ticket + (size_t)(gu - L.part_unit0) * (kTicketWaves * kTicketPitch);
   asm volatile("" ::"s"(part_), "s"(ticket_));
-  float* const logit_ = KEEP ? P.logit + (size_t)gu * ((size_t)P.capO + P.capQ) * G : nullptr;
+  float* const logit_ = KEEP ? P.logit + (size_t)(gu - P.logit_unit0) * P.logit_stride : nullptr;   // by row: Original, new, packed
   auto keep_logits = [&](bool own, int row, const float (&x)[HPL]) {
     if (!own) return;
     float* dst = logit_ + (size_t)row * G + 4 * blk;
@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, 
           Fmt::dots(pqa, t.k[tl], x[tl]);
 #pragma unroll
         for (int i = 0; i < HPL; ++i) x[tl][i] = own[tl] ? x[tl][i] * scale2 : kNegBig;
-        if constexpr (KEEP) keep_logits(own[tl], capO + row, x[tl]);
+        if constexpr (KEEP) keep_logits(own[tl], cO + 1 + row, x[tl]);
         if constexpr (FOLD) {
           const float2 ac = fold_pending<D, G>(sm_pend, npend, 0, t.ac[tl], lane, [&](int r, const uint4 (&qop)[KK], float (&xp)[HPL]) {
             if constexpr (BITS == 8) {

@@ -80,15 +80,17 @@ struct Pools {
   int*      ticket;     // [LU][kTicketWaves][kTicketPitch] splits of the unit whose wave w is done in the current launch
                         // (0 between launches), one per cache line
   float*    outf;       // [LU][G][D] fp32 output of the latest step (parity hook)
-  float*    logit;      // [LU][capO+capQ][G] a step's logits (base-2 units) per row, O pool slots first, where a tailor follows it
-                        // at once (tailor_policy 1); null with the other policy
+  // A step's logits (base-2 units), [row][G] per unit with the O pool's rows first, where a tailor follows the step at once
+  // (tailor_policy 1).  Set per launch (logit_place): units logit_unit0 and up, logit_stride floats apart.
+  float*    logit;
+  int       logit_stride, logit_unit0;
   int32_t*  n_o;        // [LU] Original target of the unit's layer/sequence
   int32_t*  nb;         // [LU] survivors outside the window (n_o + n_q) of the unit's layer/sequence
   // tailor scratch
   uint64_t* keys;       // [LU][capO+capQ] selection keys of the latest tailor's rows (0 = not eligible), O pool slots first; the
                         // plan header says how many slots of either pool held a row
   uint64_t* thr;        // [LU][2] a commit's keys of rank n_o and rank b
-  int32_t*  plan;       // [LU][plan_stride] see k_tailor_choose
+  int32_t*  plan;       // [LU][plan_stride] see k_tailor_choose; until that kernel has read them, kept logits may lie here
   int       plan_stride;
 };
 

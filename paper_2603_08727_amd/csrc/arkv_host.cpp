@@ -71,6 +71,7 @@ struct arkv_cache {
   uint64_t* ckeys = nullptr; size_t ckeys_cap = 0;
   AttnBlock attn_block[kAttnBlocks] = {};   // pieces of a prefill attention that is split over the keys (attn_scratch)
   int ckeys_layer = -1, ckeys_T = 0;
+  float* logit = nullptr; int logit_stride = 0;   // kept logits of one layer's units, where a plan is too small for them
   hipStream_t last_stream = nullptr;
   // measurement hook: events around the attention kernel
   int prefill_chunk = 1024; // keys per workgroup of the prefill scorer (halved while the grid would be small)
@@ -249,7 +250,6 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   const size_t LU = (size_t)c->L * c->U, D = (size_t)P.D, G = (size_t)P.G;
   const size_t CB = D * P.bits / 8, NG = (size_t)metas_per_row(P.D, P.bits);
   P.fin_stride = LU * G;
-  P.plan_stride = kPlanHdr + 3 * P.capO + 2 * P.capQ;
   P.max_splits = std::max(1, std::min(kMaxSplits, (1024 + c->U - 1) / c->U));   // room for launch-shape sweeps
 #define A(field, count) if ((rc = dev_alloc(c, &P.field, (count))) != ARKV_OK) { arkv_cache_destroy(c); return rc; }
   A(ok, LU * P.capO * D) A(ov, LU * P.capO * D)
@@ -259,8 +259,7 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   A(qkm, LU * P.capQ * NG) A(qvm, LU * P.capQv * MH)
   A(qpos, LU * P.capQ) A(qacc, LU * P.capQ)
   A(cnt, LU) A(fin, kRing * LU * G) A(qprev, kRing * LU * G * D) A(qscale, kRing * LU) A(part, LU * (size_t)P.max_splits * G * (D + 2)) A(outf, LU * G * D) A(n_o, LU) A(nb, LU) A(ticket, LU * kTicketWaves * kTicketPitch)
-  if (cfg->tailor_policy == 1) A(logit, LU * (size_t)(P.capO + P.capQ) * G)
-  A(keys, LU * (size_t)(P.capO + P.capQ)) A(thr, LU * 2) A(plan, LU * (size_t)P.plan_stride)
+  A(keys, LU * (size_t)(P.capO + P.capQ)) A(thr, LU * 2)
 #undef A
   hipError_t e = hipSuccess;
   for (auto& ls : c->layers) {
@@ -280,6 +279,21 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   if (e == hipSuccess) e = static_scratch_setup();      // device address of the static split-K scratch
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) { arkv_cache_destroy(c); return hip_fail(e, "cache set-up"); }
+  // Last, because with tailor_policy 1 they may be smaller: the plans, which also hold a step's kept logits (logit_place), G words
+  // for each of the N rows of a unit under a token budget.  The lists alone take 3 N + 2 capQ words, which is enough up to G = 4.
+  // A byte budget's units can hold several times N rows: what does not fit goes to a buffer for launches of one layer.  A cache
+  // that does not get the memory for more than the lists keeps no logits.
+  const int lists = (kPlanHdr + 3 * P.capO + 2 * P.capQ + 3) / 4 * 4;       // (units begin at 16-byte boundaries)
+  P.plan_stride = cfg->tailor_policy == 1 && cfg->budget_mode == 0 ? std::max(lists, (cfg->capacity_tokens * P.G + 3) / 4 * 4) : lists;
+  rc = dev_alloc(c, &P.plan, LU * (size_t)P.plan_stride);
+  if (rc != ARKV_OK && P.plan_stride > lists) {
+    P.plan_stride = lists;
+    rc = dev_alloc(c, &P.plan, LU * (size_t)P.plan_stride);
+  }
+  if (rc != ARKV_OK) { arkv_cache_destroy(c); return rc; }
+  const size_t rows = (size_t)std::max(cfg->capacity_tokens, cfg->window + P.capQ + 1);   // at most, at a tailor
+  if (cfg->tailor_policy == 1 && rows * G > (size_t)P.plan_stride && dev_alloc(c, &c->logit, (size_t)c->U * rows * G) == ARKV_OK)
+    c->logit_stride = (int)(rows * G);
   *out = c;
   return ARKV_OK;
 }
@@ -549,6 +563,20 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
   return std::max(1, std::min(splits, c->P.max_splits));
 }
 
+// Where the logits of a launch that ends with a tailor lie between its attention and the tailor's choosing kernel: in the units'
+// plans, which that kernel writes behind its last read of a logit, if a plan is large enough for a unit's rows.  false: nowhere.
+static bool logit_place(const arkv_cache* c, int32_t layer_begin, int32_t n, Pools* P) {
+  if (c->cfg.tailor_policy != 1) return false;
+  int extra = 0;
+  for (int i = 0; i < n; ++i) extra = std::max(extra, c->layers[(size_t)(layer_begin + i)].extra);
+  if (((size_t)c->cfg.capacity_tokens + (size_t)extra) * (size_t)P->G <= (size_t)P->plan_stride) {
+    P->logit = reinterpret_cast<float*>(P->plan); P->logit_stride = P->plan_stride; P->logit_unit0 = 0;
+    return true;
+  }
+  P->logit = c->logit; P->logit_stride = c->logit_stride; P->logit_unit0 = layer_begin * c->U;
+  return n == 1 && c->logit;
+}
+
 // One decode step of n layers in the same state.  static_scratch: the split-K partials and tickets of this launch
 // live in the library's static device array instead of the cache's own buffers.
 static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void* q, const void* k_new,
@@ -619,7 +647,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   a.fold = l0.n_pending == kRing - 1 ? 1 : 0;   // the ring is full: add the waiting steps now
   const bool tailor = l0.live + 1 >= N;
   // a tailor that ranks on this step alone takes its logits from this launch
-  a.keep = tailor && l0.n_pending == 0 && pools.logit ? 1 : 0;
+  a.keep = tailor && l0.n_pending == 0 && logit_place(c, layer_begin, n, &pools) ? 1 : 0;
   for (int i = 0; i < n; ++i) a.scale2[i] = softmax_scale[i] * 1.4426950408889634f;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->timing && !static_scratch) {        // the event pool grows by allocation
@@ -648,7 +676,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
     t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
     t.kept = a.keep;
-    const hipError_t te = launch_tailor(c->P, t, st);
+    const hipError_t te = launch_tailor(pools, t, st);
     if (te != hipSuccess) {
       // the attention of this step is on the stream, the tailor is not (or only partly): the device-side state of
       // these layers is no longer what the host would book, so they refuse further steps until they are reset

@@ -600,7 +600,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   const int32_t* qpos = P.qpos + (size_t)gu * P.capQ;
   float2* oacc = P.oacc + (size_t)gu * P.capO;
   float2* qacc = P.qacc + (size_t)gu * P.capQ;
-  const float* logit = KEPT ? P.logit + (size_t)gu * ((size_t)P.capO + P.capQ) * G : nullptr;
+  const float* logit = KEPT ? P.logit + (size_t)(gu - P.logit_unit0) * P.logit_stride : nullptr;   // (may be this unit's plan)
   float2 fin[G];
   if constexpr (KEPT) {
     const float2* f = P.fin + (size_t)((L.slot + kRing - 1) % kRing) * P.fin_stride + (size_t)gu * G;
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
       r.acc[j] = i < cO ? oacc[i] : qacc[i - cO];
       if constexpr (KEPT) {
         typedef float Vec __attribute__((ext_vector_type(G < 4 ? G : 4)));
-        const Vec* p = reinterpret_cast<const Vec*>(logit + (size_t)(i < cO ? i : i + slot_q) * G);
+        const Vec* p = reinterpret_cast<const Vec*>(logit + (size_t)i * G);
         if constexpr (G == 1) r.x[j][0] = *reinterpret_cast<const float*>(p);
         else
 #pragma unroll

@@ -56,6 +56,70 @@ def test_layers_entry_point_equals_per_layer_calls():
         A.arkv_cache_destroy(c1); A.arkv_cache_destroy(c2)
 
 
+@pytest.mark.parametrize("g,bits,byte_budget", [
+    (4, 4, False),        # the logits fit the tailor's plan
+    (8, 2, False),        # a plan made larger for them
+    (2, 8, True),
+    (8, 2, True),         # a buffer for one layer's logits; launches of several keep none
+])
+def test_tailor_at_every_step_through_all_entry_points(g, bits, byte_budget):
+    """With a tailor at every step, three layers in one call and the call with static scratch give the same bits as one call per
+    layer: outputs of every step and the caches behind the last, through the 17th tailor, whose moves are made elsewhere."""
+    wl = synth.C1.scaled(name="each", n_layers=3, n_q_heads=2 * g, n_kv_heads=2, head_dim=64, bits=bits, prefill=700,
+                         budget_frac=300.5 / 700, window=16, decode_steps=21)
+    L = wl.n_layers
+    cfg = make_cfg(wl, every_step=True, byte_budget=byte_budget)
+    caches = [A.arkv_cache_create(cfg) for _ in range(3)]
+    try:
+        sc = np.array([synth.softmax_scale(wl, l) for l in range(L)], np.float32)
+        for c in caches:
+            for l in range(L):
+                k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, l))
+                A.arkv_prefill_stats(c, l, qw, k, wl.prefill, float(sc[l]), torch.zeros((1, 3), device="cuda"))
+                A.arkv_prefill_commit(c, l, k, v, wl.prefill, np.full(1, 0.4, np.float32))
+        dins = [tuple(t.cuda() for t in synth.decode_inputs(wl, l)) for l in range(L)]
+        q, kn, vn = (torch.stack([d[i] for d in dins], 1).contiguous() for i in range(3))
+        outs = [torch.empty((L, 1, wl.n_q_heads, wl.head_dim), dtype=torch.bfloat16, device="cuda") for _ in caches]
+        for t in range(wl.decode_steps):
+            for l in range(L):
+                A.arkv_decode_step(caches[0], l, q[t, l], kn[t, l], vn[t, l], float(sc[l]), outs[0][l])
+                A.arkv_decode_step_static(caches[1], l, q[t, l], kn[t, l], vn[t, l], float(sc[l]), outs[1][l])
+            A.arkv_decode_step_layers(caches[2], 0, L, q[t], kn[t], vn[t], sc, outs[2])
+            for o in outs[1:]:
+                assert torch.equal(outs[0].view(torch.int16), o.view(torch.int16)), t
+        assert A.arkv_cache_progress(caches[0], 0)[0] == wl.decode_steps + 1
+        ref = _export_all(caches[0], cfg, L)
+        for c in caches[1:]:
+            for e1, e2 in zip(ref, _export_all(c, cfg, L)):
+                for k in e1:
+                    assert np.array_equal(e1[k], e2[k]), k
+    finally:
+        for c in caches:
+            A.arkv_cache_destroy(c)
+
+
+@pytest.mark.parametrize("g,bits,byte_budget", [(1, 4, False), (4, 4, False), (8, 4, False), (2, 8, True), (8, 2, True)])
+def test_memory_of_the_policy_without_slack(g, bits, byte_budget):
+    """What tailor_policy 1 allocates for logits beyond a cache of the other policy that keeps as many rows: nothing where the
+    tailor's plan can hold them (4 bytes per head and row), else what a plan lacks for N rows, with a byte budget one layer's
+    logits."""
+    L, hkv, N, W = 8, 8, 4096, 32
+    used = []
+    for policy in (0, 1):
+        cfg = A.arkv_config_default(n_layers=L, batch=1, n_q_heads=g * hkv, n_kv_heads=hkv, head_dim=64, capacity_tokens=N,
+                                    window=W, alpha=1.0, quant_bits=bits, tailor_policy=policy, budget_mode=int(byte_budget))
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        c = A.arkv_cache_create(cfg)
+        used.append(before - torch.cuda.mem_get_info()[0])
+        A.arkv_cache_destroy(c)
+    cap_q = A.arkv_budget_counts(cfg, 0.0)[2]
+    rows, plan = max(N, W + cap_q + 1), 16 + 3 * (N + 17) + 2 * cap_q
+    granule = 2 << 20                               # device memory is handed out in blocks of 2 MiB
+    extra = 0 if g * rows <= plan else hkv * rows * g * 4 if byte_budget else L * hkv * (g * N - plan + 4) * 4
+    assert used[0] > 0 and used[1] - used[0] <= extra + granule, (used, extra)
+
+
 def test_bitwise_repeatability():
     """Two runs of the same trajectory give identical bytes (no float atomics anywhere)."""
     wl = synth.C1.scaled(name="repeat", decode_steps=40)
