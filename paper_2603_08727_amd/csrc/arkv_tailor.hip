@@ -122,10 +122,6 @@ __device__ __forceinline__ Shared shared_bin(int bin, bool add, unsigned long lo
   return {first, b, (int)__popcll(__ballot(add && bin == b))};
 }
 
-// Barrier for what the workgroup keeps in LDS only: it does not wait for the wave's stores to memory, as __syncthreads does
-// (about a microsecond behind a phase that wrote there).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // load(q, s) must give the scores s[0 .. 3] of rows 4096 q + 4 * thread .. + 3, q < nq (kNoScore: not a candidate);
 // score(row), key(row) = a candidate's, for any thread; range: of the scores this thread has seen, all threads' together of
 // all candidates.  sm.thr[x]: the candidates whose key is at least that are the best k_x.  It is the key of rank k_x, its low
@@ -152,7 +148,7 @@ __device__ __forceinline__ void select_two(int nq, Load&& load, Score&& score_at
     *reinterpret_cast<int2*>(&sm.hist[top - 1]) = make_int2(0, 0);
     *reinterpret_cast<int2*>(&sm.hist[kBins + top - 1]) = make_int2(0, 0);
     if (pass == 0) {
-      lds_barrier();
+      __syncthreads();                       // (also for keys that lie in memory: load reads other threads')
       uint32_t lo = kNoScore, hi = 0;
 #pragma unroll
       for (int i = 0; i < 16; ++i) { lo = min(lo, sm.lo[i]); hi = max(hi, sm.hi[i]); }
@@ -610,7 +606,8 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   const int slot_q = P.capO - cO;                           // row i >= cO: key slot i + slot_q
   const int nq = quads(n), rounds = (n + 1023) / 1024;
   ScoreRange range;
-  // (a barrier of the selection stands between these stores and another thread's read of a key)
+  // (a __syncthreads of the selection stands between these stores and another thread's read of a key: its fence orders the
+  // workgroup's accesses to memory, which on this target needs no wait for the stores, they pass the CU's L1 in order)
   constexpr int BATCH = 4;                                  // rows requested together, one batch ahead of their use
   struct Rows { int pos[BATCH]; float2 acc[BATCH]; float x[KEPT ? BATCH : 1][G]; };
   auto fetch = [&](int q, Rows& r) {
