@@ -16,8 +16,11 @@ TOL = 2e-3                  # attention outputs, scores, statistics (fp32 accumu
 
 def rel_err(x, ref):
     """max |x - ref| / max |ref| over one tensor (element-wise relative error is meaningless for
-    values that cancel to ~0)."""
+    values that cancel to ~0).  Infinite where either side holds a value that is not finite: a NaN would be lost in the
+    folds over rows (max(worst, nan) keeps worst)."""
     x = np.asarray(x, dtype=np.float64); ref = np.asarray(ref, dtype=np.float64)
+    if not (np.isfinite(x).all() and np.isfinite(ref).all()):
+        return float("inf")
     den = np.abs(ref).max()
     return float(np.abs(x - ref).max() / den) if den > 0 else float(np.abs(x).max())
 

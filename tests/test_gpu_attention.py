@@ -69,6 +69,7 @@ def test_attention_ends_of_tiles(d, group, T):
     try:
         out = torch.zeros_like(q, device="cuda")
         _attention(cache, 0, q.cuda(), kd, vd, T, T, scale, out)
+        assert torch.isfinite(out.f32).all()
         assert _check_rows(out, q, k, v, scale, group, np.arange(T), 0) <= TOL
     finally:
         A.arkv_cache_destroy(cache)

@@ -1,11 +1,14 @@
 """The comparison rules of the GPU parity tests, checked on the CPU against the oracle alone: the free-running
 protocol's score band (a token may end in a different state on the two sides only if its score is within 2e-3 of
 the score at one of eq. 10's two cuts)."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
+import torch
 
 from oracle import arkv_oracle as O
-from helpers import TOL, score_band_check
+from helpers import TOL, rel_err, score_band_check
 
 
 def _case(seed, n=400, n_o=90, b=250):
@@ -65,3 +68,26 @@ def test_gross_score_errors_fail():
     got = O.tailor_assign(S * (1 + 0.05 * r.standard_normal(len(S))), pos, state, n_o, b)
     with pytest.raises(AssertionError):
         score_band_check(S, pos, ref, got, n_o, b)
+
+
+def test_a_value_that_is_not_finite_is_an_infinite_error():
+    """The folds over rows take max(worst, error), which drops a NaN: an error is infinite instead."""
+    ref = np.array([1.0, -2.0, 0.5])
+    assert rel_err(ref, ref) == 0.0 and rel_err(np.zeros(2), np.zeros(2)) == 0.0
+    for bad in (np.nan, np.inf, -np.inf):
+        x = ref.copy()
+        x[1] = bad
+        assert max(0.0, rel_err(x, ref)) == np.inf and max(0.0, rel_err(ref, x)) == np.inf
+
+
+def test_one_nan_among_the_attention_rows_fails():
+    """The check of the prompt attention's rows accepts the oracle's own output and not the same with one NaN."""
+    from test_gpu_attention import _check_rows
+    g = torch.Generator().manual_seed(3)
+    q, k, v = (torch.randn((1, h, 40, 64), generator=g).to(torch.bfloat16) for h in (2, 1, 1))
+    at = np.arange(40)
+    ref = O.causal_attention_rows(q[0].float().numpy(), at, k[0].float().numpy(), v[0].float().numpy(), 0.125, 2)
+    out = SimpleNamespace(f32=torch.from_numpy(np.asarray(ref, dtype=np.float32))[None].clone())
+    assert _check_rows(out, q, k, v, 0.125, 2, at, 0) <= 1e-6
+    out.f32[0, 1, 17, 3] = float("nan")
+    assert not _check_rows(out, q, k, v, 0.125, 2, at, 0) <= TOL
