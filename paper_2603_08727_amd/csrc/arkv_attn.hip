@@ -66,7 +66,7 @@ struct AttnLds {
 };
 
 // sched_group_barrier classes
-constexpr int kSgValu = 0x2, kSgMfma = 0x8, kSgDsRead = 0x100, kSgDsWrite = 0x200;
+constexpr int kSgValu = 0x2, kSgMfma = 0x8, kSgDsRead = 0x100;
 typedef _Float16 f16x2a __attribute__((ext_vector_type(2)));
 constexpr float kSumLimit = 16384.0f;   // a lane's 16 probabilities may sum to this before the reference maximum moves
 
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 
 // Adds up the pieces of the workgroups that have more than one.  grid (query blocks, units, D / 32), the same waves and
 // lanes as above; a wave takes one block of 32 channels.  Bound by the partials' bytes (34 MB written and read at 512
-// queries x 16411 keys x 32 heads: 9 us of 152).
+// queries x 16411 keys x 32 heads: 9 us of 147).
 template <int D, int G>
 __global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
   constexpr int QB = kQBlocks<G>;
@@ -471,12 +471,18 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
 }
 
 // How far to split over the keys: tiles per piece (0: no split) and the largest number of pieces of a workgroup.
-// Measured at d = 128 (d = 64: about 0.65 of it): a tile step takes 0.75 us in a workgroup that has its CU to itself and
-// 1.06 us where two share it, so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU,
-// whichever is more; the merge costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where
-// few workgroups walk many tiles: 512 queries x 16411 keys x 8 kv-heads 397 -> 152 us (4 pieces), 32 x 3000 x 16 units
-// (d = 64, G = 1) 66 -> 16 us.  It does not pay for a whole short prompt, whose imbalance is only the causal triangle
-// (1000 tokens x 8 kv-heads: 30 us unsplit, 37 us in 2 pieces), hence the margin and the floor of 32 tiles.
+// The model: a tile step takes 0.75 us in a workgroup that has its CU to itself and 1.06 us where two share it (d = 64: 0.65 of
+// that), so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU, whichever is more; the merge
+// costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where few workgroups walk many tiles: 512
+// queries x 16411 keys x 8 kv-heads 290 -> 146 us (4 pieces), 32 x 3000 x 16 units (d = 64, G = 1) 44 -> 15 us.  It does not pay
+// for a whole short prompt, whose imbalance is only the causal triangle (1100 tokens x 8 kv-heads: 29.6 us unsplit, 32.9 us in
+// 2 pieces), hence the margin and the floor of 32 tiles.
+// The constants were fitted to a loop whose loads had one step to arrive.  The present one takes, alone on its CU, 0.57 us (d =
+// 128; G = 8 0.80) and 0.43-0.45 us (d = 64; G = 8 0.58), shared 1.04 and 0.66, and the merge 9-14 us.  Every number of pieces
+// was timed on it for 830 calls (2-32 units, 1100-16411 keys, 32 queries to the whole prompt, every d, G = 1, 4, 8): the
+// chosen one is 2 % off the best at the median and more than 10 % off in 177.  These are unsplit calls on 1100 keys at d = 64 or
+// G != 4, which four pieces make 1.1-1.6 times faster (124 calls, 12 % at the median), unsplit ones at G = 8, d = 64 on 5000
+// (1.5), and 32 queries x 32 units cut in 16 where 8 are best (8003 keys, d = 128: 51 and 37 us).
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {
   *piece_tiles = 0; *max_pieces = 1;
   const int QB = G < 4 ? 4 / G : 1, nqb = (Tq + 32 * QB - 1) / (32 * QB), q0 = T - Tq;

@@ -758,7 +758,7 @@ struct DecodeHot {
 
 // KEEP launches (a tailor follows at once, which ranks on scores that include this step) store the rows' logits for it: 4 G
 // bytes per row, where a pass of its own over the keys (k_flush_scores) read 2 D (32 units x 8192 rows, G = 4: that launch's
-// 12.4 us against 0.7 here and 1 in k_tailor_choose).
+// 12.5 us against 1.6 here and about 1 in k_tailor_choose).
 template <int D, int G, int BITS, bool FOLD, bool KEEP>
 __global__ __launch_bounds__(256, 2) void k_decode_attend(DecodeHot H, Pools P, DecodeLaunch L) {
   constexpr int KK = D / 32;           // MFMA k-steps = quantisation groups per row

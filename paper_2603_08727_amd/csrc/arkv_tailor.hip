@@ -31,8 +31,9 @@ __device__ __forceinline__ float hh_score(float s1, float s2, int n, float gamma
   return mu + gamma * var;
 }
 
-// A score's first digit in the radix select (11 bits) is never all ones: those are the first digit of kNoScore, which must
-// not match a ranked row's.  Scores are >= 0 or NaN; negative NaNs with that digit count as the largest one below it.
+// The radix select looks at digits of (score - smallest score), and a row that is not ranked must not match one that is: kNoScore
+// lies at least 2^21 above every score, so after the first digit (which leaves at most 21 bits) its leading bits differ from
+// every candidate's.  Scores are >= 0 or NaN; negative NaNs above that line count as the largest value below it.
 __device__ __forceinline__ uint64_t make_key(float S, int pos) {
   return ((uint64_t)min(__float_as_uint(S), 0xFFDFFFFFu) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos);
 }
@@ -540,9 +541,11 @@ __device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, in
 
 // ------------------------------------------------------------------------------------------
 // in-place tailor: keys (eq. 9's score per row), the two thresholds, and the lists that compact both pools.
-// One workgroup per unit, one launch, bound by one CU's instruction issue and round trips (32 units x 8192 rows, one moved per
-// step: 14 us inside the kernel, of which keys 3, selection 6, fates 3, lists 2; a step with a tailor 64.3 -> 56.5 us against
-// digits of the plain score, scalar LDS reads, a fate word per row and thresholds fetched from memory).  Fates are kept as a
+// One workgroup per unit, one launch, bound by one CU's instruction issue and round trips.  32 units x 8192 rows with kept
+// logits, one row moved per step: 26.4 us, of which 22.5 between a workgroup's first instruction and its last (scores 5.7,
+// selection 8.6, fates 1.5, lists 3.4, moves 3.3) and the rest is the launch's start and end.  A step with a tailor 64.3 ->
+// 56.5 us against digits of the plain score, scalar LDS reads, a fate word per row and thresholds fetched from memory, kept
+// logits and moves not counted.  Fates are kept as a
 // bit per row (two words per 64 rows), so that the lists' counts are one thread's work per 64 rows and words with nothing to
 // list are skipped.
 //   plan: header | ohole[capO] | omov[capO] | dem[capO] | qfree[capQ] | qmov[capQ]
@@ -873,9 +876,10 @@ __device__ __forceinline__ uint32_t commit_parts(uint32_t survivors, int share_r
   return (survivors + (uint32_t)share_rows - 1) / (uint32_t)share_rows;
 }
 
-// One workgroup per unit (15 us inside the kernel for 32 units x 32768 positions; 31 us with digits of the plain score, one
-// score per LDS read and 64-bit keys in memory; whole commits of 32 x 32768 88 -> 75 us, 8 x 131072 159 -> 96 us, 8 x 1000 20.2
-// -> 19.6 us).  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
+// One workgroup per unit: 23 us for 32 units x 32768 positions, of which 15.7 between a workgroup's first instruction and its
+// last (scores into LDS 1.9, selection 9.4, blocks 4.4) and the rest is the launch's start and end.  35 us with digits of the
+// plain score, one score per LDS read and 64-bit keys in memory (whole commits of 32 x 32768 88 -> 74 us, 8 x 131072 159 -> 96,
+// 8 x 1000 20.2 -> 19.4).  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
 // last one the totals) the rows in front of it that become Original and Quantized and the parts in front of it into which
 // k_commit_scatter cuts blocks: as many as hold share_rows survivors each, wherever in the prompt the survivors sit.
 template <bool IN_LDS>
@@ -986,7 +990,8 @@ __global__ __launch_bounds__(256) void k_commit_copy(Pools P, CommitLaunch L) {
 // in flight per wave, and quantises its share of the others straight from the caller's rows.  Bound by the gathered rows'
 // bytes where the grid fills the chip (32 units x 6152 of 32768 rows, 200 MB: 43 us), by a workgroup's chain of rounds where it
 // does not, hence the parts: with one workgroup per block a whole commit of 16 units x 2200 positions (1100 kept, all packed)
-// takes 62 us instead of 26, and one of 32 x 32768 whose survivors sit in few blocks (equal scores) 335 instead of 132.
+// took 62 us instead of 26 (24 with the present selection), and one of 32 x 32768 whose survivors sit in few blocks (equal
+// scores) 335 instead of 132 (89).
 template <int D, int BITS>
 __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L, CommitScratch C, int share_rows) {
   constexpr int LPR = D / 8, LPT = 2 * LPR;         // lanes per K (V) row, per token
@@ -994,7 +999,8 @@ __global__ __launch_bounds__(256) void k_commit_scatter(Pools P, CommitLaunch L,
   __shared__ uint16_t so[1024], sq[1024];
   __shared__ uint32_t cnt[16];
   // the units run fastest: workgroups behind a unit's last part end at once, and with the slots fastest they left the CUs
-  // with unequal shares of the others (32 units x 32768 positions, total of the commit: 105 to 128 us by their number)
+  // with unequal shares of the others (32 units x 32768 positions, total of the commit: 105 to 128 us by their number, where
+  // this order took 89)
   const int lu = (int)(blockIdx.x % (unsigned)L.n_units), slot = (int)(blockIdx.x / (unsigned)L.n_units);
   const int gu = L.unit_begin + lu, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, T = L.T;
   // the block whose parts this workgroup falls among: the last one with no more parts in front of it (lane = block)
@@ -1222,7 +1228,7 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
   for (int i = 0; i < batch; ++i) kept = std::max(kept, std::min(nb_seq[i], a.T - a.window) + a.window);
   // about four workgroups per CU; below 8 rows a workgroup's lists cost more than its rows (8 units x 1000 positions, 500
   // kept: 21 us for the whole commit, 52 in one part per block), above 96 nothing is gained (32 units x 32768 positions,
-  // 6152 kept: 89 to 95 us at 64 to 1024 rows)
+  // 6152 kept: 89 to 95 us at 64 to 1024 rows; all with an earlier selection that took 2 and 12 us more)
   const int share_rows = clampi((int)((long long)a.n_units * kept / 1024 + 7) / 8 * 8, 8, 96);
   const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, c, share_rows)
                                        : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, c, share_rows);
