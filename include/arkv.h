@@ -65,7 +65,10 @@ typedef struct {
 int arkv_config_default(arkv_config* cfg);
 
 /* Allocates the pools of all layers on the current device (per unit: N bf16 K and V rows, b packed
- * rows, per-slot position / score accumulators, the latest queries per unit) and returns the cache in *out.
+ * rows, per-slot position / score accumulators, the latest queries per unit) and returns the cache in *out.  Under
+ * tailor_policy 1 also room for a step's logits, if there is memory for it: nothing up to G = 4 and 12 N bytes per unit at G = 8
+ * under a token budget; under a byte budget at most 4 G (W + b + 1) bytes per unit of ONE layer (b of arkv_budget_counts at
+ * rho = 0).  Without that room a step reads its keys twice.
  * Synchronous.  ARKV_EINVAL: null pointers, non-positive shapes, W >= N - 1, alpha outside (0,1],
  * gamma < 0, group_size != 32.  ARKV_EUNSUPPORTED: head_dim not in {64,128}, G not in {1,2,4,8}, G*W > 512,
  * quant_bits not in {2,4,8}, N > 2^20 - 64 tokens, or pools of more than 2^21 - 32 rows per unit (byte budgets
