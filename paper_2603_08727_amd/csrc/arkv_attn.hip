@@ -2,8 +2,9 @@
 // causal attention, so the pass that computes the prompt's outputs already holds the window rows' softmax
 // maxima and sums).
 //
-// One workgroup = 32 QB query positions of one (sequence, kv-head) x the G heads of its group; a wave takes 32
-// positions of one head.  QB = 4 / G for G < 4 (else 1), so that at least four waves share every key and value tile,
+// One workgroup = 32 QB query positions of one (sequence, kv-head) x H of the G heads of its group (all of them up to
+// G = 4, four or eight at G = 8, see launch_prefill_attn); a wave takes 32
+// positions of one head.  QB = 4 / H for H < 4 (else 1), so that at least four waves share every key and value tile,
 // which is fetched from HBM once per workgroup and staged
 // in LDS (keys in three buffers, values in two, one barrier per 32-key tile); the loads of a tile have two steps to
 // arrive (a step takes 0.4-1.1 us, a load that misses the L2 0.5-1 us), and their conversion and way into LDS is
@@ -80,7 +81,7 @@ __device__ unsigned long long g_attn_clock[4];
 // share it (LDS also admits few such workgroups per CU) the matrix pipe idled behind it.  One block of 32 positions at
 // G = 1, 2 against QB = 4 / G, 4096-token prompt, 8 kv-heads: d = 128 211 -> 97 us and 233 -> 119 us; d = 64, 2003 tokens,
 // 32 units, G = 1: 80.6 -> 51.7 us.
-template <int G> constexpr int kQBlocks = G < 4 ? 4 / G : 1;
+template <int H> constexpr int kQBlocks = H < 4 ? 4 / H : 1;     // H: heads of a workgroup
 
 // four adjacent channels of an output row: bf16, and fp32 for the parity hook
 template <int D>
@@ -110,6 +111,16 @@ __host__ __device__ inline AttnPieces attn_pieces(int first_pos, int piece_tiles
 // [channel block][row group][lane] (unnormalised sums), then (reference maximum, sum) per row [32], then the sum of the
 // unrounded probabilities per row [32] (EXACT).
 template <int D> constexpr int kPieceFloats = 32 * D + 96;
+
+// A launch whose workgroups take H of a unit's G heads has G / H shares per unit; the shares of a unit lie eight apart (as
+// many as there are units left in the last eight), on the same XCD, whose L2 then serves both.  share: 0 .. units G / H - 1.
+template <int G, int H>
+__device__ __forceinline__ void unit_share(int share, int units, int& u, int& head0) {
+  constexpr int N = G / H;
+  const int first = share / (8 * N) * 8, r = share % (8 * N), n = min(8, units - first);
+  u = first + r % n;
+  head0 = H * (r / n);
+}
 
 // Which unit and block of query positions a workgroup takes.  grid (units, blocks, pieces; or units, up to kMaxGridY
 // blocks, rest): the unit runs fastest, so the longest blocks of ALL units start first and the short ones fill the gaps at
@@ -150,8 +161,8 @@ static int attn_group(int D, int T, int units) {
 // probabilities before their rounding to fp16 as well.  The rounded sum is the right one for the outputs (numerator and
 // denominator then see the same numbers); as a normaliser it carries the roundings of few large probabilities, which
 // depend on the reference maximum and so on the cut.
-template <int D, int G, bool EXACT>
-__global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLaunch L) {
+template <int D, int G, int H, bool EXACT>
+__global__ __launch_bounds__(64 * H * kQBlocks<H>, 2) void k_prefill_attn(AttnLaunch L) {
 #ifdef ARKV_PHASE_TRACE
   if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) { g_attn_clock[0] = clock64(); g_attn_clock[1] = wall_clock64(); }
 #endif
@@ -159,8 +170,8 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   constexpr int KH = KK / 2;          // operands carried from the previous phase
   constexpr int CBN = D / 32;         // 32-channel blocks of the output
   constexpr int NPV = 2 * CBN;        // PV MFMAs per tile
-  constexpr int QB = kQBlocks<G>;     // blocks of 32 query positions per workgroup
-  constexpr int NT = 64 * G * QB;
+  constexpr int QB = kQBlocks<H>;     // blocks of 32 query positions per workgroup
+  constexpr int NT = 64 * H * QB;
   // Staging items of a tile, the same number for every thread (a branch would end the region in which they are
   // dealt out between MFMAs): KW channels of a key; VW channels of a pair of adjacent keys' values.
   constexpr int KW = 32 * D / NT < 8 ? 32 * D / NT : 8, KPR = D / KW, KPT = 32 * KPR / NT;
@@ -169,7 +180,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   // Of the two waves on a SIMD the one in phase A issues first, then the one in phase B: they share the issue port, and the
   // phase with vector work beside its MFMAs is the longer one.  512 queries x 16411 keys x 8 units 160-164 -> 147-156 us, 8192
   // tokens x 8 units 533 -> 527, the same at G = 8; nothing at G = 1 (164.4, 165.3) or d = 64 (321, 323).
-  constexpr bool kPrio = D == 128 && G >= 4;
+  constexpr bool kPrio = D == 128 && H >= 4;
   static_assert(NPV >= KH && NPV >= KPT + VW / 2, "operand prefetch pattern; one staging item per PV MFMA at most");
   using KItem = Words<KW / 2>;
   using VItem = Words<VW / 2>;
@@ -178,10 +189,13 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
   int u, qb;
   const bool split = L.piece_tiles > 0;
   if (!query_block(gridDim.x, blockIdx.x, blockIdx.y + (split ? 0u : blockIdx.z * (unsigned)kMaxGridY), nqb, L.group, u, qb)) return;
+  const int share = u;                              // of a unit's heads; also where its partials lie
+  int head0 = 0;
+  if constexpr (H < G) unit_share<G, H>(share, L.B * L.Hkv, u, head0);
   const int b = u / L.Hkv, g = u % L.Hkv;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int w = wave % G, wq = QB * qb + wave / G; // head of the group, block of 32 query positions
+  const int w = head0 + wave % H, wq = QB * qb + wave / H; // head of the unit, block of 32 query positions
   const int n = lane & 31, hh = lane >> 5;
   const int T = L.T, Tq = L.Tq, q0 = T - Tq;
   const int row = 32 * wq + n;                     // query row inside the block of T_q queries
@@ -389,7 +403,7 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 #endif
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   if (pc.n > 1) {
-    float* part = L.part + ((((size_t)u * nqb + qb) * gridDim.z + piece) * (G * QB) + wave) * kPieceFloats<D>;
+    float* part = L.part + ((((size_t)share * nqb + qb) * gridDim.z + piece) * (H * QB) + wave) * kPieceFloats<D>;
 #pragma unroll
     for (int cb = 0; cb < CBN; ++cb)
 #pragma unroll
@@ -424,17 +438,20 @@ __global__ __launch_bounds__(64 * G * kQBlocks<G>, 2) void k_prefill_attn(AttnLa
 // Adds up the pieces of the workgroups that have more than one.  grid (query blocks, units, D / 32), the same waves and
 // lanes as above; a wave takes one block of 32 channels.  Bound by the partials' bytes (34 MB written and read at 512
 // queries x 16411 keys x 32 heads: 9 us of 147).
-template <int D, int G>
-__global__ __launch_bounds__(64 * G * kQBlocks<G>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
-  constexpr int QB = kQBlocks<G>;
-  const int qb = blockIdx.x, u = blockIdx.y, cb = blockIdx.z, b = u / L.Hkv, g = u % L.Hkv;
+template <int D, int G, int H>
+__global__ __launch_bounds__(64 * H * kQBlocks<H>) void k_prefill_attn_merge(AttnLaunch L, int max_pieces) {
+  constexpr int QB = kQBlocks<H>;
+  const int qb = blockIdx.x, cb = blockIdx.z;
+  int u = blockIdx.y, head0 = 0;
+  if constexpr (H < G) unit_share<G, H>(blockIdx.y, L.B * L.Hkv, u, head0);
+  const int b = u / L.Hkv, g = u % L.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int w = wave % G, n = lane & 31, hh = lane >> 5;
-  const int T = L.T, Tq = L.Tq, q0 = T - Tq, row = 32 * (QB * qb + wave / G) + n;
+  const int w = head0 + wave % H, n = lane & 31, hh = lane >> 5;
+  const int T = L.T, Tq = L.Tq, q0 = T - Tq, row = 32 * (QB * qb + wave / H) + n;
   const AttnPieces pc = attn_pieces(q0 + 32 * QB * qb, L.piece_tiles);
   if (pc.n < 2 || row >= Tq) return;
-  const float* part = L.part + (((size_t)u * gridDim.x + qb) * max_pieces * (G * QB) + wave) * kPieceFloats<D>;
-  const size_t stride = (size_t)(G * QB) * kPieceFloats<D>;
+  const float* part = L.part + (((size_t)blockIdx.y * gridDim.x + qb) * max_pieces * (H * QB) + wave) * kPieceFloats<D>;
+  const size_t stride = (size_t)(H * QB) * kPieceFloats<D>;
   float M = kNegBigA;
   for (int p = 0; p < pc.n; ++p) M = fmaxf(M, part[p * stride + 32 * D + 2 * n]);
   float l = 0.f, le = 0.f, acc[16];
@@ -512,23 +529,33 @@ void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* m
   }
 }
 
-hipError_t launch_prefill_attn(const AttnLaunch& launch, int max_pieces, hipStream_t s) {
+template <int D, int G, int H>
+static hipError_t launch_attn_t(const AttnLaunch& launch, int max_pieces, hipStream_t s) {
   AttnLaunch a = launch;
-  const int U = a.B * a.Hkv, G = a.Hq / a.Hkv;
-  a.group = max_pieces > 1 ? U : attn_group(a.D, a.T, U);
-#define ARKV_AT(D_, G_)                                                                                              \
-  if (a.D == D_ && G == G_) {                                                                                        \
-    constexpr int rows = 32 * kQBlocks<G_>, nt = 64 * G_ * kQBlocks<G_>;                                             \
-    const int nqb = (a.Tq + rows - 1) / rows;                                                                        \
-    const dim3 grid(U, nqb < kMaxGridY ? nqb : kMaxGridY, max_pieces > 1 ? max_pieces : (nqb + kMaxGridY - 1) / kMaxGridY); \
-    if (max_pieces > 1 && a.rowc) hipLaunchKernelGGL((k_prefill_attn<D_, G_, true>), grid, dim3(nt), 0, s, a);       \
-    else hipLaunchKernelGGL((k_prefill_attn<D_, G_, false>), grid, dim3(nt), 0, s, a);                               \
-    if (max_pieces > 1)                                                                                              \
-      hipLaunchKernelGGL((k_prefill_attn_merge<D_, G_>), dim3(nqb, U, D_ / 32), dim3(nt), 0, s, a, max_pieces);      \
-    return hipGetLastError();                                                                                        \
-  }
-  ARKV_AT(128, 1) ARKV_AT(128, 2) ARKV_AT(128, 4) ARKV_AT(128, 8)
-  ARKV_AT(64, 1) ARKV_AT(64, 2) ARKV_AT(64, 4) ARKV_AT(64, 8)
+  constexpr int rows = 32 * kQBlocks<H>, nt = 64 * H * kQBlocks<H>;
+  const int units = a.B * a.Hkv * (G / H), nqb = (a.Tq + rows - 1) / rows;
+  a.group = max_pieces > 1 ? units : attn_group(a.D, a.T, a.B * a.Hkv) * (G / H);
+  const dim3 grid(units, nqb < kMaxGridY ? nqb : kMaxGridY, max_pieces > 1 ? max_pieces : (nqb + kMaxGridY - 1) / kMaxGridY);
+  if (max_pieces > 1 && a.rowc) hipLaunchKernelGGL((k_prefill_attn<D, G, H, true>), grid, dim3(nt), 0, s, a);
+  else hipLaunchKernelGGL((k_prefill_attn<D, G, H, false>), grid, dim3(nt), 0, s, a);
+  if (max_pieces > 1)
+    hipLaunchKernelGGL((k_prefill_attn_merge<D, G, H>), dim3(nqb, units, D / 32), dim3(nt), 0, s, a, max_pieces);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s) {
+  const int G = a.Hq / a.Hkv;
+  // Four heads per workgroup at G = 8: four waves leave twice as many workgroups to spread over the CUs as eight, and a
+  // wave that has its SIMD to itself takes a step in 0.54 us (d = 64: 0.43) instead of 0.76 (0.55).  4 / 8 heads, us: 300 x 8 units
+  // 11.9 / 16.5, 32 x 1100 x 8 (split) 14.4 / 18.4, 2003 x 8 78.7 / 91.6 (d = 64: 51.3 / 62.0), 2003 x 32 309 / 314; the best of
+  // every split taken on both sides, 138 calls on 150 to 10007 keys, 2 to 32 units: 13 % less at the median, up to 33.  Long
+  // prompts that fill the chip many times over read each key tile once for all eight heads (10007 x 8 1562 / 1589, 1024 x
+  // 10007 x 32 1179 / 1211, d = 128; 5000 x 32 the same; d = 64 956 / 994 the other way).
+  const bool eight = a.D == 128 && max_pieces == 1 && a.T >= 8192 && (long long)a.B * a.Hkv * ((a.Tq + 31) / 32) >= 512;
+#define ARKV_AT(D_, G_, H_) if (a.D == D_ && G == G_) return launch_attn_t<D_, G_, H_>(a, max_pieces, s);
+  if (eight) { ARKV_AT(128, 8, 8) }
+  ARKV_AT(128, 1, 1) ARKV_AT(128, 2, 2) ARKV_AT(128, 4, 4) ARKV_AT(128, 8, 4)
+  ARKV_AT(64, 1, 1) ARKV_AT(64, 2, 2) ARKV_AT(64, 4, 4) ARKV_AT(64, 8, 4)
 #undef ARKV_AT
   return hipErrorInvalidValue;
 }

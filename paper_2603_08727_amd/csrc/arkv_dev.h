@@ -205,7 +205,7 @@ struct AttnLaunch {
   float* rowc;            // [U][MP] max + log2(sum) of the last W rows per head, or null
   float* part;            // partial results where the keys are split (piece_tiles > 0)
   int piece_tiles;        // key tiles per piece, 0: not split
-  int group;              // units that run side by side (set by the launcher)
+  int group;              // units (shares of units) that run side by side (set by the launcher)
   int B, Hq, Hkv, D, T, Tq, W, MP;
   float scale2;
 };

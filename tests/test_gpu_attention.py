@@ -489,3 +489,28 @@ def test_attention_units_in_groups():
         assert _check_rows(out, q, k, v, scale, 1, np.array([0, 127, 128, 4095, 8000, 16383, 16384, T - 1]), 0) <= TOL
     finally:
         A.arkv_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("d,hkv,batch,Tq,T", [
+    (64, 3, 3, 70, 70),        # nine units: the shares of eight lie apart, those of the ninth side by side
+    (128, 5, 2, 33, 300),      # ten units, a chunk whose second workgroup holds one row
+    (128, 3, 3, 40, 2100),     # nine units, split over the keys
+    (128, 2, 1, 8200, 8200),   # two units of a prompt long enough for eight heads per workgroup
+])
+def test_attention_heads_of_a_workgroup(d, hkv, batch, Tq, T):
+    """Group size 8: workgroups of four heads (eight for long prompts that fill the chip).  Every row of every head is
+    written, sampled rows of all heads against the oracle."""
+    g = 8
+    wl = synth.C1.scaled(name="heads", n_q_heads=g * hkv, n_kv_heads=hkv, head_dim=d, prefill=T, batch=batch, budget_frac=2.0)
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)[:, :, T - Tq:].contiguous()
+    scale = synth.softmax_scale(wl, 0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        out = torch.full_like(q, float("nan"), device="cuda")
+        _attention(cache, 0, q.cuda(), k.cuda(), v.cuda(), Tq, T, scale, out)
+        assert bool(torch.isfinite(out).all())
+        pos = np.unique(np.clip([T - Tq, T - Tq + 31, T - Tq + 32, T - Tq // 2, T - 1], T - Tq, T - 1))
+        assert _check_rows(out, q, k, v, scale, g, pos, T - Tq) <= TOL
+    finally:
+        A.arkv_cache_destroy(cache)
