@@ -491,27 +491,29 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
 }
 
 // How far to split over the keys: tiles per piece (0: no split) and the largest number of pieces of a workgroup.
-// The model: a tile step takes 0.75 us in a workgroup that has its CU to itself and 1.06 us where two share it (d = 64: 0.65 of
-// that), so a launch takes 0.75 us x the longest workgroup's tiles or 0.53 us x the tiles per CU, whichever is more; the merge
-// costs 12 us (a dependent launch) and its partials' way out and back.  Split pays where few workgroups walk many tiles: 512
-// queries x 16411 keys x 8 kv-heads 290 -> 146 us (4 pieces), 32 x 3000 x 16 units (d = 64, G = 1) 44 -> 15 us.  It does not pay
-// for a whole short prompt, whose imbalance is only the causal triangle (1100 tokens x 8 kv-heads: 29.6 us unsplit, 32.9 us in
-// 2 pieces), hence the margin and the floor of 32 tiles.
-// The constants were fitted to a loop whose loads had one step to arrive.  The present one takes, alone on its CU, 0.57 us (d =
-// 128; G = 8 0.80) and 0.43-0.45 us (d = 64; G = 8 0.58), shared 1.04 and 0.66, and the merge 9-14 us.  Every number of pieces
-// was timed on it for 830 calls (2-32 units, 1100-16411 keys, 32 queries to the whole prompt, every d, G = 1, 4, 8): the
-// chosen one is 2 % off the best at the median and more than 10 % off in 177.  These are unsplit calls on 1100 keys at d = 64 or
-// G != 4, which four pieces make 1.1-1.6 times faster (124 calls, 12 % at the median), unsplit ones at G = 8, d = 64 on 5000
-// (1.5), and 32 queries x 32 units cut in 16 where 8 are best (8003 keys, d = 128: 51 and 37 us).
+// The model: a tile step takes `alone` us in a workgroup that has its CU to itself and `shared` us where two share it, so a
+// launch takes `alone` x the longest workgroup's tiles or half of `shared` x the tiles per CU, whichever is more; the merge costs
+// 3 us, 0.1 per piece and its partials' way out and back.  (A step timed by itself takes 0.54 and 1.04 us, d = 64: 0.43 and
+// 0.66; the constants are those with which the model chooses best.)  Split pays where few workgroups walk many tiles: 512
+// queries x 16411 keys x 8 kv-heads 290 -> 146 us (4 pieces), 32 x 1100 x 8 units (d = 64) 19.9 -> 12.1.  It does not pay for a
+// whole short prompt, whose imbalance is only the causal triangle (1100 tokens x 8 kv-heads: 29.6 us unsplit, 32.9 us in 2
+// pieces; 972 x 4, 23.1 and 24.7 in 3), hence `triangle`.  Calls of up to 900 tokens (29 tiles) are never split, so that a prompt of that length gives the
+// same bits however it is cut into chunks (32 x 600 keys: 12-17 us where the best split takes 10-13).
+// Every number of pieces timed for 400 calls (2-32 units, 150-10007 keys, 32 queries to the whole prompt, G = 1, 4, 8): the chosen
+// one takes 2.1 % longer than the best on average, 6.5 % at the ninth decile (with constants fitted to an older loop 5.1 and 18).
+// 300 drawn calls that the constants were not fitted to: 68 are cut otherwise than with the old ones, those take 8 % less on
+// average (-30 to +8 %).
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {
   *piece_tiles = 0; *max_pieces = 1;
-  const int QB = G < 4 ? 4 / G : 1, nqb = (Tq + 32 * QB - 1) / (32 * QB), q0 = T - Tq;
+  const double triangle = D == 64 ? 7.5 : 9.5;                                   // us of the average workgroup
+  const double alone = D == 64 ? 0.36 : 0.6, shared = D == 64 ? 0.6 : 0.95;
+  const int H = G < 4 ? G : 4, QB = 4 / H, nqb = (Tq + 32 * QB - 1) / (32 * QB), q0 = T - Tq;
+  const long long wgs = (long long)nqb * units * (G / H);
   const int v0 = attn_pieces(q0, 0).visible, vmax = v0 + QB * (nqb - 1);         // visible tiles: v0 + QB i, i < nqb
-  const int cu_wgs = 256 * 4 / (G < 4 ? 4 : G);                                  // four-wave workgroups' worth per CU
-  if (vmax < 32 || (long long)nqb * units > 4 * cu_wgs) return;
-  const double c = D == 64 ? 0.65 : 1.0;
-  const double busy = 0.53 * c * 0.5 * ((double)v0 + vmax) * nqb * units / cu_wgs;
-  double best = 0.9 * (0.75 * c * vmax > busy ? 0.75 * c * vmax : busy);
+  const double mean = 0.5 * ((double)v0 + vmax);
+  if (vmax < 30 || wgs > 4 * 256 || alone * mean < triangle) return;
+  const double busy = 0.5 * shared * mean * (double)wgs / 256;
+  double best = 1.05 * (alone * vmax > busy ? alone * vmax : busy);
   for (int ns = 2; ns <= 16; ++ns) {
     const int pt = (vmax + ns - 1) / ns;
     const size_t floats = attn_part_floats(D, G, units, Tq, ns);
@@ -521,10 +523,10 @@ void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* m
       const int i0 = (p * pt + 1 - v0 + QB - 1) / QB;                            // the first one (v0 + QB i > p pt)
       items += nqb - (p * pt + 1 <= v0 ? 0 : (i0 < nqb ? i0 : nqb));
     }
-    items *= units;
-    double t = items <= cu_wgs ? 0.75 * c * pt : items <= 2 * cu_wgs ? 1.06 * c * pt : busy + 0.53 * c * pt;
+    items *= units * (G / H);
+    double t = items <= 256 ? alone * pt : items <= 512 ? shared * pt : busy + 0.5 * shared * pt;
     if (t < busy) t = busy;
-    t += 12.0 + 8.0e-7 * (double)floats;
+    t += 3.0 + 0.1 * ns + 1.0e-6 * (double)floats;
     if (t < best) { best = t; *piece_tiles = pt; *max_pieces = ns; }
   }
 }
