@@ -546,3 +546,23 @@ def test_selection_alone(kind, n, in_memory):
             else:
                 assert np.count_nonzero(keys[ranked] >= np.uint64(t)) == min(k, len(ranked))
                 assert (best[: k] >= np.uint64(t)).all()
+
+
+@pytest.mark.parametrize("in_memory", [False, True])
+@pytest.mark.parametrize("few", [1, 2, 63, 64, 65, 130])
+def test_selection_of_few_candidates(few, in_memory):
+    """The last candidates of a rank are ranked among themselves up to 64 of them: rows that share their leading digits, with
+    and without equal scores, for ranks at both ends and in the middle of them."""
+    n = 6000
+    r = np.random.default_rng(few)
+    for values in (few, 3):                              # distinct scores; three values, so that ties fall on most ranks
+        bits = np.where(np.arange(n) % 2 == 0, np.uint32(0x3F800000), np.uint32(0x30000000)).astype(np.uint32)
+        rows = r.choice(n, few, replace=False)
+        bits[rows] = np.uint32(0x38000000) + r.permutation(np.arange(few) % values).astype(np.uint32)
+        above = int(np.count_nonzero(bits > 0x38FFFFFF))
+        keys = (bits.astype(np.uint64) << np.uint64(32)) | (np.uint64(0xFFFFFFFF) - np.arange(n, dtype=np.uint64))
+        best = np.sort(keys)[::-1]
+        for k0, k1 in ((above + 1, above + few), (above + (few + 1) // 2, above + (few + 1) // 2), (above, above + 1), (above + few, above + few + 1)):
+            for k, t in zip((k0, k1), A.arkv_debug_select(bits, k0, k1, in_memory)):
+                assert np.count_nonzero(keys >= np.uint64(t)) == k
+                assert (best[:k] >= np.uint64(t)).all()
