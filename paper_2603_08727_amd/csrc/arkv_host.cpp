@@ -676,6 +676,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
     t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
     t.kept = a.keep;
+    pools.ticket = c->P.ticket;       // (a static launch's tickets are its own)
     const hipError_t te = launch_tailor(pools, t, st);
     if (te != hipSuccess) {
       // the attention of this step is on the stream, the tailor is not (or only partly): the device-side state of

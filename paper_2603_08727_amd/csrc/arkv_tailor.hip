@@ -551,10 +551,23 @@ __device__ __forceinline__ void quantize_into(const Pools& P, int gu, int dst, c
   }
 }
 
+// What one workgroup of a launch writes and another reads inside the same launch goes through device-scope relaxed atomics
+// (write-through stores, loads that do not hit a stale L2 line of another XCD); no cache-wide flush.
+__device__ __forceinline__ void st_dev8(void* p, uint64_t v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_dev8(const void* p) {
+  return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// a row's running sums, `dev`: which another workgroup of this launch may have written
+__device__ __forceinline__ float2 row_sums(const float2* p, bool dev) {
+  return dev ? __builtin_bit_cast(float2, ld_dev8(p)) : *p;
+}
+
 // The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
 // nD demoted rows into free Q slots (TPW tokens per wave at once), nM tail rows of the Q pool into holes.
 template <int D, int BITS>
-__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, int nM, int first, int waves, int lane) {
+__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, int nM, int first, int waves, int lane, bool dev = false) {
   constexpr int CB = D * BITS / 8, NG = metas_per_row(D, BITS);
   constexpr int LPT = 2 * (D / 8), TPW = 64 / LPT;
   const int32_t* dem = P.plan + (size_t)gu * P.plan_stride + kPlanHdr + 2 * P.capO;
@@ -567,7 +580,7 @@ __device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, in
     quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, sl, i0 + t < nD);
     if (sl == 0 && i0 + t < nD) {
       P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
-      P.qacc[(size_t)gu * P.capQ + dst] = P.oacc[o];
+      P.qacc[(size_t)gu * P.capQ + dst] = row_sums(P.oacc + o, dev);
     }
   }
   for (int item = first; item < nM; item += waves) {
@@ -582,13 +595,13 @@ __device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, in
     uint16_t* vmu = P.qvm + (size_t)gu * P.capQv * MH;
     if (lane < MH) vmu[vmeta_index(dst, lane, MH)] = vmu[vmeta_index(src, lane, MH)];
     if (lane < NG) P.qkm[d_ * NG + lane] = P.qkm[so * NG + lane];
-    if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = P.qacc[so]; }
+    if (lane == 0) { P.qpos[d_] = P.qpos[so]; P.qacc[d_] = row_sums(P.qacc + so, dev); }
   }
 }
 
 // nM tail rows of the O pool into holes: after every demoted row of the unit has been read.
 template <int D>
-__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, int first, int waves, int lane) {
+__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, int first, int waves, int lane, bool dev = false) {
   constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;
   const int32_t* ohole = P.plan + (size_t)gu * P.plan_stride + kPlanHdr;
   const int32_t* omov = ohole + P.capO;
@@ -597,19 +610,19 @@ __device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, in
   for (int item = first * TPW + t; item < nM; item += waves * TPW) {
     const size_t so = (size_t)gu * P.capO + omov[item], d_ = (size_t)gu * P.capO + ohole[item];
     *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
-    if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = P.oacc[so]; }
+    if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = row_sums(P.oacc + so, dev); }
   }
 }
 
 // ------------------------------------------------------------------------------------------
 // in-place tailor: keys (eq. 9's score per row), the two thresholds, and the lists that compact both pools.
-// One workgroup per unit, one launch, bound by one CU's instruction issue and round trips.  32 units x 8192 rows with kept
-// logits, one row moved per step: 26.4 us, of which 22.5 between a workgroup's first instruction and its last (scores 5.7,
-// selection 8.6, fates 1.5, lists 3.4, moves 3.3) and the rest is the launch's start and end.  A step with a tailor 64.3 ->
-// 56.5 us against digits of the plain score, scalar LDS reads, a fate word per row and thresholds fetched from memory, kept
-// logits and moves not counted.  Fates are kept as a
-// bit per row (two words per 64 rows), so that the lists' counts are one thread's work per 64 rows and words with nothing to
-// list are skipped.
+// One launch; one workgroup per unit chooses, bound by its CU's instruction issue and round trips.  Where the step's logits have
+// to be turned into probabilities as well, the scores of many rows are the unit's workgroups' work (tailor_parts): they leave
+// keys and sums at the device's coherence point, and the one that draws the last ticket reads the keys back and goes on.
+// 32 units x 8192 rows with kept logits, one row moved per step: 21.4 us with the launch's start and end; 25.6 with one
+// workgroup for everything, of which scores 9.3, selection 4.4, fates 3.3, lists 1.7, moves 3.1.
+// Fates are kept as a bit per row (two words per 64 rows), so that the lists' counts are one thread's work per 64 rows and words
+// with nothing to list are skipped.
 //   plan: header | ohole[capO] | omov[capO] | dem[capO] | qfree[capQ] | qmov[capQ]
 // ------------------------------------------------------------------------------------------
 // bits 0 .. n - 1 of a word whose first bit is row `row0`: the rows below `end`
@@ -654,6 +667,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   __shared__ uint32_t scan_sm[3][16];
   __shared__ int tot[3];
   const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int parts = IN_LDS && KEPT ? (int)gridDim.y : 1, part = blockIdx.y;
   const int2 cnt = P.cnt[gu];
   const int cO = cnt.x, cQ = cnt.y, n = cO + cQ;           // rows: the O pool's, then the Q pool's
   uint64_t* keys = P.keys + (size_t)gu * (P.capO + P.capQ);
@@ -675,10 +689,10 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   // workgroup's accesses to memory, which on this target needs no wait for the stores, they pass the CU's L1 in order)
   constexpr int BATCH = 4;                                  // rows requested together, one batch ahead of their use
   struct Rows { int pos[BATCH]; float2 acc[BATCH]; float x[KEPT ? BATCH : 1][G]; };
-  auto fetch = [&](int q, Rows& r) {
+  auto fetch_rounds = [&](int round, int step, Rows& r) {      // BATCH rounds of 1024 rows, `step` apart
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
-      const int i = min(kQuad * q + 1024 * j + tid, n - 1);
+      const int i = min(1024 * (round + step * j) + tid, n - 1);
       r.pos[j] = i < cO ? opos[i] : qpos[i - cO];
       r.acc[j] = i < cO ? oacc[i] : qacc[i - cO];
       if constexpr (KEPT) {
@@ -695,6 +709,17 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
       }
     }
   };
+  auto fetch = [&](int q, Rows& r) { fetch_rounds(4 * q, 1, r); };
+  // key of row i (0: not ranked), its sums brought up to date
+  auto score_row = [&](int i, int pos, float2& acc, const float (&x)[G]) -> uint64_t {
+    if constexpr (KEPT) {
+      const float2 m = step_moments<G>(x, fin);
+      acc.x += m.x; acc.y += m.y;
+    }
+    if (i >= n || pos >= L.position + 1 - L.window) return 0;
+    const int first = pos > L.t_prefill - L.window ? pos : L.t_prefill - L.window;
+    return make_key(hh_score(acc.x, acc.y, G * (L.position - first + 1), L.gamma), pos);
+  };
   auto score_rows = [&](int q, Rows& r) {
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) {
@@ -703,33 +728,72 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
         if constexpr (IN_LDS) row_word[i] = kNoScore;
         continue;
       }
-      if constexpr (KEPT) {
-        const float2 m = step_moments<G>(r.x[j], fin);
-        r.acc[j].x += m.x; r.acc[j].y += m.y;
-        if (i < n) *(i < cO ? oacc + i : qacc + (i - cO)) = r.acc[j];
-      }
-      uint64_t key = 0;
-      if (i < n && r.pos[j] < L.position + 1 - L.window) {
-        const int first = r.pos[j] > L.t_prefill - L.window ? r.pos[j] : L.t_prefill - L.window;
-        key = make_key(hh_score(r.acc[j].x, r.acc[j].y, G * (L.position - first + 1), L.gamma), r.pos[j]);
-      }
+      const uint64_t key = score_row(i, r.pos[j], r.acc[j], r.x[KEPT ? j : 0]);
+      if (KEPT && i < n) *(i < cO ? oacc + i : qacc + (i - cO)) = r.acc[j];
       const uint32_t sb = key ? (uint32_t)(key >> 32) : kNoScore;
       range.add(sb);
       if (i < n) keys[i < cO ? i : i + slot_q] = key;
       if constexpr (IN_LDS) row_word[i] = sb;               // (whole quads)
     }
   };
-  Rows ra, rb;
-  fetch(0, ra);
-  for (int q = 0; q < nq; q += 2) {
-    fetch(min(q + 1, nq - 1), rb);
-    score_rows(q, ra);
-    if (q + 1 < nq) {
-      fetch(min(q + 2, nq - 1), ra);
-      score_rows(q + 1, rb);
+  if (parts > 1) {
+    // This workgroup's rounds of 1024 rows, every parts-th; the unit's last workgroup reads all keys back and goes on alone.
+    Rows r;
+    for (int j0 = part; j0 < rounds; j0 += parts * BATCH) {
+      fetch_rounds(j0, parts, r);
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j) {
+        const int i = 1024 * (j0 + j * parts) + tid;
+        if (i >= n) continue;
+        const uint64_t key = score_row(i, r.pos[j], r.acc[j], r.x[KEPT ? j : 0]);
+        st_dev8(i < cO ? oacc + i : qacc + (i - cO), __builtin_bit_cast(uint64_t, r.acc[j]));
+        st_dev8(keys + (i < cO ? i : i + slot_q), key);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // this wave's stores are at the device's coherence point
+    __syncthreads();
+    if (tid == 0) {
+      int* const ticket = P.ticket + (size_t)gu * (kTicketWaves * kTicketPitch);      // (zero between launches)
+      const int done = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+      if (done == parts) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      tot[0] = done;
+    }
+    __syncthreads();
+    if (tot[0] != parts) return;
+    constexpr int AHEAD = 8;
+    for (int j0 = 0; j0 < 4 * nq; j0 += AHEAD) {
+      uint64_t k[AHEAD];
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) {
+        const int i = min(1024 * (j0 + j) + tid, n - 1);
+        k[j] = ld_dev8(keys + (i < cO ? i : i + slot_q));
+      }
+#pragma unroll
+      for (int j = 0; j < AHEAD; ++j) {
+        const int i = 1024 * (j0 + j) + tid;
+        if (j0 + j >= 4 * nq) break;
+        const uint32_t sb = i < n && k[j] ? (uint32_t)(k[j] >> 32) : kNoScore;
+        range.add(sb);
+        if constexpr (IN_LDS) row_word[i] = sb;
+      }
+    }
+    __syncthreads();                                        // (tot is read above and cleared below)
+  } else {
+    Rows ra, rb;
+    fetch(0, ra);
+    for (int q = 0; q < nq; q += 2) {
+      fetch(min(q + 1, nq - 1), rb);
+      score_rows(q, ra);
+      if (q + 1 < nq) {
+        fetch(min(q + 2, nq - 1), ra);
+        score_rows(q + 1, rb);
+      }
     }
   }
-  auto key_of = [&](int i) -> uint64_t { return keys[i < cO ? i : i + slot_q]; };
+  auto key_of = [&](int i) -> uint64_t {
+    const uint64_t* k = keys + (i < cO ? i : i + slot_q);
+    return parts > 1 ? ld_dev8(k) : *k;
+  };
   auto score_of = [&](int i) -> uint32_t {
     if constexpr (IN_LDS) return row_word[i];
     const uint64_t k = key_of(i);
@@ -870,9 +934,9 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     if (!L.few_moves) return;
     __syncthreads();                                        // the lists
     auto moves = [&](auto d, auto bits) {
-      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane);
+      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane, parts > 1);
       __syncthreads();                                      // every demoted row has been read
-      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane);
+      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane, parts > 1);
     };
     using std::integral_constant;
     if (P.D == 128) {
@@ -1176,13 +1240,13 @@ __global__ __launch_bounds__(1024) void k_select_probe(const uint32_t* scores, i
 // ------------------------------------------------------------------------------------------
 // One workgroup of 1024 threads per unit with a 32-bit word of LDS per row (whole rounds of the selection).
 template <typename... Params, typename... Args>
-static hipError_t launch_rows(void (*kernel)(Params...), int n_units, int lds_rows, hipStream_t s, Args... args) {
+static hipError_t launch_rows(void (*kernel)(Params...), dim3 grid, int lds_rows, hipStream_t s, Args... args) {
   const size_t shm = (size_t)quads(lds_rows) * kQuad * sizeof(uint32_t);
   if (shm > 32 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3(n_units), dim3(1024), shm, s, args...);
+  hipLaunchKernelGGL(kernel, grid, dim3(1024), shm, s, args...);
   return hipGetLastError();
 }
 
@@ -1195,6 +1259,14 @@ static void launch_tailor_moves(const Pools& P, const TailorLaunch& a, hipStream
   hipLaunchKernelGGL((k_tailor_move_o<D>), go, dim3(256), 0, s, P, a);
 }
 
+// Workgroups of a unit that score its rows where they have the step's logits to turn into probabilities: a CU reads 28 bytes a
+// row (G = 4) and writes 16, which takes one 9 us for 8192 rows.  Spread over several, the scores' way through memory and the
+// ticket cost about 4 us (a step with a tailor, one workgroup / several: 32 units x 8192 rows 42.2 / 39.6 us, 8 x 6000 30.9 /
+// 29.3, 8 x 30000 69.0 / 54.8, 32 x 4000 32.0 / 31.8, 8 x 3000 25.2 / 25.9, 8 x 1200 23.0 / 24.2).
+static int tailor_parts(int n_units, int max_rows) {
+  return max_rows <= kQuad ? 1 : std::max(1, std::min((max_rows + 1023) / 1024, 256 / n_units));
+}
+
 hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
   if (a.n_pending > 0 && !a.kept) {
     hipError_t e = launch_flush_scores(P, a.unit_begin, a.n_units, a.n_pending, a.slot, s);
@@ -1203,12 +1275,13 @@ hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
   // the scores of a unit stay in LDS between the passes where they fit
   const bool lds = a.max_rows <= kLdsRows;
   const int rows = lds ? a.max_rows : 0;
+  const dim3 grid(a.n_units, lds && a.kept ? tailor_parts(a.n_units, a.max_rows) : 1);
 #define ARKV_CH(G_)                                                                                                     \
   case G_:                                                                                                              \
-    e = a.kept ? (lds ? launch_rows(k_tailor_choose<G_, true, true>, a.n_units, rows, s, P, a)                          \
-                      : launch_rows(k_tailor_choose<G_, false, true>, a.n_units, rows, s, P, a))                        \
-               : (lds ? launch_rows(k_tailor_choose<G_, true, false>, a.n_units, rows, s, P, a)                         \
-                      : launch_rows(k_tailor_choose<G_, false, false>, a.n_units, rows, s, P, a));                      \
+    e = a.kept ? (lds ? launch_rows(k_tailor_choose<G_, true, true>, grid, rows, s, P, a)                               \
+                      : launch_rows(k_tailor_choose<G_, false, true>, grid, rows, s, P, a))                             \
+               : (lds ? launch_rows(k_tailor_choose<G_, true, false>, grid, rows, s, P, a)                              \
+                      : launch_rows(k_tailor_choose<G_, false, false>, grid, rows, s, P, a));                           \
     break;
   hipError_t e = hipErrorInvalidValue;
   switch (P.G) { ARKV_CH(1) ARKV_CH(2) ARKV_CH(4) ARKV_CH(8) }
@@ -1292,8 +1365,8 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
   // kept: 21 us for the whole commit, 52 in one part per block), above 96 nothing is gained (32 units x 32768 positions,
   // 6152 kept: 89 to 95 us at 64 to 1024 rows; all with an earlier selection that took 2 and 12 us more)
   const int share_rows = clampi((int)((long long)a.n_units * kept / 1024 + 7) / 8 * 8, 8, 96);
-  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, a.n_units, a.T, s, P, a, c, share_rows)
-                                       : launch_rows(k_commit_select<false>, a.n_units, 0, s, P, a, c, share_rows);
+  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, dim3(a.n_units), a.T, s, P, a, c, share_rows)
+                                       : launch_rows(k_commit_select<false>, dim3(a.n_units), 0, s, P, a, c, share_rows);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)a.n_units * (unsigned)(kept / share_rows + commit_blocks(a.T)));   // (a block's last part may be short)
 #define ARKV_SC(D_, B_)                                                                                                      \
@@ -1308,8 +1381,8 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
 
 bool select_in_lds(int n) { return n <= kLdsRows; }
 hipError_t launch_select_probe(const uint32_t* scores, int n, int k0, int k1, bool in_lds, uint64_t* thr, hipStream_t s) {
-  return in_lds ? launch_rows(k_select_probe<true>, 1, n, s, scores, n, k0, k1, thr)
-                : launch_rows(k_select_probe<false>, 1, 0, s, scores, n, k0, k1, thr);
+  return in_lds ? launch_rows(k_select_probe<true>, dim3(1), n, s, scores, n, k0, k1, thr)
+                : launch_rows(k_select_probe<false>, dim3(1), 0, s, scores, n, k0, k1, thr);
 }
 
 }  // namespace arkv

@@ -566,3 +566,15 @@ def test_selection_of_few_candidates(few, in_memory):
             for k, t in zip((k0, k1), A.arkv_debug_select(bits, k0, k1, in_memory)):
                 assert np.count_nonzero(keys >= np.uint64(t)) == k
                 assert (best[:k] >= np.uint64(t)).all()
+
+
+@pytest.mark.parametrize("hq,hkv,d,bits,n", [(4, 1, 64, 4, 4097), (8, 1, 128, 8, 5121), (2, 2, 64, 2, 6200), (2, 1, 128, 4, 4160)])
+def test_every_step_policy_rows_of_several_workgroups(hq, hkv, d, bits, n):
+    """A tailor at every step over more than 4096 rows: several workgroups score a unit's rows (the last one a few rows only),
+    the unit's last one chooses.  More than 16 steps, so that the choosing workgroup makes the moves at the end as well."""
+    t = n + 700
+    wl = synth.C1.scaled(name=f"parts{n}", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, bits=bits, prefill=t, batch=1,
+                         budget_frac=(n + 0.5) / t, decode_steps=21)
+    assert wl.capacity == n
+    sb = _run(wl, rho=0.4, check_every=7, every_step=True)
+    assert all(len(u.pos) == n - 1 for u in sb.oracles[(0, 0)].units)
