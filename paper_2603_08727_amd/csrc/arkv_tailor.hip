@@ -565,18 +565,22 @@ __device__ __forceinline__ float2 row_sums(const float2* p, bool dev) {
 }
 
 // The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
-// nD demoted rows into free Q slots (TPW tokens per wave at once), nM tail rows of the Q pool into holes.
-template <int D, int BITS>
-__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, int nM, int first, int waves, int lane, bool dev = false) {
+// nD demoted rows into free Q slots (TPW tokens per wave at once), nM tail rows of the Q pool into holes.  list(l, i): entry i
+// of a list.
+enum MoveList { kOHole = 0, kOMov, kDem, kQFree, kQMov, kMoveLists };
+// where a list begins in a unit's plan
+__device__ __forceinline__ size_t list_begin(const Pools& P, int l) {
+  return (size_t)kPlanHdr + (size_t)(l < kQMov ? l : kQFree) * P.capO + (size_t)(l < kQMov ? 0 : P.capQ);
+}
+template <int D, int BITS, typename List>
+__device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, int nM, int first, int waves, int lane, bool dev,
+                                              List&& list) {
   constexpr int CB = D * BITS / 8, NG = metas_per_row(D, BITS);
   constexpr int LPT = 2 * (D / 8), TPW = 64 / LPT;
-  const int32_t* dem = P.plan + (size_t)gu * P.plan_stride + kPlanHdr + 2 * P.capO;
-  const int32_t* qfree = dem + P.capO;
-  const int32_t* qmov = qfree + P.capQ;
   const int t = lane / LPT, sl = lane % LPT;
   for (int i0 = first * TPW; i0 < nD; i0 += waves * TPW) {
-    const int item = min(i0 + t, nD - 1), dst = qfree[item];
-    const size_t o = (size_t)gu * P.capO + dem[item];
+    const int item = min(i0 + t, nD - 1), dst = list(kQFree, item);
+    const size_t o = (size_t)gu * P.capO + list(kDem, item);
     quantize_into<D, BITS>(P, gu, dst, P.ok + o * D, P.ov + o * D, sl, i0 + t < nD);
     if (sl == 0 && i0 + t < nD) {
       P.qpos[(size_t)gu * P.capQ + dst] = P.opos[o];
@@ -584,7 +588,7 @@ __device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, in
     }
   }
   for (int item = first; item < nM; item += waves) {
-    const int dst = qfree[nD + item], src = qmov[item];
+    const int dst = list(kQFree, nD + item), src = list(kQMov, item);
     const size_t so = (size_t)gu * P.capQ + src, d_ = (size_t)gu * P.capQ + dst;
     // K: code bytes, 4 per lane; V: one byte column per lane (token-minor blocks)
     for (int b = lane * 4; b < CB; b += 256)
@@ -600,15 +604,13 @@ __device__ __forceinline__ void tailor_move_q(const Pools& P, int gu, int nD, in
 }
 
 // nM tail rows of the O pool into holes: after every demoted row of the unit has been read.
-template <int D>
-__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, int first, int waves, int lane, bool dev = false) {
+template <int D, typename List>
+__device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, int first, int waves, int lane, bool dev, List&& list) {
   constexpr int LPR = D / 8, LPT = 2 * LPR, TPW = 64 / LPT;
-  const int32_t* ohole = P.plan + (size_t)gu * P.plan_stride + kPlanHdr;
-  const int32_t* omov = ohole + P.capO;
   const int t = lane / LPT, sl = lane % LPT, sub = sl % LPR;
   uint16_t* base = sl < LPR ? P.ok : P.ov;
   for (int item = first * TPW + t; item < nM; item += waves * TPW) {
-    const size_t so = (size_t)gu * P.capO + omov[item], d_ = (size_t)gu * P.capO + ohole[item];
+    const size_t so = (size_t)gu * P.capO + list(kOMov, item), d_ = (size_t)gu * P.capO + list(kOHole, item);
     *reinterpret_cast<uint4*>(base + d_ * D + sub * 8) = *reinterpret_cast<const uint4*>(base + so * D + sub * 8);
     if (sl == 0) { P.opos[d_] = P.opos[so]; P.oacc[d_] = row_sums(P.oacc + so, dev); }
   }
@@ -619,8 +621,9 @@ __device__ __forceinline__ void tailor_move_o(const Pools& P, int gu, int nM, in
 // One launch; one workgroup per unit chooses, bound by its CU's instruction issue and round trips.  Where the step's logits have
 // to be turned into probabilities as well, the scores of many rows are the unit's workgroups' work (tailor_parts): they leave
 // keys and sums at the device's coherence point, and the one that draws the last ticket reads the keys back and goes on.
-// 32 units x 8192 rows with kept logits, one row moved per step: 21.4 us with the launch's start and end; 25.6 with one
-// workgroup for everything, of which scores 9.3, selection 4.4, fates 3.3, lists 1.7, moves 3.1.
+// 32 units x 8192 rows with kept logits, one row moved per step: 20.2 us with the launch's start and end; 25.6 with one
+// workgroup for everything (scores 9.3, selection 4.4, fates 3.3, lists 1.7, moves 3.1), a ballot per 64 rows for the fates and
+// the lists of the moved rows fetched back from memory (the last two 1.2 us together).
 // Fates are kept as a bit per row (two words per 64 rows), so that the lists' counts are one thread's work per 64 rows and words
 // with nothing to list are skipped.
 //   plan: header | ohole[capO] | omov[capO] | dem[capO] | qfree[capQ] | qmov[capQ]
@@ -660,12 +663,14 @@ __device__ __forceinline__ float2 step_moments(const float (&x)[G], const float2
 
 // KEPT: the pending step's logits are in Pools::logit (see k_decode_attend); its probabilities are added to the sums here,
 // and few moved rows (L.few_moves) are moved here as well.
+constexpr int kNearList = 64;
 template <int G, bool IN_LDS, bool KEPT>
 __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L) {
   extern __shared__ __align__(16) uint32_t row_word[];      // IN_LDS: score of row i
   __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
   __shared__ uint32_t scan_sm[3][16];
   __shared__ int tot[3];
+  __shared__ int32_t near_list[kMoveLists][KEPT ? kNearList : 1];
   const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int parts = IN_LDS && KEPT ? (int)gridDim.y : 1, part = blockIdx.y;
   const int2 cnt = P.cnt[gu];
@@ -813,78 +818,65 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   select_two(nq, load, score_of, key_of, range, P.n_o[gu], P.nb[gu], sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
 
-  // What becomes of the 64 rows of a wave's round: whether they stay in their pool (window rows do), are demoted, or (neither)
-  // are evicted.
+  // What becomes of the rows: each stays in its pool (window rows do), is demoted, or (neither) is evicted.  Most stay: a
+  // chunk's words start out so, and only the rows that leave touch them (with a ballot for every 64 rows this took 3.3 us
+  // of 22 for 8192 rows).
   const uint32_t so = (uint32_t)(thr_o >> 32), sq = (uint32_t)(thr_b >> 32);
   const bool ties = __builtin_amdgcn_readfirstlane((uint32_t)thr_o | (uint32_t)thr_b) != 0;
-  auto classify = [&](int i, uint32_t sb, uint64_t& stay, uint64_t& dem) {
-    bool geo = sb >= so, geb = sb >= sq;
-    if (ties && __any(sb != kNoScore && (sb == so || sb == sq))) {     // scores that tie with a threshold: the whole key decides
-      if (sb != kNoScore) {
-        const uint64_t key = key_of(i);
-        geo = key >= thr_o; geb = key >= thr_b;
+  // the rows of rounds j0 .. j0 + nj - 1 of 1024: marks them in the words, and counts those that leave their pool
+  auto fates = [&](int j0, int nj, bool mark, bool count) {
+    if (mark) {
+      if (tid < 16 * nj) { sel.stay[tid] = rows_below(1024 * j0 + 64 * tid, n); sel.dem[tid] = 0; }
+      __syncthreads();
+    }
+    uint32_t leaveO = 0, demoted = 0, leaveQ = 0;
+    for (int q = 0; q < quads(1024 * nj); ++q) {
+      uint32_t s4[4];
+      load(j0 / 4 + q, s4);
+      const int i0 = 1024 * j0 + kQuad * q + 4 * tid;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + e;
+        const uint32_t sb = s4[e];
+        const bool o = i < cO, none = sb == kNoScore;
+        bool geo = sb >= so, geb = sb >= sq;                 // (a row that is not ranked: both, and it stays Original)
+        if (ties && !none && (sb == so || sb == sq)) {       // scores that tie with a threshold: the whole key decides
+          const uint64_t key = key_of(i);
+          geo = key >= thr_o; geb = key >= thr_b;
+        }
+        if (i < n && !(o ? geo : geb && !none)) {
+          const bool d = o && geb;
+          leaveO += o ? 1 : 0; demoted += d ? 1 : 0; leaveQ += o ? 0 : 1;
+          if (mark) {
+            const int word = (i - 1024 * j0) >> 5;
+            const uint32_t bit = 1u << (i & 31);
+            atomicAnd(reinterpret_cast<uint32_t*>(sel.stay) + word, ~bit);
+            if (d) atomicOr(reinterpret_cast<uint32_t*>(sel.dem) + word, bit);
+          }
+        }
       }
     }
-    const bool o = i < cO, none = sb == kNoScore;
-    stay = __ballot(o ? none || geo : geb && !none);
-    dem = __ballot(o && !none && geb && !geo);
-  };
-  // four rounds of 1024 rows: a row's word, a wave's 64 rows at a time (kNoScore behind the last row)
-  auto words = [&](int q, uint32_t (&s)[4]) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int i = kQuad * q + 1024 * e + tid;
-      if constexpr (IN_LDS) s[e] = row_word[i];
-      else s[e] = i < n ? score_of(i) : kNoScore;
+    if (count && __any((leaveO | leaveQ) != 0)) {
+      const uint32_t a = wave_prefix_sum(leaveO), b = wave_prefix_sum(demoted), c = wave_prefix_sum(leaveQ);
+      if (lane == 63) { atomicAdd(&tot[0], (int)a); atomicAdd(&tot[1], (int)b); atomicAdd(&tot[2], (int)c); }
     }
+    __syncthreads();
   };
-  // rows that stay Original, are demoted, stay Quantized
-  int keepO = 0, nDem = 0, keepQ = 0;
   const bool one_chunk = rounds <= kRounds;
-  for (int q = 0; q < nq; ++q) {
-    uint32_t s4[4];
-    words(q, s4);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int j = 4 * q + e;
-      if (j >= rounds) continue;
-      uint64_t stay, dem;
-      classify(1024 * j + tid, s4[e], stay, dem);
-      const uint64_t o = rows_below(1024 * j + 64 * w, cO);
-      keepO += __popcll(stay & o);
-      nDem += __popcll(dem);
-      keepQ += __popcll(stay & ~o);
-      if (one_chunk && lane == 0) { sel.stay[16 * j + w] = stay; sel.dem[16 * j + w] = dem; }
-    }
-  }
-  if (lane == 0) { atomicAdd(&tot[0], keepO); atomicAdd(&tot[1], nDem); atomicAdd(&tot[2], keepQ); }
-  __syncthreads();
-  const int cOn = tot[0], nD = tot[1], cQn = tot[2] + nD;
+  fates(0, rounds, one_chunk, true);
+  const int cOn = cO - tot[0], nD = tot[1], cQn = cQ - tot[2] + nD;
 
   int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  int32_t* ohole = plan + kPlanHdr;
-  int32_t* omov = ohole + P.capO;
-  int32_t* dem_ = omov + P.capO;
-  int32_t* qfree = dem_ + P.capO;
-  int32_t* qmov = qfree + P.capQ;
+  // a list's first entries stay in LDS where this workgroup makes the moves
+  const bool here = KEPT && L.few_moves;
+  auto put = [&](int l, int i, int32_t v) {
+    if (KEPT && here && i < kNearList) near_list[l][i] = v;
+    else plan[list_begin(P, l) + i] = v;
+  };
   int base_hole = 0, base_mov = 0, base_dem = 0, base_free = 0, base_qmov = 0;
   for (int j0 = 0; j0 < rounds; j0 += kRounds) {
     const int nj = rounds - j0 < kRounds ? rounds - j0 : kRounds, entries = 16 * nj;
-    if (!one_chunk) {
-      for (int q = 0; q < quads(1024 * nj); ++q) {
-        uint32_t s4[4];
-        words(j0 / 4 + q, s4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int j = 4 * q + e;
-          if (j >= nj) continue;
-          uint64_t stay, dem;
-          classify(1024 * (j0 + j) + tid, s4[e], stay, dem);
-          if (lane == 0) { sel.stay[16 * j + w] = stay; sel.dem[16 * j + w] = dem; }
-        }
-      }
-      __syncthreads();
-    }
+    if (!one_chunk) fates(j0, nj, true, false);
     uint32_t v[3] = {0, 0, 0}, total[3];
     if (tid < entries) {                                    // thread = 64 rows
       const ListFlags f = list_flags(sel.stay[tid], sel.dem[tid], 1024 * j0 + 64 * tid, cO, n, cOn, cQn);
@@ -912,11 +904,11 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
       const ListFlags f = list_flags(of(m_stay), of(m_dem), row0, cO, n, cOn, cQn);
       const uint32_t hm = sel.off[0][e], df = sel.off[1][e], qm = sel.off[2][e];
       auto has = [&](uint64_t m) { return ((m >> lane) & 1) != 0; };
-      if (has(f.hole)) ohole[base_hole + (int)(hm & 0xFFFF) + place(f.hole, lane)] = i;
-      if (has(f.mov)) omov[base_mov + (int)(hm >> 16) + place(f.mov, lane)] = i;
-      if (has(f.dem)) dem_[base_dem + (int)(df & 0xFFFF) + place(f.dem, lane)] = i;
-      if (has(f.fr)) qfree[base_free + (int)(df >> 16) + place(f.fr, lane)] = i - cO;
-      if (has(f.qm)) qmov[base_qmov + (int)qm + place(f.qm, lane)] = i - cO;
+      if (has(f.hole)) put(kOHole, base_hole + (int)(hm & 0xFFFF) + place(f.hole, lane), i);
+      if (has(f.mov)) put(kOMov, base_mov + (int)(hm >> 16) + place(f.mov, lane), i);
+      if (has(f.dem)) put(kDem, base_dem + (int)(df & 0xFFFF) + place(f.dem, lane), i);
+      if (has(f.fr)) put(kQFree, base_free + (int)(df >> 16) + place(f.fr, lane), i - cO);
+      if (has(f.qm)) put(kQMov, base_qmov + (int)qm + place(f.qm, lane), i - cO);
     }
     base_hole += (int)(total[0] & 0xFFFF); base_mov += (int)(total[0] >> 16);
     base_dem += (int)(total[1] & 0xFFFF); base_free += (int)(total[1] >> 16);
@@ -924,7 +916,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     if (j0 + kRounds < rounds) __syncthreads();            // the next chunk's flags go into the same table
   }
   // slots behind the Q pool's old end
-  for (int i = tid; i < cQn - cQ; i += 1024) qfree[base_free + i] = cQ + i;
+  for (int i = tid; i < cQn - cQ; i += 1024) put(kQFree, base_free + i, cQ + i);
   if (tid == 0) {
     plan[PL_CO_NEW] = cOn; plan[PL_CQ_NEW] = cQn; plan[PL_N_DEM] = nD;
     plan[PL_N_QMOV] = base_qmov; plan[PL_N_OMOV] = base_mov;
@@ -933,10 +925,11 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   if constexpr (KEPT) {
     if (!L.few_moves) return;
     __syncthreads();                                        // the lists
+    auto list = [&](int l, int i) { return i < kNearList ? near_list[l][i] : plan[list_begin(P, l) + i]; };
     auto moves = [&](auto d, auto bits) {
-      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane, parts > 1);
+      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane, parts > 1, list);
       __syncthreads();                                      // every demoted row has been read
-      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane, parts > 1);
+      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane, parts > 1, list);
     };
     using std::integral_constant;
     if (P.D == 128) {
@@ -954,14 +947,16 @@ template <int D, int BITS>
 __global__ __launch_bounds__(256) void k_tailor_move_q(Pools P, TailorLaunch L) {
   const int gu = L.unit_begin + blockIdx.y;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  tailor_move_q<D, BITS>(P, gu, plan[PL_N_DEM], plan[PL_N_QMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
+  tailor_move_q<D, BITS>(P, gu, plan[PL_N_DEM], plan[PL_N_QMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63, false,
+                         [&](int l, int i) { return plan[list_begin(P, l) + i]; });
 }
 
 template <int D>
 __global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) {
   const int gu = L.unit_begin + blockIdx.y;
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
-  tailor_move_o<D>(P, gu, plan[PL_N_OMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63);
+  tailor_move_o<D>(P, gu, plan[PL_N_OMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63, false,
+                   [&](int l, int i) { return plan[list_begin(P, l) + i]; });
   if (blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
 }
 
