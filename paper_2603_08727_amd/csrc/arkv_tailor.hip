@@ -23,12 +23,13 @@ typedef uint32_t u32x4t __attribute__((ext_vector_type(4)));   // 16 bytes; arra
 // ------------------------------------------------------------------------------------------
 // score -> key
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float hh_score(float s1, float s2, int n, float gamma) {
-  const float nf = (float)n;
-  const float mu = s1 / nf;
-  const float ex2 = s2 / nf;
+__device__ __forceinline__ float hh_moments_score(float mu, float ex2, float gamma) {
   const float var = fmaxf(ex2 - mu * mu, 0.0f);
   return mu + gamma * var;
+}
+__device__ __forceinline__ float hh_score(float s1, float s2, int n, float gamma) {
+  const float nf = (float)n;
+  return hh_moments_score(s1 / nf, s2 / nf, gamma);
 }
 
 // The radix select looks at digits of (score - smallest score), and a row that is not ranked must not match one that is: kNoScore
@@ -52,6 +53,7 @@ __device__ __forceinline__ uint64_t make_key(float S, int pos) {
 // ------------------------------------------------------------------------------------------
 constexpr uint32_t kNoScore = 0xFFFFFFFFu;   // not ranked (above every score, see make_key)
 constexpr int kLdsRows = 32768;              // units of up to this many rows keep their scores in LDS (128 KB)
+constexpr int kFusedRows = 8192;             // prompts of up to this many positions are scored by the workgroup that selects
 constexpr int kRounds = 32;                  // rounds of 1024 rows per list chunk
 constexpr int kBins = 2048, kDigit = 11;
 constexpr int kFew = 64;                     // candidates of a rank that one wave ranks among themselves, a lane each
@@ -970,8 +972,8 @@ struct CommitScratch { uint32_t* scores; int pitch; uint2* ranges; int4* blocks;
 __host__ __device__ constexpr int commit_ranges(int T) { return (T + 63) / 64; }
 __host__ __device__ constexpr int commit_blocks(int T) { return (T + 1023) / 1024; }
 
-// Scores of the prompt's positions (kNoScore: window, and what fills the pitch), over the whole chip (two IEEE divisions per
-// position: in the one workgroup that selects they took longer than the selection), each 64 positions' range of scores, and
+// Scores of a long prompt's positions (kNoScore: window, and what fills the pitch), over the whole chip (two IEEE divisions per
+// position: in the one workgroup that selects they took longer than the selection; see launch_commit for the line), each 64 positions' range of scores, and
 // the layer's budgets (a launch of their own took 5 us).
 __global__ __launch_bounds__(256) void k_commit_keys(Pools P, CommitLaunch L, CommitScratch C, int hkv, BudgetArgs budgets) {
   const int lu = blockIdx.y;
@@ -1003,8 +1005,11 @@ __device__ __forceinline__ uint32_t commit_parts(uint32_t survivors, int share_r
 // 8 x 1000 20.2 -> 19.4).  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
 // last one the totals) the rows in front of it that become Original and Quantized and the parts in front of it into which
 // k_commit_scatter cuts blocks: as many as hold share_rows survivors each, wherever in the prompt the survivors sit.
-template <bool IN_LDS>
-__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, CommitScratch C, int share_rows) {
+//
+// SCORES: the scores are formed here as well (and stored for k_commit_scatter), and the budgets come with this launch: short
+// prompts, see launch_commit.
+template <bool IN_LDS, bool SCORES>
+__global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L, CommitScratch C, int share_rows, int hkv, BudgetArgs budgets) {
   extern __shared__ __align__(16) uint32_t row_word[];     // IN_LDS: the positions' scores
   __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
   __shared__ uint32_t cnt[kRounds / 4][16];  // per (round of 4096 positions, wave): Original | Quantized << 16
@@ -1019,12 +1024,44 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
     return i < C.pitch ? *reinterpret_cast<const u32x4t*>(scores + i) : none;
   };
   ScoreRange range;
-  for (int i = tid; i < commit_ranges(T); i += 1024) {
-    const uint2 r = C.ranges[(size_t)lu * commit_ranges(T) + i];
-    range.lo = min(range.lo, r.x);
-    range.hi = max(range.hi, r.y);
+  int k_o, k_b;
+  if constexpr (SCORES) {
+    k_o = budgets.n_o[lu / hkv];
+    k_b = budgets.nb[lu / hkv];
+    if (tid == 0) { P.n_o[gu] = k_o; P.nb[gu] = k_b; }
+    const float2* pre = L.pre + (size_t)lu * T;
+    const int samples = P.G * L.window;
+    const bool pow2 = (samples & (samples - 1)) == 0;        // the usual window: a product gives the quotient's very bits
+    const float inv = 1.0f / (float)samples;
+    float2 a[kFusedRows / kQuad][4];         // (all requested together)
+#pragma unroll
+    for (int q = 0; q < kFusedRows / kQuad; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[q][e] = pre[min(kQuad * q + 4 * tid + e, T - 1)];
+#pragma unroll
+    for (int q = 0; q < kFusedRows / kQuad; ++q) {
+      const int i = kQuad * q + 4 * tid;
+      u32x4t v = {kNoScore, kNoScore, kNoScore, kNoScore};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float2 t = a[q][e];
+        const float S = pow2 ? hh_moments_score(t.x * inv, t.y * inv, L.gamma) : hh_score(t.x, t.y, samples, L.gamma);
+        if (i + e < n_cand) v[e] = (uint32_t)(make_key(S, i + e) >> 32);
+        range.add(v[e]);
+      }
+      if (i < C.pitch) *reinterpret_cast<u32x4t*>(C.scores + (size_t)lu * C.pitch + i) = v;
+      if (q < nq) *reinterpret_cast<u32x4t*>(row_word + i) = v;
+    }
+  } else {
+    k_o = P.n_o[gu];
+    k_b = P.nb[gu];
+    for (int i = tid; i < commit_ranges(T); i += 1024) {
+      const uint2 r = C.ranges[(size_t)lu * commit_ranges(T) + i];
+      range.lo = min(range.lo, r.x);
+      range.hi = max(range.hi, r.y);
+    }
   }
-  if constexpr (IN_LDS) {
+  if constexpr (IN_LDS && !SCORES) {
     u32x4t v[kLdsRows / kQuad];              // (all requested together; a thread only reads what it stores here)
 #pragma unroll
     for (int q = 0; q < kLdsRows / kQuad; ++q)
@@ -1045,7 +1082,7 @@ __global__ __launch_bounds__(1024) void k_commit_select(Pools P, CommitLaunch L,
     else return scores[i];
   };
   auto key_of = [&](int i) -> uint64_t { return ((uint64_t)score_of(i) << 32) | (0xFFFFFFFFu - (uint32_t)i); };
-  select_two(nq, load, score_of, key_of, range, P.n_o[gu], P.nb[gu], sel);
+  select_two(nq, load, score_of, key_of, range, k_o, k_b, sel);
   const uint64_t thr_o = sel.thr[0], thr_b = sel.thr[1];
   int4* blocks = C.blocks + (size_t)lu * (rounds + 1);
   int bo = 0, bq = 0, bp = 0;
@@ -1352,16 +1389,22 @@ hipError_t launch_commit(const Pools& P, const CommitLaunch& a, int hkv, const i
     return hipGetLastError();
   }
   const CommitScratch c = commit_scratch(scratch, a.n_units, a.T);
-  hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, c, with_keys ? hkv : 0,
-                     budget_args(n_o_seq, nb_seq, with_keys ? batch : 0));
+  const BudgetArgs budgets = budget_args(n_o_seq, nb_seq, with_keys ? batch : 0);
+  // Short prompts: the selecting workgroup forms its unit's scores itself and a launch falls away (a whole ingest, with / without
+  // the scores' own launch: 8 units x 1000 positions 43.5 / 40.8 us, 32 x 2000 52.3 / 49.3, 8 x 4000 44.3 / 41.8, 8 x 8192 58.0 /
+  // 57.0, 32 x 8192 88.5 / 87.5; beyond that one CU takes longer over 8 bytes a position than the launch).
+  const bool fused = with_keys && a.T <= kFusedRows;
+  if (!fused)
+    hipLaunchKernelGGL(k_commit_keys, dim3((a.T + 255) / 256, a.n_units), dim3(256), 0, s, P, a, c, with_keys ? hkv : 0, budgets);
   int kept = 0;                                             // the most rows that a unit keeps
   for (int i = 0; i < batch; ++i) kept = std::max(kept, std::min(nb_seq[i], a.T - a.window) + a.window);
   // about four workgroups per CU; below 8 rows a workgroup's lists cost more than its rows (8 units x 1000 positions, 500
   // kept: 21 us for the whole commit, 52 in one part per block), above 96 nothing is gained (32 units x 32768 positions,
   // 6152 kept: 89 to 95 us at 64 to 1024 rows; all with an earlier selection that took 2 and 12 us more)
   const int share_rows = clampi((int)((long long)a.n_units * kept / 1024 + 7) / 8 * 8, 8, 96);
-  const hipError_t e = a.T <= kLdsRows ? launch_rows(k_commit_select<true>, dim3(a.n_units), a.T, s, P, a, c, share_rows)
-                                       : launch_rows(k_commit_select<false>, dim3(a.n_units), 0, s, P, a, c, share_rows);
+  const hipError_t e = fused ? launch_rows(k_commit_select<true, true>, dim3(a.n_units), a.T, s, P, a, c, share_rows, hkv, budgets)
+                       : a.T <= kLdsRows ? launch_rows(k_commit_select<true, false>, dim3(a.n_units), a.T, s, P, a, c, share_rows, hkv, budgets)
+                                         : launch_rows(k_commit_select<false, false>, dim3(a.n_units), 0, s, P, a, c, share_rows, hkv, budgets);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)a.n_units * (unsigned)(kept / share_rows + commit_blocks(a.T)));   // (a block's last part may be short)
 #define ARKV_SC(D_, B_)                                                                                                      \

@@ -578,3 +578,41 @@ def test_every_step_policy_rows_of_several_workgroups(hq, hkv, d, bits, n):
     assert wl.capacity == n
     sb = _run(wl, rho=0.4, check_every=7, every_step=True)
     assert all(len(u.pos) == n - 1 for u in sb.oracles[(0, 0)].units)
+
+
+@pytest.mark.parametrize("T,n,window,batch", [(300, 120, 48, 1), (4096, 1000, 32, 2), (4097, 1001, 32, 1), (8191, 700, 48, 1),
+                                              (8192, 700, 16, 1), (8193, 700, 32, 1), (200, 90, 16, 65)])
+def test_commit_scores_are_the_formula_bit_for_bit(T, n, window, batch):
+    """The scores that a commit ranks on, formed by the selecting workgroups (prompts of up to 8192 positions) or by a launch of
+    their own (longer ones, more than 64 sequences): of every survivor, eq. 9's fp32 formula on its exported sums, and the n_o
+    (b) best scores are those that became Original (survived)."""
+    g, hkv, d = 2, 3, 64
+    wl = synth.C1.scaled(name="formula", n_q_heads=g * hkv, n_kv_heads=hkv, head_dim=d, prefill=T, batch=batch, n_layers=1,
+                         window=window, budget_frac=(n + 0.5) / T)
+    assert wl.capacity == n
+    cfg = make_cfg(wl)
+    cache = A.arkv_cache_create(cfg)
+    try:
+        k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+        stats = torch.zeros((batch, 3), dtype=torch.float32, device="cuda")
+        A.arkv_prefill_stats(cache, 0, qw, k, T, synth.softmax_scale(wl, 0), stats)
+        rho = [0.3 + 0.4 * b / batch for b in range(batch)]
+        A.arkv_prefill_commit(cache, 0, k, v, T, rho)
+        units = batch * hkv
+        e = A.arkv_cache_export(cache, 0, cfg, rows=False, codes=False)
+        cnt, pos, score = A.arkv_debug_last_tailor_scores(cache, 0, units, T)
+        for u in range(units):
+            assert cnt[u] == T - window and (pos[u, : cnt[u]] == np.arange(T - window)).all()
+            m = int(e["n_live"][u])
+            p, st = e["pos"][u, :m], e["state"][u, :m]
+            ranked = p < T - window
+            nf = np.float32(g * window)
+            mu, ex2 = e["s1"][u, :m] / nf, e["s2"][u, :m] / nf
+            S = mu + np.float32(cfg.gamma) * np.maximum(ex2 - mu * mu, np.float32(0))
+            assert (S[ranked].view(np.uint32) == score[u, p[ranked]].view(np.uint32)).all()
+            order = np.lexsort((pos[u, : cnt[u]], -score[u, : cnt[u]].astype(np.float64)))     # ties: the older token first
+            n_o, n_q, _ = A.arkv_budget_counts(cfg, rho[u // hkv])
+            original = st == st[-1]                           # (the window's tokens are Original)
+            assert set(order[:n_o]) == set(p[ranked & original]) and set(order[n_o : n_o + n_q]) == set(p[~original])
+    finally:
+        A.arkv_cache_destroy(cache)
