@@ -71,6 +71,7 @@ struct Pools {
   float2*   qacc;       // [LU][capQ]
   // per unit
   int2*     cnt;        // [LU] (tokens in O pool, tokens in Q pool)
+  unsigned long long* cnt_host;   // [LU] pinned host memory: the counts behind the latest decode-time tailor (count_word)
   float2*   fin;        // [kRing][LU][G] (row max in base-2 units, 1/denominator) of the latest steps, ring by step
   size_t    fin_stride; // LU*G
   uint16_t* qprev;      // [kRing][LU][G][D] bf16 queries of the latest steps (the score update recomputes logits)
@@ -131,6 +132,11 @@ struct DecodeLaunch {
   float scale2[kMaxLayersPerLaunch];  // softmax scale * log2(e), per launched layer
 };
 
+// A unit's counts and the name of the tailor that left them, in one word: one store of a kernel, one load of the host.
+__host__ __device__ constexpr unsigned long long count_word(int o, int q, uint16_t seq) {
+  return (unsigned long long)(unsigned)o | (unsigned long long)(unsigned)q << 24 | (unsigned long long)seq << 48;
+}
+
 struct TailorLaunch {
   int unit_begin, n_units;
   int position;       // P of the latest token
@@ -140,7 +146,9 @@ struct TailorLaunch {
   int n_pending, slot;  // pending steps to add to (s1,s2) before ranking; slot the NEXT step would write
   int max_rows;         // no unit holds more rows than this
   int kept;             // 1: the one pending step's logits are in Pools::logit
-  int few_moves;        // 1: each unit moves a few rows, its choosing workgroup does it (with kept)
+  int few_moves;        // 1: each unit moves a few rows, its choosing workgroup does it
+  int tell_host;        // 1: the counts go to Pools::cnt_host as well
+  uint16_t seq[kMaxLayersPerLaunch];   // names of the launched layers' tailors
 };
 
 struct CommitLaunch {

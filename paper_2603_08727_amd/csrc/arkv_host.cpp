@@ -43,12 +43,11 @@ struct LayerState {
   // appends happen; a decode-time tailor makes the split data dependent and invalidates it
   bool cnt_valid = false;
   std::vector<int32_t> cnt_o, cnt_q;   // [U]
-  // after a decode-time tailor the counts are copied back asynchronously; the mirror is valid again once
-  // the copy has landed (checked without waiting at the following steps)
-  int2* cnt_host = nullptr;     // pinned, [U]
-  hipEvent_t cnt_ev = nullptr;
+  // a decode-time tailor stores the counts in pinned host memory, a word per unit that names the tailor; the mirror is valid
+  // again once all words of the latest one are there (checked without waiting at the following steps)
   bool cnt_refresh = false;
-  int cnt_refresh_P = 0;        // position of the step whose tailor the snapshot follows
+  int cnt_refresh_P = 0;        // position of the step whose tailor the words follow
+  uint16_t cnt_seq = 0;         // the latest tailor's name; goes on through resets, so that no older word has it
 };
 
 // Blocks in which a split prefill attention keeps its pieces: the first one at least this large, every later one at least
@@ -64,6 +63,7 @@ struct arkv_cache {
   int L = 0, U = 0, b = 0;
   std::vector<LayerState> layers;
   std::vector<void*> allocs;
+  unsigned long long* cnt_host = nullptr;   // pinned, [L][U]: units' counts after their latest decode-time tailor (count_word)
   // grow-only scratch shared by all layers (calls on one cache are stream-ordered)
   float2* rowstat = nullptr; size_t rowstat_cap = 0;
   float* rowc = nullptr; size_t rowc_cap = 0;
@@ -262,9 +262,10 @@ int arkv_cache_create(const arkv_config* cfg, arkv_cache** out) {
   A(keys, LU * (size_t)(P.capO + P.capQ)) A(thr, LU * 2)
 #undef A
   hipError_t e = hipSuccess;
-  for (auto& ls : c->layers) {
-    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ls.cnt_host), (size_t)c->U * sizeof(int2), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ls.cnt_ev, hipEventDisableTiming);
+  e = hipHostMalloc(reinterpret_cast<void**>(&c->cnt_host), LU * sizeof(unsigned long long), hipHostMallocMapped | hipHostMallocCoherent);
+  if (e == hipSuccess) {
+    memset(c->cnt_host, 0, LU * sizeof(unsigned long long));
+    e = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->P.cnt_host), c->cnt_host, 0);
   }
   // value blocks are read whole, stale slots included (their probabilities are zero): what they hold must be finite
   if (e == hipSuccess) e = hipMemset(P.qvc, 0, LU * P.capQv * CB);
@@ -302,11 +303,9 @@ int arkv_cache_destroy(arkv_cache* c) {
   if (!c) return ARKV_OK;
   (void)hipDeviceSynchronize();
   for (void* p : c->allocs) (void)hipFree(p);
-  for (auto& ls : c->layers) {
+  for (auto& ls : c->layers)
     if (ls.pre) (void)hipFree(ls.pre);
-    if (ls.cnt_host) (void)hipHostFree(ls.cnt_host);
-    if (ls.cnt_ev) (void)hipEventDestroy(ls.cnt_ev);
-  }
+  if (c->cnt_host) (void)hipHostFree(c->cnt_host);
   if (c->rowstat) (void)hipFree(c->rowstat);
   if (c->rowc) (void)hipFree(c->rowc);
   if (c->stat_ticket) (void)hipFree(c->stat_ticket);
@@ -624,9 +623,15 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   for (int i = 0; i < n; ++i) {
     LayerState& li = c->layers[(size_t)(layer_begin + i)];
     if (li.cnt_valid || !li.cnt_refresh) continue;
-    if (hipEventQuery(li.cnt_ev) != hipSuccess) { (void)hipGetLastError(); continue; }   // not landed yet
+    const unsigned long long* words = c->cnt_host + (size_t)(layer_begin + i) * U;
     const int steps = li.P - li.cnt_refresh_P;
-    for (int u = 0; u < U; ++u) { li.cnt_o[(size_t)u] = li.cnt_host[u].x + steps; li.cnt_q[(size_t)u] = li.cnt_host[u].y; }
+    int u = 0;
+    for (; u < U; ++u) {
+      const unsigned long long word = __atomic_load_n(words + u, __ATOMIC_RELAXED);
+      if ((uint16_t)(word >> 48) != li.cnt_seq) break;                 // not there yet
+      li.cnt_o[(size_t)u] = (int)(word & 0xFFFFFF) + steps; li.cnt_q[(size_t)u] = (int)(word >> 24 & 0xFFFFFF);
+    }
+    if (u < U) continue;
     li.cnt_valid = true; li.cnt_refresh = false;
   }
   a.cnt_known = 0;
@@ -676,6 +681,8 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
     t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
     t.kept = a.keep;
+    t.tell_host = cfg.tailor_policy == 0 ? 1 : 0;       // (with a tailor at every step the mirror would never be used)
+    for (int i = 0; i < n; ++i) t.seq[i] = ++c->layers[(size_t)(layer_begin + i)].cnt_seq;
     pools.ticket = c->P.ticket;       // (a static launch's tickets are its own)
     const hipError_t te = launch_tailor(pools, t, st);
     if (te != hipSuccess) {
@@ -693,12 +700,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     for (auto& v : li.cnt_o) v += 1;
     if (tailor) {
       li.n_tailors += 1; li.last_tailor = 2; li.cnt_valid = false; li.cnt_refresh = false;
-      if (cfg.tailor_policy == 0) {       // with a tailor at every step the snapshot would never be used
-        HIP_TRY(hipMemcpyAsync(li.cnt_host, c->P.cnt + (size_t)(layer_begin + i) * U, (size_t)U * sizeof(int2),
-                               hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipEventRecord(li.cnt_ev, st));
-        li.cnt_refresh = true; li.cnt_refresh_P = P;
-      }
+      if (cfg.tailor_policy == 0) { li.cnt_refresh = true; li.cnt_refresh_P = P; }
     }
   }
   c->last_stream = st;

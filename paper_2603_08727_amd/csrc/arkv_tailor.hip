@@ -566,6 +566,13 @@ __device__ __forceinline__ float2 row_sums(const float2* p, bool dev) {
   return dev ? __builtin_bit_cast(float2, ld_dev8(p)) : *p;
 }
 
+// The unit's counts behind its tailor, by one thread.  The host's copy spares a copy of its own behind every tailor.
+__device__ __forceinline__ void publish_counts(const Pools& P, const TailorLaunch& L, int gu, int o, int q) {
+  P.cnt[gu] = make_int2(o, q);
+  if (L.tell_host)
+    __hip_atomic_store(P.cnt_host + gu, count_word(o, q, L.seq[(gu - L.unit_begin) / P.U]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The moves of a unit's tailor.  first: index of this wave among the `waves` that share them.
 // nD demoted rows into free Q slots (TPW tokens per wave at once), nM tail rows of the Q pool into holes.  list(l, i): entry i
 // of a list.
@@ -941,7 +948,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
       const integral_constant<int, 64> d;
       if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
     }
-    if (tid == 0) P.cnt[gu] = make_int2(cOn, cQn);
+    if (tid == 0) publish_counts(P, L, gu, cOn, cQn);
   }
 }
 
@@ -959,7 +966,7 @@ __global__ __launch_bounds__(256) void k_tailor_move_o(Pools P, TailorLaunch L) 
   const int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
   tailor_move_o<D>(P, gu, plan[PL_N_OMOV], blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4, threadIdx.x & 63, false,
                    [&](int l, int i) { return plan[list_begin(P, l) + i]; });
-  if (blockIdx.x == 0 && threadIdx.x == 0) P.cnt[gu] = make_int2(plan[PL_CO_NEW], plan[PL_CQ_NEW]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) publish_counts(P, L, gu, plan[PL_CO_NEW], plan[PL_CQ_NEW]);
 }
 
 // ------------------------------------------------------------------------------------------

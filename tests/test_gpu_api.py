@@ -242,3 +242,48 @@ def test_measurement_hooks():
             assert 0 < us < 1e4
     finally:
         A.arkv_cache_destroy(c)
+
+
+@pytest.mark.parametrize("layers_per_call", [1, 2])
+def test_counts_behind_tailors_reach_the_host_across_resets(layers_per_call):
+    """After a decode-time tailor the host learns the units' counts from words that the kernels store in pinned memory.  A cache
+    that went through tailors, was reset and took another prompt gives the same bits as a fresh one, whether or not the words of
+    the earlier tailors had arrived; so do its counters."""
+    L, hq, hkv, d, T, N, steps = 2, 8, 2, 64, 200, 90, 70
+    wl = synth.C1.scaled(name="words", n_layers=L, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=2, budget_frac=(N + 0.5) / T)
+    assert wl.capacity == N
+    other = wl.scaled(name="words2", seed=wl.seed + 77)
+    cfg = make_cfg(wl)
+
+    def session(cache, w, wait):
+        stats = torch.zeros((w.batch, 3), dtype=torch.float32, device="cuda")
+        for l in range(L):
+            k, v, qw = (t.cuda() for t in synth.prefill_inputs(w, l))
+            A.arkv_prefill_stats(cache, l, qw, k, T, 0.1, stats)
+            A.arkv_prefill_commit(cache, l, k, v, T, [0.4] * w.batch)
+        q, kn, vn = (torch.stack(x).cuda() for x in zip(*[synth.decode_inputs(w, l, steps) for l in range(L)]))
+        outs = torch.zeros((steps, L, w.batch, hq, d), dtype=torch.bfloat16, device="cuda")
+        for i in range(steps):
+            if layers_per_call == L:
+                A.arkv_decode_step_layers(cache, 0, L, q[:, i].contiguous(), kn[:, i].contiguous(), vn[:, i].contiguous(), [0.1] * L, outs[i])
+            else:
+                for l in range(L):
+                    A.arkv_decode_step(cache, l, q[l, i], kn[l, i], vn[l, i], 0.1, outs[i, l])
+            if wait:
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        return outs, [A.arkv_cache_counters(cache, l, w.batch * hkv) for l in range(L)]
+
+    used, fresh = A.arkv_cache_create(cfg), A.arkv_cache_create(cfg)
+    try:
+        session(used, other, wait=False)
+        assert A.arkv_cache_progress(used, 0)[0] >= 3
+        A.arkv_cache_reset(used, -1)
+        a, ca = session(used, wl, wait=False)
+        b, cb = session(fresh, wl, wait=True)
+        assert torch.equal(a, b)
+        for x, y in zip(ca, cb):
+            assert all(np.array_equal(i, j) for i, j in zip(x, y))
+    finally:
+        A.arkv_cache_destroy(used)
+        A.arkv_cache_destroy(fresh)
