@@ -679,7 +679,9 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     // A tailor at every step settles to a few moved rows per unit: the choosing workgroup moves them (3 us instead of a
     // launch's 7.6).  The first ones after a commit move many (32 units x 8192 rows, one workgroup per unit: 41 us at the
     // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
-    t.few_moves = cfg.tailor_policy == 1 && l0.n_tailors > 16 ? 1 : 0;
+    // So does that of a small cache, whose moves are few whatever the policy (a tailor at its natural cadence, two more launches /
+    // the choosing workgroup: 8 units, 250 rows 22 / 19 us, 700 rows 32 / 26; from 2000 rows on no difference).
+    t.few_moves = t.max_rows <= 1024 || (cfg.tailor_policy == 1 && l0.n_tailors > 16) ? 1 : 0;
     t.kept = a.keep;
     t.tell_host = cfg.tailor_policy == 0 ? 1 : 0;       // (with a tailor at every step the mirror would never be used)
     for (int i = 0; i < n; ++i) t.seq[i] = ++c->layers[(size_t)(layer_begin + i)].cnt_seq;

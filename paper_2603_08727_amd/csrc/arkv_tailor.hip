@@ -679,7 +679,7 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
   __shared__ __align__(16) SelectLds<typename std::conditional<IN_LDS, uint16_t, uint32_t>::type> sel;
   __shared__ uint32_t scan_sm[3][16];
   __shared__ int tot[3];
-  __shared__ int32_t near_list[kMoveLists][KEPT ? kNearList : 1];
+  __shared__ int32_t near_list[kMoveLists][kNearList];
   const int gu = L.unit_begin + blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int parts = IN_LDS && KEPT ? (int)gridDim.y : 1, part = blockIdx.y;
   const int2 cnt = P.cnt[gu];
@@ -877,9 +877,9 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
 
   int32_t* plan = P.plan + (size_t)gu * P.plan_stride;
   // a list's first entries stay in LDS where this workgroup makes the moves
-  const bool here = KEPT && L.few_moves;
+  const bool here = L.few_moves;
   auto put = [&](int l, int i, int32_t v) {
-    if (KEPT && here && i < kNearList) near_list[l][i] = v;
+    if (here && i < kNearList) near_list[l][i] = v;
     else plan[list_begin(P, l) + i] = v;
   };
   int base_hole = 0, base_mov = 0, base_dem = 0, base_free = 0, base_qmov = 0;
@@ -931,25 +931,23 @@ __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L)
     plan[PL_N_QMOV] = base_qmov; plan[PL_N_OMOV] = base_mov;
     plan[PL_CO_OLD] = cO; plan[PL_CQ_OLD] = cQ;
   }
-  if constexpr (KEPT) {
-    if (!L.few_moves) return;
-    __syncthreads();                                        // the lists
-    auto list = [&](int l, int i) { return i < kNearList ? near_list[l][i] : plan[list_begin(P, l) + i]; };
-    auto moves = [&](auto d, auto bits) {
-      tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane, parts > 1, list);
-      __syncthreads();                                      // every demoted row has been read
-      tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane, parts > 1, list);
-    };
-    using std::integral_constant;
-    if (P.D == 128) {
-      const integral_constant<int, 128> d;
-      if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
-    } else {
-      const integral_constant<int, 64> d;
-      if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
-    }
-    if (tid == 0) publish_counts(P, L, gu, cOn, cQn);
+  if (!here) return;
+  __syncthreads();                                        // the lists
+  auto list = [&](int l, int i) { return i < kNearList ? near_list[l][i] : plan[list_begin(P, l) + i]; };
+  auto moves = [&](auto d, auto bits) {
+    tailor_move_q<decltype(d)::value, decltype(bits)::value>(P, gu, nD, base_qmov, w, 16, lane, parts > 1, list);
+    __syncthreads();                                      // every demoted row has been read
+    tailor_move_o<decltype(d)::value>(P, gu, base_mov, w, 16, lane, parts > 1, list);
+  };
+  using std::integral_constant;
+  if (P.D == 128) {
+    const integral_constant<int, 128> d;
+    if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
+  } else {
+    const integral_constant<int, 64> d;
+    if (P.bits == 4) moves(d, integral_constant<int, 4>()); else if (P.bits == 2) moves(d, integral_constant<int, 2>()); else moves(d, integral_constant<int, 8>());
   }
+  if (tid == 0) publish_counts(P, L, gu, cOn, cQn);
 }
 
 template <int D, int BITS>
@@ -1326,7 +1324,7 @@ hipError_t launch_tailor(const Pools& P, const TailorLaunch& a, hipStream_t s) {
   switch (P.G) { ARKV_CH(1) ARKV_CH(2) ARKV_CH(4) ARKV_CH(8) }
   if (e != hipSuccess) return e;
 #undef ARKV_CH
-  if (a.kept && a.few_moves) return hipSuccess;             // done by the choosing workgroups
+  if (a.few_moves) return hipSuccess;                       // done by the choosing workgroups
   if (P.D == 128 && P.bits == 4) launch_tailor_moves<128, 4>(P, a, s);
   else if (P.D == 128 && P.bits == 2) launch_tailor_moves<128, 2>(P, a, s);
   else if (P.D == 64 && P.bits == 4) launch_tailor_moves<64, 4>(P, a, s);
