@@ -470,12 +470,15 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
   L.stats[b * 3 + 2] = m2 > 0 ? (float)(m4 / (m2 * m2)) : 0.f;
 }
 
-// Up to this many key chunks the column pass merges the first pass's partials itself (one batch of loads in its prologue)
-// and k_prefill_rowfinal, a launch of 5 us, is left out: 2000 keys x 8 units 20.6 -> 18.5 us.  With more chunks every
-// workgroup of the column pass reads more than the launch costs to save (32 chunks: 130 us either way).
+// Up to kMergeChunks key chunks, or more of them in a launch of up to kMergeGrid workgroups, the column pass merges the first
+// pass's partials itself (in its prologue, 16 to a batch of loads) and k_prefill_rowfinal, a launch of 5 us, is left out.
+// Otherwise every workgroup of the column pass reads more than the launch costs.  Merged / with the launch, us: 8 units x 4000
+// keys (32 chunks) 20.2 / 22.3, 2 x 3000 17.4 / 20.2, 32 x 32768 (32) 112.6 / 115.5, 8 x 10000 (79
+// chunks, 632 workgroups) 33.6 / 35.1, 2 x 32768 (256, 512) 34.9 / 38.8; 16 x 8192 (64, 1024) 43.9 / 43.9, 8 x 16384 (128, 1024)
+// 50.4 / 46.8, 24 x 10000 (79, 1896) 66.3 / 61.1, 32 x 6000 (47, 1504) 51.5 / 50.6.
 // The two add a row's partials in different orders, so a row constant, and with it a score, can differ in its last bit from
 // what the other gives.
-constexpr int kMergeChunks = 16;
+constexpr int kMergeChunks = 32, kMergeGrid = 640;
 
 template <int D, int RT>
 static hipError_t launch_prefill_t(const PrefillLaunch& a, float* rowc, hipStream_t s) {
@@ -506,7 +509,7 @@ static hipError_t launch_prefill_t(const PrefillLaunch& a, float* rowc, hipStrea
 // rowc: scratch [U][MP] floats followed by U*n_chunks + 3*B*ceil((T-W)/512) doubles for the statistics partials
 hipError_t launch_prefill_stats(const PrefillLaunch& launch, float* rowc, hipStream_t s) {
   PrefillLaunch a = launch;
-  a.merge_rows = !a.have_rowc && a.n_chunks <= kMergeChunks ? 1 : 0;
+  a.merge_rows = !a.have_rowc && (a.n_chunks <= kMergeChunks || (long long)a.n_chunks * a.B * a.Hkv <= kMergeGrid) ? 1 : 0;
   const int M = a.G * a.W;
   int RT = 1;
   while (RT * 32 < M) RT *= 2;

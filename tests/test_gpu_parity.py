@@ -616,3 +616,25 @@ def test_commit_scores_are_the_formula_bit_for_bit(T, n, window, batch):
             assert set(order[:n_o]) == set(p[ranked & original]) and set(order[n_o : n_o + n_q]) == set(p[~original])
     finally:
         A.arkv_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("hq,hkv,batch,d,T", [(4, 1, 1, 128, 4096), (4, 1, 1, 128, 4097), (8, 2, 1, 64, 9000), (8, 1, 1, 64, 20000),
+                                              (40, 20, 1, 64, 4096), (40, 20, 1, 64, 4097)])
+def test_row_constants_of_many_chunks(hq, hkv, batch, d, T):
+    """The scorer's row constants put together from 32, 33 and more chunks of 128 keys, by the column pass (up to 32 chunks or 640
+    workgroups) or by a launch of their own, against the few chunks of 4096 keys.  A row constant is at most 2^6 here, so its last
+    bit is 4e-6 and a probability's relative error 2.7e-6; the kurtosis has the fourth power."""
+    wl = synth.C1.scaled(name="chunks", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=batch, n_layers=1, budget_frac=0.25)
+    k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+    got = []
+    for chunk in (128, 4096):
+        cache = A.arkv_cache_create(make_cfg(wl))
+        try:
+            A.arkv_debug_set_launch_shape(cache, prefill_chunk=chunk)
+            stats = torch.zeros((batch, 3), dtype=torch.float32, device="cuda")
+            A.arkv_prefill_stats(cache, 0, qw, k, T, synth.softmax_scale(wl, 0), stats)
+            torch.cuda.synchronize()
+            got.append(stats.cpu().numpy())
+        finally:
+            A.arkv_cache_destroy(cache)
+    assert np.all(np.isfinite(got[0])) and np.all(np.abs(got[0] - got[1]) <= 4 * 2.7e-6 * np.abs(got[1]))
