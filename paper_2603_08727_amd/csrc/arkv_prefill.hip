@@ -417,14 +417,18 @@ __device__ __forceinline__ double ld_dev_d(const double* p) { return __hip_atomi
 constexpr int kStatChunk = 512;    // keys per workgroup
 // Bound by its chain of round trips and barriers (keys' loads, normaliser, sums, ticket, sums): the keys' loads go out
 // before the normaliser is reduced and the three sums share their barriers (2000 keys x 8 heads: 13 -> 8 us).
+// Up to 1024 keys one workgroup does it all and the chain ends with the first sums: no ticket, no second reading (the whole
+// scorer, 8 heads x 400 keys 19.1 -> 17.5 us, x 600 19.1 -> 17.8, x 1000 19.0 -> 18.5; with 1024 threads for up to 2048 keys the
+// logarithms took longer than that saves, 2000 keys 18.7 -> 20.4).
 
+template <int KPT>                  // keys per thread
 __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const double* zpart, double* mpart) {
   __shared__ double sm[16];
   __shared__ int last;
   const int b = blockIdx.y, ch = blockIdx.x, n = L.T - L.W, nch = gridDim.x;
   const float2* pre = L.pre + (size_t)b * L.Hkv * L.T;
   // the keys' sums over the heads do not wait for the normaliser: their loads are on the way while it is reduced
-  constexpr int KPT = kStatChunk / 256;
+  constexpr int kChunk = 256 * KPT;
   double c[KPT];
 #pragma unroll
   for (int i = 0; i < KPT; ++i) c[i] = 0;
@@ -432,7 +436,7 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
   for (int g = 0; g < L.Hkv; ++g)
 #pragma unroll
     for (int i = 0; i < KPT; ++i)
-      c[i] += (double)pre[(size_t)g * L.T + min(ch * kStatChunk + (int)threadIdx.x + 256 * i, n - 1)].x;
+      c[i] += (double)pre[(size_t)g * L.T + min(ch * kChunk + (int)threadIdx.x + 256 * i, n - 1)].x;
   double Z = 0;
   for (int i = threadIdx.x; i < L.Hkv * L.n_chunks; i += 256) Z += zpart[(size_t)b * L.Hkv * L.n_chunks + i];
   Z = block_sum_d(Z, sm);
@@ -440,7 +444,7 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
   double m[3] = {0, 0, 0};            // sums of -p ln p, (p - pbar)^2, (p - pbar)^4
 #pragma unroll
   for (int i = 0; i < KPT; ++i) {
-    if (ch * kStatChunk + (int)threadIdx.x + 256 * i < n) {
+    if (ch * kChunk + (int)threadIdx.x + 256 * i < n) {
       const double p = c[i] / Z;
       if (p > 0) m[0] -= p * log(p);
       const double d = p - pbar, d2 = d * d;
@@ -448,22 +452,24 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
     }
   }
   block_sums_d(m, sm);
-  if (threadIdx.x == 0) {
-    double* o = mpart + ((size_t)b * nch + ch) * 3;
-    st_dev_d(o, m[0]); st_dev_d(o + 1, m[1]); st_dev_d(o + 2, m[2]);
-    __builtin_amdgcn_s_waitcnt(0);                    // the partials are at the device's coherence point
-    last = __hip_atomic_fetch_add(L.stat_ticket + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nch - 1;
+  if (nch > 1) {                                      // (uniform)
+    if (threadIdx.x == 0) {
+      double* o = mpart + ((size_t)b * nch + ch) * 3;
+      st_dev_d(o, m[0]); st_dev_d(o + 1, m[1]); st_dev_d(o + 2, m[2]);
+      __builtin_amdgcn_s_waitcnt(0);                    // the partials are at the device's coherence point
+      last = __hip_atomic_fetch_add(L.stat_ticket + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nch - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    m[0] = m[1] = m[2] = 0;
+    for (int i = threadIdx.x; i < nch; i += 256) {
+      const double* o = mpart + ((size_t)b * nch + i) * 3;
+      m[0] += ld_dev_d(o); m[1] += ld_dev_d(o + 1); m[2] += ld_dev_d(o + 2);
+    }
+    block_sums_d(m, sm);
+    if (threadIdx.x == 0) __hip_atomic_store(L.stat_ticket + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
   }
-  __syncthreads();
-  if (!last) return;
-  m[0] = m[1] = m[2] = 0;
-  for (int i = threadIdx.x; i < nch; i += 256) {
-    const double* o = mpart + ((size_t)b * nch + i) * 3;
-    m[0] += ld_dev_d(o); m[1] += ld_dev_d(o + 1); m[2] += ld_dev_d(o + 2);
-  }
-  block_sums_d(m, sm);
   if (threadIdx.x != 0) return;
-  __hip_atomic_store(L.stat_ticket + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
   const double m2 = m[1] / (double)n, m4 = m[2] / (double)n;
   L.stats[b * 3 + 0] = (float)m[0];
   L.stats[b * 3 + 1] = (float)m2;
@@ -498,11 +504,14 @@ static hipError_t launch_prefill_t(const PrefillLaunch& a, float* rowc, hipStrea
     hipLaunchKernelGGL((k_prefill_rows<D, RT, NW>), grid, dim3(64 * NW), shm, s, a);
     if (!a.merge_rows) hipLaunchKernelGGL(k_prefill_rowfinal, dim3(MP / 32, U), dim3(256), 0, s, a, MP, rowc);
   }
-  const int nch = (a.T - a.W + kStatChunk - 1) / kStatChunk;
+  const int n = a.T - a.W;
+  const bool one = n > kStatChunk && n <= 2 * kStatChunk;      // one workgroup of twice the keys: no ticket
+  const int nch = one ? 1 : (n + kStatChunk - 1) / kStatChunk;
   double* zpart = reinterpret_cast<double*>(rowc + (size_t)U * MP);      // [U][n_chunks], then [B][nch][3]
   double* mpart = zpart + (size_t)U * a.n_chunks;
   hipLaunchKernelGGL((k_prefill_cols<D, RT, NW>), grid, dim3(64 * NW), shm + (size_t)MP * 8, s, a, (const float*)rowc, zpart);
-  hipLaunchKernelGGL(k_prefill_stats, dim3(nch, a.B), dim3(256), 0, s, a, (const double*)zpart, mpart);
+  if (one) hipLaunchKernelGGL(k_prefill_stats<2 * kStatChunk / 256>, dim3(nch, a.B), dim3(256), 0, s, a, (const double*)zpart, mpart);
+  else hipLaunchKernelGGL(k_prefill_stats<kStatChunk / 256>, dim3(nch, a.B), dim3(256), 0, s, a, (const double*)zpart, mpart);
   return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@ import torch
 from paper_2603_08727_amd import binding as A
 from paper_2603_08727_amd import synth
 from helpers import SideBySide, make_cfg
+from oracle import arkv_oracle as O
 
 pytestmark = pytest.mark.gpu
 
@@ -638,3 +639,25 @@ def test_row_constants_of_many_chunks(hq, hkv, batch, d, T):
         finally:
             A.arkv_cache_destroy(cache)
     assert np.all(np.isfinite(got[0])) and np.all(np.abs(got[0] - got[1]) <= 4 * 2.7e-6 * np.abs(got[1]))
+
+
+@pytest.mark.parametrize("T", [40, 544, 545, 1056, 1057, 2080])
+def test_statistics_at_the_ends_of_their_workgroups(T):
+    """A sequence's statistics come from one workgroup for 512 (1024) keys in front of the window, else from several whose last
+    one adds them up: both sides of every line, a few keys, several sequences, twice in a row.  From 32-bit probabilities the three
+    numbers are a few 1e-7 off; 1e-5 is what their order of summation could make of it."""
+    wl = synth.C1.scaled(name=f"stats{T}", prefill=T, batch=3, n_layers=1, budget_frac=2.0)
+    cache = A.arkv_cache_create(make_cfg(wl))
+    try:
+        k, v, qw = synth.prefill_inputs(wl, 0)
+        scale = synth.softmax_scale(wl, 0)
+        for _ in range(2):
+            stats = torch.zeros((wl.batch, 3), dtype=torch.float32, device="cuda")
+            A.arkv_prefill_stats(cache, 0, qw.cuda(), k.cuda(), T, scale, stats)
+            got = stats.cpu().numpy()
+            for b in range(wl.batch):
+                a = O.window_attention(synth.to_numpy_f32(qw[b]), synth.to_numpy_f32(k[b]), scale, wl.group)
+                ref = np.array(O.layer_statistics(a, wl.window)[:3])
+                assert np.all(np.abs(got[b] - ref) <= 1e-5 * np.abs(ref) + 1e-30)
+    finally:
+        A.arkv_cache_destroy(cache)
