@@ -287,3 +287,32 @@ def test_counts_behind_tailors_reach_the_host_across_resets(layers_per_call):
     finally:
         A.arkv_cache_destroy(used)
         A.arkv_cache_destroy(fresh)
+
+
+def test_static_steps_with_scores_of_several_workgroups():
+    """A static step's own tickets are not those of the tailor behind it, whose rows are scored by several workgroups: the same
+    bits as the other entry point, through the first tailors (moves in launches of their own) and the later ones."""
+    N, T, steps = 4300, 4800, 20
+    wl = synth.C1.scaled(name="static_parts", n_q_heads=8, n_kv_heads=2, head_dim=64, prefill=T, batch=2, n_layers=1, budget_frac=(N + 0.5) / T)
+    cfg = make_cfg(wl, every_step=True)
+    k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+    q, kn, vn = (t.cuda() for t in synth.decode_inputs(wl, 0, steps))
+    caches = [A.arkv_cache_create(cfg) for _ in range(2)]
+    try:
+        outs = []
+        for cache, step in zip(caches, (A.arkv_decode_step, A.arkv_decode_step_static)):
+            stats = torch.zeros((wl.batch, 3), dtype=torch.float32, device="cuda")
+            A.arkv_prefill_stats(cache, 0, qw, k, T, 0.1, stats)
+            A.arkv_prefill_commit(cache, 0, k, v, T, [0.5] * wl.batch)
+            out = torch.zeros((steps,) + tuple(q[0].shape), dtype=torch.bfloat16, device="cuda")
+            for i in range(steps):
+                step(cache, 0, q[i], kn[i], vn[i], 0.1, out[i])
+            torch.cuda.synchronize()
+            outs.append((out, A.arkv_cache_export(cache, 0, cfg)))
+        assert torch.equal(outs[0][0], outs[1][0])
+        for name in outs[0][1]:
+            assert np.array_equal(outs[0][1][name], outs[1][1][name]), name
+        assert A.arkv_cache_progress(caches[0], 0)[0] == 1 + steps
+    finally:
+        for cache in caches:
+            A.arkv_cache_destroy(cache)
