@@ -1005,7 +1005,7 @@ __device__ __forceinline__ uint32_t commit_parts(uint32_t survivors, int share_r
 }
 
 // One workgroup per unit: 23 us for 32 units x 32768 positions, of which 15.7 between a workgroup's first instruction and its
-// last (scores into LDS 1.9, selection 9.4, blocks 4.4) and the rest is the launch's start and end; 3.5 less since one wave ranks
+// last (scores into LDS 1.9, selection 9.4, blocks 4.4) and the rest is the launch's start and end; 21.4 since one wave ranks
 // the last candidates.  35 us with digits of the
 // plain score, one score per LDS read and 64-bit keys in memory (whole commits of 32 x 32768 88 -> 74 us, 8 x 131072 159 -> 96,
 // 8 x 1000 20.2 -> 19.4).  The two thresholds of a unit, and per block of 1024 positions (blocks [units][rounds + 1], the
