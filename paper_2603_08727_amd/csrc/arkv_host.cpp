@@ -43,7 +43,7 @@ struct LayerState {
   // appends happen; a decode-time tailor makes the split data dependent and invalidates it
   bool cnt_valid = false;
   std::vector<int32_t> cnt_o, cnt_q;   // [U]
-  // a decode-time tailor stores the counts in pinned host memory, a word per unit that names the tailor; the mirror is valid
+  // a decode-time tailor that is not captured stores the counts in pinned host memory, a word per unit that names the tailor; the mirror is valid
   // again once all words of the latest one are there (checked without waiting at the following steps)
   bool cnt_refresh = false;
   int cnt_refresh_P = 0;        // position of the step whose tailor the words follow
@@ -398,6 +398,13 @@ int arkv_prefill_stats_lse(arkv_cache* c, int32_t layer, const void* q_win, cons
                     nullptr, 1, lse);
 }
 
+// Whether what is launched on the stream now goes into a graph (also where that cannot be told).
+static bool being_captured(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return true; }
+  return cap != hipStreamCaptureStatusNone;
+}
+
 // Scratch for the pieces of a prefill attention: the smallest block that holds them, allocated if there is none.  A call
 // that is captured leaves its block's address in the graph, so no block is freed before the cache is; the sizes double, so
 // the blocks of a cache are less than 256 MB together.  The allocation must not break a capture on another stream (in the
@@ -410,10 +417,7 @@ static float* attn_scratch(arkv_cache* c, size_t floats, hipStream_t s) {
     if (c->attn_block[i].floats >= floats) return c->attn_block[i].p;
     size = std::max(floats, std::min(2 * c->attn_block[i].floats, kAttnPartFloats));
   }
-  if (i == kAttnBlocks) return nullptr;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
-  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  if (i == kAttnBlocks || being_captured(s)) return nullptr;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   void* p = nullptr;
@@ -670,6 +674,10 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
   const int P = l0.P + 1, live = l0.live + 1;
   const int n_pending = (a.fold ? 0 : l0.n_pending) + 1, slot = (l0.slot + 1) % kRing;
   int live_after = live;
+  // Whether the host learns the counts behind this step's tailor.  Not with a tailor at every step, where the mirror would
+  // never be used, and not from a captured one: its words would carry one name at every replay, and an earlier replay's
+  // would be taken for the latest one's.
+  const bool tell = tailor && cfg.tailor_policy == 0 && !being_captured(st);
   if (tailor) {
     TailorLaunch t;
     t.unit_begin = a.unit_begin; t.n_units = a.n_units;
@@ -683,8 +691,12 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     // the choosing workgroup: 8 units, 250 rows 22 / 19 us, 700 rows 32 / 26; from 2000 rows on no difference).
     t.few_moves = t.max_rows <= 1024 || (cfg.tailor_policy == 1 && l0.n_tailors > 16) ? 1 : 0;
     t.kept = a.keep;
-    t.tell_host = cfg.tailor_policy == 0 ? 1 : 0;       // (with a tailor at every step the mirror would never be used)
-    for (int i = 0; i < n; ++i) t.seq[i] = ++c->layers[(size_t)(layer_begin + i)].cnt_seq;
+    t.tell_host = tell ? 1 : 0;
+    for (int i = 0; i < n; ++i) {
+      LayerState& li = c->layers[(size_t)(layer_begin + i)];
+      if (tell) ++li.cnt_seq;
+      t.seq[i] = li.cnt_seq;
+    }
     pools.ticket = c->P.ticket;       // (a static launch's tickets are its own)
     const hipError_t te = launch_tailor(pools, t, st);
     if (te != hipSuccess) {
@@ -702,7 +714,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     for (auto& v : li.cnt_o) v += 1;
     if (tailor) {
       li.n_tailors += 1; li.last_tailor = 2; li.cnt_valid = false; li.cnt_refresh = false;
-      if (cfg.tailor_policy == 0) { li.cnt_refresh = true; li.cnt_refresh_P = P; }
+      if (tell) { li.cnt_refresh = true; li.cnt_refresh_P = P; }
     }
   }
   c->last_stream = st;

@@ -316,3 +316,73 @@ def test_static_steps_with_scores_of_several_workgroups():
     finally:
         for cache in caches:
             A.arkv_cache_destroy(cache)
+
+
+def test_eager_steps_behind_a_replayed_tailor():
+    """A graph that holds a prompt's commit and steps through a tailor serves two prompts in turn.  The eager steps behind the
+    second replay are launched before its tailor has run, when all that the host could know are the first prompt's counts: the
+    same bits as without a graph."""
+    T, N, steps = 400, 150, 60
+    wl = synth.C1.scaled(name="replayed", n_q_heads=8, n_kv_heads=4, head_dim=64, prefill=T, batch=2, n_layers=1, budget_frac=(N + 0.5) / T)
+    assert wl.capacity == N
+    prompts = [synth.prefill_inputs(w, 0) for w in (wl, wl.scaled(name="replayed2", seed=wl.seed + 91))]
+    q, kn, vn = (t.cuda() for t in synth.decode_inputs(wl, 0, steps))
+    k, v, qw = (t.cuda() for t in prompts[0])
+    stats = torch.zeros((wl.batch, 3), dtype=torch.float32, device="cuda")
+    outs = torch.zeros((steps, wl.batch, 8, 64), dtype=torch.bfloat16, device="cuda")
+    cfg = make_cfg(wl)
+
+    def ingest(cache):
+        A.arkv_prefill_stats(cache, 0, qw, k, T, 0.1, stats)
+        A.arkv_prefill_commit(cache, 0, k, v, T, [0.4] * wl.batch)
+
+    def step(cache, i):
+        A.arkv_decode_step(cache, 0, q[i], kn[i], vn[i], 0.1, outs[i])
+
+    def load(i):
+        for dst, src in zip((k, v, qw), prompts[i]):
+            dst.copy_(src)
+
+    graphed, plain = A.arkv_cache_create(cfg), A.arkv_cache_create(cfg)
+    try:
+        ingest(graphed)                                     # (the scratch of scorer and commit)
+        A.arkv_cache_reset(graphed, 0)
+        torch.cuda.synchronize()
+        first = 0                                           # steps of the graph: up to its tailor
+        s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            ingest(graphed)
+            while A.arkv_cache_progress(graphed, 0)[0] < 2:
+                step(graphed, first)
+                first += 1
+        assert 2 < first < steps - 10
+        counts = []
+        busy = torch.randn(4096, 4096, device="cuda")
+        for i in range(2):
+            torch.cuda.synchronize()
+            load(i)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(s):
+                if i == 1:
+                    for _ in range(20):                     # the replay waits behind some 10 ms of work
+                        busy @ busy
+                graph.replay()
+                if i == 1:
+                    for j in range(first, steps):
+                        step(graphed, j)
+            torch.cuda.synchronize()
+            if i == 0:
+                counts.append(A.arkv_cache_counters(graphed, 0, wl.batch * 4))
+        got, end = outs.clone(), A.arkv_cache_counters(graphed, 0, wl.batch * 4)
+        ingest(plain)
+        for j in range(steps):
+            step(plain, j)
+            if j == first - 1:
+                counts.append(A.arkv_cache_counters(plain, 0, wl.batch * 4))
+        torch.cuda.synchronize()
+        assert not np.array_equal(counts[0][0], counts[1][0])            # (the prompts' counts do differ there)
+        assert torch.equal(got, outs)
+        assert all(np.array_equal(a, b) for a, b in zip(end, A.arkv_cache_counters(plain, 0, wl.batch * 4)))
+    finally:
+        A.arkv_cache_destroy(graphed)
+        A.arkv_cache_destroy(plain)
