@@ -117,8 +117,8 @@ int arkv_prefill_stats_lse(arkv_cache* cache, int32_t layer, const void* q_win, 
  * stats == NULL: attention only.  stats != NULL ([B][3] DEVICE fp32, needs T_q >= W, T > W, layer not
  * committed): the call also does what arkv_prefill_stats does for the last W queries; the softmax maxima and
  * sums of those rows come out of the attention pass, so the scorer reads the keys once instead of twice.
- * Calls with few query rows against many keys split a row's keys over workgroups and merge the parts in fp32 (from
- * about 1000 keys; by shape alone).  A part has a softmax reference of its own, against which its probabilities are rounded
+ * Calls with few query rows against many keys split a row's keys over workgroups and merge the parts in fp32 (on
+ * 993 keys or more, by shape alone: a prompt of up to 992 tokens gives the same bits however it is cut into chunks).  A part has a softmax reference of its own, against which its probabilities are rounded
  * to fp16, so such a row differs from the same row of an unsplit call by the roundings of its probabilities and by the
  * order of its fp32 sums (2e-4 of the output's 2-norm at 512 queries x 16411 keys; equally far from the exact result).
  * The parts' scratch belongs to the cache: blocks of up to 128 MB (less than 256 MB together), allocated on first use

@@ -232,6 +232,17 @@ def test_attention_split_pieces():
             A.arkv_debug_attention_split(*bad)
 
 
+def test_attention_split_leaves_short_prompts_whole():
+    """No call on up to 992 keys is split, whatever its queries, so that cutting such a prompt into chunks changes no bit;
+    from there on some are."""
+    for d in (64, 128):
+        for g in (1, 2, 4, 8):
+            for units in (1, 2, 6, 8, 32):
+                for T in (850, 897, 900, 929, 960, 961, 991, 992):
+                    assert all(A.arkv_debug_attention_split(d, g, units, T, T_q)[0] == 0 for T_q in range(1, T + 1))
+            assert any(A.arkv_debug_attention_split(d, g, 1, T, 32)[0] for T in (993, 1300))
+
+
 def test_phase_trace_names_the_launches_that_update_the_scores():
     """The library adds the waiting steps when kRing - 1 of them wait (and then the step itself waits)."""
     import subprocess

@@ -230,6 +230,19 @@ def test_attention_whole_prompt_and_chunks_agree_bitwise_600():
     assert torch.equal(out, out2)
 
 
+@pytest.mark.parametrize("hq,hkv,d,T", [(4, 4, 64, 992), (8, 1, 128, 961), (8, 2, 128, 930)])
+def test_attention_cuts_of_the_longest_unsplit_prompts(hq, hkv, d, T):
+    """Prompts of up to 992 tokens in one call and in chunks, the last ones of few queries against nearly all keys: same bits."""
+    wl = synth.C1.scaled(name="cuts", n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=1, budget_frac=2.0)
+    k, v, qw = synth.prefill_inputs(wl, 0)
+    q = _full_queries(wl, 0, qw)
+    scale = synth.softmax_scale(wl, 0)
+    out = _run_attention(wl, q, k, v, scale, T, T)
+    assert _check_rows(out, q, k, v, scale, hq // hkv, np.array([0, 500, T - 1]), 0) <= TOL
+    for a in (T - 131, T - 33, T - 32, T - 1):
+        assert torch.equal(out[:, :, a:], _run_attention(wl, q[:, :, a:], k, v, scale, T - a, T)), a
+
+
 @pytest.mark.parametrize("seed", range(12))
 def test_attention_drawn_shapes_and_chunks(seed):
     """Drawn group size, head dimension, prompt length, batch and chunking: sampled rows against the oracle and
