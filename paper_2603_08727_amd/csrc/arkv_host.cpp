@@ -566,13 +566,19 @@ static int split_factor(const arkv_cache* c, int32_t layer_begin, int32_t n, int
   return std::max(1, std::min(splits, c->P.max_splits));
 }
 
+// No unit of these layers holds more rows at a tailor: N under a token budget; under a byte budget N are booked and `extra`
+// more can be held.
+static int most_rows(const arkv_cache* c, int32_t layer_begin, int32_t n) {
+  int extra = 0;
+  for (int i = 0; i < n; ++i) extra = std::max(extra, c->layers[(size_t)(layer_begin + i)].extra);
+  return c->cfg.capacity_tokens + extra;
+}
+
 // Where the logits of a launch that ends with a tailor lie between its attention and the tailor's choosing kernel: in the units'
 // plans, which that kernel writes behind its last read of a logit, if a plan is large enough for a unit's rows.  false: nowhere.
 static bool logit_place(const arkv_cache* c, int32_t layer_begin, int32_t n, Pools* P) {
   if (c->cfg.tailor_policy != 1) return false;
-  int extra = 0;
-  for (int i = 0; i < n; ++i) extra = std::max(extra, c->layers[(size_t)(layer_begin + i)].extra);
-  if (((size_t)c->cfg.capacity_tokens + (size_t)extra) * (size_t)P->G <= (size_t)P->plan_stride) {
+  if ((size_t)most_rows(c, layer_begin, n) * (size_t)P->G <= (size_t)P->plan_stride) {
     P->logit = reinterpret_cast<float*>(P->plan); P->logit_stride = P->plan_stride; P->logit_unit0 = 0;
     return true;
   }
@@ -683,7 +689,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     t.unit_begin = a.unit_begin; t.n_units = a.n_units;
     t.position = P; t.t_prefill = l0.T; t.window = W; t.gamma = cfg.gamma;
     t.n_pending = n_pending; t.slot = slot;
-    t.max_rows = cfg.budget_mode == 1 ? c->P.capO + c->P.capQ : N;      // live <= N in token mode
+    t.max_rows = most_rows(c, layer_begin, n);
     // A tailor at every step settles to a few moved rows per unit: the choosing workgroup moves them (3 us instead of a
     // launch's 7.6).  The first ones after a commit move many (32 units x 8192 rows, one workgroup per unit: 41 us at the
     // first, 17 at the twelfth, against 12 us for two launches over the whole chip).

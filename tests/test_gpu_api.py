@@ -1,5 +1,7 @@
 """GPU tests of the C ABI beyond plain parity: the multi-layer entry point, call-order errors,
 bitwise repeatability, reset and re-commit, the measurement hooks."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -386,3 +388,51 @@ def test_eager_steps_behind_a_replayed_tailor():
     finally:
         A.arkv_cache_destroy(graphed)
         A.arkv_cache_destroy(plain)
+
+
+def _launches(cache, step):
+    """Kernels that a step launches: the nodes of the graph that captures it (which is not run, so the cache is done with)."""
+    lib, s = A.load(), torch.cuda.Stream()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        assert lib.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 2) == 0
+        try:
+            step()
+        finally:
+            assert lib.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph)) == 0
+    assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert lib.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+def _launches_of_a_tailor(cfg, T, rho):
+    """A prompt of T tokens of one layer, steps up to the first tailor behind it, and what the step that ends with it launches."""
+    wl = synth.C1.scaled(name="tailor_launches", n_layers=1, batch=cfg.batch, n_q_heads=cfg.n_q_heads, n_kv_heads=cfg.n_kv_heads,
+                         head_dim=cfg.head_dim, prefill=T)
+    k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, 0))
+    q, kn, vn = (t.cuda() for t in synth.decode_inputs(wl, 0, 1))
+    cache = A.arkv_cache_create(cfg)
+    try:
+        stats = torch.zeros((wl.batch, 3), dtype=torch.float32, device="cuda")
+        out = torch.zeros_like(q[0])
+        A.arkv_prefill_stats(cache, 0, qw, k, T, 0.1, stats)
+        A.arkv_prefill_commit(cache, 0, k, v, T, [rho] * wl.batch)
+        while A.arkv_cache_progress(cache, 0)[1] + 1 < cfg.capacity_tokens:
+            A.arkv_decode_step(cache, 0, q[0], kn[0], vn[0], 0.1, out)
+        tailors = A.arkv_cache_progress(cache, 0)[0]
+        n = _launches(cache, lambda: A.arkv_decode_step(cache, 0, q[0], kn[0], vn[0], 0.1, out))
+        assert A.arkv_cache_progress(cache, 0)[0] == tailors + 1
+        return n
+    finally:
+        A.arkv_cache_destroy(cache)
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_tailor_of_a_small_byte_budget_goes_by_the_rows_it_can_hold(policy):
+    """A unit of 250 rows' bytes holds some 600 rows at most with this ratio, however many more its pools have room for: its tailor
+    takes the launches of a token budget's (attention, waiting scores, and the choice that also moves; or two with kept logits)."""
+    common = dict(n_layers=1, batch=2, n_q_heads=8, n_kv_heads=2, head_dim=128, capacity_tokens=250, window=32, quant_bits=2,
+                  tailor_policy=policy)
+    n = [_launches_of_a_tailor(A.arkv_config_default(budget_mode=m, **common), 900, 0.6) for m in (0, 1)]
+    assert n[0] == n[1] == 3 - policy
