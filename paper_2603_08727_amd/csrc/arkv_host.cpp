@@ -586,6 +586,34 @@ static bool logit_place(const arkv_cache* c, int32_t layer_begin, int32_t n, Poo
   return n == 1 && c->logit;
 }
 
+// Whether each unit's choosing workgroup makes its tailor's moves, instead of two launches over the whole chip.  ranked: rows of
+// a unit that are not in the window.  (Below: us of a step that ends with the tailor, two launches / the choosing workgroup, 4-bit
+// rows, d = 128, 8 units unless said otherwise.)
+// A tailor at every step settles to a few moved rows per unit: 29 / 25 at up to 1000 rows from the first one behind a commit on.
+// Large caches' first ones move many (32 units x 8192 rows: 41 us of moves at the first, 17 at the twelfth, 12 in two launches).
+// A small cache's moves are few enough at its natural cadence too, the later the fewer, as its choice settles.  alpha 0.4 to 0.98,
+// rho 0 to 0.6: 350 rows, first behind a commit 28-34 / 25-33, then 28-35 / 25-31; 500 rows, first 28-37 / 27-36, second 28-37 / 26-34;
+// 700 rows 28-37 / 28-40, 28-37 / 26-35; 1000 rows, first 30-38 / 29-46, second 29-39 / 28-39, third 29-39 / 28-37, eighth
+// 30-39 / 27-36.  Up to five times the packed rows, under a byte budget, does not move the line.
+// The first tailor of a prompt that fitted its cache demotes everything behind the Original budget at once, of which one CU
+// does 128 channels x 15 rows per us: 37 rows 28 / 26, 57 rows 29 / 29, 83 rows 30 / 32, 148 rows 30 / 37, 948 rows 33 / 91;
+// d = 64: 83 rows 29 / 27, 121 rows 29 / 29, 213 rows 29 / 31.
+constexpr int kSmallCache = 1024;                           // rows
+constexpr int kFewChannels = 8192;                          // demoted rows x channels
+static bool few_moves(const arkv_cache* c, int32_t layer_begin, int32_t n, int max_rows, int ranked) {
+  const int n_tailors = c->layers[(size_t)layer_begin].n_tailors;
+  if (n_tailors == 0) {
+    int demoted = 0;
+    for (int i = 0; i < n; ++i) {
+      const LayerState& li = c->layers[(size_t)(layer_begin + i)];
+      for (int32_t no : li.n_o) demoted = std::max(demoted, std::min(c->b + li.extra, ranked) - no);
+    }
+    return max_rows <= kSmallCache && demoted * c->P.D <= kFewChannels;
+  }
+  if (c->cfg.tailor_policy == 1) return max_rows <= kSmallCache || n_tailors > 16;
+  return max_rows <= std::min(kSmallCache, 128 + 256 * std::min(n_tailors, 4));
+}
+
 // One decode step of n layers in the same state.  static_scratch: the split-K partials and tickets of this launch
 // live in the library's static device array instead of the cache's own buffers.
 static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void* q, const void* k_new,
@@ -690,12 +718,7 @@ static int decode_impl(arkv_cache* c, int32_t layer_begin, int32_t n, const void
     t.position = P; t.t_prefill = l0.T; t.window = W; t.gamma = cfg.gamma;
     t.n_pending = n_pending; t.slot = slot;
     t.max_rows = most_rows(c, layer_begin, n);
-    // A tailor at every step settles to a few moved rows per unit: the choosing workgroup moves them (3 us instead of a
-    // launch's 7.6).  The first ones after a commit move many (32 units x 8192 rows, one workgroup per unit: 41 us at the
-    // first, 17 at the twelfth, against 12 us for two launches over the whole chip).
-    // So does that of a small cache, whose moves are few whatever the policy (a tailor at its natural cadence, two more launches /
-    // the choosing workgroup: 8 units, 250 rows 22 / 19 us, 700 rows 32 / 26; from 2000 rows on no difference).
-    t.few_moves = t.max_rows <= 1024 || (cfg.tailor_policy == 1 && l0.n_tailors > 16) ? 1 : 0;
+    t.few_moves = few_moves(c, layer_begin, n, t.max_rows, live - std::min(W, P + 1)) ? 1 : 0;
     t.kept = a.keep;
     t.tell_host = tell ? 1 : 0;
     for (int i = 0; i < n; ++i) {

@@ -430,9 +430,25 @@ def _launches_of_a_tailor(cfg, T, rho):
 
 @pytest.mark.parametrize("policy", [0, 1])
 def test_tailor_of_a_small_byte_budget_goes_by_the_rows_it_can_hold(policy):
-    """A unit of 250 rows' bytes holds some 600 rows at most with this ratio, however many more its pools have room for: its tailor
+    """A unit of 250 rows' bytes holds 350 to 580 rows at most with this ratio, however many more its pools have room for: its tailor
     takes the launches of a token budget's (attention, waiting scores, and the choice that also moves; or two with kept logits)."""
     common = dict(n_layers=1, batch=2, n_q_heads=8, n_kv_heads=2, head_dim=128, capacity_tokens=250, window=32, quant_bits=2,
                   tailor_policy=policy)
-    n = [_launches_of_a_tailor(A.arkv_config_default(budget_mode=m, **common), 900, 0.6) for m in (0, 1)]
+    n = [_launches_of_a_tailor(A.arkv_config_default(budget_mode=m, **common), 900, 0.65) for m in (0, 1)]
     assert n[0] == n[1] == 3 - policy
+
+
+@pytest.mark.parametrize("d,N,T,rho,policy,here", [
+    (128, 1000, 997, 0.0, 0, False), (128, 1000, 997, 0.95, 0, True),      # some 950 rows demoted at once, and 30
+    (128, 1000, 997, 0.0, 1, False), (128, 98, 95, 0.0, 0, True), (128, 99, 96, 0.0, 0, False),      # 64 and 65 of them
+    (64, 160, 157, 0.0, 0, True), (64, 165, 162, 0.0, 0, False),           # 125 and 130
+    (128, 384, 900, 0.5, 0, True), (128, 385, 900, 0.5, 0, False),         # the first one behind a commit that chose
+    (128, 1024, 1200, 0.5, 1, True), (128, 1025, 1200, 0.5, 1, False),
+])
+def test_where_a_tailors_moves_are_made(d, N, T, rho, policy, here):
+    """Attention, waiting scores (unless the logits are kept) and choice; two launches more unless the choosing workgroups move
+    the rows, which only pays for few of them."""
+    cfg = A.arkv_config_default(n_layers=1, batch=1, n_q_heads=8, n_kv_heads=2, head_dim=d, capacity_tokens=N, window=32, alpha=0.98,
+                                quant_bits=4, tailor_policy=policy)
+    kept = policy == 1 and T >= N
+    assert _launches_of_a_tailor(cfg, T, rho) == (2 if kept else 3) + (0 if here else 2)
