@@ -554,10 +554,16 @@ hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t 
   // 11.9 / 16.5, 32 x 1100 x 8 (split) 14.4 / 18.4, 2003 x 8 78.7 / 91.6 (d = 64: 51.3 / 62.0), 2003 x 32 309 / 314; the best of
   // every split taken on both sides, 138 calls on 150 to 10007 keys, 2 to 32 units: 13 % less at the median, up to 33.  Long
   // prompts that fill the chip many times over read each key tile once for all eight heads (10007 x 8 1562 / 1589, 1024 x
-  // 10007 x 32 1179 / 1211, d = 128; 5000 x 32 the same; d = 64 956 / 994 the other way).
-  const bool eight = a.D == 128 && max_pieces == 1 && a.T >= 8192 && (long long)a.B * a.Hkv * ((a.Tq + 31) / 32) >= 512;
+  // 10007 x 32 1179 / 1211, d = 128; 5000 x 32 the same; d = 64 956 / 994 the other way).  At d = 64 a CU holds three
+  // workgroups of four waves or two of eight: where blocks that are much alike fill at most two of eight per CU, but more than
+  // three of four, the smaller ones take a second round (474 x 2688 x 32 units, 480 blocks, 121 / 105; 499 x 6055 x 32, 512
+  // blocks, 267 / 233; 102 calls of 385 to 512 blocks with at most 0.4 of the keys as queries 9 % on average, -7 to 24; of 330 to 384
+  // and 513 to 590 blocks 9 to 27 % the other way, and where the blocks' lengths differ more).
+  const long long blocks = (long long)a.B * a.Hkv * ((a.Tq + 31) / 32);
+  const bool eight = max_pieces == 1 && (a.D == 128 ? a.T >= 8192 && blocks >= 512
+                                                    : blocks > 3 * 128 && blocks <= 4 * 128 && 5ll * a.Tq <= 2ll * a.T);
 #define ARKV_AT(D_, G_, H_) if (a.D == D_ && G == G_) return launch_attn_t<D_, G_, H_>(a, max_pieces, s);
-  if (eight) { ARKV_AT(128, 8, 8) }
+  if (eight) { ARKV_AT(128, 8, 8) ARKV_AT(64, 8, 8) }
   ARKV_AT(128, 1, 1) ARKV_AT(128, 2, 2) ARKV_AT(128, 4, 4) ARKV_AT(128, 8, 4)
   ARKV_AT(64, 1, 1) ARKV_AT(64, 2, 2) ARKV_AT(64, 4, 4) ARKV_AT(64, 8, 4)
 #undef ARKV_AT

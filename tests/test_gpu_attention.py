@@ -509,9 +509,10 @@ def test_attention_units_in_groups():
     (128, 5, 2, 33, 300),      # ten units, a chunk whose second workgroup holds one row
     (128, 3, 3, 40, 2100),     # nine units, split over the keys
     (128, 2, 1, 8200, 8200),   # two units of a prompt long enough for eight heads per workgroup
+    (64, 8, 2, 770, 2000),     # 400 blocks of nearly the same length: eight heads, two workgroups per CU
 ])
 def test_attention_heads_of_a_workgroup(d, hkv, batch, Tq, T):
-    """Group size 8: workgroups of four heads (eight for long prompts that fill the chip).  Every row of every head is
+    """Group size 8: workgroups of four heads (eight for long prompts that fill the chip, and where that saves a round).  Every row of every head is
     written, sampled rows of all heads against the oracle."""
     g = 8
     wl = synth.C1.scaled(name="heads", n_q_heads=g * hkv, n_kv_heads=hkv, head_dim=d, prefill=T, batch=batch, budget_frac=2.0)
