@@ -497,22 +497,23 @@ size_t attn_part_floats(int D, int G, int units, int Tq, int max_pieces) {
 // 0.66; the constants are those with which the model chooses best.)  Split pays where few workgroups walk many tiles: 512
 // queries x 16411 keys x 8 kv-heads 290 -> 146 us (4 pieces), 32 x 1100 x 8 units (d = 64) 19.9 -> 12.1.  It does not pay for a
 // whole short prompt, whose imbalance is only the causal triangle (1100 tokens x 8 kv-heads: 29.6 us unsplit, 32.9 us in 2
-// pieces; 972 x 4, 23.1 and 24.7 in 3), hence `triangle`.  Calls on up to 992 keys (kUnsplitKeys, whatever a workgroup's rows make
+// pieces; 972 x 4, 23.1 and 24.7 in 3; d = 64, 1379 x 4 22.5 and 25.0 in 4), hence `triangle`; with most CUs idle it pays earlier (d = 64, 1249 x
+// 1 20.6 and 15.3 in 5, 1272 x 1 20.7 and 15.0).  Calls on up to 992 keys (kUnsplitKeys, whatever a workgroup's rows make
 // of their tiles) are never split, so that a prompt of that length gives the same bits however it is cut into chunks (32 x 600
 // keys: 12-17 us where the best split takes 10-13).
-// Every number of pieces timed for 400 calls (2-32 units, 150-10007 keys, 32 queries to the whole prompt, G = 1, 4, 8): the chosen
-// one takes 2.1 % longer than the best on average, 6.5 % at the ninth decile (with constants fitted to an older loop 5.1 and 18).
-// 300 drawn calls that the constants were not fitted to: 68 are cut otherwise than with the old ones, those take 8 % less on
-// average (-30 to +8 %).
+// Every number of pieces timed for 1700 drawn calls (1-32 units, 993-13000 keys, 16 queries to the whole prompt, every G): the
+// chosen one takes 3.8 % longer than the best on average, 12 % at the ninth decile, 42 at most (with constants fitted to an older
+// loop 6.2, 17 and 65).  394 of them are cut otherwise than with those, these take 9 % less at the mean (-39 to +12 %, 34
+// above +3).
 constexpr int kUnsplitKeys = 992;
 void attn_split(int D, int G, int units, int T, int Tq, int* piece_tiles, int* max_pieces) {
   *piece_tiles = 0; *max_pieces = 1;
-  const double triangle = D == 64 ? 7.5 : 9.5;                                   // us of the average workgroup
   const double alone = D == 64 ? 0.36 : 0.6, shared = D == 64 ? 0.6 : 0.95;
   const int H = G < 4 ? G : 4, QB = 4 / H, nqb = (Tq + 32 * QB - 1) / (32 * QB), q0 = T - Tq;
   const long long wgs = (long long)nqb * units * (G / H);
   const int v0 = attn_pieces(q0, 0).visible, vmax = v0 + QB * (nqb - 1);         // visible tiles: v0 + QB i, i < nqb
   const double mean = 0.5 * ((double)v0 + vmax);
+  const double triangle = D == 128 ? 9.5 : wgs > 128 ? 7.5 : 6.6;                // us of the average workgroup
   if (T <= kUnsplitKeys || wgs > 4 * 256 || alone * mean < triangle) return;
   const double busy = 0.5 * shared * mean * (double)wgs / 256;
   double best = 1.05 * (alone * vmax > busy ? alone * vmax : busy);

@@ -243,6 +243,14 @@ def test_attention_split_leaves_short_prompts_whole():
             assert any(A.arkv_debug_attention_split(d, g, 1, T, 32)[0] for T in (993, 1300))
 
 
+def test_attention_split_of_whole_prompts_on_few_cus():
+    """A whole prompt of some 1150 to 1300 tokens at d = 64 is split where its workgroups leave most CUs idle, and not where
+    they do not."""
+    for T in (1153, 1249, 1300):
+        assert A.arkv_debug_attention_split(64, 4, 1, T, T)[1] > 1 and A.arkv_debug_attention_split(64, 1, 3, T, T)[1] > 1
+    assert all(A.arkv_debug_attention_split(64, 4, units, 1249, 1249)[1] == 1 for units in (4, 8, 16))
+
+
 def test_phase_trace_names_the_launches_that_update_the_scores():
     """The library adds the waiting steps when kRing - 1 of them wait (and then the step itself waits)."""
     import subprocess
