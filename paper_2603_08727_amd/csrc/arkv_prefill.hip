@@ -476,12 +476,13 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
   L.stats[b * 3 + 2] = m2 > 0 ? (float)(m4 / (m2 * m2)) : 0.f;
 }
 
-// Up to kMergeChunks key chunks, or more of them in a launch of up to kMergeGrid workgroups, the column pass merges the first
-// pass's partials itself (in its prologue, 16 to a batch of loads) and k_prefill_rowfinal, a launch of 5 us, is left out.
-// Otherwise every workgroup of the column pass reads more than the launch costs.  Merged / with the launch, us: 8 units x 4000
-// keys (32 chunks) 20.2 / 22.3, 2 x 3000 17.4 / 20.2, 32 x 32768 (32) 112.6 / 115.5, 8 x 10000 (79
-// chunks, 632 workgroups) 33.6 / 35.1, 2 x 32768 (256, 512) 34.9 / 38.8; 16 x 8192 (64, 1024) 43.9 / 43.9, 8 x 16384 (128, 1024)
-// 50.4 / 46.8, 24 x 10000 (79, 1896) 66.3 / 61.1, 32 x 6000 (47, 1504) 51.5 / 50.6.
+// Up to kMergeChunks key chunks, or more of them in a launch of up to kMergeGrid workgroups of up to 128 query rows (half as many
+// of 256, a quarter of 512), the column pass puts the row constants together itself, in its prologue, and k_prefill_rowfinal, a
+// launch of 5 us, is left out.  Otherwise every workgroup of the column pass reads more than the launch costs: 8 bytes per row
+// and chunk.  In the column pass / with the launch, us, d = 128, 128 rows: 8 units x 4000 keys (32 chunks) 19.8 / 21.7, 2 x 3000 19.2 /
+// 20.8, 32 x 32768 (32) 109.5 / 111.5, 8 x 10000 (79 chunks, 632 workgroups) 33.7 / 34.3, 2 x 32768 (256, 512) 34.6 / 37.3; 16 x 8192
+// (64, 1024) 43.3 / 43.6, 8 x 16384 (128, 1024) 49.9 / 47.3, 24 x 10000 (79, 1896) 66.3 / 61.3.  256 rows: 2 x 9000 (141 workgroups)
+// 26.5 / 28.3, 4 x 18763 (588, d = 64) 43.6 / 39.7.  512 rows: 1 x 36919 (289) 84.9 / 68.8, 4 x 9324 (292, d = 64) 47.8 / 45.2.
 // The two add a row's partials in different orders, so a row constant, and with it a score, can differ in its last bit from
 // what the other gives.
 constexpr int kMergeChunks = 32, kMergeGrid = 640;
@@ -518,11 +519,12 @@ static hipError_t launch_prefill_t(const PrefillLaunch& a, float* rowc, hipStrea
 // rowc: scratch [U][MP] floats followed by U*n_chunks + 3*B*ceil((T-W)/512) doubles for the statistics partials
 hipError_t launch_prefill_stats(const PrefillLaunch& launch, float* rowc, hipStream_t s) {
   PrefillLaunch a = launch;
-  a.merge_rows = !a.have_rowc && (a.n_chunks <= kMergeChunks || (long long)a.n_chunks * a.B * a.Hkv <= kMergeGrid) ? 1 : 0;
   const int M = a.G * a.W;
   int RT = 1;
   while (RT * 32 < M) RT *= 2;
   if (RT > 16) return hipErrorInvalidValue;
+  const long long wgs = (long long)a.n_chunks * a.B * a.Hkv;
+  a.merge_rows = !a.have_rowc && (a.n_chunks <= kMergeChunks || (wgs <= kMergeGrid && 32 * RT * wgs <= 128 * kMergeGrid)) ? 1 : 0;
 #define ARKV_PF(D_, RT_) if (a.D == D_ && RT == RT_) return launch_prefill_t<D_, RT_>(a, rowc, s);
   ARKV_PF(128, 1) ARKV_PF(128, 2) ARKV_PF(128, 4) ARKV_PF(128, 8) ARKV_PF(128, 16)
   ARKV_PF(64, 1) ARKV_PF(64, 2) ARKV_PF(64, 4) ARKV_PF(64, 8) ARKV_PF(64, 16)

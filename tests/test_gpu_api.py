@@ -452,3 +452,33 @@ def test_where_a_tailors_moves_are_made(d, N, T, rho, policy, here):
                                 quant_bits=4, tailor_policy=policy)
     kept = policy == 1 and T >= N
     assert _launches_of_a_tailor(cfg, T, rho) == (2 if kept else 3) + (0 if here else 2)
+
+
+def _one_prompt(hq, hkv, d, W, T, seed=5):
+    g = torch.Generator().manual_seed(seed)
+    return tuple(torch.randn((1, h, t, d), generator=g).to(torch.bfloat16).cuda() for h, t in ((hq, W), (hkv, T)))
+
+
+def _scorer_cache(hq, hkv, d, W, batch):
+    return A.arkv_cache_create(A.arkv_config_default(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d,
+                                                     capacity_tokens=W + 200, window=W))
+
+
+@pytest.mark.parametrize("hq,hkv,W,T,launches", [
+    (4, 1, 32, 16, 3), (4, 1, 32, 640, 3), (4, 1, 32, 641, 4),         # 128 rows of one unit: chunks of 128 keys
+    (8, 1, 32, 320, 3), (8, 1, 32, 321, 4), (8, 1, 64, 160, 3), (8, 1, 64, 161, 4), (8, 2, 64, 32, 3), (20, 20, 32, 32, 3), (20, 20, 32, 33, 4),
+])
+def test_where_row_constants_are_formed(hq, hkv, W, T, launches):
+    """Three launches of the scorer where the column pass forms the row constants, four where that takes longer than a launch of
+    its own: many workgroups (beyond 32 chunks), fewer of them the more rows they have.  T: chunks of 128 keys."""
+    T *= 128
+    q, k = _one_prompt(hq, hkv, 64, W, T)
+    cache = _scorer_cache(hq, hkv, 64, W, 1)
+    try:
+        A.arkv_debug_set_launch_shape(cache, prefill_chunk=128)
+        stats = torch.zeros((1, 3), dtype=torch.float32, device="cuda")
+        score = lambda: A.arkv_prefill_stats(cache, 0, q, k, T, 0.1, stats)
+        score()                                             # (the scratch)
+        assert _launches(cache, score) == launches
+    finally:
+        A.arkv_cache_destroy(cache)
