@@ -90,7 +90,9 @@ int arkv_cache_reset(arkv_cache* cache, int32_t layer);
  * Window query i (position T-W+i) attends causally to keys 0..T-W+i with
  * softmax(softmax_scale * q.k); the layer statistics use keys < T-W only.  As a side effect the
  * per-(kv-head, token) sums of attention and squared attention over the window are kept inside the
- * cache for arkv_prefill_commit.  Asynchronous, except that scratch is allocated on first use and when T grows
+ * cache for arkv_prefill_commit.  The order in which a row's partial sums are added follows from the launch's size (keys, window
+ * rows, units), so the same sequence in another batch can differ in the last bits of its statistics and scores.
+ * Asynchronous, except that scratch is allocated on first use and when T grows
  * (an allocation may synchronise the device).
  * A prompt must be longer than the window: T <= W returns ARKV_EINVAL, because eqs. 3-5 are taken over the
  * keys outside the window and there are none.  Such a prompt needs no cache management until it has grown (below

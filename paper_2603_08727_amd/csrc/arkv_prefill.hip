@@ -289,10 +289,14 @@ __device__ __forceinline__ void block_sums_d(double (&v)[N], double* sm /*[N][4]
   }
 }
 
-// c_r = max + log2(sum) of a row from the first pass's partials per key chunk (rowstat: the row's first, MP apart).
-// Partials are requested 16 at a time.
+// c_r = max + log2(sum) of a row from the first pass's partials per key chunk (rowstat: the row's first, MP apart), by one
+// thread.  Partials are requested 16 at a time and added in CHAINS chains: one for up to 16 chunks, eight for more, as in
+// k_prefill_rowfinal, from whose bits this can differ where a later batch moves the maximum.
+template <int CHAINS>
 __device__ __forceinline__ float row_constant(const float2* rowstat, int n_chunks, int MP) {
-  float mn = kNegBigP, s = 0.f;
+  float mn = kNegBigP, s[CHAINS];
+#pragma unroll
+  for (int i = 0; i < CHAINS; ++i) s[i] = 0.f;
   for (int c0 = 0; c0 < n_chunks; c0 += 16) {
     float2 t[16];
 #pragma unroll
@@ -300,20 +304,73 @@ __device__ __forceinline__ float row_constant(const float2* rowstat, int n_chunk
     float m = mn;
 #pragma unroll
     for (int i = 0; i < 16; ++i) m = fmaxf(m, t[i].x);
-    s *= pexp2(mn - m);
+    const float f = pexp2(mn - m);
+#pragma unroll
+    for (int i = 0; i < CHAINS; ++i) s[i] *= f;
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      if (c0 + i < n_chunks) s += t[i].y * pexp2(t[i].x - m);
+      if (c0 + i < n_chunks) s[i % CHAINS] += t[i].y * pexp2(t[i].x - m);
     mn = m;
   }
-  return s > 0.f ? mn + log2f(s) : 0.f;
+  float tot = s[0];
+#pragma unroll
+  for (int i = 1; i < CHAINS; ++i) tot += s[i];
+  return tot > 0.f ? mn + log2f(tot) : 0.f;
+}
+
+// The same of 8 GROUPS rows (r, r + 8 waves, ...) from up to 8 J chunks, by a wave: eight lanes a row, each every eighth chunk,
+// added up in k_prefill_rowfinal's order, so that a constant's bits do not depend on which of the two forms it.  All partials
+// are requested together and stay in registers between the maximum and the sum.
+template <int MP, int NW, int J, int GROUPS>
+__device__ __forceinline__ void row_constants_of(const float2* rowstat, int n_chunks, int r, int M, float* crow) {
+  const int lane = threadIdx.x & 63, part = lane >> 3;
+  float2 t[GROUPS][J];
+#pragma unroll
+  for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const int c = part + 8 * j;
+      const unsigned at = (unsigned)(min(c, n_chunks - 1) * MP + r + 8 * NW * g) * 8u;
+      t[g][j] = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(rowstat) + at);
+      if (c >= n_chunks) t[g][j].y = 0.f;                 // (adds nothing; its maximum is another's)
+    }
+#pragma unroll
+  for (int g = 0; g < GROUPS; ++g) {
+    float m = kNegBigP, s = 0.f, tot = 0.f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) m = fmaxf(m, t[g][j].x);
+#pragma unroll
+    for (int o = 8; o < 64; o *= 2) m = fmaxf(m, __shfl_xor(m, o));
+#pragma unroll
+    for (int j = 0; j < J; ++j) s += t[g][j].y * pexp2(t[g][j].x - m);
+#pragma unroll
+    for (int p = 0; p < 8; ++p) tot += __shfl(s, 8 * p + (lane & 7));
+    const int row = r + 8 * NW * g;
+    if (part == 0) crow[row] = row < M ? -(tot > 0.f ? m + log2f(tot) : 0.f) : kNegBigP;
+  }
+}
+
+// crow[r] = -c_r of all rows, by the whole workgroup, from 17 to 64 chunks.  Up to 128 rows (with more, eight rows' 64 bytes per chunk
+// and lane octet are too little of a line: 256 rows 5 % slower than a thread per row, 128 rows 2 % faster, 32 rows 7 %).
+constexpr int kWaveChunks = 64, kWaveRows = 128;
+template <int MP, int NW>
+__device__ __forceinline__ void row_constants(const float2* rowstat, int n_chunks, int M, float* crow) {
+  constexpr int ALL = MP / (8 * NW);                      // groups of eight rows per wave
+  const int r0 = 8 * (threadIdx.x >> 6) + (threadIdx.x & 7);
+  auto all = [&](auto j) {
+    constexpr int J = decltype(j)::value, GROUPS = ALL < 16 / J ? ALL : 16 / J;
+#pragma unroll 1
+    for (int i = 0; i < ALL; i += GROUPS) row_constants_of<MP, NW, J, GROUPS>(rowstat, n_chunks, r0 + 8 * NW * i, M, crow);
+  };
+  using std::integral_constant;
+  if (n_chunks <= 32) all(integral_constant<int, 4>()); else all(integral_constant<int, 8>());
 }
 
 // Second pass.  Here the MFMA is turned round (query rows on the M side, keys on the N side) so that a
 // lane owns ONE key and the sums over the M = G*W query rows are in-register additions: C[i] is row
 // rt*32 + 8(i/4) + 4(lane/32) + i%4 against key j0 + lane%32.  The row constants c_r come from LDS.
 template <int D, int RT, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void k_prefill_cols(PrefillLaunch L, const float* rowc, double* zpart) {
+__global__ __launch_bounds__(64 * NW, NW > 4 ? 2 : D == 64 && RT <= 4 ? 5 : 3) void k_prefill_cols(PrefillLaunch L, const float* rowc, double* zpart) {
   extern __shared__ __align__(16) unsigned char sm[];
   constexpr int RB = 2 * D + 16;
   constexpr int NT = 64 * NW;
@@ -323,14 +380,20 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) void k_prefill_cols(Prefi
   stage_q<D, NT>(sm, L.q_win + (size_t)u * L.G * L.q_head_stride, L.q_head_stride, L.W, M, MP);
   float* crow = reinterpret_cast<float*>(sm + (size_t)MP * RB);   // [MP] -c_r (padded rows: -1e30 -> p = 0)
   int* lastk = reinterpret_cast<int*>(crow + MP);                 // [MP] last visible key of the row
+  const bool by_wave = MP <= kWaveRows && L.merge_rows && L.n_chunks > 16 && L.n_chunks <= kWaveChunks;
+  const float2* rowstat = L.rowstat + (size_t)u * L.n_chunks * MP;
+  if constexpr (RT * 32 <= kWaveRows) {
+    if (by_wave) row_constants<RT * 32, NW>(rowstat, L.n_chunks, M, crow);
+  }
   for (int r = tid; r < MP; r += NT) {
     // the row constant in base-2 units: from the first pass / the attention pass, or from the caller's
     // log-sum-exp (natural log of the sum over visible keys of exp(scale q.k), what attention kernels commonly
     // return per query row; row r = (head inside the group) * W + (window query))
     float cr = 0.f;
-    if (L.merge_rows) cr = row_constant(L.rowstat + (size_t)u * L.n_chunks * MP + r, L.n_chunks, MP);
-    else if (r < M) cr = L.lse ? L.lse[((size_t)u * L.G + r / L.W) * L.W + r % L.W] * 1.4426950408889634f : rowc[(size_t)u * MP + r];
-    crow[r] = r < M ? -cr : kNegBigP;
+    if (L.merge_rows) {
+      if (!by_wave) cr = L.n_chunks <= 16 ? row_constant<1>(rowstat + r, L.n_chunks, MP) : row_constant<8>(rowstat + r, L.n_chunks, MP);
+    } else if (r < M) cr = L.lse ? L.lse[((size_t)u * L.G + r / L.W) * L.W + r % L.W] * 1.4426950408889634f : rowc[(size_t)u * MP + r];
+    if (!by_wave) crow[r] = r < M ? -cr : kNegBigP;
     lastk[r] = r < M ? T - L.W + (r % L.W) : -1;
   }
   __syncthreads();
@@ -483,8 +546,6 @@ __global__ __launch_bounds__(256) void k_prefill_stats(PrefillLaunch L, const do
 // 20.8, 32 x 32768 (32) 109.5 / 111.5, 8 x 10000 (79 chunks, 632 workgroups) 33.7 / 34.3, 2 x 32768 (256, 512) 34.6 / 37.3; 16 x 8192
 // (64, 1024) 43.3 / 43.6, 8 x 16384 (128, 1024) 49.9 / 47.3, 24 x 10000 (79, 1896) 66.3 / 61.3.  256 rows: 2 x 9000 (141 workgroups)
 // 26.5 / 28.3, 4 x 18763 (588, d = 64) 43.6 / 39.7.  512 rows: 1 x 36919 (289) 84.9 / 68.8, 4 x 9324 (292, d = 64) 47.8 / 45.2.
-// The two add a row's partials in different orders, so a row constant, and with it a score, can differ in its last bit from
-// what the other gives.
 constexpr int kMergeChunks = 32, kMergeGrid = 640;
 
 template <int D, int RT>

@@ -464,6 +464,31 @@ def _scorer_cache(hq, hkv, d, W, batch):
                                                      capacity_tokens=W + 200, window=W))
 
 
+@pytest.mark.parametrize("hq,d,W,T", [(2, 64, 32, 2200), (4, 128, 20, 4000), (8, 128, 32, 4100), (8, 64, 32, 8190), (2, 128, 5, 6000)])
+def test_row_constants_do_not_depend_on_the_pass_that_forms_them(hq, d, W, T):
+    """From 17 to 64 chunks of 128 keys and up to 128 rows: a sequence alone, where the column pass forms the row constants, and
+    among so many that a launch of its own does.  Same bits of its statistics and of every key's window sums (what a commit keeps)."""
+    hkv = 2
+    q, k = _one_prompt(hq, hkv, d, W, T)
+    many = 640 // ((T + 127) // 128 * hkv) + 1
+    got = []
+    for batch in (1, many):
+        cfg = A.arkv_config_default(n_layers=1, batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, capacity_tokens=T + 50, window=W)
+        cache = A.arkv_cache_create(cfg)
+        try:
+            A.arkv_debug_set_launch_shape(cache, prefill_chunk=128)
+            stats = torch.zeros((batch, 3), dtype=torch.float32, device="cuda")
+            qb, kb = (x.expand(batch, -1, -1, -1).contiguous() for x in (q, k))
+            A.arkv_prefill_stats(cache, 0, qb, kb, T, 0.1, stats)
+            A.arkv_prefill_commit(cache, 0, kb, kb, T, [0.5] * batch)
+            e = A.arkv_cache_export(cache, 0, cfg, rows=False, codes=False)
+            got.append((stats.cpu().numpy(), e["s1"].reshape(batch, hkv, -1), e["s2"].reshape(batch, hkv, -1)))
+        finally:
+            A.arkv_cache_destroy(cache)
+    for one, all_ in zip(*got):
+        assert np.isfinite(one).all() and (all_.view(np.uint32) == one.view(np.uint32)).all()
+
+
 @pytest.mark.parametrize("hq,hkv,W,T,launches", [
     (4, 1, 32, 16, 3), (4, 1, 32, 640, 3), (4, 1, 32, 641, 4),         # 128 rows of one unit: chunks of 128 keys
     (8, 1, 32, 320, 3), (8, 1, 32, 321, 4), (8, 1, 64, 160, 3), (8, 1, 64, 161, 4), (8, 2, 64, 32, 3), (20, 20, 32, 32, 3), (20, 20, 32, 33, 4),
