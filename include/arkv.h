@@ -276,10 +276,17 @@ int arkv_debug_select(const uint32_t* scores, int32_t n, int32_t k0, int32_t k1,
 int arkv_debug_attention_split(int32_t head_dim, int32_t group, int32_t units, int32_t T, int32_t T_q, int32_t* out);
 
 /* Parity hook, HOST, pure: out[0] = unit and out[1] = block of query positions that the index-th of a prefill-attention
- * launch's units * n_blocks workgroups takes (index runs over the units first; split != 0: one piece of a split launch).
+ * launch's units * n_blocks workgroups takes where each takes all heads of its unit, as below group size 8 (index runs over the units first; split != 0: one piece of a split launch).
  * ARKV_EINVAL: null pointer, head_dim not built, sizes < 1, index outside [0, units * n_blocks). */
 int arkv_debug_attention_block(int32_t head_dim, int32_t units, int32_t T, int32_t n_blocks, int32_t split, int32_t index,
                                int32_t* out);
+
+/* Parity hook, HOST, pure: what the index-th workgroup (of a piece) of arkv_prefill_attention takes in a call of T_q queries
+ * against T keys for units = B H_kv and group = H_q / H_kv: out[0] = unit, out[1] = the first of its heads (0 .. group - 1),
+ * out[2] = how many, out[3] = block of query positions (of 32 positions times 4 / out[2] where a workgroup takes fewer than
+ * four heads).  ARKV_EINVAL: null pointer, head_dim or group not built, units < 1, T_q outside [1, T], index not that of a
+ * workgroup. */
+int arkv_debug_attention_heads(int32_t head_dim, int32_t group, int32_t units, int32_t T, int32_t T_q, int32_t index, int32_t* out);
 
 /* Measurement hook of profiling builds (the library compiled with -DARKV_PHASE_TRACE, see the package's build
  * script; the product build returns ARKV_EUNSUPPORTED and its kernels carry none of this).  In such a build

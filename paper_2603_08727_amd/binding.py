@@ -23,7 +23,7 @@ EXPORTED = [
     "arkv_decode_step", "arkv_decode_step_static", "arkv_decode_step_layers", "arkv_cache_counters", "arkv_cache_export",
     "arkv_debug_last_tailor_scores", "arkv_debug_last_out_f32", "arkv_debug_prefill_attention_f32", "arkv_cache_progress",
     "arkv_debug_time_attend", "arkv_debug_attend_time", "arkv_debug_set_launch_shape", "arkv_debug_split_range", "arkv_debug_phase_trace",
-    "arkv_debug_attention_split", "arkv_debug_attention_block", "arkv_debug_select",
+    "arkv_debug_attention_split", "arkv_debug_attention_block", "arkv_debug_attention_heads", "arkv_debug_select",
     "arkv_strerror",
     "arkv_last_hip_error",
 ]
@@ -401,4 +401,13 @@ def arkv_debug_attention_block(head_dim, units, T, n_blocks, split, index):
     lib.arkv_debug_attention_block.argtypes = [C.c_int32] * 6 + [C.POINTER(C.c_int32)]
     lib.arkv_debug_attention_block.restype = C.c_int
     _check(lib.arkv_debug_attention_block(head_dim, units, T, n_blocks, split, index, r), "arkv_debug_attention_block")
+    return tuple(r)
+
+
+def arkv_debug_attention_heads(head_dim, group, units, T, T_q, index):
+    r = (C.c_int32 * 4)()
+    lib = load()
+    lib.arkv_debug_attention_heads.argtypes = [C.c_int32] * 6 + [C.POINTER(C.c_int32)]
+    lib.arkv_debug_attention_heads.restype = C.c_int
+    _check(lib.arkv_debug_attention_heads(head_dim, group, units, T, T_q, index, r), "arkv_debug_attention_heads")
     return tuple(r)

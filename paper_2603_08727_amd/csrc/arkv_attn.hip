@@ -115,9 +115,9 @@ template <int D> constexpr int kPieceFloats = 32 * D + 96;
 // A launch whose workgroups take H of a unit's G heads has G / H shares per unit; the shares of a unit lie eight apart (as
 // many as there are units left in the last eight), on the same XCD, whose L2 then serves both.  share: 0 .. units G / H - 1.
 template <int G, int H>
-__device__ __forceinline__ void unit_share(int share, int units, int& u, int& head0) {
+__host__ __device__ __forceinline__ void unit_share(int share, int units, int& u, int& head0) {
   constexpr int N = G / H;
-  const int first = share / (8 * N) * 8, r = share % (8 * N), n = min(8, units - first);
+  const int first = share / (8 * N) * 8, r = share % (8 * N), n = units - first < 8 ? units - first : 8;
   u = first + r % n;
   head0 = H * (r / n);
 }
@@ -150,11 +150,12 @@ __host__ __device__ __forceinline__ bool query_block(unsigned units, unsigned x,
   qb = nqb - 1 - (int)rank;
   return true;
 }
-// Units that run side by side: as many as 128 MB of keys and values, in eights (one per XCD), at least eight.
-static int attn_group(int D, int T, int units) {
+// Units that run side by side: as many as 128 MB of keys and values, in eights (one per XCD), at least eight; in a split
+// launch all of them.
+static int attn_group(int D, int T, int units, bool split) {
   const long long per_unit = 4ll * D * T;
   const long long n = (128ll << 20) / per_unit / 8 * 8;
-  return (int)(n < 8 ? (units < 8 ? units : 8) : (n < units ? n : units));
+  return split ? units : (int)(n < 8 ? (units < 8 ? units : 8) : (n < units ? n : units));
 }
 
 // EXACT (a split launch that also hands the scorer its row constants): the window rows' normalisers are summed from the
@@ -539,7 +540,7 @@ static hipError_t launch_attn_t(const AttnLaunch& launch, int max_pieces, hipStr
   AttnLaunch a = launch;
   constexpr int rows = 32 * kQBlocks<H>, nt = 64 * H * kQBlocks<H>;
   const int units = a.B * a.Hkv * (G / H), nqb = (a.Tq + rows - 1) / rows;
-  a.group = max_pieces > 1 ? units : attn_group(a.D, a.T, a.B * a.Hkv) * (G / H);
+  a.group = attn_group(a.D, a.T, a.B * a.Hkv, max_pieces > 1) * (G / H);
   const dim3 grid(units, nqb < kMaxGridY ? nqb : kMaxGridY, max_pieces > 1 ? max_pieces : (nqb + kMaxGridY - 1) / kMaxGridY);
   if (max_pieces > 1 && a.rowc) hipLaunchKernelGGL((k_prefill_attn<D, G, H, true>), grid, dim3(nt), 0, s, a);
   else hipLaunchKernelGGL((k_prefill_attn<D, G, H, false>), grid, dim3(nt), 0, s, a);
@@ -548,8 +549,8 @@ static hipError_t launch_attn_t(const AttnLaunch& launch, int max_pieces, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s) {
-  const int G = a.Hq / a.Hkv;
+// Heads of a unit that a workgroup takes.
+static int attn_heads(int D, int G, int units, int T, int Tq, bool split) {
   // Four heads per workgroup at G = 8: four waves leave twice as many workgroups to spread over the CUs as eight, and a
   // wave that has its SIMD to itself takes a step in 0.54 us (d = 64: 0.43) instead of 0.76 (0.55).  4 / 8 heads, us: 300 x 8 units
   // 11.9 / 16.5, 32 x 1100 x 8 (split) 14.4 / 18.4, 2003 x 8 78.7 / 91.6 (d = 64: 51.3 / 62.0), 2003 x 32 309 / 314; the best of
@@ -560,11 +561,15 @@ hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t 
   // three of four, the smaller ones take a second round (474 x 2688 x 32 units, 480 blocks, 121 / 105; 499 x 6055 x 32, 512
   // blocks, 267 / 233; 102 calls of 385 to 512 blocks with at most 0.4 of the keys as queries 9 % on average, -7 to 24; of 330 to 384
   // and 513 to 590 blocks 9 to 27 % the other way, and where the blocks' lengths differ more).
-  const long long blocks = (long long)a.B * a.Hkv * ((a.Tq + 31) / 32);
-  const bool eight = max_pieces == 1 && (a.D == 128 ? a.T >= 8192 && blocks >= 512
-                                                    : blocks > 3 * 128 && blocks <= 4 * 128 && 5ll * a.Tq <= 2ll * a.T);
-#define ARKV_AT(D_, G_, H_) if (a.D == D_ && G == G_) return launch_attn_t<D_, G_, H_>(a, max_pieces, s);
-  if (eight) { ARKV_AT(128, 8, 8) ARKV_AT(64, 8, 8) }
+  const long long blocks = (long long)units * ((Tq + 31) / 32);
+  const bool eight = !split && (D == 128 ? T >= 8192 && blocks >= 512 : blocks > 3 * 128 && blocks <= 4 * 128 && 5ll * Tq <= 2ll * T);
+  return G < 8 ? G : eight ? 8 : 4;
+}
+
+hipError_t launch_prefill_attn(const AttnLaunch& a, int max_pieces, hipStream_t s) {
+  const int G = a.Hq / a.Hkv, H = attn_heads(a.D, G, a.B * a.Hkv, a.T, a.Tq, max_pieces > 1);
+#define ARKV_AT(D_, G_, H_) if (a.D == D_ && G == G_ && H == H_) return launch_attn_t<D_, G_, H_>(a, max_pieces, s);
+  ARKV_AT(128, 8, 8) ARKV_AT(64, 8, 8)
   ARKV_AT(128, 1, 1) ARKV_AT(128, 2, 2) ARKV_AT(128, 4, 4) ARKV_AT(128, 8, 4)
   ARKV_AT(64, 1, 1) ARKV_AT(64, 2, 2) ARKV_AT(64, 4, 4) ARKV_AT(64, 8, 4)
 #undef ARKV_AT
@@ -593,9 +598,26 @@ extern "C" int arkv_debug_attention_block(int32_t head_dim, int32_t units, int32
     return ARKV_EINVAL;
   const unsigned x = (unsigned)index % (unsigned)units, rank = (unsigned)index / (unsigned)units;
   int u = -1, qb = -1;
-  if (!arkv::query_block((unsigned)units, x, rank, n_blocks, split ? units : arkv::attn_group(head_dim, T, units), u, qb))
+  if (!arkv::query_block((unsigned)units, x, rank, n_blocks, arkv::attn_group(head_dim, T, units, split != 0), u, qb))
     return ARKV_EINVAL;
   out[0] = u; out[1] = qb;
+  return ARKV_OK;
+}
+
+extern "C" int arkv_debug_attention_heads(int32_t head_dim, int32_t group, int32_t units, int32_t T, int32_t T_q, int32_t index, int32_t* out) {
+  if (!out || (head_dim != 64 && head_dim != 128) || (group != 1 && group != 2 && group != 4 && group != 8) || units < 1 ||
+      T_q < 1 || T_q > T || index < 0)
+    return ARKV_EINVAL;
+  int tiles, pieces;
+  arkv::attn_split(head_dim, group, units, T, T_q, &tiles, &pieces);
+  const int H = arkv::attn_heads(head_dim, group, units, T, T_q, pieces > 1), shares = group / H;
+  const int rows = 32 * (H < 4 ? 4 / H : 1), nqb = (T_q + rows - 1) / rows;
+  if ((long long)index >= (long long)units * shares * nqb) return ARKV_EINVAL;
+  const unsigned n = (unsigned)(units * shares), x = (unsigned)index % n, rank = (unsigned)index / n;
+  int u = -1, qb = -1, head0 = 0;
+  if (!arkv::query_block(n, x, rank, nqb, arkv::attn_group(head_dim, T, units, pieces > 1) * shares, u, qb)) return ARKV_EINVAL;
+  if (shares == 2) { const int share = u; arkv::unit_share<8, 4>(share, units, u, head0); }
+  out[0] = u; out[1] = head0; out[2] = H; out[3] = qb;
   return ARKV_OK;
 }
 

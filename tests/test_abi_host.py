@@ -216,6 +216,29 @@ def test_attention_workgroups_cover_every_block_once(units, T, n_blocks, split):
         A.arkv_debug_attention_block(128, units, T, n_blocks, split, units * n_blocks)
 
 
+@pytest.mark.parametrize("d,g,units,T,T_q,heads", [
+    (64, 8, 9, 70, 70, 4), (128, 8, 10, 300, 33, 4), (128, 8, 9, 2100, 40, 4), (64, 8, 1, 500, 500, 4), (128, 8, 23, 700, 200, 4),
+    (128, 8, 32, 11000, 480, 4), (128, 8, 37, 11003, 400, 4), (64, 8, 70, 12000, 600, 4),       # in groups of units
+    (128, 8, 33, 8200, 700, 8), (64, 8, 16, 2000, 770, 8), (128, 4, 13, 900, 300, 4), (64, 2, 9, 5000, 129, 2), (128, 1, 5, 400, 400, 1),
+])
+def test_attention_workgroups_cover_every_head_once(d, g, units, T, T_q, heads):
+    """The same with the heads: every (unit, head, block) is taken by exactly one workgroup, also where workgroups take half a
+    unit's heads, with unit counts that are no multiple of eight and where units go in groups."""
+    rows = 32 * max(1, 4 // heads)
+    blocks = (T_q + rows - 1) // rows
+    n = units * (g // heads) * blocks
+    order = [A.arkv_debug_attention_heads(d, g, units, T, T_q, i) for i in range(n)]
+    assert {h for _, _, h, _ in order} == {heads}
+    taken = sorted((u, h0 + h, b) for u, h0, hs, b in order for h in range(hs))
+    assert taken == [(u, h, b) for u in range(units) for h in range(g) for b in range(blocks)]
+    # a unit's shares are eight workgroups apart (fewer behind the last eight), so on one XCD
+    if g // heads == 2 and units % 8 == 0:
+        assert all(order[i][0] == order[i + 8][0] for i in range(0, n, 16))
+    for bad in (-1, n):
+        with pytest.raises(A.ArkvError):
+            A.arkv_debug_attention_heads(d, g, units, T, T_q, bad)
+
+
 def test_attention_split_pieces():
     """Host logic of the split over the keys: never more pieces than the scratch is sized for, none for short prompts or
     launches that fill the chip."""

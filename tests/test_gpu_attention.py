@@ -509,6 +509,7 @@ def test_attention_units_in_groups():
     (128, 5, 2, 33, 300),      # ten units, a chunk whose second workgroup holds one row
     (128, 3, 3, 40, 2100),     # nine units, split over the keys
     (128, 2, 1, 8200, 8200),   # two units of a prompt long enough for eight heads per workgroup
+    (128, 8, 4, 480, 11000),   # 32 units in two groups, four heads, not split
     (64, 8, 2, 770, 2000),     # 400 blocks of nearly the same length: eight heads, two workgroups per CU
 ])
 def test_attention_heads_of_a_workgroup(d, hkv, batch, Tq, T):
