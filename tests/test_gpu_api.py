@@ -66,9 +66,11 @@ def test_layers_entry_point_equals_per_layer_calls():
 ])
 def test_tailor_at_every_step_through_all_entry_points(g, bits, byte_budget):
     """With a tailor at every step, three layers in one call and the call with static scratch give the same bits as one call per
-    layer: outputs of every step and the caches behind the last, through the 17th tailor, whose moves are made elsewhere."""
-    wl = synth.C1.scaled(name="each", n_layers=3, n_q_heads=2 * g, n_kv_heads=2, head_dim=64, bits=bits, prefill=700,
-                         budget_frac=300.5 / 700, window=16, decode_steps=21)
+    layer: outputs of every step and the caches behind the last, through the 17th tailor, whose moves (of more than 1024 rows) are
+    made elsewhere."""
+    wl = synth.C1.scaled(name="each", n_layers=3, n_q_heads=2 * g, n_kv_heads=2, head_dim=64, bits=bits, prefill=1500,
+                         budget_frac=1100.5 / 1500, window=16, decode_steps=21)
+    assert wl.capacity == 1100
     L = wl.n_layers
     cfg = make_cfg(wl, every_step=True, byte_budget=byte_budget)
     caches = [A.arkv_cache_create(cfg) for _ in range(3)]
@@ -250,7 +252,7 @@ def test_measurement_hooks():
 def test_counts_behind_tailors_reach_the_host_across_resets(layers_per_call):
     """After a decode-time tailor the host learns the units' counts from words that the kernels store in pinned memory.  A cache
     that went through tailors, was reset and took another prompt gives the same bits as a fresh one, whether or not the words of
-    the earlier tailors had arrived; so do its counters."""
+    the earlier tailors had arrived; so do its counters.  (A step of several layers does not hand its counts to the kernel.)"""
     L, hq, hkv, d, T, N, steps = 2, 8, 2, 64, 200, 90, 70
     wl = synth.C1.scaled(name="words", n_layers=L, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=2, budget_frac=(N + 0.5) / T)
     assert wl.capacity == N
@@ -289,6 +291,45 @@ def test_counts_behind_tailors_reach_the_host_across_resets(layers_per_call):
     finally:
         A.arkv_cache_destroy(used)
         A.arkv_cache_destroy(fresh)
+
+
+def test_counts_behind_a_tailor_of_several_layers_reach_each_layers_next_steps():
+    """A tailor of two layers in one launch names each layer's counts apart.  The single-layer steps behind it, with the words
+    there, hand those counts to the kernel: the same bits as a cache that was driven layer by layer, with layers whose budgets and
+    counts differ."""
+    L, hq, hkv, d, T, N, steps = 2, 8, 2, 64, 200, 90, 70
+    wl = synth.C1.scaled(name="words3", n_layers=L, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, prefill=T, batch=2, budget_frac=(N + 0.5) / T)
+    cfg = make_cfg(wl)
+    q, kn, vn = (torch.stack(x).cuda() for x in zip(*[synth.decode_inputs(wl, l, steps) for l in range(L)]))
+    got = []
+    for together in (True, False):
+        cache = A.arkv_cache_create(cfg)
+        try:
+            stats = torch.zeros((wl.batch, 3), dtype=torch.float32, device="cuda")
+            for l in range(L):
+                k, v, qw = (t.cuda() for t in synth.prefill_inputs(wl, l))
+                A.arkv_prefill_stats(cache, l, qw, k, T, 0.1, stats)
+                A.arkv_prefill_commit(cache, l, k, v, T, [(0.2, 0.7)[l]] * wl.batch)
+            outs, layers_tailors = torch.zeros((steps, L, wl.batch, hq, d), dtype=torch.bfloat16, device="cuda"), 0
+            for i in range(steps):
+                if together and A.arkv_cache_progress(cache, 0)[1] + 1 >= N:       # this step ends with a tailor
+                    A.arkv_decode_step_layers(cache, 0, L, q[:, i].contiguous(), kn[:, i].contiguous(), vn[:, i].contiguous(), [0.1] * L, outs[i])
+                    torch.cuda.synchronize()
+                    layers_tailors += 1
+                    assert not np.array_equal(A.arkv_cache_counters(cache, 0, wl.batch * hkv)[0],
+                                              A.arkv_cache_counters(cache, 1, wl.batch * hkv)[0])
+                else:
+                    for l in range(L):
+                        A.arkv_decode_step(cache, l, q[l, i], kn[l, i], vn[l, i], 0.1, outs[i, l])
+            torch.cuda.synchronize()
+            assert layers_tailors == (A.arkv_cache_progress(cache, 0)[0] - 1 if together else 0)
+            got.append((outs, [A.arkv_cache_export(cache, l, cfg) for l in range(L)]))
+        finally:
+            A.arkv_cache_destroy(cache)
+    assert torch.equal(got[0][0], got[1][0])
+    for a, b in zip(got[0][1], got[1][1]):
+        for name in a:
+            assert np.array_equal(a[name], b[name]), name
 
 
 def test_static_steps_with_scores_of_several_workgroups():

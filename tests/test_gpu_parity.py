@@ -499,10 +499,35 @@ def test_selection_in_a_narrow_range_of_scores(T, N, gain, steps):
 ])
 def test_tailor_from_kept_logits(g, d, bits, T, N, rho, byte_budget):
     """With a tailor at every step the scores' update takes the step's logits from the attention launch, and from the 17th
-    tailor on the choosing workgroup moves the rows: 19 steps against the oracle, states and rows exactly."""
+    tailor on (up to 1024 rows: from the first behind the commit) the choosing workgroup moves the rows: 19 steps against the
+    oracle, states and rows exactly."""
     wl = synth.C1.scaled(name="kept", n_q_heads=2 * g, n_kv_heads=2, head_dim=d, bits=bits, prefill=T, budget_frac=(N + 0.5) / T,
                          window=16, decode_steps=19)
     _run(wl, rho=rho, check_every=6, stats=False, every_step=True, byte_budget=byte_budget)
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [1500, 1090])          # with a tailor at the commit; a prompt that fits its cache
+def test_natural_cadence_above_a_small_cache(T, d, bits):
+    """Tailors of more than 1024 rows at their natural cadence move rows in two launches over the whole chip: every row format and
+    both head dimensions, through two tailors, states and rows exactly."""
+    wl = synth.C1.scaled(name="natural", n_q_heads=4, n_kv_heads=2, head_dim=d, bits=bits, prefill=T, budget_frac=1100.5 / T, alpha=0.98,
+                         decode_steps=46 if T > 1100 else 34)
+    assert wl.capacity == 1100
+    sb = _run(wl, rho=0.4, check_every=12)
+    assert sb.oracles[(0, 0)].n_tailors == (3 if T > 1100 else 2)
+
+
+@pytest.mark.parametrize("n", [1024, 1025])
+def test_natural_cadence_at_the_line_of_small_caches(n):
+    """1024 rows: the choosing workgroup makes the moves from the fifth tailor on (the commit's is the first), before that two
+    launches do; 1025 rows: always the launches.  Through six tailors."""
+    wl = synth.C1.scaled(name="line", n_q_heads=4, n_kv_heads=2, head_dim=64, prefill=1400, budget_frac=(n + 0.5) / 1400, alpha=0.99,
+                         decode_steps=58)
+    assert wl.capacity == n
+    sb = _run(wl, rho=0.3, check_every=10)
+    assert sb.oracles[(0, 0)].n_tailors >= 6
 
 
 def _scores(kind, n):
