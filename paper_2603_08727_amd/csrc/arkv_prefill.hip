@@ -350,8 +350,9 @@ __device__ __forceinline__ void row_constants_of(const float2* rowstat, int n_ch
   }
 }
 
-// crow[r] = -c_r of all rows, by the whole workgroup, from 17 to 64 chunks.  Up to 128 rows (with more, eight rows' 64 bytes per chunk
-// and lane octet are too little of a line: 256 rows 5 % slower than a thread per row, 128 rows 2 % faster, 32 rows 7 %).
+// crow[r] = -c_r of all rows, by the whole workgroup, from 17 to 64 chunks.  Up to 128 rows (the whole scorer with eight lanes / a
+// thread per row: 256 rows 5 % slower, 128 rows the same, 64 and 32 rows 2 to 9 % faster, d = 128, 8 units x 6000 keys 20.1 / 21.4 us;
+// beyond 64 chunks 16 partials a lane at a time leave too few rows in flight, 128 rows 7 to 27 % slower).
 constexpr int kWaveChunks = 64, kWaveRows = 128;
 template <int MP, int NW>
 __device__ __forceinline__ void row_constants(const float2* rowstat, int n_chunks, int M, float* crow) {
@@ -369,6 +370,7 @@ __device__ __forceinline__ void row_constants(const float2* rowstat, int n_chunk
 // Second pass.  Here the MFMA is turned round (query rows on the M side, keys on the N side) so that a
 // lane owns ONE key and the sums over the M = G*W query rows are in-register additions: C[i] is row
 // rt*32 + 8(i/4) + 4(lane/32) + i%4 against key j0 + lane%32.  The row constants c_r come from LDS.
+// (The launch bounds keep the prologue from taking more registers than the loop: 96 at d = 64.)
 template <int D, int RT, int NW>
 __global__ __launch_bounds__(64 * NW, NW > 4 ? 2 : D == 64 && RT <= 4 ? 5 : 3) void k_prefill_cols(PrefillLaunch L, const float* rowc, double* zpart) {
   extern __shared__ __align__(16) unsigned char sm[];

@@ -670,8 +670,8 @@ __device__ __forceinline__ float2 step_moments(const float (&x)[G], const float2
   return m[0];
 }
 
-// KEPT: the pending step's logits are in Pools::logit (see k_decode_attend); its probabilities are added to the sums here,
-// and few moved rows (L.few_moves) are moved here as well.
+// KEPT: the pending step's logits are in Pools::logit (see k_decode_attend); its probabilities are added to the sums here.
+// L.few_moves (with and without them): the moves are made here as well.
 constexpr int kNearList = 64;
 template <int G, bool IN_LDS, bool KEPT>
 __global__ __launch_bounds__(1024) void k_tailor_choose(Pools P, TailorLaunch L) {
