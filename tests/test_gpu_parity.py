@@ -530,6 +530,19 @@ def test_natural_cadence_at_the_line_of_small_caches(n):
     assert sb.oracles[(0, 0)].n_tailors >= 6
 
 
+@pytest.mark.parametrize("every_step", [False, True])
+def test_byte_budget_whose_rows_fit_lds_though_its_pools_do_not(every_step):
+    """2-bit rows under a byte budget: some 19000 rows of a unit, pools for 44000 (more than a workgroup's LDS has scores for).  The
+    tailors go by the rows that the layer's ratio lets a unit hold: states and rows exactly."""
+    n, t = 7000, 22000
+    wl = synth.C1.scaled(name="pools", n_q_heads=2, n_kv_heads=1, head_dim=64, bits=2, prefill=t, batch=1, budget_frac=(n + 0.5) / t,
+                         alpha=0.999, decode_steps=3 if every_step else 9)
+    cfg = make_cfg(wl, every_step=every_step, byte_budget=True)
+    assert n + A.arkv_budget_counts(cfg, 0.0)[2] > 32768 > n + A.arkv_budget_counts(cfg, 0.6)[2]
+    sb = _run(wl, rho=0.6, check_every=3, stats=False, every_step=every_step, byte_budget=True)
+    assert sb.oracles[(0, 0)].n_tailors >= 2
+
+
 def _scores(kind, n):
     """fp32 bits of n scores (0xFFFFFFFF: not ranked)."""
     r = np.random.default_rng(n)
